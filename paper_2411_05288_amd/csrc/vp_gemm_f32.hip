@@ -1,84 +1,207 @@
-// fp32 path of the output layer: a plain LDS-tiled FMA GEMM with arbitrary operand strides.
-// It serves the fp32 configuration, where the products must be true fp32 contractions
-// (no bf16 operands), and doubles as the simple reference shape of the three products of
-// section 4.2:  Y = X W^T,  dX += D W,  dW = D^T X.
+// fp32 path of the output layer: fp32 products on the matrix cores (v_mfma_f32_32x32x2_f32: fp32
+// operands, fp32 products and accumulation) with arbitrary operand layouts.  It serves the three
+// products of section 4.2 for fp32 storage:  Y = X W^T,  dX += D W,  dW = D^T X.
 //
-// C[m, n] (+)= sum_k A[m*sam + k*sak] * B[n*sbn + k*sbk]
-// 64x64 output tile per 256-thread workgroup, 4x4 outputs per thread, K step 16.
+// C[m, n] (+)= sum_k A(m, k) * B(n, k), each operand stored K-contiguous ([rows][K]) or K-strided
+// ([K][rows]).
+//
+// What bounds it: the fp32 matrix rate (157 TFLOP/s dense; one MFMA keeps a SIMD's matrix core busy
+// for 64 cycles and needs one operand register per side, so LDS and load traffic are light).  A
+// vector-ALU version of this kernel (64 x 64 tiles, no double buffering) took 411 us per product of
+// N=1000, h=1024, Vs=4000 (20 TFLOP/s); this one takes 88 us on the outputs of 256 tiles of 128 x 128
+// (one workgroup per compute unit, 94 TFLOP/s) and 120 us on the 1000 x 1024 output.
+//
+// Workgroup: 4 wavefronts (2 x 2) on a TM x TN tile, TM = TN = 128 (64 x 64 per wavefront) or 64.
+// K advances 32 at a time through two LDS stages; the global loads of step k + 1 are in flight in
+// registers while step k is multiplied (4096 cycles at 128 x 128), one barrier per step; two
+// workgroups share a compute unit and fill each other's barriers.
+//
+// LDS: K-contiguous tile [rows][32 + 4]: one ds_read_b128 gives four k of one row, and lanes 32-63
+// take the next four, so MFMA step j of a group multiplies k = j and k = 4 + j (the order of the k
+// does not matter as long as both operands use it).  K-strided tile [32][rows + 8]: one ds_read_b32
+// per step; 4 * (rows + 8) words are 32 banks apart, so both lane halves fall into different banks.
 //
 // Small outputs with a long K (dX of the tiny configuration: 128 x 256 outputs, K = 4096) would
 // occupy a handful of compute units.  With scratch memory the K range is cut into S slices
-// (grid.z); every slice writes its partial tile to scratch[z], and a second kernel adds the S
+// (grid.y); every slice writes its partial tile to scratch[z], and a second kernel adds the S
 // partials in ascending z (a fixed order: results repeat bit for bit).
 #include "vp_internal.h"
 
 namespace vp {
 
-constexpr int FT = 64, FK = 16;
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int64_t sam, int64_t sak,
-                                                       const float* __restrict__ B, int64_t sbn, int64_t sbk,
-                                                       float* __restrict__ C, int64_t ldc, int M, int N, int K,
-                                                       int accumulate, int k_per_slice, int64_t slice_stride) {
-    __shared__ float sA[FK][FT + 1];
-    __shared__ float sB[FK][FT + 1];
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    const int m0 = blockIdx.y * FT, n0 = blockIdx.x * FT;
+constexpr int FK = 32;             // K step
+constexpr int F_THREADS = 256;
+constexpr unsigned F_OOB = 0x80000000u;   // beyond every buffer descriptor below (each covers at most 2^29 bytes)
 
-    float acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+struct GemmF32Params {
+    const float* A;
+    const float* B;
+    float* C;
+    int64_t lda, ldb, ldc;
+    int M, N, K;
+    int a_vec, b_vec;              // 1: 16-byte loads allowed (rows 16-byte aligned, and K % 4 == 0 if K-contiguous)
+    int accumulate;
+    int k_per_slice;
+    int64_t slice_stride;          // floats between the partial outputs of consecutive slices
+};
 
-    // slice z of the K range; with one slice this is all of K and C is the real output
-    const int k_begin = blockIdx.z * k_per_slice;
-    const int k_end = min(K, k_begin + k_per_slice);
-    C += (int64_t)blockIdx.z * slice_stride;
-    for (int k0 = k_begin; k0 < k_end; k0 += FK) {
-        // 64 x 16 elements per operand, 4 per thread; pick the index order that walks the
-        // contiguous dimension of the operand with consecutive threads
+template <bool KC, int ROWS>
+struct F32Tile {
+    static constexpr int RS = KC ? FK + 4 : ROWS + 8;                // row stride in floats
+    static constexpr int FLOATS = KC ? ROWS * RS : FK * RS;
+    static constexpr int CHUNKS = ROWS * FK / 4 / F_THREADS;         // 16-byte chunks per thread
+};
+
+template <bool KC, int ROWS>
+using F32Chunks = uintx4[F32Tile<KC, ROWS>::CHUNKS];
+
+// Global -> registers for one ROWS x FK operand tile.  Out-of-range elements come back as zeros: the
+// descriptor covers exactly the rows of this tile that exist (K-contiguous) or the k-rows that exist
+// (K-strided), and elements past the end of a K-contiguous row get an offset beyond it.  (Rows past the
+// end of a K-strided operand read the neighbouring k-row: finite values for outputs never stored.)
+template <bool KC, int ROWS>
+__device__ __forceinline__ void f32_load(F32Chunks<KC, ROWS>& r, const float* p, int64_t ld, int r0,
+                                         int k0, int rows, int k_end, int vec, int tid) {
+    constexpr int CPR = KC ? FK / 4 : ROWS / 4;     // chunks per stored row of the tile
+    const float* base = KC ? p + (int64_t)r0 * ld + k0 : p + (int64_t)k0 * ld + r0;
+    const int left = KC ? rows - r0 : k_end - k0;   // stored rows that exist from here on
+    const int have = left < 0 ? 0 : (left < (KC ? ROWS : FK) ? left : (KC ? ROWS : FK));
+    // bytes from `base` to the end of the last existing stored row
+    const int64_t in_row = KC ? (int64_t)k_end - k0 : (int64_t)rows - r0;
+    const int64_t bytes = have > 0 && in_row > 0 ? (((int64_t)have - 1) * ld + in_row) * 4 : 0;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = tid + 256 * i;
-            int r, k;
-            if (sak == 1) { k = e & 15; r = e >> 4; } else { r = e & 63; k = e >> 6; }
-            const int gm = m0 + r, gk = k0 + k;
-            sA[k][r] = (gm < M && gk < k_end) ? A[(int64_t)gm * sam + (int64_t)gk * sak] : 0.f;
-            if (sbk == 1) { k = e & 15; r = e >> 4; } else { r = e & 63; k = e >> 6; }
-            const int gn = n0 + r;
-            const int gk2 = k0 + k;
-            sB[k][r] = (gn < N && gk2 < k_end) ? B[(int64_t)gn * sbn + (int64_t)gk2 * sbk] : 0.f;
+    for (int i = 0; i < F32Tile<KC, ROWS>::CHUNKS; ++i) {
+        const int q = tid + F_THREADS * i;
+        const int row = q / CPR, c = (q % CPR) * 4;
+        const unsigned off = ((unsigned)row * (unsigned)ld + (unsigned)c) * 4u;
+        if (vec) {
+            r[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(KC && k0 + c >= k_end ? F_OOB : off), 0, 0);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                r[i][e] = __builtin_amdgcn_raw_buffer_load_b32(
+                    rs, (int)(KC && k0 + c + e >= k_end ? F_OOB : off + 4u * e), 0, 0);
         }
-        __syncthreads();
+    }
+}
+
+template <bool KC, int ROWS>
+__device__ __forceinline__ void f32_store(const F32Chunks<KC, ROWS>& r, float* s, int tid) {
+    constexpr int CPR = KC ? FK / 4 : ROWS / 4;
 #pragma unroll
-        for (int k = 0; k < FK; ++k) {
-            float a[4], b[4];
+    for (int i = 0; i < F32Tile<KC, ROWS>::CHUNKS; ++i) {
+        const int q = tid + F_THREADS * i;
+        *reinterpret_cast<uintx4*>(s + (q / CPR) * F32Tile<KC, ROWS>::RS + (q % CPR) * 4) = r[i];
+    }
+}
+
+// The four k values (8q + 4 hf .. + 3) of tile row `row`
+template <bool KC, int ROWS>
+__device__ __forceinline__ floatx4 f32_frag(const float* s, int row, int q, int hf) {
+    constexpr int RS = F32Tile<KC, ROWS>::RS;
+    if (KC) return *reinterpret_cast<const floatx4*>(s + row * RS + 8 * q + 4 * hf);
+    floatx4 v;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = sA[k][ty + 16 * i];
+    for (int j = 0; j < 4; ++j) v[j] = s[(8 * q + 4 * hf + j) * RS + row];
+    return v;
+}
+
+template <bool A_KC, bool B_KC, int TM, int TN>
+__global__ __launch_bounds__(F_THREADS, TM == 128 ? 2 : 4) void gemm_f32_kernel(GemmF32Params g) {
+    constexpr int MT = TM / 64, NT = TN / 64;            // 32 x 32 MFMA tiles per wavefront and direction
+    typedef F32Tile<A_KC, TM> TA;
+    typedef F32Tile<B_KC, TN> TB;
+    __shared__ __attribute__((aligned(16))) float sA[2][TA::FLOATS];
+    __shared__ __attribute__((aligned(16))) float sB[2][TB::FLOATS];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, hf = lane >> 5;
+
+    // Tiles in panels of 8 tile rows, column by column; workgroups are dealt to the 8 XCDs round-robin, so
+    // every XCD takes a contiguous run of tiles and shares the operand panels of its run in its L2.
+    const int tiles_m = (g.M + TM - 1) / TM, tiles_n = (g.N + TN - 1) / TN;
+    const int total = tiles_m * tiles_n, b = blockIdx.x;
+    const int x = b & 7, per = total >> 3, rem = total & 7;
+    const int t = x * per + (x < rem ? x : rem) + (b >> 3);
+    const int panel = t / (8 * tiles_n), in_panel = t - panel * 8 * tiles_n;
+    const int prows = min(8, tiles_m - panel * 8);
+    const int m0 = (panel * 8 + in_panel % prows) * TM, n0 = (in_panel / prows) * TN;
+
+    // slice y of the K range; with one slice this is all of K and C is the real output
+    const int k_begin = blockIdx.y * g.k_per_slice;
+    const int k_end = min(g.K, k_begin + g.k_per_slice);
+    float* C = g.C + (int64_t)blockIdx.y * g.slice_stride;
+
+    floatx16 acc[MT][NT];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = sB[k][tx + 16 * j];
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < NT; ++j)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    uintx4 ra[TA::CHUNKS], rb[TB::CHUNKS];
+    f32_load<A_KC, TM>(ra, g.A, g.lda, m0, k_begin, g.M, k_end, g.a_vec, tid);
+    f32_load<B_KC, TN>(rb, g.B, g.ldb, n0, k_begin, g.N, k_end, g.b_vec, tid);
+    f32_store<A_KC, TM>(ra, sA[0], tid);
+    f32_store<B_KC, TN>(rb, sB[0], tid);
+    __syncthreads();
+    int cur = 0;
+    for (int k0 = k_begin; k0 < k_end; k0 += FK, cur ^= 1) {
+        const bool more = k0 + FK < k_end;
+        if (more) {
+            f32_load<A_KC, TM>(ra, g.A, g.lda, m0, k0 + FK, g.M, k_end, g.a_vec, tid);
+            f32_load<B_KC, TN>(rb, g.B, g.ldb, n0, k0 + FK, g.N, k_end, g.b_vec, tid);
+        }
+#pragma unroll
+        for (int q = 0; q < FK / 8; ++q) {
+            floatx4 a[MT], bb[NT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[i] = f32_frag<A_KC, TM>(sA[cur], (wm * MT + i) * 32 + l32, q, hf);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) bb[j] = f32_frag<B_KC, TN>(sB[cur], (wn * NT + j) * 32 + l32, q, hf);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], bb[j][e], acc[i][j], 0, 0, 0);
+        }
+        if (more) {     // the other stage was last read before the previous barrier
+            f32_store<A_KC, TM>(ra, sA[cur ^ 1], tid);
+            f32_store<B_KC, TN>(rb, sB[cur ^ 1], tid);
         }
         __syncthreads();
     }
+
+    // register r of lane l of a tile holds C[8 (r/4) + 4 (l/32) + r%4][l%32]: 128 contiguous bytes per row and store
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int gm = m0 + ty + 16 * i;
-        if (gm >= M) continue;
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int gn = n0 + tx + 16 * j;
-            if (gn < N) {
-                float* c = C + (int64_t)gm * ldc + gn;
-                *c = accumulate ? (*c + acc[i][j]) : acc[i][j];
+        for (int j = 0; j < NT; ++j) {
+            const int col = n0 + (wn * NT + j) * 32 + l32;
+            const int row0 = m0 + (wm * MT + i) * 32 + 4 * hf;
+            if (col >= g.N) continue;
+            float* c = C + (int64_t)row0 * g.ldc + col;
+            if (g.accumulate) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int dr = 8 * (r >> 2) + (r & 3);
+                    if (row0 + dr < g.M) acc[i][j][r] += c[(int64_t)dr * g.ldc];
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int dr = 8 * (r >> 2) + (r & 3);
+                if (row0 + dr < g.M) c[(int64_t)dr * g.ldc] = acc[i][j][r];
             }
         }
-    }
 }
 
 // C (+)= sum over the S partial matrices [M, N] in scratch, ascending slice index
@@ -92,9 +215,9 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     *c = accumulate ? (*c + acc) : acc;
 }
 
-// K slices for an [M, N] output: enough workgroups to cover the chip, slices of at least 64.
+// K slices for an [M, N] output: enough workgroups of 64 x 64 tiles to cover the chip, slices of at least 64.
 static int splitk_slices(int M, int N, int K) {
-    const int64_t tiles = ceil_div(M, FT) * ceil_div(N, FT);
+    const int64_t tiles = ceil_div(M, 64) * ceil_div(N, 64);
     int64_t S = 256 / tiles;
     if (S > 32) S = 32;
     if (S > K / 64) S = K / 64;
@@ -106,28 +229,47 @@ size_t gemm_f32_scratch_floats(int64_t M, int64_t N, int64_t K) {
     return S > 1 ? (size_t)S * (size_t)M * (size_t)N : 0;
 }
 
+template <bool A_KC, bool B_KC>
+static void launch_f32_t(const GemmF32Params& g, int tile, int slices, hipStream_t st) {
+    const unsigned tiles = (unsigned)(ceil_div(g.M, tile) * ceil_div(g.N, tile));
+    if (tile == 128)
+        hipLaunchKernelGGL((gemm_f32_kernel<A_KC, B_KC, 128, 128>), dim3(tiles, slices), dim3(F_THREADS), 0, st, g);
+    else
+        hipLaunchKernelGGL((gemm_f32_kernel<A_KC, B_KC, 64, 64>), dim3(tiles, slices), dim3(F_THREADS), 0, st, g);
+}
+
 hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float* B, int64_t sbn, int64_t sbk,
                            float* C, int64_t ldc, int M, int N, int K, bool accumulate, float* scratch,
                            hipStream_t st) {
     if (M <= 0 || N <= 0 || K <= 0) return hipErrorInvalidValue;
-    dim3 grid((unsigned)ceil_div(N, FT), (unsigned)ceil_div(M, FT));
-    if (grid.y > 65535u) return hipErrorInvalidValue;
+    if ((sam != 1 && sak != 1) || (sbn != 1 && sbk != 1)) return hipErrorInvalidValue;
     ProfScope prof(K_GEMM_F32, st);
+    const bool a_kc = sak == 1, b_kc = sbk == 1;
+    GemmF32Params g{};
+    g.A = A; g.B = B;
+    g.lda = a_kc ? sam : sak; g.ldb = b_kc ? sbn : sbk;
+    g.M = M; g.N = N; g.K = K;
     const int S = scratch ? splitk_slices(M, N, K) : 1;
-    if (S > 1) {
-        const int kps = (int)(ceil_div(ceil_div(K, S), FK) * FK);     // multiple of the K step
-        grid.z = (unsigned)ceil_div(K, kps);
-        const int64_t MN = (int64_t)M * N;
-        hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, st, A, sam, sak, B, sbn, sbk, scratch, (int64_t)N, M, N, K,
-                           0, kps, MN);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)ceil_div(MN, 256)), dim3(256), 0, st, scratch,
-                           (int)grid.z, MN, N, C, ldc, accumulate ? 1 : 0);
-        return hipGetLastError();
+    g.k_per_slice = S > 1 ? (int)(ceil_div(ceil_div(K, S), FK) * FK) : K;     // multiple of the K step
+    const int slices = (int)ceil_div(K, g.k_per_slice);
+    g.a_vec = g.lda % 4 == 0 && ((uintptr_t)A & 15u) == 0 && (!a_kc || K % 4 == 0);
+    g.b_vec = g.ldb % 4 == 0 && ((uintptr_t)B & 15u) == 0 && (!b_kc || K % 4 == 0);
+    const int64_t MN = (int64_t)M * N;
+    if (slices > 1) {
+        g.C = scratch; g.ldc = N; g.accumulate = 0; g.slice_stride = MN;
+    } else {
+        g.C = C; g.ldc = ldc; g.accumulate = accumulate ? 1 : 0; g.slice_stride = 0;
     }
-    hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, st, A, sam, sak, B, sbn, sbk, C, ldc, M, N, K,
-                       accumulate ? 1 : 0, K, (int64_t)0);
+    // 128 x 128 tiles (half the LDS and load traffic per flop) once they give every compute unit a workgroup
+    const int tile = ceil_div(M, 128) * ceil_div(N, 128) * slices >= 256 ? 128 : 64;
+    if (a_kc && b_kc) launch_f32_t<true, true>(g, tile, slices, st);
+    else if (a_kc) launch_f32_t<true, false>(g, tile, slices, st);
+    else if (!b_kc) launch_f32_t<false, false>(g, tile, slices, st);
+    else return hipErrorInvalidValue;
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || slices == 1) return e;
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)ceil_div(MN, 256)), dim3(256), 0, st, scratch, slices, MN, N,
+                       C, ldc, accumulate ? 1 : 0);
     return hipGetLastError();
 }
 
