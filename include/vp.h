@@ -223,6 +223,18 @@ vp_status vp_embed_bwd(const void* grad_out, const int64_t* ids,
                        float* dtable_shard, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * The same for p consecutive shards of Vs rows each that live on one device, in as few launches as
+ * possible: shard r owns rows [shard_offset + r Vs, shard_offset + (r + 1) Vs).  table_shards, outs and
+ * dtable_shards are HOST arrays of p device pointers; the arrays are read before the call returns.
+ * Results equal those of p single calls bit for bit.  The workspace is that of the single call.
+ */
+vp_status vp_embed_fwd_group(const void* const* table_shards, const int64_t* ids, int32_t p, int64_t N, int64_t h,
+                             int64_t Vs, int64_t shard_offset, vp_dtype dt, void* const* outs, void* stream);
+vp_status vp_embed_bwd_group(const void* grad_out, const int64_t* ids, int32_t p, int64_t N, int64_t h, int64_t Vs,
+                             int64_t shard_offset, vp_dtype dt, float* const* dtable_shards, void* workspace,
+                             size_t workspace_bytes, void* stream);
+
+/*
  * Measurement aid, not part of the method.  While enabled, every kernel launch made by the
  * entry points above is bracketed by two HIP events on the launch stream (events are created
  * on demand and pooled; this is the only state the library ever holds, and none exists while

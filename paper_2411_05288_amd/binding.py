@@ -76,6 +76,10 @@ def load_library() -> ctypes.CDLL:
     lib.vp_embed_fwd.argtypes = [vp, vp, i64, i64, i64, i64, c.c_int, vp, vp]
     lib.vp_embed_bwd.restype = c.c_int
     lib.vp_embed_bwd.argtypes = [vp, vp, i64, i64, i64, i64, c.c_int, vp, vp, sz, vp]
+    lib.vp_embed_fwd_group.restype = c.c_int
+    lib.vp_embed_fwd_group.argtypes = [vp, vp, i32, i64, i64, i64, i64, c.c_int, vp, vp]
+    lib.vp_embed_bwd_group.restype = c.c_int
+    lib.vp_embed_bwd_group.argtypes = [vp, vp, i32, i64, i64, i64, i64, c.c_int, vp, vp, sz, vp]
     lib.vp_profile_mfma_loop.restype = c.c_int
     lib.vp_profile_mfma_loop.argtypes = [vp, vp, i32, i32, vp]
     lib.vp_profile_mfma_variant.restype = c.c_int
@@ -129,6 +133,11 @@ def _ptr(t: Optional[torch.Tensor], name: str, dtypes=None, shape=None) -> Optio
     if shape is not None and tuple(t.shape) != tuple(shape):
         raise VPError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
     return t.data_ptr()
+
+
+def _ptrs(ts, name: str, dtypes, shape):
+    """Array of the device pointers of one tensor per shard."""
+    return (ctypes.c_void_p * len(ts))(*[_ptr(t, name, dtypes, shape) for t in ts])
 
 
 def _stream(stream) -> int:
@@ -300,6 +309,30 @@ def vp_embed_bwd(grad_out, ids, shard_offset: int, dtable_shard, workspace, stre
         _ptr(grad_out, "grad_out"), _ptr(ids, "ids", (torch.int64,), (N,)), N, h, Vs, shard_offset, dt,
         _ptr(dtable_shard, "dtable_shard", (torch.float32,), (Vs, h)), wp, wb, _stream(stream))
     _check(st, "vp_embed_bwd")
+
+
+def vp_embed_fwd_group(table_shards, ids, shard_offset: int, outs, stream=None) -> None:
+    """vp_embed_fwd for consecutive shards of equal size in one call; shard_offset is that of the first."""
+    Vs, h = table_shards[0].shape
+    N, p = ids.shape[0], len(table_shards)
+    if len(outs) != p:
+        raise VPError("one output per shard")
+    dtype = table_shards[0].dtype
+    st = load_library().vp_embed_fwd_group(
+        _ptrs(table_shards, "table_shards", (dtype,), (Vs, h)), _ptr(ids, "ids", (torch.int64,), (N,)), p, N, h, Vs,
+        shard_offset, _dtype_code(table_shards[0]), _ptrs(outs, "outs", (dtype,), (N, h)), _stream(stream))
+    _check(st, "vp_embed_fwd_group")
+
+
+def vp_embed_bwd_group(grad_out, ids, shard_offset: int, dtable_shards, workspace, stream=None) -> None:
+    """vp_embed_bwd for consecutive shards of equal size in one call; shard_offset is that of the first."""
+    N, h = grad_out.shape
+    Vs = dtable_shards[0].shape[0]
+    wp, wb = _ws(workspace)
+    st = load_library().vp_embed_bwd_group(
+        _ptr(grad_out, "grad_out"), _ptr(ids, "ids", (torch.int64,), (N,)), len(dtable_shards), N, h, Vs, shard_offset,
+        _dtype_code(grad_out), _ptrs(dtable_shards, "dtable_shards", (torch.float32,), (Vs, h)), wp, wb, _stream(stream))
+    _check(st, "vp_embed_bwd_group")
 
 
 def vp_profile_mfma_loop(operands, out, iters: int, blocks: int, stream=None) -> None:

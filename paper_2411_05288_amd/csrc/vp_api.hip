@@ -113,7 +113,7 @@ size_t vp_workspace_bytes(vp_call which, int64_t N, int64_t h, int64_t Vs, vp_dt
             return f32_matrix_bytes(N, Vs) + align_up(f32_bwd_scratch(N, h, Vs), 256);
         case VP_CALL_EMBED_BWD:
             if (N < 1 || N > ((int64_t)1 << 24)) return (size_t)-1;
-            return align_up(embed_bwd_workspace(N), 256);
+            return align_up(embed_bwd_workspace(N, h, Vs, dt == VP_BF16 ? 2 : 4), 256);
         case VP_CALL_COMBINE_STATS:
         case VP_CALL_EMBED_FWD:
             return 0;
@@ -349,7 +349,7 @@ vp_status vp_output_fwd_alg2(const void* H, const void* W_shard, const int64_t* 
         a.C = A_out; a.ldc = (int)h;
         a.kernel_id = K_GEMM_A_ALG2;
         if ((e = launch_gemm_bf16(a, st)) != hipSuccess) return VP_ERR_DEVICE;
-        return dev(launch_embed_fwd(W_shard, labels, (int)N, (int)h, (int)Vs, shard_offset, 2, B_out, st));
+        return dev(launch_embed_fwd(&W_shard, labels, 1, (int)N, (int)h, (int)Vs, shard_offset, 2, &B_out, st));
     }
 
     // fp32: logits in the caller's buffer or the workspace, softmax' in the workspace (in place when they coincide)
@@ -369,7 +369,7 @@ vp_status vp_output_fwd_alg2(const void* H, const void* W_shard, const int64_t* 
                              st)) !=
         hipSuccess)
         return VP_ERR_DEVICE;
-    return dev(launch_embed_fwd(W_shard, labels, (int)N, (int)h, (int)Vs, shard_offset, 4, B_out, st));
+    return dev(launch_embed_fwd(&W_shard, labels, 1, (int)N, (int)h, (int)Vs, shard_offset, 4, &B_out, st));
 }
 
 vp_status vp_output_dx_alg2(const float* A, const void* B, const float* local_max, const float* local_sumexp,
@@ -384,27 +384,41 @@ vp_status vp_output_dx_alg2(const float* A, const void* B, const float* local_ma
                               (int)h, grad_scale, (flags & VP_DH_OVERWRITE) != 0, dH_accum, (hipStream_t)stream));
 }
 
+vp_status vp_embed_fwd_group(const void* const* table_shards, const int64_t* ids, int32_t p, int64_t N, int64_t h, int64_t Vs,
+                             int64_t shard_offset, vp_dtype dt, void* const* outs, void* stream) {
+    if (!table_shards || !ids || !outs || p < 1) return VP_ERR_INVALID_ARG;
+    if (!sizes_ok(N, h, Vs) || !dtype_ok(dt) || shard_offset < 0) return VP_ERR_INVALID_ARG;
+    for (int32_t r = 0; r < p; ++r)
+        if (!table_shards[r] || !outs[r] || !aligned16(table_shards[r]) || !aligned16(outs[r])) return VP_ERR_INVALID_ARG;
+    if (!sizes_supported(N, h, Vs)) return VP_ERR_UNSUPPORTED;
+    return dev(launch_embed_fwd(table_shards, ids, p, (int)N, (int)h, (int)Vs, shard_offset, dt == VP_BF16 ? 2 : 4, outs,
+                                (hipStream_t)stream));
+}
+
+vp_status vp_embed_bwd_group(const void* grad_out, const int64_t* ids, int32_t p, int64_t N, int64_t h, int64_t Vs,
+                             int64_t shard_offset, vp_dtype dt, float* const* dtable_shards, void* workspace,
+                             size_t workspace_bytes, void* stream) {
+    if (!grad_out || !ids || !dtable_shards || p < 1) return VP_ERR_INVALID_ARG;
+    if (!sizes_ok(N, h, Vs) || !dtype_ok(dt) || shard_offset < 0) return VP_ERR_INVALID_ARG;
+    if (!aligned16(grad_out) || !aligned16(workspace)) return VP_ERR_INVALID_ARG;
+    for (int32_t r = 0; r < p; ++r)
+        if (!dtable_shards[r] || !aligned16(dtable_shards[r])) return VP_ERR_INVALID_ARG;
+    if (!sizes_supported(N, h, Vs) || N > ((int64_t)1 << 24)) return VP_ERR_UNSUPPORTED;
+    const size_t need = vp_workspace_bytes(VP_CALL_EMBED_BWD, N, h, Vs, dt, 0);
+    if (!workspace || workspace_bytes < need) return VP_ERR_WORKSPACE;
+    return dev(launch_embed_bwd(grad_out, ids, p, (int)N, (int)h, (int)Vs, shard_offset, dt == VP_BF16 ? 1 : 0, dtable_shards,
+                                workspace, (hipStream_t)stream));
+}
+
 vp_status vp_embed_fwd(const void* table_shard, const int64_t* ids, int64_t N, int64_t h, int64_t Vs,
                        int64_t shard_offset, vp_dtype dt, void* out, void* stream) {
-    if (!table_shard || !ids || !out) return VP_ERR_INVALID_ARG;
-    if (!sizes_ok(N, h, Vs) || !dtype_ok(dt) || shard_offset < 0) return VP_ERR_INVALID_ARG;
-    if (!aligned16(table_shard) || !aligned16(out)) return VP_ERR_INVALID_ARG;
-    if (!sizes_supported(N, h, Vs)) return VP_ERR_UNSUPPORTED;
-    return dev(launch_embed_fwd(table_shard, ids, (int)N, (int)h, (int)Vs, shard_offset, dt == VP_BF16 ? 2 : 4, out,
-                                (hipStream_t)stream));
+    return vp_embed_fwd_group(&table_shard, ids, 1, N, h, Vs, shard_offset, dt, &out, stream);
 }
 
 vp_status vp_embed_bwd(const void* grad_out, const int64_t* ids, int64_t N, int64_t h, int64_t Vs,
                        int64_t shard_offset, vp_dtype dt, float* dtable_shard, void* workspace, size_t workspace_bytes,
                        void* stream) {
-    if (!grad_out || !ids || !dtable_shard) return VP_ERR_INVALID_ARG;
-    if (!sizes_ok(N, h, Vs) || !dtype_ok(dt) || shard_offset < 0) return VP_ERR_INVALID_ARG;
-    if (!aligned16(grad_out) || !aligned16(dtable_shard) || !aligned16(workspace)) return VP_ERR_INVALID_ARG;
-    if (!sizes_supported(N, h, Vs) || N > ((int64_t)1 << 24)) return VP_ERR_UNSUPPORTED;
-    const size_t need = vp_workspace_bytes(VP_CALL_EMBED_BWD, N, h, Vs, dt, 0);
-    if (!workspace || workspace_bytes < need) return VP_ERR_WORKSPACE;
-    return dev(launch_embed_bwd(grad_out, ids, (int)N, (int)h, (int)Vs, shard_offset, dt == VP_BF16 ? 1 : 0,
-                                dtable_shard, workspace, (hipStream_t)stream));
+    return vp_embed_bwd_group(grad_out, ids, 1, N, h, Vs, shard_offset, dt, &dtable_shard, workspace, workspace_bytes, stream);
 }
 
 }  // extern "C"

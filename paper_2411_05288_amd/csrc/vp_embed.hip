@@ -1,115 +1,98 @@
-// Input (embedding) layer of one vocabulary shard (appendix C of the paper): the gather that
-// builds the full-size [N, h] output with zero rows for ids the shard does not own, and the
-// scatter-add of the output gradient into the shard's fp32 table gradient.
+// Input (embedding) layer of the vocabulary shards one device holds (appendix C of the paper): the
+// gather that builds every shard's full-size [N, h] output with zero rows for ids it does not own, and
+// the scatter-add of the output gradient into the shards' fp32 table gradients.
 //
-// The scatter-add uses no atomics.  Tokens are keyed by (local row, token position), the keys
-// are sorted (bitonic network; keys are unique so the order is total), and every run of equal
-// rows is summed by one workgroup in increasing token position, starting from the value
-// already in the table gradient.  The result does not depend on scheduling.
+// A launch serves up to EMBED_GROUP_MAX shards (shard s of the group owns rows [off + s Vs, off + (s+1) Vs)):
+// the tokens are sorted once for all of them, and small shards fill the chip together.
+//
+// The scatter-add uses no atomics on the gradient.  Tokens are keyed by (row, token position), the keys
+// are sorted (they are unique, so the order is total), and every run of equal rows is summed in
+// increasing token position, starting from the value already in the table gradient.  The result does
+// not depend on scheduling.
 #include "vp_internal.h"
 
 namespace vp {
 
 typedef unsigned long long u64;
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-constexpr u64 KEY_NONE = ~0ull;          // sorts after every real key
-constexpr int SORT_CHUNK = 16384;        // keys sorted inside one workgroup's LDS (128 KB)
-constexpr int SORT_THREADS = 1024;
 
-// ------------------------------------------------------------------------- forward
-// One workgroup per token row; VEC bytes per thread per step.
-template <typename V>
-__global__ __launch_bounds__(256) void embed_fwd_kernel(const V* __restrict__ table, const int64_t* __restrict__ ids,
-                                                        int row_vecs, int Vs, int64_t off, V* __restrict__ out) {
-    const int i = blockIdx.x;
-    const int64_t loc = ids[i] - off;
-    V* o = out + (size_t)i * row_vecs;
-    // the output is written once and read much later (by the reduce over shards): streaming stores
-    if (loc >= 0 && loc < Vs) {
-        const V* t = table + (size_t)loc * row_vecs;
-        for (int c = threadIdx.x; c < row_vecs; c += 256) __builtin_nontemporal_store(t[c], o + c);
-    } else {
-        V z = V(0);
-        for (int c = threadIdx.x; c < row_vecs; c += 256) __builtin_nontemporal_store(z, o + c);
-    }
-}
-
-hipError_t launch_embed_fwd(const void* table, const int64_t* ids, int N, int h, int Vs, int64_t off, int elem_bytes,
-                            void* out, hipStream_t st) {
-    const int64_t row_bytes = (int64_t)h * elem_bytes;
-    ProfScope prof(K_EMBED_FWD, st);
-    if (row_bytes % 16 == 0) {
-        hipLaunchKernelGGL((embed_fwd_kernel<uintx4>), dim3(N), dim3(256), 0, st, (const uintx4*)table, ids,
-                           (int)(row_bytes / 16), Vs, off, (uintx4*)out);
-    } else if (elem_bytes == 4) {
-        hipLaunchKernelGGL((embed_fwd_kernel<unsigned>), dim3(N), dim3(256), 0, st, (const unsigned*)table, ids, h, Vs,
-                           off, (unsigned*)out);
-    } else {
-        hipLaunchKernelGGL((embed_fwd_kernel<u16>), dim3(N), dim3(256), 0, st, (const u16*)table, ids, h, Vs, off,
-                           (u16*)out);
-    }
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------- backward: keys + sort
-__device__ __forceinline__ u64 token_key(const int64_t* __restrict__ ids, int i, int N, int Vs, int64_t off) {
-    if (i < N) {
-        const int64_t loc = ids[i] - off;
-        if (loc >= 0 && loc < Vs) return ((u64)loc << 32) | (u64)(unsigned)i;
-    }
-    return KEY_NONE;
-}
-
-__device__ __forceinline__ void cmp_swap(u64& x, u64& y, bool asc) {
-    if ((x > y) == asc) { const u64 t = x; x = y; y = t; }
-}
-
-// LEVELS consecutive passes (distances j, j/2, ...) of stage k of the bitonic network on
-// LDS-resident keys, done in registers on groups of 2^LEVELS keys: one LDS round trip and one
-// barrier instead of LEVELS.  gbase = global index of sh[0]; k > j, so the direction is the
-// same for all keys of a group.
-template <int LEVELS>
-__device__ __forceinline__ void bitonic_levels_lds(u64* sh, int ch, int j, int k, int gbase) {
-    constexpr int G = 1 << LEVELS;
-    const int low = j >> (LEVELS - 1);          // smallest distance of this group of passes
-    for (int t = threadIdx.x; t < ch / G; t += SORT_THREADS) {
-        // spread t around the LEVELS index bits low .. j, which enumerate the group
-        const int base = ((t & ~(low - 1)) << LEVELS) | (t & (low - 1));
-        const bool asc = (((gbase + base) & k) == 0);
-        u64 v[G];
-#pragma unroll
-        for (int e = 0; e < G; ++e) v[e] = sh[base + e * low];
-#pragma unroll
-        for (int d = G >> 1; d > 0; d >>= 1)
-#pragma unroll
-            for (int e = 0; e < G; ++e)
-                if ((e & d) == 0) cmp_swap(v[e], v[e | d], asc);
-#pragma unroll
-        for (int e = 0; e < G; ++e) sh[base + e * low] = v[e];
-    }
-    __syncthreads();
-}
-
-// passes j_first, j_first/2, ..., 1 of stage k, three at a time
-__device__ __forceinline__ void bitonic_stage_tail_lds(u64* sh, int ch, int j_first, int k, int gbase) {
-    int j = j_first;
-    for (; j >= 4; j >>= 3) bitonic_levels_lds<3>(sh, ch, j, k, gbase);
-    if (j == 2) bitonic_levels_lds<2>(sh, ch, 2, k, gbase);
-    else if (j == 1) bitonic_levels_lds<1>(sh, ch, 1, k, gbase);
-}
-
-// Workspace after the keys: the positions (in the sorted key array) where a run of equal rows
-// starts, in no particular order, and their number.
-struct RunList {
-    unsigned* starts;   // [n_pad]
-    unsigned* count;    // [1]
+struct EmbedFwdGroup {
+    const void* table[EMBED_GROUP_MAX];
+    void* out[EMBED_GROUP_MAX];
+};
+struct EmbedBwdGroup {
+    float* dtable[EMBED_GROUP_MAX];
 };
 
-__device__ __forceinline__ bool starts_run(const u64* keys, int s) {
-    const u64 k = keys[s];
-    return k != KEY_NONE && (s == 0 || (unsigned)(keys[s - 1] >> 32) != (unsigned)(k >> 32));
+// ------------------------------------------------------------------------- forward
+// Bound by the stores: p full-size outputs leave, at most N table rows come in.  Workgroup (x, s) writes rows_per_wg
+// consecutive rows of shard s's output, one wavefront per row and 64 * V bytes per store, so that a workgroup's
+// stores cover one contiguous range of about 32 KB whatever the row length.  Measured: 8 shards, N = 8192, h = 4096,
+// bf16: 102 us (5.3 TB/s) in one launch, 103 us in eight; N = 512, h = 1024, fp32: 5 us for 8 launches of 2.7 us.
+template <typename V>
+__global__ __launch_bounds__(256) void embed_fwd_kernel(EmbedFwdGroup g, const int64_t* __restrict__ ids, int N,
+                                                        int row_vecs, int Vs, int64_t off, int rows_per_wg) {
+    const int s = blockIdx.y;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const V* __restrict__ table = (const V*)g.table[s];
+    V* __restrict__ out = (V*)g.out[s];
+    const int64_t first = off + (int64_t)s * Vs;
+    const int end = min(N, (int)(blockIdx.x + 1) * rows_per_wg);
+    // the output is written once and read much later (by the reduce over shards): streaming stores
+    for (int i = blockIdx.x * rows_per_wg + wave; i < end; i += 4) {
+        const int64_t loc = ids[i] - first;
+        V* o = out + (size_t)i * row_vecs;
+        if (loc >= 0 && loc < Vs) {
+            const V* t = table + (size_t)loc * row_vecs;
+            int c = lane;
+            for (; c + 192 < row_vecs; c += 256) {
+                const V a = t[c], b = t[c + 64], d = t[c + 128], e = t[c + 192];
+                __builtin_nontemporal_store(a, o + c);
+                __builtin_nontemporal_store(b, o + c + 64);
+                __builtin_nontemporal_store(d, o + c + 128);
+                __builtin_nontemporal_store(e, o + c + 192);
+            }
+            for (; c < row_vecs; c += 64) __builtin_nontemporal_store(t[c], o + c);
+        } else {
+            const V z = V(0);
+            for (int c = lane; c < row_vecs; c += 64) __builtin_nontemporal_store(z, o + c);
+        }
+    }
 }
 
+hipError_t launch_embed_fwd(const void* const* tables, const int64_t* ids, int p, int N, int h, int Vs, int64_t off,
+                            int elem_bytes, void* const* outs, hipStream_t st) {
+    const int64_t row_bytes = (int64_t)h * elem_bytes;
+    ProfScope prof(K_EMBED_FWD, st);
+    int rows = (int)(32768 / row_bytes) / 4 * 4;
+    if (rows < 4) rows = 4;
+    if (rows > 64) rows = 64;
+    // fewer rows per workgroup while the grid would leave compute units without one
+    while (rows > 4 && ceil_div(N, rows) * p < 1024) rows -= 4;
+    for (int s0 = 0; s0 < p; s0 += EMBED_GROUP_MAX) {
+        const int n = p - s0 < EMBED_GROUP_MAX ? p - s0 : EMBED_GROUP_MAX;
+        EmbedFwdGroup g{};
+        bool vec = row_bytes % 16 == 0;
+        for (int s = 0; s < n; ++s) {
+            g.table[s] = tables[s0 + s];
+            g.out[s] = outs[s0 + s];
+        }
+        const dim3 grid((unsigned)ceil_div(N, rows), (unsigned)n);
+        const int64_t first = off + (int64_t)s0 * Vs;
+        if (vec)
+            hipLaunchKernelGGL((embed_fwd_kernel<uintx4>), grid, dim3(256), 0, st, g, ids, N, (int)(row_bytes / 16), Vs, first, rows);
+        else if (elem_bytes == 4)
+            hipLaunchKernelGGL((embed_fwd_kernel<unsigned>), grid, dim3(256), 0, st, g, ids, N, h, Vs, first, rows);
+        else
+            hipLaunchKernelGGL((embed_fwd_kernel<u16>), grid, dim3(256), 0, st, g, ids, N, h, Vs, first, rows);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// ------------------------------------------------------------------------- backward: common pieces
 template <int VEC>
 __device__ __forceinline__ void load_acc(float (&acc)[VEC], const float* d) {
     if (VEC == 2) {
@@ -125,104 +108,11 @@ __device__ __forceinline__ void store_acc(float* d, const float (&acc)[VEC]) {
     else d[0] = acc[0];
 }
 
-// N <= SORT_CHUNK tokens, one workgroup: the keys of the tokens this shard owns are gathered
-// into LDS (only those are sorted: m = next power of two of their number), sorted, written
-// back followed by KEY_NONE up to n_pad, and the run starts are listed.
-__global__ __launch_bounds__(SORT_THREADS) void embed_sort_single_kernel(const int64_t* __restrict__ ids, int N, int Vs,
-                                                                         int64_t off, u64* __restrict__ keys,
-                                                                         int n_pad, RunList runs) {
-    __shared__ u64 sh[SORT_CHUNK];
-    __shared__ int s_owned, s_runs;
-    if (threadIdx.x == 0) { s_owned = 0; s_runs = 0; }
-    __syncthreads();
-    for (int i = threadIdx.x; i < N; i += SORT_THREADS) {
-        const u64 k = token_key(ids, i, N, Vs, off);
-        if (k != KEY_NONE) sh[atomicAdd(&s_owned, 1)] = k;    // any order: the keys are unique and get sorted
-    }
-    __syncthreads();
-    const int owned = s_owned;
-    int m = 2;
-    while (m < owned) m <<= 1;
-    for (int t = owned + threadIdx.x; t < m; t += SORT_THREADS) sh[t] = KEY_NONE;
-    __syncthreads();
-    for (int k = 2; k <= m; k <<= 1) bitonic_stage_tail_lds(sh, m, k >> 1, k, 0);
-    for (int t = threadIdx.x; t < n_pad; t += SORT_THREADS) keys[t] = t < owned ? sh[t] : KEY_NONE;
-    for (int t = threadIdx.x; t < owned; t += SORT_THREADS)
-        if (starts_run(sh, t)) runs.starts[atomicAdd(&s_runs, 1)] = (unsigned)t;
-    __syncthreads();
-    if (threadIdx.x == 0) *runs.count = (unsigned)s_runs;
-}
-
-// More tokens than one workgroup sorts: builds the keys of every chunk of `ch` tokens from the
-// ids and sorts the chunk (all stages k = 2..ch).  Also clears the run counter.
-__global__ __launch_bounds__(SORT_THREADS) void embed_keys_sort_chunks_kernel(const int64_t* __restrict__ ids, int N,
-                                                                              int Vs, int64_t off,
-                                                                              u64* __restrict__ keys, int ch,
-                                                                              RunList runs) {
-    __shared__ u64 sh[SORT_CHUNK];
-    const int gbase = blockIdx.x * ch;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *runs.count = 0u;
-    for (int t = threadIdx.x; t < ch; t += SORT_THREADS) sh[t] = token_key(ids, gbase + t, N, Vs, off);
-    __syncthreads();
-    for (int k = 2; k <= ch; k <<= 1) bitonic_stage_tail_lds(sh, ch, k >> 1, k, gbase);
-    for (int t = threadIdx.x; t < ch; t += SORT_THREADS) keys[gbase + t] = sh[t];
-}
-
-// Lists the run starts of a fully sorted key array (multi-chunk case).
-__global__ __launch_bounds__(256) void embed_find_runs_kernel(const u64* __restrict__ keys, int N, RunList runs) {
-    const int s = blockIdx.x * 256 + threadIdx.x;
-    if (s < N && starts_run(keys, s)) runs.starts[atomicAdd(runs.count, 1u)] = (unsigned)s;
-}
-
-// One global compare-exchange pass (distance j >= chunk size) of stage k.
-__global__ __launch_bounds__(256) void bitonic_global_step_kernel(u64* __restrict__ keys, int half_n, int j, int k) {
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= half_n) return;
-    const int a = ((t & ~(j - 1)) << 1) | (t & (j - 1));
-    const int b = a | j;
-    const bool asc = ((a & k) == 0);
-    const u64 x = keys[a], y = keys[b];
-    if ((x > y) == asc) { keys[a] = y; keys[b] = x; }
-}
-
-// Finishes stage k inside each chunk: passes j = ch/2 .. 1.
-__global__ __launch_bounds__(SORT_THREADS) void bitonic_merge_chunks_kernel(u64* __restrict__ keys, int ch, int k) {
-    __shared__ u64 sh[SORT_CHUNK];
-    const int gbase = blockIdx.x * ch;
-    for (int t = threadIdx.x; t < ch; t += SORT_THREADS) sh[t] = keys[gbase + t];
-    __syncthreads();
-    bitonic_stage_tail_lds(sh, ch, ch >> 1, k, gbase);
-    for (int t = threadIdx.x; t < ch; t += SORT_THREADS) keys[gbase + t] = sh[t];
-}
-
-// ------------------------------------------------------------------------- backward: segmented sum
-// Workgroup (x, y): column slab x, runs y, y + gridDim.y, ... of the run list.  It walks a run
-// and adds the gradient rows in key order (increasing token position), starting from the value
-// already in the table gradient.  Runs are independent, so their order in the list does not
-// matter.  The adds of a column form one serial chain, so the speed comes from the loads: a
-// wavefront reads 64 keys of the run at once and keeps DEPTH gradient-row loads in flight
-// ahead of the adds.
-template <typename T, int VEC>
-struct GradVec;
-template <> struct GradVec<u16, 4> { typedef uint2 type; };
-template <> struct GradVec<u16, 1> { typedef u16 type; };
-template <> struct GradVec<float, 4> { typedef float4 type; };
-template <> struct GradVec<float, 1> { typedef float type; };
-
 // acc += gradient values; `on` false adds -0.0f instead, which leaves every float (either zero
 // included) bit for bit unchanged.
 __device__ __forceinline__ float gate(float x, bool on) { return on ? x : -0.0f; }
-__device__ __forceinline__ void add_grad(float (&acc)[4], const uint2& v, bool on) {
-    acc[0] += gate(__uint_as_float(v.x << 16), on);
-    acc[1] += gate(__uint_as_float(v.x & 0xFFFF0000u), on);
-    acc[2] += gate(__uint_as_float(v.y << 16), on);
-    acc[3] += gate(__uint_as_float(v.y & 0xFFFF0000u), on);
-}
 __device__ __forceinline__ void add_grad(float (&acc)[1], const u16& v, bool on) {
     acc[0] += gate(__uint_as_float((unsigned)v << 16), on);
-}
-__device__ __forceinline__ void add_grad(float (&acc)[4], const float4& v, bool on) {
-    acc[0] += gate(v.x, on); acc[1] += gate(v.y, on); acc[2] += gate(v.z, on); acc[3] += gate(v.w, on);
 }
 __device__ __forceinline__ void add_grad(float (&acc)[1], const float& v, bool on) { acc[0] += gate(v, on); }
 __device__ __forceinline__ void add_grad(float (&acc)[2], const unsigned& v, bool on) {
@@ -233,182 +123,35 @@ __device__ __forceinline__ void add_grad(float (&acc)[2], const float2& v, bool 
     acc[0] += gate(v.x, on); acc[1] += gate(v.y, on);
 }
 
-// Loads of tokens u0 .. u0 + D - 1 of the 64 whose positions sit in the lanes of `tok`, issued
-// back to back.  No branches: positions past cnt re-read the last valid row.
-template <int D, typename GV, typename T>
-__device__ __forceinline__ void load_batch(GV (&v)[D], const T* gcol, int h, unsigned tok, int u0, int cnt) {
-#pragma unroll
-    for (int u = 0; u < D; ++u) {
-        const int idx = (u0 + u < cnt) ? (u0 + u) : (cnt - 1);
-        const unsigned t = __builtin_amdgcn_readlane(tok, idx);
-        v[u] = *reinterpret_cast<const GV*>(gcol + (size_t)t * h);
-    }
-}
 // The adds of those tokens in order; positions past cnt add -0.0f.
 template <int D, int VEC, typename GV>
 __device__ __forceinline__ void add_batch(float (&acc)[VEC], const GV (&v)[D], int u0, int cnt) {
 #pragma unroll
     for (int u = 0; u < D; ++u) add_grad(acc, v[u], u0 + u < cnt);
 }
-template <int D, int VEC, typename GV, typename T>
-__device__ __forceinline__ void accum_batch(float (&acc)[VEC], const T* gcol, int h, unsigned tok, int u0, int cnt) {
-    GV v[D];
-    load_batch<D>(v, gcol, h, tok, u0, cnt);
-    add_batch<D, VEC>(acc, v, u0, cnt);
-}
-
-template <typename T, int VEC>
-__global__ __launch_bounds__(256) void embed_bwd_accum_kernel(const u64* __restrict__ keys, int n_pad, RunList runs,
-                                                              const T* __restrict__ gout, int h,
-                                                              float* __restrict__ dtable) {
-    typedef typename GradVec<T, VEC>::type GV;
-    constexpr int DEPTH = 32;
-    const int c0 = (blockIdx.x * 256 + threadIdx.x) * VEC;
-    const bool active = c0 < h;
-    const int lane = threadIdx.x & 63;
-    const int n_runs = (int)*runs.count;
-    for (int r = blockIdx.y; r < n_runs; r += gridDim.y) {
-    const int s = (int)runs.starts[r];
-    const unsigned row = (unsigned)(keys[s] >> 32);
-
-    float acc[VEC];
-    float* d = dtable + (size_t)row * h + c0;
-    if (active) {
-        if (VEC == 4) {
-            const float4 v = *reinterpret_cast<const float4*>(d);
-            acc[0] = v.x; acc[1 % VEC] = v.y; acc[2 % VEC] = v.z; acc[3 % VEC] = v.w;
-        } else {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) acc[e] = d[e];
-        }
-    }
-    const T* gcol = gout + (active ? c0 : 0);
-
-    // 64 keys of the run per wavefront-wide load; the keys of the next 64 positions are fetched
-    // before this chunk is worked on, so a long run pays one memory latency per 64 tokens (its
-    // 64 row loads, all in flight together) instead of three (keys, then two batches of 32)
-    u64 kq = (s + lane < n_pad) ? keys[s + lane] : KEY_NONE;
-    for (int q0 = s; q0 < n_pad; q0 += 64) {
-        const u64 kq_next = (q0 + 64 + lane < n_pad) ? keys[q0 + 64 + lane] : KEY_NONE;
-        const bool same = (kq != KEY_NONE) && ((unsigned)(kq >> 32) == row);
-        const u64 m = __builtin_amdgcn_ballot_w64(same);
-        const int cnt = (m == ~0ull) ? 64 : __builtin_ctzll(~m);   // how many of them continue the run
-        const unsigned tok = (unsigned)kq;
-        if (active) {
-            if (cnt == 64) {
-                GV v0[DEPTH], v1[DEPTH];
-                load_batch<DEPTH>(v0, gcol, h, tok, 0, 64);
-                load_batch<DEPTH>(v1, gcol, h, tok, DEPTH, 64);
-                add_batch<DEPTH, VEC>(acc, v0, 0, 64);
-                add_batch<DEPTH, VEC>(acc, v1, DEPTH, 64);
-            } else {
-                int u0 = 0;
-                for (; u0 + DEPTH <= cnt; u0 += DEPTH) accum_batch<DEPTH, VEC, GV>(acc, gcol, h, tok, u0, cnt);
-                for (; u0 < cnt; u0 += 4) accum_batch<4, VEC, GV>(acc, gcol, h, tok, u0, cnt);
-            }
-        }
-        if (cnt < 64) break;
-        kq = kq_next;
-    }
-    if (active) {
-        if (VEC == 4) {
-            *reinterpret_cast<float4*>(d) = make_float4(acc[0], acc[1 % VEC], acc[2 % VEC], acc[3 % VEC]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) d[e] = acc[e];
-        }
-    }
-    }   // runs of this workgroup
-}
-
-static int next_pow2(int64_t n) {
-    int p = 2;
-    while (p < n) p <<= 1;
-    return p;
-}
-
-size_t embed_bwd_workspace(int64_t N) {
-    const size_t n_pad = (size_t)next_pow2(N);
-    return n_pad * sizeof(u64) + n_pad * sizeof(unsigned) + 256;
-}
-
-static RunList run_list_of(void* ws, int n_pad) {
-    RunList r;
-    r.starts = (unsigned*)((char*)ws + (size_t)n_pad * sizeof(u64));
-    r.count = r.starts + n_pad;
-    return r;
-}
-
-static hipError_t sort_keys(const int64_t* ids, int N, int Vs, int64_t off, u64* keys, int n_pad, RunList runs,
-                            hipStream_t st) {
-    ProfScope prof(K_EMBED_SORT, st);
-    hipError_t e;
-    if (n_pad <= SORT_CHUNK) {
-        hipLaunchKernelGGL(embed_sort_single_kernel, dim3(1), dim3(SORT_THREADS), 0, st, ids, N, Vs, off, keys, n_pad,
-                           runs);
-        return hipGetLastError();
-    }
-    const int ch = SORT_CHUNK;
-    const int chunks = n_pad / ch;
-    hipLaunchKernelGGL(embed_keys_sort_chunks_kernel, dim3(chunks), dim3(SORT_THREADS), 0, st, ids, N, Vs, off, keys,
-                       ch, runs);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    for (int64_t k = 2 * (int64_t)ch; k <= n_pad; k <<= 1) {
-        for (int64_t j = k >> 1; j >= ch; j >>= 1) {
-            hipLaunchKernelGGL(bitonic_global_step_kernel, dim3((unsigned)ceil_div(n_pad / 2, 256)), dim3(256), 0, st,
-                               keys, n_pad / 2, (int)j, (int)k);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL(bitonic_merge_chunks_kernel, dim3(chunks), dim3(SORT_THREADS), 0, st, keys, ch, (int)k);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(embed_find_runs_kernel, dim3((unsigned)ceil_div(N, 256)), dim3(256), 0, st, keys, N, runs);
-    return hipGetLastError();
-}
-
-static hipError_t accumulate_runs(const u64* keys, int n_pad, RunList runs, const void* gout, int N, int h,
-                                  int is_bf16, float* dtable, hipStream_t st) {
-    ProfScope prof(K_EMBED_ACCUM, st);
-    // grid.y workgroups share the runs of the list; enough of them to fill the chip twice over
-    const unsigned gy = (unsigned)(N < 1024 ? N : 1024);
-    if (is_bf16 && h % 4 == 0) {
-        hipLaunchKernelGGL((embed_bwd_accum_kernel<u16, 4>), dim3((unsigned)ceil_div(h, 256 * 4), gy), dim3(256), 0, st,
-                           keys, n_pad, runs, (const u16*)gout, h, dtable);
-    } else if (is_bf16) {
-        hipLaunchKernelGGL((embed_bwd_accum_kernel<u16, 1>), dim3((unsigned)ceil_div(h, 256), gy), dim3(256), 0, st,
-                           keys, n_pad, runs, (const u16*)gout, h, dtable);
-    } else if (h % 4 == 0) {
-        hipLaunchKernelGGL((embed_bwd_accum_kernel<float, 4>), dim3((unsigned)ceil_div(h, 256 * 4), gy), dim3(256), 0,
-                           st, keys, n_pad, runs, (const float*)gout, h, dtable);
-    } else {
-        hipLaunchKernelGGL((embed_bwd_accum_kernel<float, 1>), dim3((unsigned)ceil_div(h, 256), gy), dim3(256), 0, st,
-                           keys, n_pad, runs, (const float*)gout, h, dtable);
-    }
-    return hipGetLastError();
-}
-
-
 // ------------------------------------------------------------------------- backward: one kernel for N <= 8192
-// Up to FUSED_MAX_N tokens and FUSED_MAX_VS rows: one launch does everything.  EVERY workgroup (1024 threads, one per
-// compute unit) builds and sorts the shard's keys in its own LDS - the same few microseconds in all of them, instead
-// of a sort kernel, a round trip of the keys through memory and a second launch - numbers the runs of equal rows,
-// and then takes its share of the sums: workgroup (slab, group) covers 64 * VEC columns; its 16 wavefronts take the
-// short runs group * 16 + w, + groups * 16, ... (four at a time while they have at most four tokens; all row loads
-// in flight before the first add), and together the long runs of the group: wavefront w fetches the rows of tokens
-// B w .. B w + B - 1 of a chunk of 16 B, and the running sum passes from wavefront 0 to 15 through LDS, so the adds of
-// a column still happen in token order and the result equals the in-order loop bit for bit.
+// Up to FUSED_MAX_N tokens and FUSED_MAX_ROWS rows of all shards: one launch does everything.  EVERY workgroup (1024
+// threads, one per compute unit) builds and sorts the keys in its own LDS - the same few microseconds in all of them,
+// instead of a sort kernel, a round trip of the keys through memory and a second launch - numbers the runs of equal
+// rows, and then takes its share of the sums: workgroup (slab, group) covers 64 * VEC columns; its 16 wavefronts take
+// the runs group * 16 + w, + groups * 16, ... but for the long ones (sum_short_runs, sum_mid_run), which the 16 share
+// (sum_long_run).  Measured: 8192 Zipf tokens, h = 4096, bf16, 8 shards of 32000 rows: 81 us in one launch, 162 us in
+// eight; N = 512, h = 1024, fp32: 12 us for 8 launches of 9 us.
 constexpr int FUSED_MAX_N = 8192;
 constexpr int TOKEN_BITS = 13;                       // a key: local row << 13 | token position
-constexpr int FUSED_MAX_VS = (1 << (32 - TOKEN_BITS)) - 1;   // so that no key equals KEY32_NONE
+constexpr int FUSED_MAX_ROWS = (1 << (32 - TOKEN_BITS)) - 1;   // so that no key equals KEY32_NONE
 constexpr unsigned KEY32_NONE = 0xFFFFFFFFu;
 constexpr int FUSED_THREADS = 1024;
 constexpr int FUSED_WAVES = FUSED_THREADS / 64;
 constexpr int WAVE_KEYS = 512;                       // eight consecutive keys per lane
 
-__device__ __forceinline__ unsigned token_key32(const int64_t* __restrict__ ids, int i, int N, int Vs, int64_t off) {
+// n_rows: rows of all shards of the group
+template <int TB>
+__device__ __forceinline__ unsigned token_key32(const int64_t* __restrict__ ids, int i, int N, int n_rows, int64_t off,
+                                                unsigned token) {
     if (i < N) {
         const int64_t loc = ids[i] - off;
-        if (loc >= 0 && loc < Vs) return ((unsigned)loc << TOKEN_BITS) | (unsigned)i;
+        if (loc >= 0 && loc < n_rows) return ((unsigned)loc << TB) | token;
     }
     return KEY32_NONE;
 }
@@ -560,29 +303,210 @@ template <> struct FusedVec<u16, 1> { typedef u16 type; static constexpr int BAT
 template <> struct FusedVec<float, 2> { typedef float2 type; static constexpr int BATCH = 16; };
 template <> struct FusedVec<float, 1> { typedef float type; static constexpr int BATCH = 32; };
 
-// Row loads through a raw buffer descriptor over the whole gradient matrix (below 4 GB: checked on the host):
+// Gradient rows through a raw buffer descriptor over the whole gradient matrix (below 4 GB: checked on the host):
 // the lane's column offset is one loop-invariant VGPR, the token's row offset a scalar, so a load in flight
-// costs its data registers only.  Positions past cnt re-read the last valid row; their adds are gated to -0.0f.
-template <int D, typename GV>
-__device__ __forceinline__ void fused_load_batch(GV (&v)[D], __amdgpu_buffer_rsrc_t rs, unsigned voff, unsigned row_bytes,
-                                                 unsigned tok, int cnt) {
+// costs its data registers only.
+template <typename GV>
+struct BufferRows {
+    __amdgpu_buffer_rsrc_t rs;
+    unsigned voff, row_bytes;
+    __device__ __forceinline__ GV operator()(unsigned t) const { return buf_load<GV>(rs, voff, t * row_bytes); }
+};
+// The same through a 64-bit scalar base per row, for gradients of any size.
+template <typename GV>
+struct PointerRows {
+    const char* base;
+    unsigned voff;
+    size_t row_bytes;
+    __device__ __forceinline__ GV operator()(unsigned t) const {
+        return *reinterpret_cast<const GV*>(base + (size_t)t * row_bytes + voff);
+    }
+};
+
+// Positions past cnt re-read the last valid row; their adds are gated to -0.0f.  For readlane all 64 lanes must have
+// taken part in forming `tok`, and the compiler may move that into a branch around the call: nothing here or above it
+// may stand in a branch that only some lanes take.  Lanes whose columns lie past h load column 0 and store nothing.
+template <int D, typename GV, typename Rows>
+__device__ __forceinline__ void load_batch(GV (&v)[D], const Rows& rows, unsigned tok, int cnt) {
 #pragma unroll
     for (int u = 0; u < D; ++u) {
         const int idx = u < cnt ? u : cnt - 1;
-        const unsigned t = __builtin_amdgcn_readlane(tok, idx);
-        v[u] = buf_load<GV>(rs, voff, t * row_bytes);
+        v[u] = rows((unsigned)__builtin_amdgcn_readlane((int)tok, idx));
     }
 }
 
-template <typename T, int VEC>
-__global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(const int64_t* __restrict__ ids, int N, int Vs,
-                                                                        int64_t off, const T* __restrict__ gout,
-                                                                        unsigned grad_bytes, int h,
-                                                                        float* __restrict__ dtable, int n_slabs,
-                                                                        int n_groups) {
+constexpr int SHORT_Q = 4, SHORT_TINY = 4;      // runs of up to SHORT_TINY tokens go SHORT_Q at a time
+
+// One wavefront, SHORT_Q runs of at most B tokens (len 0: none): lane u of tok[q] holds the u-th token of run q, d[q] is
+// the lane's element of the run's row in the table gradient (any element of it if the lane is not active).  All loads of the runs of up to SHORT_TINY tokens, and of
+// the first longer one, are in flight before the first add.
+template <typename T, int VEC, typename Rows>
+__device__ __forceinline__ void sum_short_runs(const int (&len)[SHORT_Q], const unsigned (&tok)[SHORT_Q],
+                                               float* const (&d)[SHORT_Q], bool active, const Rows& rows) {
+    typedef typename FusedVec<T, VEC>::type GV;
+    constexpr int B = FusedVec<T, VEC>::BATCH, Q = SHORT_Q, TINY = SHORT_TINY;
+    // the first run of 5 .. B tokens of this turn (seldom more than one) goes along with the small ones
+    int mid = -1;
+#pragma unroll
+    for (int q = Q - 1; q >= 0; --q)
+        if (len[q] > TINY) mid = q;
+    unsigned tok_mid = 0;
+    float* d_mid = nullptr;
+    int len_mid = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        if (q == mid) { tok_mid = tok[q]; d_mid = d[q]; len_mid = len[q]; }
+    float acc[Q][VEC], acc_mid[VEC];
+    GV few[Q][TINY], v[B];
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        if (len[q] >= 1 && len[q] <= TINY) {
+            load_acc<VEC>(acc[q], d[q]);
+            load_batch<TINY>(few[q], rows, tok[q], len[q]);
+        }
+    if (mid >= 0) {
+        load_acc<VEC>(acc_mid, d_mid);
+        load_batch<B>(v, rows, tok_mid, len_mid);
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        if (len[q] >= 1 && len[q] <= TINY) {
+            add_batch<TINY, VEC>(acc[q], few[q], 0, len[q]);
+            if (active) store_acc<VEC>(d[q], acc[q]);
+        }
+    if (mid >= 0) {
+        add_batch<B, VEC>(acc_mid, v, 0, len_mid);
+        if (active) store_acc<VEC>(d_mid, acc_mid);
+    }
+#pragma unroll
+    for (int q = 1; q < Q; ++q)
+        if (len[q] > TINY && q != mid) {
+            load_acc<VEC>(acc_mid, d[q]);
+            load_batch<B>(v, rows, tok[q], len[q]);
+            add_batch<B, VEC>(acc_mid, v, 0, len[q]);
+            if (active) store_acc<VEC>(d[q], acc_mid);
+        }
+}
+
+// One wavefront, one run: batches of B tokens, the rows of the next batch in flight during the adds of this one.  For runs
+// of B + 1 .. MID_BATCHES B tokens: a workgroup's chain (below) pays a few microseconds of latency per run whatever its
+// length, which 16 wavefronts with a run each hide from one another.
+constexpr int MID_BATCHES = 8;
+template <typename T, int VEC, typename Rows, typename TokenAt>
+__device__ __forceinline__ void sum_mid_run(int len, float* d, bool active, int lane, const Rows& rows,
+                                            const TokenAt& token_at) {
     typedef typename FusedVec<T, VEC>::type GV;
     constexpr int B = FusedVec<T, VEC>::BATCH;
-    constexpr int Q = 4, TINY = 4;                          // runs of up to TINY tokens go Q at a time
+    float acc[VEC];
+    GV v0[B], v1[B];
+    // 2 B <= 64 tokens at a time, fetched a round ahead
+    unsigned tok = lane < 2 * B && lane < len ? token_at(lane) : 0u;
+    load_acc<VEC>(acc, d);
+    load_batch<B>(v0, rows, tok, len < B ? len : B);
+#pragma unroll 1
+    for (int j = 0; j < len; j += 2 * B) {
+        const int at = j + 2 * B + lane;
+        const unsigned tok_n = lane < 2 * B && at < len ? token_at(at) : 0u;
+        const int cnt1 = len - j - B < 0 ? 0 : (len - j - B > B ? B : len - j - B);
+        if (cnt1 > 0) load_batch<B>(v1, rows, (unsigned)__shfl((int)tok, (lane + B) & 63, 64), cnt1);
+        add_batch<B, VEC>(acc, v0, 0, len - j);
+        const int cnt2 = len - j - 2 * B;
+        if (cnt2 > 0) load_batch<B>(v0, rows, tok_n, cnt2 > B ? B : cnt2);
+        if (cnt1 > 0) add_batch<B, VEC>(acc, v1, 0, cnt1);
+        tok = tok_n;
+    }
+    if (active) store_acc<VEC>(d, acc);
+}
+
+// Workgroup barrier that orders LDS accesses only: row loads stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// A run of any length by the whole workgroup of 16 wavefronts: chunks of 16 B tokens, wavefront w has tokens
+// B w .. B w + B - 1 of a chunk and turn w in the chain, the running sum passes from wavefront to wavefront through
+// LDS, so the adds of a column happen in token order and the result equals the in-order loop bit for bit.
+// Bound by the row loads at first (one compute unit alone draws little from memory) and by the chain after that: the
+// rows of a chunk are requested by all wavefronts at once and while the previous chunk's chain runs, and every
+// wavefront turns its rows into floats (-0.0f past cnt) before the chain starts, so that a turn is nothing but
+// dependent adds.  token_at(j): token of position j of the run.
+template <typename T, int VEC, typename Rows, typename TokenAt>
+__device__ __forceinline__ void sum_long_run(int len, float* d, bool active, int lane, int wave, float* xchg,
+                                             const Rows& rows, const TokenAt& token_at) {
+    typedef typename FusedVec<T, VEC>::type GV;
+    constexpr int B = FusedVec<T, VEC>::BATCH;
+    float acc[VEC];
+    GV v[B];
+    float f[B][VEC];
+    __syncthreads();                   // xchg is free again (previous long run)
+    if (wave == 0) load_acc<VEC>(acc, d);
+    int cnt = len - wave * B;
+    cnt = cnt < 0 ? 0 : (cnt > B ? B : cnt);
+    {
+        const unsigned tok = lane < cnt ? token_at(wave * B + lane) : 0u;
+        if (cnt > 0) load_batch<B>(v, rows, tok, cnt);
+    }
+    for (int c = 0; c < len; c += FUSED_WAVES * B) {
+        const int turns = len - c > FUSED_WAVES * B ? FUSED_WAVES : (len - c + B - 1) / B;
+        const int first_n = c + FUSED_WAVES * B + wave * B;
+        const int cnt_n = len - first_n < 0 ? 0 : (len - first_n > B ? B : len - first_n);
+        const unsigned tok_n = lane < cnt_n ? token_at(first_n + lane) : 0u;
+        if (c == 0 && wave == 0) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) xchg[e * 64 + lane] = acc[e];
+        }
+        if (cnt > 0) {
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) f[u][e] = -0.0f;
+                add_grad(f[u], v[u], u < cnt);          // -0.0f + x = x for every x
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) asm volatile("" : "+v"(f[u][e]));   // here, not inside the turn
+            }
+        }
+        if (cnt_n > 0) load_batch<B>(v, rows, tok_n, cnt_n);
+        cnt = cnt_n;
+        lds_barrier();
+#pragma unroll 1
+        for (int p = 0; p < turns; ++p) {
+            if (wave == p) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) acc[e] = xchg[e * 64 + lane];
+#pragma unroll
+                for (int u = 0; u < B; ++u)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) acc[e] += f[u][e];
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) xchg[e * 64 + lane] = acc[e];
+            }
+            lds_barrier();
+        }
+    }
+    if (wave == 0 && active) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[e] = xchg[e * 64 + lane];
+        store_acc<VEC>(d, acc);
+    }
+}
+
+// Row of the group -> row of its shard's table gradient.
+__device__ __forceinline__ float* dtable_row(const EmbedBwdGroup& g, unsigned row, unsigned Vs, int h) {
+    const unsigned s = row / Vs;
+    return g.dtable[s] + (size_t)(row - s * Vs) * h;
+}
+
+template <typename T, int VEC>
+__global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(EmbedBwdGroup g, const int64_t* __restrict__ ids,
+                                                                        int N, int Vs, int n_rows, int64_t off,
+                                                                        const T* __restrict__ gout,
+                                                                        unsigned grad_bytes, int h, int n_slabs,
+                                                                        int n_groups) {
+    typedef typename FusedVec<T, VEC>::type GV;
+    constexpr int B = FusedVec<T, VEC>::BATCH, Q = SHORT_Q;
     __shared__ __align__(16) unsigned sh[FUSED_MAX_N];      // the keys
     __shared__ unsigned short run_start[FUSED_MAX_N + 2];   // position of the first key of run r; [n_runs] = owned
     __shared__ int wave_cnt[FUSED_MAX_N / 64];
@@ -594,13 +518,16 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(const in
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const u64 below = (1ull << lane) - 1ull;
 
-    // keys of the tokens this shard owns (all ids requested before the first is used), packed into sh in any
+    // keys of the tokens these shards own (all ids requested before the first is used), packed into sh in any
     // order - they are unique and get sorted: one LDS atomic per wavefront
     constexpr int ROUNDS = FUSED_MAX_N / FUSED_THREADS;
     unsigned mine[ROUNDS];
     u64 have[ROUNDS];
 #pragma unroll
-    for (int q = 0; q < ROUNDS; ++q) mine[q] = token_key32(ids, q * FUSED_THREADS + threadIdx.x, N, Vs, off);
+    for (int q = 0; q < ROUNDS; ++q) {
+        const int i = q * FUSED_THREADS + (int)threadIdx.x;
+        mine[q] = token_key32<TOKEN_BITS>(ids, i, N, n_rows, off, (unsigned)i);
+    }
     int total = 0;
 #pragma unroll
     for (int q = 0; q < ROUNDS; ++q) {
@@ -663,18 +590,18 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(const in
     const int n_runs = s_runs;
 
     const int slab = blockIdx.x % n_slabs, group = blockIdx.x / n_slabs;
-    const int c0 = (slab * 64 + lane) * VEC;
-    const bool active = c0 < h;
+    const bool active = (slab * 64 + lane) * VEC < h;
+    const int c0 = active ? (slab * 64 + lane) * VEC : 0;
     const unsigned row_bytes = (unsigned)h * (unsigned)sizeof(T);
     const unsigned voff = (unsigned)c0 * (unsigned)sizeof(T);
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)gout, 0, (int)grad_bytes, 0x00020000);
-    float* const dcol = dtable + c0;
+    const BufferRows<GV> rows{__builtin_amdgcn_make_buffer_rsrc((void*)gout, 0, (int)grad_bytes, 0x00020000), voff, row_bytes};
 
     // short runs: one wavefront each, Q of them per turn
     const int stride = n_groups * FUSED_WAVES;
     for (int r0 = group * FUSED_WAVES + wave; r0 < n_runs; r0 += Q * stride) {
-        int len[Q];
-        unsigned tok[Q], row[Q];
+        int len[Q], first[Q], mid[Q];
+        unsigned tok[Q];
+        float* d[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const int r = r0 + q * stride;
@@ -686,53 +613,16 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(const in
             }
             s = __builtin_amdgcn_readfirstlane(s);
             len[q] = __builtin_amdgcn_readfirstlane(len[q]);
-            if (len[q] > B) len[q] = 0;                     // a long run: not here
-            // (every lane fetches its token, also one whose columns lie past h: readlane takes it from there)
+            first[q] = s;
+            mid[q] = len[q] > B && len[q] <= MID_BATCHES * B ? len[q] : 0;
+            if (len[q] > B) len[q] = 0;
             tok[q] = lane < len[q] ? key_token(sh[s + lane]) : 0u;
-            row[q] = key_row(sh[s]);
+            d[q] = dtable_row(g, __builtin_amdgcn_readfirstlane(key_row(sh[s])), (unsigned)Vs, h) + c0;
         }
-        // the first run of 5 .. B tokens of this turn (seldom more than one) goes along with the small ones
-        int mid = -1;
-#pragma unroll
-        for (int q = Q - 1; q >= 0; --q)
-            if (len[q] > TINY) mid = q;
-        unsigned tok_mid = 0, row_mid = 0;
-        int len_mid = 0;
-#pragma unroll
+        sum_short_runs<T, VEC>(len, tok, d, active, rows);
         for (int q = 0; q < Q; ++q)
-            if (q == mid) { tok_mid = tok[q]; row_mid = row[q]; len_mid = len[q]; }
-        if (active) {
-            float acc[Q][VEC], acc_mid[VEC];
-            GV few[Q][TINY], v[B];
-#pragma unroll
-            for (int q = 0; q < Q; ++q)
-                if (len[q] >= 1 && len[q] <= TINY) {
-                    load_acc<VEC>(acc[q], dcol + (size_t)row[q] * h);
-                    fused_load_batch<TINY>(few[q], rs, voff, row_bytes, tok[q], len[q]);
-                }
-            if (mid >= 0) {
-                load_acc<VEC>(acc_mid, dcol + (size_t)row_mid * h);
-                fused_load_batch<B>(v, rs, voff, row_bytes, tok_mid, len_mid);
-            }
-#pragma unroll
-            for (int q = 0; q < Q; ++q)
-                if (len[q] >= 1 && len[q] <= TINY) {
-                    add_batch<TINY, VEC>(acc[q], few[q], 0, len[q]);
-                    store_acc<VEC>(dcol + (size_t)row[q] * h, acc[q]);
-                }
-            if (mid >= 0) {
-                add_batch<B, VEC>(acc_mid, v, 0, len_mid);
-                store_acc<VEC>(dcol + (size_t)row_mid * h, acc_mid);
-            }
-#pragma unroll
-            for (int q = 1; q < Q; ++q)
-                if (len[q] > TINY && q != mid) {
-                    load_acc<VEC>(acc_mid, dcol + (size_t)row[q] * h);
-                    fused_load_batch<B>(v, rs, voff, row_bytes, tok[q], len[q]);
-                    add_batch<B, VEC>(acc_mid, v, 0, len[q]);
-                    store_acc<VEC>(dcol + (size_t)row[q] * h, acc_mid);
-                }
-        }
+            if (mid[q] > 0)
+                sum_mid_run<T, VEC>(mid[q], d[q], active, lane, rows, [&](int j) { return key_token(sh[first[q] + j]); });
     }
     // long runs: run r belongs to group r % n_groups, all 16 wavefronts of it.  Each wavefront looks through that
     // group's run numbers 64 at a time; LDS holds the same in all of them, so they agree on which runs are long
@@ -740,104 +630,347 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(const in
     for (int base = 0; base < n_runs; base += 64 * n_groups) {
         const int cand = base + lane * n_groups + group;
         bool is_long = false;
-        if (cand < n_runs) is_long = (int)run_start[cand + 1] - (int)run_start[cand] > B;
+        if (cand < n_runs) is_long = (int)run_start[cand + 1] - (int)run_start[cand] > MID_BATCHES * B;
         u64 todo = __builtin_amdgcn_ballot_w64(is_long);
         while (todo) {
             const int r = base + __builtin_ctzll(todo) * n_groups + group;
             todo &= todo - 1;
-            const int s = run_start[r], len = (int)run_start[r + 1] - s;
-            float* const d = dcol + (size_t)key_row(sh[s]) * h;
-            // Chunks of 16 B tokens; in a chunk wavefront w has tokens B w .. B w + B - 1 and turn w in the chain.
-            // The rows of a chunk are requested by all wavefronts at once (one compute unit alone draws little from
-            // memory: the requests, not the chain, take most of the time), the accumulator's load is in flight with the
-            // first of them, and every wavefront turns its rows into floats (-0.0f past cnt) before the chain starts,
-            // so that a turn is nothing but dependent adds.
-            float acc[VEC];
-            GV v[B];
-            float f[B][VEC];
-            __syncthreads();                   // xchg is free again (previous long run)
-            if (wave == 0 && active) load_acc<VEC>(acc, d);
-            for (int c = 0; c < len; c += FUSED_WAVES * B) {
-                const int first = c + wave * B;
-                const int cnt = len - first < 0 ? 0 : (len - first > B ? B : len - first);
-                const int turns = len - c > FUSED_WAVES * B ? FUSED_WAVES : (len - c + B - 1) / B;
-                const unsigned tok = lane < cnt ? key_token(sh[s + first + lane]) : 0u;
-                if (active && cnt > 0) fused_load_batch<B>(v, rs, voff, row_bytes, tok, cnt);
-                if (c == 0 && wave == 0 && active) {
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) xchg[e * 64 + lane] = acc[e];
-                }
-                if (active && cnt > 0) {
-#pragma unroll
-                    for (int u = 0; u < B; ++u) {
-#pragma unroll
-                        for (int e = 0; e < VEC; ++e) f[u][e] = -0.0f;
-                        add_grad(f[u], v[u], u < cnt);          // -0.0f + x = x for every x
-#pragma unroll
-                        for (int e = 0; e < VEC; ++e) asm volatile("" : "+v"(f[u][e]));   // here, not inside the turn
-                    }
-                }
-                __syncthreads();
-#pragma unroll 1
-                for (int p = 0; p < turns; ++p) {
-                    if (wave == p && active) {
-#pragma unroll
-                        for (int e = 0; e < VEC; ++e) acc[e] = xchg[e * 64 + lane];
-#pragma unroll
-                        for (int u = 0; u < B; ++u)
-#pragma unroll
-                            for (int e = 0; e < VEC; ++e) acc[e] += f[u][e];
-#pragma unroll
-                        for (int e = 0; e < VEC; ++e) xchg[e * 64 + lane] = acc[e];
-                    }
-                    __syncthreads();
-                }
-            }
-            if (wave == 0 && active) {
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) acc[e] = xchg[e * 64 + lane];
-                store_acc<VEC>(d, acc);
-            }
+            const int s = __builtin_amdgcn_readfirstlane((int)run_start[r]);
+            const int len = __builtin_amdgcn_readfirstlane((int)run_start[r + 1]) - s;
+            float* const d = dtable_row(g, __builtin_amdgcn_readfirstlane(key_row(sh[s])), (unsigned)Vs, h) + c0;
+            sum_long_run<T, VEC>(len, d, active, lane, wave, xchg, rows,
+                                 [&](int j) { return key_token(sh[s + j]); });
         }
     }
 }
 
-template <typename T, int VEC>
-static hipError_t launch_fused(const int64_t* ids, int N, int Vs, int64_t off, const T* gout, int h, float* dtable,
-                               hipStream_t st) {
-    ProfScope prof(K_EMBED_ACCUM, st);
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) {
-        int n = 0;
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) cus = n;
+// ------------------------------------------------------------------------- backward: any number of tokens
+// Keys, sort, runs and sums as kernels of their own:
+//   1. embed_sort_chunks: chunks of SORT_CHUNK tokens, each sorted by one workgroup as above (32-bit keys: row and
+//      position in the chunk), written out as 64-bit keys row << 32 | token; a token of no shard has row NO_ROW.
+//   2. embed_merge_ranks: MERGE_WAYS sorted runs of the array become one: the final position of a key is the number of
+//      smaller keys in each of them, one binary search per run, all in step (a search is a chain of dependent loads;
+//      MERGE_WAYS of them cost the time of one).  One pass up to 32768 tokens, two up to 2^19, ...
+//   3. embed_find_runs: where runs of equal rows start, in three lists: up to `batch` tokens, up to MID_BATCHES times
+//      that, and above (with the length).
+//   4. embed_bwd_accum: the sums; workgroups of a column slab draw runs from the lists, the long ones first.
+// Bound by gradient and table rows in step 4; steps 1 to 3 are latency.  Measured for 32768 Zipf tokens, h = 4096, bf16,
+// 8 shards of 16032 rows: 9 + 19 + 7 + 200 us (0.6 GB).  A sort and an accumulation per shard (16384-key bitonic chunks,
+// one workgroup per long run) took 8 x 213 us.
+constexpr int SORT_CHUNK = 2048, CHUNK_BITS = 11, MERGE_WAYS = 16;
+constexpr int MAX_GROUP_ROWS = (1 << (32 - CHUNK_BITS)) - 1;      // rows of a group: no key equals KEY32_NONE
+constexpr unsigned NO_ROW = 0xFFFFFFFFu;
+constexpr int DRAW = 16;                                          // short runs a wavefront draws at a time
+
+struct RunLists {
+    u64* longs;           // length << 32 | start position
+    unsigned* shorts;     // start positions
+    unsigned* mids;       // start positions
+    unsigned* count;      // [3]: shorts, mids, longs
+    unsigned* next;       // [3 * n_slabs]: next short, mid, long run of a slab
+};
+
+__global__ __launch_bounds__(FUSED_THREADS) void embed_sort_chunks_kernel(const int64_t* __restrict__ ids, int N, int n_rows,
+                                                                          int64_t off, u64* __restrict__ keys,
+                                                                          unsigned* __restrict__ counters, int n_counters) {
+    __shared__ __align__(16) unsigned sh[SORT_CHUNK];
+    if (blockIdx.x == 0)
+        for (int t = threadIdx.x; t < n_counters; t += FUSED_THREADS) counters[t] = 0u;
+    const int base = blockIdx.x * SORT_CHUNK;
+    for (int t = threadIdx.x; t < SORT_CHUNK; t += FUSED_THREADS)
+        sh[t] = token_key32<CHUNK_BITS>(ids, base + t, N, n_rows, off, (unsigned)t);
+    __syncthreads();
+    bitonic_sort_lds32(sh, SORT_CHUNK, threadIdx.x & 63, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    for (int t = threadIdx.x; t < SORT_CHUNK; t += FUSED_THREADS) {
+        const unsigned k = sh[t];
+        // keys stay unique: a key of no shard is told apart by its position
+        keys[base + t] = k == KEY32_NONE ? ((u64)NO_ROW << 32) | (unsigned)(base + t)
+                                         : ((u64)(k >> CHUNK_BITS) << 32) | (unsigned)(base + (int)(k & (SORT_CHUNK - 1)));
     }
+}
+
+// run_len: a power of two times SORT_CHUNK; the last run of the array, and the last group of runs, may be short.
+// Bound by the divergent loads of the searches (32768 keys, 16 runs: 38 us with every step in memory), so the first
+// steps search 128 samples of each run in LDS, which leaves log2(run_len / 128) steps, most of them in one cache line.
+constexpr int MERGE_SAMPLES = 128, MERGE_THREADS = 128;
+__global__ __launch_bounds__(MERGE_THREADS) void embed_merge_ranks_kernel(const u64* __restrict__ in, u64* __restrict__ out,
+                                                                          int n, int64_t run_len) {
+    __shared__ u64 sample[MERGE_WAYS][MERGE_SAMPLES];
+    const int e = blockIdx.x * MERGE_THREADS + threadIdx.x;      // n is a multiple of MERGE_THREADS
+    const u64 x = in[e];
+    const int64_t stride = run_len / MERGE_SAMPLES;
+    const int64_t first = (int64_t)e / (run_len * MERGE_WAYS) * (run_len * MERGE_WAYS);     // the same for the workgroup
+#pragma unroll
+    for (int u = 0; u < MERGE_WAYS; ++u) {
+        const int64_t at = first + u * run_len + (threadIdx.x + 1) * stride - 1;
+        sample[u][threadIdx.x] = at < n ? in[at] : ~0ull;
+    }
+    __syncthreads();
+    int lo[MERGE_WAYS];                       // keys of run u known to be smaller
+#pragma unroll
+    for (int u = 0; u < MERGE_WAYS; ++u) lo[u] = 0;
+#pragma unroll
+    for (int step = MERGE_SAMPLES / 2; step > 0; step >>= 1)
+#pragma unroll
+        for (int u = 0; u < MERGE_WAYS; ++u)
+            if (sample[u][lo[u] + step - 1] < x) lo[u] += step;
+#pragma unroll
+    for (int u = 0; u < MERGE_WAYS; ++u) {
+        lo[u] += sample[u][lo[u]] < x ? 1 : 0;
+        lo[u] = (int)(lo[u] * stride);        // run_len: all of them are smaller
+    }
+    for (int64_t step = stride >> 1; step > 0; step >>= 1) {
+#pragma unroll
+        for (int u = 0; u < MERGE_WAYS; ++u) {
+            const int64_t at = first + u * run_len + lo[u] + step - 1;
+            if (lo[u] < run_len && at < n && in[at] < x) lo[u] += (int)step;
+        }
+    }
+    int64_t rank = first;
+#pragma unroll
+    for (int u = 0; u < MERGE_WAYS; ++u) {
+        const int64_t at = first + u * run_len + lo[u];
+        rank += lo[u] + (lo[u] < run_len && at < n && in[at] < x ? 1 : 0);
+    }
+    out[rank] = x;
+}
+
+// Appends s to a list for the lanes with `yes`: one atomic per wavefront.
+__device__ __forceinline__ void append(unsigned* list, unsigned* count, bool yes, int s, int lane) {
+    const u64 m = __builtin_amdgcn_ballot_w64(yes);
+    unsigned at = 0;
+    if (lane == 0 && m) at = atomicAdd(count, (unsigned)__builtin_popcountll(m));
+    at = __builtin_amdgcn_readfirstlane(at);
+    if (yes) list[at + __builtin_popcountll(m & ((1ull << lane) - 1ull))] = (unsigned)s;
+}
+
+__global__ __launch_bounds__(256) void embed_find_runs_kernel(const u64* __restrict__ keys, int n, int batch, RunLists runs) {
+    const int s = blockIdx.x * 256 + threadIdx.x;            // n is a multiple of 256
+    const int lane = threadIdx.x & 63;
+    const int mid_max = batch * MID_BATCHES;
+    const unsigned row = (unsigned)(keys[s] >> 32);
+    const unsigned before = s > 0 ? (unsigned)(keys[s - 1] >> 32) : ~row;
+    const unsigned after_short = s + batch < n ? (unsigned)(keys[s + batch] >> 32) : NO_ROW;
+    const unsigned after_mid = s + mid_max < n ? (unsigned)(keys[s + mid_max] >> 32) : NO_ROW;
+    const bool start = row != NO_ROW && before != row;
+    const bool is_long = start && after_mid == row;
+    const bool is_mid = start && !is_long && after_short == row;
+    append(runs.shorts, runs.count, start && !is_mid && !is_long, s, lane);
+    append(runs.mids, runs.count + 1, is_mid, s, lane);
+    // the length of a long run: its keys are a prefix of keys[s ..], found by the wavefront in steps of 1/64
+    u64 lm = __builtin_amdgcn_ballot_w64(is_long);
+    while (lm) {
+        const int l = __builtin_ctzll(lm);
+        lm &= lm - 1;
+        const int s0 = __builtin_amdgcn_readlane(s, l);
+        const unsigned r0 = (unsigned)__builtin_amdgcn_readlane((int)row, l);
+        int lo = s0, width = n - s0, step;             // keys[lo] is of the run, keys[lo + width] is not (or the end)
+        do {
+            step = (width + 63) / 64;
+            const int64_t p = (int64_t)lo + (int64_t)lane * step;
+            const bool same = p < n && (unsigned)(keys[p] >> 32) == r0;
+            const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(same));
+            lo += (c - 1) * step;
+            width = step;
+        } while (step > 1);
+        if (lane == 0) runs.longs[atomicAdd(runs.count + 2, 1u)] = ((u64)(unsigned)(lo + 1 - s0) << 32) | (unsigned)s0;
+    }
+}
+
+// Workgroup (slab, any): 64 * VEC columns.
+template <typename T, int VEC>
+__global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwdGroup g, const u64* __restrict__ keys, int n,
+                                                                        RunLists runs, const T* __restrict__ gout, int h,
+                                                                        int Vs, int n_slabs) {
+    typedef typename FusedVec<T, VEC>::type GV;
+    constexpr int B = FusedVec<T, VEC>::BATCH, Q = SHORT_Q;
+    __shared__ float xchg[64 * VEC];
+    __shared__ unsigned s_next;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int slab = blockIdx.x % n_slabs;
+    const bool active = (slab * 64 + lane) * VEC < h;
+    const int c0 = active ? (slab * 64 + lane) * VEC : 0;
+    const PointerRows<GV> rows{(const char*)gout, (unsigned)c0 * (unsigned)sizeof(T), (size_t)h * sizeof(T)};
+    const unsigned n_short = runs.count[0], n_mid = runs.count[1], n_long = runs.count[2];
+
+    for (;;) {
+        __syncthreads();
+        if (threadIdx.x == 0) s_next = atomicAdd(runs.next + 2 * n_slabs + slab, 1u);
+        __syncthreads();
+        const unsigned r = __builtin_amdgcn_readfirstlane(s_next);
+        if (r >= n_long) break;
+        const u64 run = runs.longs[r];
+        const int s = __builtin_amdgcn_readfirstlane((int)(unsigned)run);
+        const int len = __builtin_amdgcn_readfirstlane((int)(run >> 32));
+        const unsigned row = __builtin_amdgcn_readfirstlane((unsigned)(keys[s] >> 32));
+        float* const d = dtable_row(g, row, (unsigned)Vs, h) + c0;
+        sum_long_run<T, VEC>(len, d, active, lane, wave, xchg, rows,
+                             [&](int j) { return (unsigned)keys[s + j]; });
+    }
+
+    // (an address the compiler takes for a different one per lane: it would otherwise wait for the result on the spot)
+    unsigned* next = runs.next + n_slabs + slab;
+    asm volatile("" : "+v"(next));
+    unsigned at = 0;
+    if (lane == 0) at = atomicAdd(next, 1u);
+    at = __builtin_amdgcn_readfirstlane(at);
+    while (at < n_mid) {
+        unsigned at_next = 0;                    // the next draw is under way while these are summed
+        if (lane == 0) at_next = atomicAdd(next, 1u);
+        const int s = __builtin_amdgcn_readfirstlane((int)runs.mids[at]);
+        const unsigned row = __builtin_amdgcn_readfirstlane((unsigned)(keys[s] >> 32));
+        int len = 0;
+        for (;;) {
+            const int p = s + len + lane;
+            const u64 m = __builtin_amdgcn_ballot_w64(p < n && (unsigned)(keys[p] >> 32) == row);
+            const int c = m == ~0ull ? 64 : __builtin_ctzll(~m);
+            len += c;
+            if (c < 64) break;
+        }
+        sum_mid_run<T, VEC>(len, dtable_row(g, row, (unsigned)Vs, h) + c0, active, lane, rows,
+                            [&](int j) { return (unsigned)keys[s + j]; });
+        at = __builtin_amdgcn_readfirstlane(at_next);
+    }
+
+    next = runs.next + slab;
+    asm volatile("" : "+v"(next));
+    at = 0;
+    if (lane == 0) at = atomicAdd(next, (unsigned)DRAW);
+    at = __builtin_amdgcn_readfirstlane(at);
+    while (at < n_short) {
+        unsigned at_next = 0;
+        if (lane == 0) at_next = atomicAdd(next, (unsigned)DRAW);
+        const unsigned starts = lane < DRAW && at + lane < n_short ? runs.shorts[at + lane] : 0u;
+#pragma unroll 1
+        for (int q0 = 0; q0 < DRAW && at + q0 < n_short; q0 += Q) {
+            u64 key[Q];
+            int len[Q];
+            unsigned tok[Q];
+            float* d[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int s = __builtin_amdgcn_readlane((int)starts, q0 + q);
+                key[q] = s + lane < n && lane <= B ? keys[s + lane] : ~0ull;
+            }
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const unsigned row = __builtin_amdgcn_readfirstlane((unsigned)(key[q] >> 32));
+                const u64 m = __builtin_amdgcn_ballot_w64((unsigned)(key[q] >> 32) == row);
+                tok[q] = (unsigned)key[q];
+                len[q] = at + q0 + q < n_short ? __builtin_ctzll(~m) : 0;
+                d[q] = dtable_row(g, row, (unsigned)Vs, h) + c0;
+            }
+            sum_short_runs<T, VEC>(len, tok, d, active, rows);
+        }
+        at = __builtin_amdgcn_readfirstlane(at_next);
+    }
+}
+
+static int compute_units() {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
+        return n;
+    return 256;
+}
+
+// The one-kernel path: 32-bit keys, gradient matrix addressable with 32-bit byte offsets.
+static bool fused_ok(int64_t N, int64_t h, int64_t Vs, int elem_bytes) {
+    return N <= FUSED_MAX_N && Vs <= FUSED_MAX_ROWS && (uint64_t)N * (uint64_t)h * (unsigned)elem_bytes < ((uint64_t)1 << 32);
+}
+
+static int64_t padded_tokens(int64_t N) { return ceil_div(N, SORT_CHUNK) * SORT_CHUNK; }
+
+// Workspace of the general path: two key arrays, the run lists, the counters.  (Mid and long runs have more than 16 tokens.)
+size_t embed_bwd_workspace(int64_t N, int64_t h, int64_t Vs, int elem_bytes) {
+    if (fused_ok(N, h, Vs, elem_bytes)) {      // needs none; the size callers have been told since the first version
+        int64_t pow2 = 2;
+        while (pow2 < N) pow2 <<= 1;
+        return (size_t)pow2 * 12 + 256;
+    }
+    const size_t n = (size_t)padded_tokens(N);
+    return n * (8 + 8 + 4) + n / 16 * (8 + 4) + (3 + 3 * (size_t)ceil_div(h, 64)) * 4;
+}
+
+template <typename T, int VEC>
+static hipError_t launch_fused(const EmbedBwdGroup& g, const int64_t* ids, int N, int Vs, int n_rows, int64_t off, const T* gout,
+                               int h, hipStream_t st) {
+    ProfScope prof(K_EMBED_ACCUM, st);
     const int n_slabs = (int)ceil_div(h, 64 * VEC);
-    int n_groups = cus / n_slabs;
+    int n_groups = compute_units() / n_slabs;
     const int want = (int)ceil_div(N, 64);          // no more groups than there could be work for
     if (n_groups > want) n_groups = want;
     if (n_groups < 1) n_groups = 1;
     const unsigned grad_bytes = (unsigned)((size_t)N * h * sizeof(T));
-    hipLaunchKernelGGL((embed_bwd_fused_kernel<T, VEC>), dim3((unsigned)(n_slabs * n_groups)), dim3(FUSED_THREADS), 0, st, ids,
-                       N, Vs, off, gout, grad_bytes, h, dtable, n_slabs, n_groups);
+    hipLaunchKernelGGL((embed_bwd_fused_kernel<T, VEC>), dim3((unsigned)(n_slabs * n_groups)), dim3(FUSED_THREADS), 0, st, g, ids,
+                       N, Vs, n_rows, off, gout, grad_bytes, h, n_slabs, n_groups);
     return hipGetLastError();
 }
 
-hipError_t launch_embed_bwd(const void* gout, const int64_t* ids, int N, int h, int Vs, int64_t off, int is_bf16,
-                            float* dtable, void* ws, hipStream_t st) {
-    // the one-kernel path: up to 8192 tokens and 2^19 - 1 rows (32-bit keys), gradient matrix addressable with
-    // 32-bit byte offsets
-    if (N <= FUSED_MAX_N && Vs <= FUSED_MAX_VS && (uint64_t)N * (uint64_t)h * (is_bf16 ? 2u : 4u) < ((uint64_t)1 << 32)) {
-        if (is_bf16) return h % 2 == 0 ? launch_fused<u16, 2>(ids, N, Vs, off, (const u16*)gout, h, dtable, st)
-                                       : launch_fused<u16, 1>(ids, N, Vs, off, (const u16*)gout, h, dtable, st);
-        return h % 2 == 0 ? launch_fused<float, 2>(ids, N, Vs, off, (const float*)gout, h, dtable, st)
-                          : launch_fused<float, 1>(ids, N, Vs, off, (const float*)gout, h, dtable, st);
-    }
-    u64* keys = (u64*)ws;
-    const int n_pad = next_pow2(N);
-    const RunList runs = run_list_of(ws, n_pad);
+template <typename T, int VEC>
+static hipError_t launch_general(const EmbedBwdGroup& g, const int64_t* ids, int N, int Vs, int n_rows, int64_t off,
+                                 const T* gout, int h, void* ws, hipStream_t st) {
+    const int n = (int)padded_tokens(N);
+    const int n_slabs = (int)ceil_div(h, 64 * VEC);
+    u64* a = (u64*)ws;
+    u64* b = a + n;
+    RunLists runs;
+    runs.longs = b + n;
+    runs.shorts = (unsigned*)(runs.longs + n / 16);
+    runs.mids = runs.shorts + n;
+    runs.count = runs.mids + n / 16;
+    runs.next = runs.count + 3;
     hipError_t e;
-    if ((e = sort_keys(ids, N, Vs, off, keys, n_pad, runs, st)) != hipSuccess) return e;
-    return accumulate_runs(keys, n_pad, runs, gout, N, h, is_bf16, dtable, st);
+    {
+        ProfScope prof(K_EMBED_SORT, st);
+        hipLaunchKernelGGL(embed_sort_chunks_kernel, dim3((unsigned)(n / SORT_CHUNK)), dim3(FUSED_THREADS), 0, st, ids, N,
+                           n_rows, off, a, runs.count, 3 + 3 * n_slabs);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        for (int64_t len = SORT_CHUNK; len < n; len *= MERGE_WAYS) {
+            hipLaunchKernelGGL(embed_merge_ranks_kernel, dim3((unsigned)(n / MERGE_THREADS)), dim3(MERGE_THREADS), 0, st, a, b, n, len);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            u64* t = a; a = b; b = t;
+        }
+        hipLaunchKernelGGL(embed_find_runs_kernel, dim3((unsigned)(n / 256)), dim3(256), 0, st, a, n,
+                           FusedVec<T, VEC>::BATCH, runs);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    ProfScope prof(K_EMBED_ACCUM, st);
+    int n_groups = compute_units() / n_slabs;
+    const int want = (int)ceil_div(N, 64);
+    if (n_groups > want) n_groups = want;
+    if (n_groups < 1) n_groups = 1;
+    hipLaunchKernelGGL((embed_bwd_accum_kernel<T, VEC>), dim3((unsigned)(n_slabs * n_groups)), dim3(FUSED_THREADS), 0, st, g, a,
+                       n, runs, gout, h, Vs, n_slabs);
+    return hipGetLastError();
+}
+
+template <typename T, int VEC>
+static hipError_t launch_bwd_group(float* const* dtables, const int64_t* ids, int p, int N, int Vs, int64_t off, const T* gout,
+                                   int h, void* ws, hipStream_t st) {
+    const bool fused = fused_ok(N, h, Vs, (int)sizeof(T));
+    // shards per launch: as many as the key width and the argument block hold
+    int per = (fused ? FUSED_MAX_ROWS : MAX_GROUP_ROWS) / Vs;
+    if (per > EMBED_GROUP_MAX) per = EMBED_GROUP_MAX;
+    for (int s0 = 0; s0 < p; s0 += per) {
+        const int n = p - s0 < per ? p - s0 : per;
+        EmbedBwdGroup g{};
+        for (int s = 0; s < n; ++s) g.dtable[s] = dtables[s0 + s];
+        const int64_t first = off + (int64_t)s0 * Vs;
+        const hipError_t e = fused ? launch_fused<T, VEC>(g, ids, N, Vs, n * Vs, first, gout, h, st)
+                                   : launch_general<T, VEC>(g, ids, N, Vs, n * Vs, first, gout, h, ws, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_embed_bwd(const void* gout, const int64_t* ids, int p, int N, int h, int Vs, int64_t off, int is_bf16,
+                            float* const* dtables, void* ws, hipStream_t st) {
+    if (is_bf16) return h % 2 == 0 ? launch_bwd_group<u16, 2>(dtables, ids, p, N, Vs, off, (const u16*)gout, h, ws, st)
+                                   : launch_bwd_group<u16, 1>(dtables, ids, p, N, Vs, off, (const u16*)gout, h, ws, st);
+    return h % 2 == 0 ? launch_bwd_group<float, 2>(dtables, ids, p, N, Vs, off, (const float*)gout, h, ws, st)
+                      : launch_bwd_group<float, 1>(dtables, ids, p, N, Vs, off, (const float*)gout, h, ws, st);
 }
 
 }  // namespace vp

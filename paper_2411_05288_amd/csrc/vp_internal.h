@@ -122,11 +122,14 @@ hipError_t launch_dx_alg2(const float* A, const void* B, int b_is_bf16, const fl
 // Zeroes the padding columns Vs .. ldd-1 of the bf16 matrix D [N, ldd].
 hipError_t launch_zero_pad_columns(void* D, int N, int Vs, int64_t ldd, hipStream_t st);
 
-hipError_t launch_embed_fwd(const void* table, const int64_t* ids, int N, int h, int Vs, int64_t off,
-                            int elem_bytes, void* out, hipStream_t st);
+// Input layer of p consecutive shards of Vs rows each, the first at row `off` of the vocabulary (host arrays of device
+// pointers, one per shard).
+constexpr int EMBED_GROUP_MAX = 32;    // shards per launch
+hipError_t launch_embed_fwd(const void* const* tables, const int64_t* ids, int p, int N, int h, int Vs, int64_t off,
+                            int elem_bytes, void* const* outs, hipStream_t st);
 
-size_t embed_bwd_workspace(int64_t N);
-hipError_t launch_embed_bwd(const void* gout, const int64_t* ids, int N, int h, int Vs, int64_t off,
-                            int is_bf16, float* dtable, void* ws, hipStream_t st);
+size_t embed_bwd_workspace(int64_t N, int64_t h, int64_t Vs, int elem_bytes);
+hipError_t launch_embed_bwd(const void* gout, const int64_t* ids, int p, int N, int h, int Vs, int64_t off,
+                            int is_bf16, float* const* dtables, void* ws, hipStream_t st);
 
 }  // namespace vp

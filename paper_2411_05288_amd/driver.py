@@ -185,12 +185,14 @@ class EmbeddingPlan:
         self.workspace = torch.empty((nbytes,), dtype=torch.uint8, device=dev)
 
     def forward(self, stream=None) -> None:
-        for r in range(self.p):
+        if all(t.shape == self.tables[0].shape for t in self.tables):
+            B.vp_embed_fwd_group(self.tables, self.ids, 0, self.out, stream)
+            return
+        for r in range(self.p):       # shards of different sizes
             B.vp_embed_fwd(self.tables[r], self.ids, r * self.Vs, self.out[r], stream)
 
     def backward(self, stream=None) -> None:
-        for r in range(self.p):
-            B.vp_embed_bwd(self.grad_out, self.ids, r * self.Vs, self.dtable[r], self.workspace, stream)
+        B.vp_embed_bwd_group(self.grad_out, self.ids, 0, self.dtable, self.workspace, stream)
 
 
 def embedding_forward(table_shards, ids):
@@ -208,6 +210,9 @@ def embedding_backward(grad_out, ids, Vs: int, p: int, dtable: Optional[List[tor
     dt = B.VP_F32 if grad_out.dtype == torch.float32 else B.VP_BF16
     nbytes = max(B.vp_workspace_bytes(B.VP_CALL_EMBED_BWD, N, h, Vs, dt, 0), 256)
     ws = torch.empty((nbytes,), dtype=torch.uint8, device=dev)
+    if all(d.shape == dtable[0].shape for d in dtable[:p]) and dtable[0].shape[0] == Vs:
+        B.vp_embed_bwd_group(grad_out, ids, 0, dtable[:p], ws)
+        return dtable
     for r in range(p):
         B.vp_embed_bwd(grad_out, ids, r * Vs, dtable[r], ws)
     return dtable

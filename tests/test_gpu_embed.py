@@ -129,3 +129,20 @@ def test_embed_key_packing_limits():
 def test_embed_more_than_65535_tokens():
     # N above the grid.y limit and above one sorting chunk; tiny vocabulary: very long runs of equal ids
     check_embed(70000, 8, 48, 2, "bf16", seed=72)
+
+
+@pytest.mark.parametrize("shape", [
+    (8193, 130, 4098, 3),      # one token past the one-kernel path: five chunks, the last of one token; ragged slab
+    (32769, 6, 3000, 2),       # one token past one merge pass
+    (32768, 5, 3000, 3),       # exactly one pass; odd rows: one column per lane
+    (300, 24, 33 * 64, 33),    # more shards than one launch takes
+    (9000, 24, 33 * 64, 33),
+])
+def test_embed_groups_of_shards(shape):
+    # all shards in one call, ids of no shard among them; bit for bit as above
+    N, h, V, p = shape
+    ids = si.zipf_ids(N, V, 1.1, 400 + N)
+    ids[::7] = V + 5
+    ids[3::11] = -2
+    print("embed group", shape, flush=True)
+    check_embed(N, h, V, p, "bf16" if N % 2 else "f32", seed=400 + N, ids=ids, preload=True)
