@@ -127,15 +127,18 @@ def gemm_roofline(cfg, kernels):
     if not names:
         return None
     dom = max(names, key=lambda k: kernels[k]["ms_per_step"])
-    flops_per_launch = 2.0 * cfg.N * cfg.h * cfg.Vs
+    # a launch serves several shards: what one step computes, over the launches it takes
+    shards = cfg.p / kernels[dom]["launches_per_step"]
+    flops_per_launch = 2.0 * cfg.N * cfg.h * cfg.Vs * shards
     ach = flops_per_launch / (kernels[dom]["ms_per_launch"] * 1e-3) / 1e12
-    pmc = PMC_KIB.get(cfg.name, {}).get(dom)
+    pmc = PMC_KIB.get(cfg.name, {}).get(dom) if shards == 1 else None       # counters of launches of one shard
     traffic = None if pmc is None else (PMC_FETCH_FACTOR * pmc[0] + PMC_WRITE_FACTOR * pmc[1]) * 1024.0
     # algorithmic bytes of one launch: both operands read once, the output written once (dH += also reads it)
-    ab = {"gemm_bf16_fwd_stats": 2.0 * (cfg.N * cfg.h + cfg.Vs * cfg.h) + (2.0 * cfg.N * cfg.Vs if cfg.save_logits else 0.0),
-          "gemm_bf16_dlogits": 2.0 * (cfg.N * cfg.h + cfg.Vs * cfg.h) + 2.0 * cfg.N * cfg.Vs,
-          "gemm_bf16_dH": 2.0 * (cfg.N * cfg.Vs + cfg.Vs * cfg.h) + 8.0 * cfg.N * cfg.h,
-          "gemm_bf16_dW": 2.0 * (cfg.N * cfg.Vs + cfg.N * cfg.h) + 4.0 * cfg.Vs * cfg.h}.get(dom)
+    N, h, V = cfg.N, cfg.h, cfg.Vs * shards
+    ab = {"gemm_bf16_fwd_stats": 2.0 * (N * h + V * h) + (2.0 * N * V if cfg.save_logits else 0.0),
+          "gemm_bf16_dlogits": 2.0 * (N * h + V * h) + 2.0 * N * V,
+          "gemm_bf16_dH": 2.0 * (N * V + V * h) + 4.0 * N * h,
+          "gemm_bf16_dW": 2.0 * (N * V + N * h) + 4.0 * V * h}.get(dom)
     return {"bound": "mfma", "kernel": dom, "achieved": ach, "peak": BF16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
             "frac": ach / BF16_MFMA_PEAK_TFLOPS, "flops_per_launch": flops_per_launch,
             "avg_launch_ms": kernels[dom]["ms_per_launch"], "traffic": traffic, "traffic_unit": "bytes per launch",
@@ -206,10 +209,10 @@ def bench_embedding(vp, cfg, steps, warmup):
         "unique_ids": uniq, "kernels": kern,
         # dominant kernel of the input layer: the gather (algorithmic bytes of one shard over its launch time)
         "roofline": {"bound": "hbm", "kernel": "embed_fwd",
-                     "achieved": fwd_bytes / cfg.p / (kern["embed_fwd"]["ms_per_launch"] * 1e-3) / 1e9,
+                     "achieved": fwd_bytes / (kern["embed_fwd"]["ms_per_step"] * 1e-3) / 1e9,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": fwd_bytes / cfg.p / (kern["embed_fwd"]["ms_per_launch"] * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                     "bytes_per_launch": fwd_bytes / cfg.p, "avg_launch_ms": kern["embed_fwd"]["ms_per_launch"],
+                     "frac": fwd_bytes / (kern["embed_fwd"]["ms_per_step"] * 1e-3) / 1e9 / HBM_PEAK_GBS,
+                     "bytes_per_launch": fwd_bytes / kern["embed_fwd"]["launches_per_step"], "avg_launch_ms": kern["embed_fwd"]["ms_per_launch"],
                      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 per launch (profiles/input_layer_cfg5_embedding.txt)
                      "traffic": (2.0 * 2524.4 + 65564.3) * 1024.0, "traffic_unit": "bytes per launch",
                      "traffic_kind": "L2-miss / fabric bytes (2.0 x FETCH_SIZE + WRITE_SIZE)",
@@ -266,7 +269,7 @@ def gemm_timeline(vp, cfg, reps=3):
     for _ in range(2):
         pl.step()
     torch.cuda.synchronize()
-    buf = torch.zeros(8 + 256 * 64 * 8, dtype=torch.int64, device="cuda")
+    buf = torch.zeros(8 + 256 * 160 * 8, dtype=torch.int64, device="cuda")
     runs = ["gemm_bf16_fwd_stats", "gemm_bf16_dH", "gemm_bf16_dW"]
     if not cfg.save_logits:
         runs.insert(1, "gemm_bf16_dlogits")

@@ -200,6 +200,27 @@ vp_status vp_output_dx_alg2(const float* A, const void* B,
                             float* dH_accum, void* stream);
 
 /*
+ * vp_output_fwd / vp_output_bwd for p shards that live on one device, in as few launches as possible: shard r owns the
+ * rows[r] >= 1 vocabulary rows from shard_offsets[r] on.  W_shards, logits_out, logits_saved and dW_shards are HOST arrays
+ * of p device pointers, rows and shard_offsets HOST arrays; all are read before the call returns.  The statistics are
+ * [p, N].  vp_output_bwd_group adds every shard's term to dH_accum in ascending order of the vocabulary (with
+ * VP_DH_OVERWRITE: writes their sum).  Checks, statistics, logits and dW are those of p single calls; dH may differ from
+ * theirs in the order of its fp32 sums.  The workspace is that of vp_output_group_workspace_bytes (VP_CALL_OUTPUT_FWD or
+ * VP_CALL_OUTPUT_BWD; (size_t)-1 on invalid arguments).
+ */
+size_t vp_output_group_workspace_bytes(vp_call which, int32_t p, int64_t N, int64_t h, const int64_t* rows, vp_dtype dt,
+                                       uint32_t flags);
+vp_status vp_output_fwd_group(const void* H, const void* const* W_shards, const int64_t* rows,
+                              const int64_t* shard_offsets, int32_t p, const int64_t* labels, int64_t N, int64_t h,
+                              vp_dtype dt, uint32_t flags, float* local_max, float* local_sumexp, float* local_target,
+                              void* const* logits_out, void* workspace, size_t workspace_bytes, void* stream);
+vp_status vp_output_bwd_group(const void* H, const void* const* W_shards, const int64_t* rows,
+                              const int64_t* shard_offsets, int32_t p, const int64_t* labels, int64_t N, int64_t h,
+                              vp_dtype dt, uint32_t flags, const float* global_max, const float* global_sumexp,
+                              const void* const* logits_saved, float grad_scale, float* dH_accum,
+                              float* const* dW_shards, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * Input layer forward on one shard (appendix C): the full-size [N,h] output, row i being
  * table_shard[ids[i] - shard_offset] when the shard owns ids[i] and all +0 otherwise, so
  * that the sum over shards is the embedding lookup.  Pure data movement, bit exact.

@@ -68,6 +68,12 @@ def load_library() -> ctypes.CDLL:
     lib.vp_combine_stats.argtypes = [vp, vp, vp, i32, i64, vp, vp, vp, vp, vp]
     lib.vp_output_bwd.restype = c.c_int
     lib.vp_output_bwd.argtypes = [vp, vp, vp, i64, i64, i64, i64, c.c_int, u32, vp, vp, vp, fl, vp, vp, vp, sz, vp]
+    lib.vp_output_group_workspace_bytes.restype = sz
+    lib.vp_output_group_workspace_bytes.argtypes = [c.c_int, i32, i64, i64, vp, c.c_int, u32]
+    lib.vp_output_fwd_group.restype = c.c_int
+    lib.vp_output_fwd_group.argtypes = [vp, vp, vp, vp, i32, vp, i64, i64, c.c_int, u32, vp, vp, vp, vp, vp, sz, vp]
+    lib.vp_output_bwd_group.restype = c.c_int
+    lib.vp_output_bwd_group.argtypes = [vp, vp, vp, vp, i32, vp, i64, i64, c.c_int, u32, vp, vp, vp, fl, vp, vp, vp, sz, vp]
     lib.vp_output_fwd_alg2.restype = c.c_int
     lib.vp_output_fwd_alg2.argtypes = [vp, vp, vp, i64, i64, i64, i64, c.c_int, u32, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.vp_output_dx_alg2.restype = c.c_int
@@ -252,6 +258,74 @@ def vp_output_bwd(H, W_shard, labels, shard_offset: int, global_max, global_sume
         _ptr(dH_accum, "dH_accum", f, (N, h)), _ptr(dW_shard, "dW_shard", f, (Vs, h)),
         wp, wb, _stream(stream))
     _check(st, "vp_output_bwd")
+
+
+def _i64s(xs):
+    return (ctypes.c_int64 * len(xs))(*xs)
+
+
+def vp_output_group_workspace_bytes(which: int, N: int, h: int, rows, dt: int, flags: int = 0) -> int:
+    n = load_library().vp_output_group_workspace_bytes(which, len(rows), N, h, _i64s(rows), dt, flags)
+    if n == ctypes.c_size_t(-1).value:
+        raise VPError("vp_output_group_workspace_bytes: invalid arguments")
+    return n
+
+
+def _shards(H, W_shards, offsets):
+    """dtype code and row counts of the shards of a group call."""
+    dt = _dtype_code(H)
+    if len(offsets) != len(W_shards):
+        raise VPError("one offset per shard")
+    for w in W_shards:
+        if _dtype_code(w) != dt or w.shape[1] != H.shape[1]:
+            raise VPError("W_shards must be [rows, h] with the dtype of H")
+    return dt, [int(w.shape[0]) for w in W_shards]
+
+
+def _each(ts, name, dtypes, shapes):
+    if ts is None:
+        return None
+    if len(ts) != len(shapes):
+        raise VPError("%s: one tensor per shard" % name)
+    return (ctypes.c_void_p * len(ts))(*[_ptr(t, name, dtypes, s) for t, s in zip(ts, shapes)])
+
+
+def vp_output_fwd_group(H, W_shards, labels, shard_offsets, local_max, local_sumexp, local_target, logits_out=None,
+                        workspace=None, stream=None) -> None:
+    """vp_output_fwd for several shards on this device in one call; the statistics are [p, N]."""
+    N, h = H.shape
+    dt, rows = _shards(H, W_shards, shard_offsets)
+    p = len(rows)
+    same = (torch.float32,) if dt == VP_F32 else _BF16_LIKE
+    f = (torch.float32,)
+    wp, wb = _ws(workspace)
+    st = load_library().vp_output_fwd_group(
+        _ptr(H, "H"), _each(W_shards, "W_shards", None, [(n, h) for n in rows]), _i64s(rows), _i64s(shard_offsets), p,
+        _ptr(labels, "labels", (torch.int64,), (N,)), N, h, dt, VP_SAVE_LOGITS if logits_out is not None else 0,
+        _ptr(local_max, "local_max", f, (p, N)), _ptr(local_sumexp, "local_sumexp", f, (p, N)),
+        _ptr(local_target, "local_target", f, (p, N)), _each(logits_out, "logits_out", same, [(N, n) for n in rows]),
+        wp, wb, _stream(stream))
+    _check(st, "vp_output_fwd_group")
+
+
+def vp_output_bwd_group(H, W_shards, labels, shard_offsets, global_max, global_sumexp, logits_saved, grad_scale: float,
+                        dH_accum, dW_shards, workspace, stream=None, dh_overwrite: bool = False) -> None:
+    """vp_output_bwd for several shards on this device in one call (arguments as there, one entry per shard)."""
+    N, h = H.shape
+    dt, rows = _shards(H, W_shards, shard_offsets)
+    same = (torch.float32,) if dt == VP_F32 else _BF16_LIKE
+    f = (torch.float32,)
+    wp, wb = _ws(workspace)
+    st = load_library().vp_output_bwd_group(
+        _ptr(H, "H"), _each(W_shards, "W_shards", None, [(n, h) for n in rows]), _i64s(rows), _i64s(shard_offsets),
+        len(rows), _ptr(labels, "labels", (torch.int64,), (N,)), N, h, dt,
+        (VP_SAVE_LOGITS if logits_saved is not None else 0) | (VP_SKIP_DH if dH_accum is None else 0)
+        | (VP_DH_OVERWRITE if (dh_overwrite and dH_accum is not None) else 0),
+        _ptr(global_max, "global_max", f, (N,)), _ptr(global_sumexp, "global_sumexp", f, (N,)),
+        _each(logits_saved, "logits_saved", same, [(N, n) for n in rows]), float(grad_scale),
+        _ptr(dH_accum, "dH_accum", f, (N, h)), _each(dW_shards, "dW_shards", f, [(n, h) for n in rows]),
+        wp, wb, _stream(stream))
+    _check(st, "vp_output_bwd_group")
 
 
 def vp_output_fwd_alg2(H, W_shard, labels, shard_offset: int, local_max, local_sumexp, local_target,

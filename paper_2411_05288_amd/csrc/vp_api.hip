@@ -41,6 +41,63 @@ size_t f32_bwd_scratch(int64_t N, int64_t h, int64_t Vs) {
 }
 size_t f32_matrix_bytes(int64_t N, int64_t Vs) { return align_up((size_t)N * Vs * sizeof(float), 256); }
 
+// One shard as a list for the kernels that take several.
+ShardList one_shard(int64_t Vs, int64_t off) {
+    ShardList l{};
+    l.n = 1;
+    l.rows[0] = (int)Vs;
+    l.first[1] = (int)fwd_tiles(Vs);
+    l.offset[0] = off;
+    l.ldd[0] = d_row_stride(Vs);
+    return l;
+}
+
+// The bf16 shards of a group call are taken in parts of at most GEMM_GROUP_MAX shards whose D matrices (all kept until
+// the part's dH and dW products are done) take at most this much workspace together, or of one shard.
+constexpr size_t GROUP_D_BYTES = (size_t)4 << 30;
+
+size_t d_bytes(int64_t N, int64_t Vs) { return align_up((size_t)N * d_row_stride(Vs) * 2, 256); }
+
+// Shards of the part that begins at shard r0.
+int part_shards(const int64_t* rows, int p, int r0, int64_t N) {
+    size_t b = d_bytes(N, rows[r0]);
+    int n = 1;
+    while (r0 + n < p && n < GEMM_GROUP_MAX && b + d_bytes(N, rows[r0 + n]) <= GROUP_D_BYTES) b += d_bytes(N, rows[r0 + n++]);
+    return n;
+}
+
+struct PartSizes {
+    size_t d, slices, stats;     // bytes: D matrices, K-slice partials of dH, statistics partials of the forward pass
+    int64_t tiles;               // column tiles of the forward pass
+    int S;
+};
+PartSizes part_sizes(const int64_t* rows, int r0, int n, int64_t N, int64_t h) {
+    PartSizes z{};
+    int64_t kt = 0;
+    for (int r = r0; r < r0 + n; ++r) {
+        z.d += d_bytes(N, rows[r]);
+        z.tiles += fwd_tiles(rows[r]);
+        kt += ceil_div(rows[r], 64);
+    }
+    z.S = h % 8 == 0 ? gemm_bf16_slices(N, h, kt) : 1;
+    z.slices = z.S > 1 ? (size_t)z.S * N * h * sizeof(float) : 0;
+    z.stats = align_up((size_t)(2 * z.tiles + n) * N * sizeof(float), 256);
+    return z;
+}
+
+GemmBf16Params logits_product(const void* H, const int64_t* labels, int64_t N, int64_t h, Epi epi) {
+    GemmBf16Params g{};
+    g.A = (const u16*)H;
+    g.M = (int)N; g.K = (int)h;
+    g.lda = (int)h; g.ldb = (int)h;
+    g.a_kcontig = 1; g.b_kcontig = 1;
+    g.vec_ok = (h % 8 == 0) ? 1 : 0;
+    g.epi = epi;
+    g.labels = labels;
+    g.kernel_id = epi == Epi::FwdStats ? K_GEMM_FWD_STATS : K_GEMM_DLOGITS;
+    return g;
+}
+
 vp_status dev(hipError_t e) { return e == hipSuccess ? VP_OK : VP_ERR_DEVICE; }
 
 // Scratch of vp_output_fwd_noalloc: device memory that belongs to the library's code object, so the
@@ -152,8 +209,8 @@ vp_status vp_output_fwd(const void* H, const void* W_shard, const int64_t* label
         g.part_max = pm; g.part_sum = ps; g.part_tgt = pt;
         hipError_t e = launch_gemm_bf16(g, st);
         if (e != hipSuccess) return VP_ERR_DEVICE;
-        return dev(launch_fold_partials(pm, ps, pt, (int)tiles, (int)N, labels, shard_offset, (int)Vs, local_max,
-                                        local_sumexp, local_target, st));
+        return dev(launch_fold_partials(pm, ps, pt, one_shard(Vs, shard_offset), (int)N, labels, local_max, local_sumexp,
+                                        local_target, st));
     }
     float* Y = logits_out ? (float*)logits_out : (float*)workspace;
     float* scratch = f32_fwd_scratch(N, h, Vs) ? (float*)((char*)workspace + (logits_out ? 0 : f32_matrix_bytes(N, Vs)))
@@ -241,7 +298,11 @@ vp_status vp_output_bwd(const void* H, const void* W_shard, const int64_t* label
             g.labels = labels; g.shard_offset = shard_offset;
             g.gmax = global_max; g.gsum = global_sumexp; g.scale = grad_scale;
             e = launch_gemm_bf16(g, st);
-            if (e == hipSuccess) e = launch_zero_pad_columns(D, (int)N, (int)Vs, ldd, st);
+            if (e == hipSuccess) {
+                ShardList l = one_shard(Vs, shard_offset);
+                l.D[0] = D;
+                e = launch_zero_pad_columns(l, (int)N, st);
+            }
         }
         if (e != hipSuccess) return VP_ERR_DEVICE;
         if (!skip_dh) {   // dH += D W_shard : M = N tokens, N = h, K = Vs; W_shard is stored [K][N]
@@ -292,6 +353,189 @@ vp_status vp_output_bwd(const void* H, const void* W_shard, const int64_t* label
     return dev(e);
 }
 
+// ---- several shards on this device
+
+size_t vp_output_group_workspace_bytes(vp_call which, int32_t p, int64_t N, int64_t h, const int64_t* rows, vp_dtype dt,
+                                       uint32_t flags) {
+    if ((which != VP_CALL_OUTPUT_FWD && which != VP_CALL_OUTPUT_BWD) || p < 1 || !rows) return (size_t)-1;
+    size_t need = 0;
+    for (int32_t r = 0; r < p; ++r) {       // what the shards need one by one (paths that are not grouped)
+        const size_t b = vp_workspace_bytes(which, N, h, rows[r], dt, flags);
+        if (b == (size_t)-1) return b;
+        need = b > need ? b : need;
+    }
+    if (dt != VP_BF16 || h % 8) return need;
+    for (int r = 0; r < p;) {
+        const int n = part_shards(rows, p, r, N);
+        const PartSizes z = part_sizes(rows, r, n, N, h);
+        const size_t b = which == VP_CALL_OUTPUT_FWD ? z.stats : z.d + ((flags & VP_SKIP_DH) ? 0 : align_up(z.slices, 256));
+        need = b > need ? b : need;
+        r += n;
+    }
+    return need;
+}
+
+vp_status vp_output_fwd_group(const void* H, const void* const* W_shards, const int64_t* rows, const int64_t* shard_offsets,
+                              int32_t p, const int64_t* labels, int64_t N, int64_t h, vp_dtype dt, uint32_t flags,
+                              float* local_max, float* local_sumexp, float* local_target, void* const* logits_out,
+                              void* workspace, size_t workspace_bytes, void* stream) {
+    if (!H || !W_shards || !rows || !shard_offsets || p < 1 || !labels || !local_max || !local_sumexp || !local_target)
+        return VP_ERR_INVALID_ARG;
+    if (!dtype_ok(dt) || (flags & ~(uint32_t)VP_SAVE_LOGITS)) return VP_ERR_INVALID_ARG;
+    if (((flags & VP_SAVE_LOGITS) != 0) != (logits_out != nullptr)) return VP_ERR_INVALID_ARG;
+    if (!aligned16(H) || !aligned16(workspace)) return VP_ERR_INVALID_ARG;
+    for (int32_t r = 0; r < p; ++r) {
+        if (!W_shards[r] || !aligned16(W_shards[r]) || !sizes_ok(N, h, rows[r]) || shard_offsets[r] < 0) return VP_ERR_INVALID_ARG;
+        if (logits_out && (!logits_out[r] || !aligned16(logits_out[r]))) return VP_ERR_INVALID_ARG;
+        if (!sizes_supported(N, h, rows[r])) return VP_ERR_UNSUPPORTED;
+    }
+    const size_t need = vp_output_group_workspace_bytes(VP_CALL_OUTPUT_FWD, p, N, h, rows, dt, flags);
+    if (need == (size_t)-1) return VP_ERR_UNSUPPORTED;
+    if (need > 0 && (!workspace || workspace_bytes < need)) return VP_ERR_WORKSPACE;
+    hipStream_t st = (hipStream_t)stream;
+    for (int r0 = 0; r0 < p;) {
+        int n = 1;
+        if (dt == VP_BF16 && (n = part_shards(rows, p, r0, N)) > 1) {
+            const PartSizes z = part_sizes(rows, r0, n, N, h);
+            float* pm = (float*)workspace;
+            GemmBf16Group g{};
+            ShardList l{};
+            g.base = logits_product(H, labels, N, h, Epi::FwdStats);
+            g.base.part_max = pm;
+            g.base.part_sum = pm + z.tiles * N;
+            g.base.part_tgt = pm + 2 * z.tiles * N;
+            l.n = n;
+            for (int k = 0; k < n; ++k) {
+                const int r = r0 + k;
+                g.sh[k].B = (const u16*)W_shards[r];
+                g.sh[k].out = logits_out ? logits_out[r] : nullptr;
+                g.sh[k].ld = g.sh[k].rows = l.rows[k] = (int)rows[r];
+                g.sh[k].offset = l.offset[k] = shard_offsets[r];
+                l.first[k + 1] = l.first[k] + (int)fwd_tiles(rows[r]);
+            }
+            gemm_bf16_group_finish(g, n);
+            if (gemm_bf16_group_ok(g)) {
+                if (launch_gemm_bf16_group(g, st) != hipSuccess ||
+                    launch_fold_partials(g.base.part_max, g.base.part_sum, g.base.part_tgt, l, (int)N, labels,
+                                         local_max + r0 * N, local_sumexp + r0 * N, local_target + r0 * N, st) != hipSuccess)
+                    return VP_ERR_DEVICE;
+                r0 += n;
+                continue;
+            }
+        }
+        for (int r = r0; r < r0 + n; ++r) {
+            const vp_status s = vp_output_fwd(H, W_shards[r], labels, N, h, rows[r], shard_offsets[r], dt, flags,
+                                              local_max + r * N, local_sumexp + r * N, local_target + r * N,
+                                              logits_out ? logits_out[r] : nullptr, workspace, workspace_bytes, stream);
+            if (s != VP_OK) return s;
+        }
+        r0 += n;
+    }
+    return VP_OK;
+}
+
+vp_status vp_output_bwd_group(const void* H, const void* const* W_shards, const int64_t* rows, const int64_t* shard_offsets,
+                              int32_t p, const int64_t* labels, int64_t N, int64_t h, vp_dtype dt, uint32_t flags,
+                              const float* global_max, const float* global_sumexp, const void* const* logits_saved,
+                              float grad_scale, float* dH_accum, float* const* dW_shards, void* workspace,
+                              size_t workspace_bytes, void* stream) {
+    if (!H || !W_shards || !rows || !shard_offsets || p < 1 || !labels || !global_max || !global_sumexp || !dW_shards)
+        return VP_ERR_INVALID_ARG;
+    if (!dH_accum && !(flags & VP_SKIP_DH)) return VP_ERR_INVALID_ARG;
+    if (!dtype_ok(dt) || (flags & ~(uint32_t)(VP_SAVE_LOGITS | VP_SKIP_DH | VP_DH_OVERWRITE))) return VP_ERR_INVALID_ARG;
+    if ((flags & VP_SKIP_DH) && (flags & VP_DH_OVERWRITE)) return VP_ERR_INVALID_ARG;
+    if (((flags & VP_SAVE_LOGITS) != 0) != (logits_saved != nullptr)) return VP_ERR_INVALID_ARG;
+    if (!aligned16(H) || !aligned16(workspace) || !aligned16(dH_accum)) return VP_ERR_INVALID_ARG;
+    for (int32_t r = 0; r < p; ++r) {
+        if (!W_shards[r] || !aligned16(W_shards[r]) || !dW_shards[r] || !aligned16(dW_shards[r]) || !sizes_ok(N, h, rows[r]) ||
+            shard_offsets[r] < 0)
+            return VP_ERR_INVALID_ARG;
+        if (logits_saved && (!logits_saved[r] || !aligned16(logits_saved[r]))) return VP_ERR_INVALID_ARG;
+        if (!sizes_supported(N, h, rows[r])) return VP_ERR_UNSUPPORTED;
+    }
+    const size_t need = vp_output_group_workspace_bytes(VP_CALL_OUTPUT_BWD, p, N, h, rows, dt, flags);
+    if (need == (size_t)-1) return VP_ERR_UNSUPPORTED;
+    if (!workspace || workspace_bytes < need) return VP_ERR_WORKSPACE;
+    hipStream_t st = (hipStream_t)stream;
+    const bool skip_dh = (flags & VP_SKIP_DH) != 0;
+    for (int r0 = 0; r0 < p;) {
+        const bool overwrite = (flags & VP_DH_OVERWRITE) != 0 && r0 == 0;
+        int n = 1;
+        if (dt == VP_BF16 && h % 8 == 0) {
+            n = part_shards(rows, p, r0, N);
+            const PartSizes z = part_sizes(rows, r0, n, N, h);
+            GemmBf16Group y{}, gh{}, gw{};      // logits again, dH, dW
+            ShardList l{};
+            y.base = logits_product(H, labels, N, h, Epi::DLogits);
+            y.base.gmax = global_max; y.base.gsum = global_sumexp; y.base.scale = grad_scale;
+            float* slices = (float*)((char*)workspace + z.d);
+            gh.base.M = (int)N; gh.base.N = (int)h;
+            gh.base.ldb = (int)h;
+            gh.base.a_kcontig = 1; gh.base.b_kcontig = 0;
+            gh.base.vec_ok = 1;
+            gh.base.epi = (z.S > 1 || overwrite) ? Epi::StoreF32 : Epi::AccumF32;
+            gh.base.kernel_id = K_GEMM_DH;
+            gh.base.C = z.S > 1 ? slices : dH_accum; gh.base.ldc = (int)h;
+            gh.slices = z.S;
+            gw.base.B = (const u16*)H;
+            gw.base.N = (int)h; gw.base.K = (int)N;
+            gw.base.ldb = (int)h;
+            gw.base.a_kcontig = 0; gw.base.b_kcontig = 0;
+            gw.base.vec_ok = 1;
+            gw.base.epi = Epi::StoreF32;
+            gw.base.kernel_id = K_GEMM_DW;
+            gw.base.ldc = (int)h;
+            l.n = n;
+            char* d = (char*)workspace;
+            for (int k = 0; k < n; ++k) {
+                const int r = r0 + k;
+                const int ldd = (int)d_row_stride(rows[r]);
+                y.sh[k].B = gh.sh[k].B = (const u16*)W_shards[r];
+                y.sh[k].out = d;
+                gh.sh[k].A = gw.sh[k].A = (const u16*)d;
+                gw.sh[k].out = dW_shards[r];
+                y.sh[k].ld = gh.sh[k].ld = gw.sh[k].ld = ldd;
+                y.sh[k].rows = gh.sh[k].rows = gw.sh[k].rows = l.rows[k] = (int)rows[r];
+                y.sh[k].offset = l.offset[k] = shard_offsets[r];
+                l.ldd[k] = ldd;
+                l.Y[k] = logits_saved ? logits_saved[r] : nullptr;
+                l.D[k] = d;
+                d += d_bytes(N, rows[r]);
+            }
+            gemm_bf16_group_finish(y, n);
+            gemm_bf16_group_finish(gh, n);
+            gemm_bf16_group_finish(gw, n);
+            if ((n > 1 || z.S > 1) && N <= MAX_ROW && (logits_saved || gemm_bf16_group_ok(y)) &&
+                (skip_dh || gemm_bf16_group_ok(gh)) && gemm_bf16_group_ok(gw)) {
+                hipError_t e;
+                if (logits_saved) {
+                    e = launch_dlogits_group(l, labels, global_max, global_sumexp, grad_scale, (int)N, st);
+                } else {
+                    e = launch_gemm_bf16_group(y, st);
+                    if (e == hipSuccess) e = launch_zero_pad_columns(l, (int)N, st);
+                }
+                if (e == hipSuccess && !skip_dh) {
+                    e = launch_gemm_bf16_group(gh, st);
+                    if (e == hipSuccess && z.S > 1) e = launch_sum_slices(slices, z.S, N * h, dH_accum, !overwrite, st);
+                }
+                if (e == hipSuccess) e = launch_gemm_bf16_group(gw, st);
+                if (e != hipSuccess) return VP_ERR_DEVICE;
+                r0 += n;
+                continue;
+            }
+        }
+        for (int r = r0; r < r0 + n; ++r) {
+            const uint32_t f = (flags & ~(uint32_t)VP_DH_OVERWRITE) | (r == r0 && overwrite ? (uint32_t)VP_DH_OVERWRITE : 0u);
+            const vp_status s = vp_output_bwd(H, W_shards[r], labels, N, h, rows[r], shard_offsets[r], dt, f, global_max,
+                                              global_sumexp, logits_saved ? logits_saved[r] : nullptr, grad_scale, dH_accum,
+                                              dW_shards[r], workspace, workspace_bytes, stream);
+            if (s != VP_OK) return s;
+        }
+        r0 += n;
+    }
+    return VP_OK;
+}
+
 vp_status vp_output_fwd_alg2(const void* H, const void* W_shard, const int64_t* labels, int64_t N, int64_t h,
                              int64_t Vs, int64_t shard_offset, vp_dtype dt, uint32_t flags, float* local_max,
                              float* local_sumexp, float* local_target, void* logits_out, float* A_out, void* B_out,
@@ -332,8 +576,8 @@ vp_status vp_output_fwd_alg2(const void* H, const void* W_shard, const int64_t* 
         g.labels = labels; g.shard_offset = shard_offset;
         g.part_max = pm; g.part_sum = ps; g.part_tgt = pt;
         if ((e = launch_gemm_bf16(g, st)) != hipSuccess) return VP_ERR_DEVICE;
-        if ((e = launch_fold_partials(pm, ps, pt, (int)tiles, (int)N, labels, shard_offset, (int)Vs, local_max,
-                                      local_sumexp, local_target, st)) != hipSuccess)
+        if ((e = launch_fold_partials(pm, ps, pt, one_shard(Vs, shard_offset), (int)N, labels, local_max, local_sumexp,
+                                      local_target, st)) != hipSuccess)
             return VP_ERR_DEVICE;
         // softmax' with the shard's own statistics (no one-hot term, scale 1), rows padded and zero-filled
         if ((e = launch_dlogits(Y, ldy, P, ldd, 1, nullptr, shard_offset, local_max, local_sumexp, 1.0f, (int)N,

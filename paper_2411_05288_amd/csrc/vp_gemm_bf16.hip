@@ -174,23 +174,27 @@ static hipError_t launch_t(const GemmBf16Params& p, hipStream_t st) {
 // Test switch: route every product through the generic kernel.
 static std::atomic<bool> g_force_generic{false};
 void gemm_bf16_force_generic(bool on) { g_force_generic.store(on, std::memory_order_relaxed); }
+bool gemm_bf16_generic_forced() { return g_force_generic.load(std::memory_order_relaxed); }
+
+// the epilogue addresses the 256 rows of an output tile with 32-bit byte offsets
+bool gemm_bf16_out_ok(const GemmBf16Params& p) {
+    const bool f32_out = p.epi == Epi::StoreF32 || p.epi == Epi::AccumF32;
+    return f32_out ? (long long)p.ldc * 4 <= EPI_MAX_ROW_BYTES : (!p.Y || (long long)p.ldy * 2 <= EPI_MAX_ROW_BYTES);
+}
 
 hipError_t launch_gemm_bf16(const GemmBf16Params& p, hipStream_t st) {
     if (p.M <= 0 || p.N <= 0 || p.K <= 0) return hipErrorInvalidValue;
-    // the epilogue addresses the 256 rows of an output tile with 32-bit byte offsets
-    const bool f32_out = p.epi == Epi::StoreF32 || p.epi == Epi::AccumF32;
-    if (f32_out ? (long long)p.ldc * 4 > EPI_MAX_ROW_BYTES : (p.Y && (long long)p.ldy * 2 > EPI_MAX_ROW_BYTES))
-        return hipErrorInvalidValue;
+    if (!gemm_bf16_out_ok(p)) return hipErrorInvalidValue;
     const int kid = p.kernel_id ? p.kernel_id
                   : p.epi == Epi::FwdStats ? K_GEMM_FWD_STATS
                   : p.epi == Epi::DLogits  ? K_GEMM_DLOGITS
                   : p.epi == Epi::AccumF32 ? K_GEMM_DH : K_GEMM_DW;
-    ProfScope prof(kid, st);
-    if (!g_force_generic.load(std::memory_order_relaxed) && gemm_bf16_fast_ok(p)) {
+    if (!gemm_bf16_generic_forced() && gemm_bf16_fast_ok(p)) {
         GemmBf16Params q = p;
         q.kernel_id = kid;
         return launch_gemm_bf16_fast(q, st);
     }
+    ProfScope prof(kid, st);
     // only the operand-layout / epilogue combinations the output layer uses are instantiated
     if (p.a_kcontig && p.b_kcontig && p.epi == Epi::FwdStats) return launch_t<true, true, Epi::FwdStats>(p, st);
     if (p.a_kcontig && p.b_kcontig && p.epi == Epi::DLogits) return launch_t<true, true, Epi::DLogits>(p, st);

@@ -122,6 +122,25 @@ __device__ __forceinline__ void tile_of_block(int v, int nb, int total, int tile
     tn = 16 * cb + 4 * sc + rem / hs;
 }
 
+// The same for tiles cut into K slices: the work items are the tiles of slice 0, then those of slice 1, and so on; every
+// XCD takes one contiguous run of them (so its workgroups read the same few slices), within a slice in panels of 8 tile
+// rows.  nb must be a multiple of 8 if there is more than one round.
+__device__ __forceinline__ void sliced_tile_of_block(int v, int nb, int tiles, int slices, int tiles_m, int tiles_n,
+                                                     int& tm, int& tn, int& slice) {
+    const int total = tiles * slices;
+    const int round = v / nb, b = v - round * nb;
+    const int x = b & 7, per = total >> 3, rem = total & 7;
+    const int logical = ((nb & 7) != 0 && total > nb) ? v
+                                                      : x * per + (x < rem ? x : rem) + round * (nb >> 3) + (b >> 3);
+    slice = logical / tiles;
+    const int t = logical - slice * tiles;
+    const int panel = t / (8 * tiles_n);
+    const int rows = min(8, tiles_m - panel * 8);
+    const int in_panel = t - panel * 8 * tiles_n;
+    tm = panel * 8 + in_panel % rows;
+    tn = in_panel / rows;
+}
+
 // Stores four consecutive fp32 values of a row at column `col` (a multiple of 4), clipped to
 // n_cols.  vec: row start and leading dimension allow an aligned 16-byte access.
 template <bool ACCUM>

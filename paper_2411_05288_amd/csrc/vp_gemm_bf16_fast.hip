@@ -32,6 +32,7 @@
 //       the four k-rows kb..kb+3.  f makes the 4 k-rows of a group, and the 8 of two groups,
 //       fall into different banks.
 #include <atomic>
+#include <climits>
 
 #include "vp_gemm_bf16_common.h"
 
@@ -204,22 +205,34 @@ __device__ __forceinline__ void trace_stamp(const GemmBf16Params& g, int tile_id
     }
 }
 
+// Shard that owns tile (or k tile) t of the concatenated dimension.
+__device__ __forceinline__ int shard_of(const GemmBf16Group& gg, int t) {
+    int r = 0;
+#pragma unroll
+    for (int i = 1; i < GEMM_GROUP_MAX; ++i) r += t >= gg.first[i] ? 1 : 0;
+    return __builtin_amdgcn_readfirstlane(r);
+}
+
+// Several shards in one launch (see GemmBf16Group) because one shard alone leaves the chip partly idle: the last round
+// of its tiles is not full, every launch ends with its slowest workgroup and its epilogue's stores, and the small ones
+// have fewer tiles than there are compute units.  Whole steps, one launch per shard and product -> one per product:
+// N=512 h=2048 V=32000 p=4: 954 -> 290 us; N=1999 h=3072 V=50001 p=8: 3048 -> 1888; N=4096 h=4096 V=32000 p=8: 2940 -> 2692;
+// N=4096 h=8192 V=256000 p=16: 52.6 -> 51.5 ms; the loss alone, N=64 h=4096 V=128256 p=8: 653 -> 253 us.
 template <bool A_KC, bool B_KC, Epi EPI, bool STREAM, bool TRACE>
-__global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Params g) {
+__global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Group gg) {
+    constexpr bool CAT_N = A_KC && B_KC, CAT_M = !A_KC && !B_KC, CAT_K = A_KC && !B_KC;
+    const GemmBf16Params& g = gg.base;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keeps LDS bases in SGPRs
     const int wm = wave >> 1, wn = wave & 1;
 
-    const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-    const int total_tiles = tiles_m * tiles_n;
+    const int tiles_m = CAT_M ? gg.total : (g.M + BM - 1) / BM;
+    const int tiles_n = CAT_N ? gg.total : (g.N + BN - 1) / BN;
+    const int plane = tiles_m * tiles_n;
+    const int total_tiles = CAT_K ? plane * gg.slices : plane;
 
-    // raw buffer descriptors sized exactly to the operands: reads beyond return zero
-    const unsigned a_bytes = (unsigned)(A_KC ? g.M : g.K) * (unsigned)g.lda * 2u;
-    const unsigned b_bytes = (unsigned)(B_KC ? g.N : g.K) * (unsigned)g.ldb * 2u;
-    const unsigned a_kstep = A_KC ? (unsigned)BK * 2u : (unsigned)BK * (unsigned)g.lda * 2u;
-    const unsigned b_kstep = B_KC ? (unsigned)BK * 2u : (unsigned)BK * (unsigned)g.ldb * 2u;
-    const unsigned a_half = a_kstep >> 1, b_half = b_kstep >> 1;
+    const unsigned a_row = CAT_K || CAT_M ? 0u : (unsigned)g.lda;      // row stride of A if the shards share it
 
     int abase[4], bbase[4];
     frag_offsets<A_KC>(abase, wm, lane);
@@ -235,15 +248,55 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Params g) {
     int tile_idx = 0;
     for (int v = blockIdx.x; v < total_tiles; v += gridDim.x, ++tile_idx) {
     trace_stamp<TRACE>(g, tile_idx, 0);
-    int tile_m, tile_n;
-    tile_of_block(v, gridDim.x, total_tiles, tiles_m, tiles_n, tile_m, tile_n);
+    int tile_m, tile_n, slice = 0;      // tile_m / tile_n: within the shard
+    if (CAT_K && gg.slices > 1) sliced_tile_of_block(v, gridDim.x, plane, gg.slices, tiles_m, tiles_n, tile_m, tile_n, slice);
+    else tile_of_block(v, gridDim.x, total_tiles, tiles_m, tiles_n, tile_m, tile_n);
+
+    // the shard, and for dH the range [kt_at, kt_end) of k tiles of this work item (over all shards)
+    int shard, kt_at = 0, kt_end = 0;
+    if constexpr (CAT_K) {
+        kt_at = (int)((long long)gg.total * slice / gg.slices);
+        kt_end = (int)((long long)gg.total * (slice + 1) / gg.slices);
+        shard = shard_of(gg, kt_at);
+    } else {
+        shard = shard_of(gg, CAT_N ? tile_n : tile_m);
+        if constexpr (CAT_N) tile_n -= gg.first[shard];
+        else tile_m -= gg.first[shard];
+    }
     const int m0 = tile_m * BM, n0 = tile_n * BN;
 
+    // operands of the shard; raw buffer descriptors sized exactly to them: reads beyond return zero
+    const u16 *opA, *opB;
+    unsigned a_bytes, b_bytes, a_kstep, b_kstep, a_half, b_half;
+    int cols_n;                  // columns of the output (N)
+    int kt_base, nkt;            // first k tile and number of k tiles of this pass over K
     unsigned avoff[4], bvoff[4];
-    half_voffsets<A_KC>(avoff, m0, g.lda, wave, lane);
-    half_voffsets<B_KC>(bvoff, n0, g.ldb, wave, lane);
-
-    const int nkt = (g.K + BK - 1) / BK;
+    auto bind_shard = [&]() {
+        const GemmBf16Shard& s = gg.sh[shard];
+        const unsigned lda = CAT_N ? a_row : (unsigned)s.ld;
+        opA = CAT_N ? g.A : s.A;
+        opB = CAT_M ? g.B : s.B;
+        const int K = CAT_K ? s.rows : g.K;
+        cols_n = CAT_N ? s.rows : g.N;
+        const int rows_m = CAT_M ? s.rows : g.M;
+        a_bytes = (unsigned)(A_KC ? rows_m : K) * lda * 2u;
+        b_bytes = (unsigned)(B_KC ? cols_n : K) * (unsigned)g.ldb * 2u;
+        a_kstep = A_KC ? (unsigned)BK * 2u : (unsigned)BK * lda * 2u;
+        b_kstep = B_KC ? (unsigned)BK * 2u : (unsigned)BK * (unsigned)g.ldb * 2u;
+        a_half = a_kstep >> 1;
+        b_half = b_kstep >> 1;
+        const int all = (K + BK - 1) / BK;
+        if constexpr (CAT_K) {
+            kt_base = kt_at - gg.first[shard];
+            nkt = min(all - kt_base, kt_end - kt_at);
+        } else {
+            kt_base = 0;
+            nkt = all;
+        }
+        half_voffsets<A_KC>(avoff, m0, (int)lda, wave, lane);
+        half_voffsets<B_KC>(bvoff, n0, g.ldb, wave, lane);
+    };
+    bind_shard();
 
     // Instruction-mix hints for the scheduler: the next N MFMAs, LDS reads, global loads.
 #define VP_SCHED_MFMA(n) __builtin_amdgcn_sched_group_barrier(0x008, n, 0)
@@ -252,8 +305,8 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Params g) {
     constexpr int DS_PER_STEP = (A_KC ? 4 : 8) + (B_KC ? 4 : 8);   // LDS reads per 16-wide k sub-step
 
     // Loads of k tile T into the slots (2T) % 5 and (2T + 1) % 5.
-#define VP_LOAD_A(T, S0, S1) issue_operand_loads<false, S0, S1>(g.A, a_bytes, (unsigned)(T) * a_kstep, a_half, avoff, wave)
-#define VP_LOAD_B(T, S0, S1) issue_operand_loads<true, S0, S1>(g.B, b_bytes, (unsigned)(T) * b_kstep, b_half, bvoff, wave)
+#define VP_LOAD_A(T, S0, S1) issue_operand_loads<false, S0, S1>(opA, a_bytes, (unsigned)(kt_base + (T)) * a_kstep, a_half, avoff, wave)
+#define VP_LOAD_B(T, S0, S1) issue_operand_loads<true, S0, S1>(opB, b_bytes, (unsigned)(kt_base + (T)) * b_kstep, b_half, bvoff, wave)
     // Waits (s_waitcnt immediates: vmcnt in bits 3:0 and 15:14, lgkmcnt in bits 11:8, expcnt 6:4 left at 7).
 #define VP_WAIT_LGKM0() __builtin_amdgcn_s_waitcnt(0xC07F)                 /* lgkmcnt(0), vmcnt(63) */
 #define VP_WAIT_VM16_LGKM0() __builtin_amdgcn_s_waitcnt(0x4070)            /* vmcnt(16) lgkmcnt(0) */
@@ -263,11 +316,13 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Params g) {
     asm volatile("" ::: "memory")
 
     // prologue: k tiles 0 and 1 are requested at once; tile 0 has landed after the first 16 of the 32 loads
-    VP_LOAD_A(0, 0, 1);
-    VP_LOAD_B(0, 0, 1);
-    VP_LOAD_A(1, 2, 3);
-    VP_LOAD_B(1, 2, 3);
-    asm volatile("" ::: "memory");
+#define VP_PROLOGUE()        \
+    VP_LOAD_A(0, 0, 1);      \
+    VP_LOAD_B(0, 0, 1);      \
+    VP_LOAD_A(1, 2, 3);      \
+    VP_LOAD_B(1, 2, 3);      \
+    asm volatile("" ::: "memory")
+    VP_PROLOGUE();
     // (while those loads are on their way)
     // accumulators are zeroed directly in the AGPR half of the register file: zeroing them as
     // ordinary vectors first would need 256 more VGPRs for a moment and spill everything else
@@ -278,11 +333,13 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Params g) {
         for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) { float z; asm volatile("v_accvgpr_write_b32 %0, 0" : "=a"(z)); acc[i][j][r] = z; }
-    if (EPI == Epi::FwdStats && n0 + BN > g.N) init_acc_ragged<4, 2>(acc, g.N, tile_n);
+    if (EPI == Epi::FwdStats && n0 + BN > cols_n) init_acc_ragged<4, 2>(acc, cols_n, tile_n);
 
+    // one pass per shard whose k tiles this work item has (dH); one pass otherwise
+    for (bool first_pass = true;; first_pass = false) {
     VP_WAIT_VM16_LGKM0();
     VP_BARRIER();
-    trace_stamp<TRACE>(g, tile_idx, 1);
+    if (first_pass) trace_stamp<TRACE>(g, tile_idx, 1);
     bf16x8 af0[4], bf0[4], af1[4], bf1[4];
     read_frags<A_KC, B_KC>(af0, bf0, lds_slot<0>(), abase, bbase, 0);
 
@@ -362,6 +419,17 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Params g) {
             }
         }
     }
+    __syncthreads();   // every wavefront is done with the slots, and no load is in flight, before they are reused
+    if constexpr (!CAT_K) break;
+    else {
+        kt_at += nkt;
+        if (kt_at >= kt_end) break;
+        ++shard;       // (every shard has at least one k tile)
+        bind_shard();
+        VP_PROLOGUE();
+    }
+    }
+#undef VP_PROLOGUE
 #undef VP_TILE
 #undef VP_MIX_LOADS
 #undef VP_LOAD_A
@@ -372,14 +440,33 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Params g) {
 #undef VP_SCHED_MFMA
 #undef VP_SCHED_DSRD
 #undef VP_SCHED_VMEM
-    __syncthreads();   // every wavefront is done with the slots, and no load is in flight, before the epilogue reuses them
     trace_stamp<TRACE>(g, tile_idx, 2);
 
     // keep the epilogue's address arithmetic from being hoisted above the main loop, where it
     // would occupy registers (and spill) for the whole kernel
-    asm volatile("" : "+s"(tile_m), "+s"(tile_n));
+    asm volatile("" : "+s"(tile_m), "+s"(tile_n), "+s"(shard), "+s"(slice));
+    GemmBf16Params e = g;        // the shard's output
+    {
+        const GemmBf16Shard& s = gg.sh[shard];
+        if constexpr (CAT_N) {
+            e.N = s.rows;
+            e.Y = (u16*)s.out;
+            e.ldy = s.ld;
+            e.shard_offset = s.offset;
+            if constexpr (EPI == Epi::FwdStats) {
+                e.part_max = g.part_max + (size_t)gg.first[shard] * g.M;
+                e.part_sum = g.part_sum + (size_t)gg.first[shard] * g.M;
+                e.part_tgt = g.part_tgt + (size_t)shard * g.M;
+            }
+        } else if constexpr (CAT_M) {
+            e.M = s.rows;
+            e.C = (float*)s.out;
+        } else {
+            e.C = g.C + (size_t)slice * g.M * g.ldc;
+        }
+    }
     // exchange area at the start of slot 0; staging block of wavefront w in slot w (behind the exchange area in slot 0)
-    gemm_epilogue<EPI, 4, 2, STREAM>(acc, g, tile_m, tile_n, g_slot0,
+    gemm_epilogue<EPI, 4, 2, STREAM>(acc, e, tile_m, tile_n, g_slot0,
                                      wave == 0 ? g_slot0 + EPI_XCHG_BYTES : wave == 1 ? g_slot1 : wave == 2 ? g_slot2 : g_slot3);
     __syncthreads();   // the epilogue's LDS exchange is over before the next tile streams in
     trace_stamp<TRACE>(g, tile_idx, 3);
@@ -411,18 +498,19 @@ void gemm_bf16_set_trace(void* buf, size_t bytes, int kernel_id) {
 }
 
 template <bool A_KC, bool B_KC, Epi EPI>
-static hipError_t launch_fast_t(const GemmBf16Params& p0, hipStream_t st) {
-    GemmBf16Params p = p0;
-    const int tiles = (int)(ceil_div(p.M, BM) * ceil_div(p.N, BN));
+static hipError_t launch_fast_t(const GemmBf16Group& p0, hipStream_t st) {
+    GemmBf16Group p = p0;
+    const int64_t tm = !A_KC && !B_KC ? p.total : ceil_div(p.base.M, BM), tn = A_KC && B_KC ? p.total : ceil_div(p.base.N, BN);
+    const int tiles = (int)(tm * tn) * (A_KC && !B_KC ? p.slices : 1);
     const int cus = compute_unit_count();
     const int grid = tiles > cus ? cus : tiles;
     unsigned long long* tb = g_trace_buf.load();
     const int want = g_trace_kernel.load();
-    if (tb && (want < 0 || want == p.kernel_id)) {   // measurement aid: the instrumented instantiation, if the buffer holds this launch's records
+    if (tb && (want < 0 || want == p.base.kernel_id)) {   // measurement aid: the instrumented instantiation, if the buffer holds this launch's records
         const int per_wg = (int)ceil_div(tiles, grid);
         if ((size_t)TRACE_HEADER + (size_t)grid * per_wg * TRACE_STAMPS <= g_trace_words.load()) {
-            p.trace = tb;
-            p.trace_cap = per_wg;
+            p.base.trace = tb;
+            p.base.trace_cap = per_wg;
             if (tiles > cus)
                 hipLaunchKernelGGL((gemm_bf16_fast_kernel<A_KC, B_KC, EPI, true, true>), dim3(grid), dim3(NT), 0, st, p);
             else
@@ -452,13 +540,100 @@ bool gemm_bf16_fast_ok(const GemmBf16Params& p) {
     return a_ext < lim && b_ext < lim;
 }
 
-hipError_t launch_gemm_bf16_fast(const GemmBf16Params& p, hipStream_t st) {
-    if (p.a_kcontig && p.b_kcontig && p.epi == Epi::FwdStats) return launch_fast_t<true, true, Epi::FwdStats>(p, st);
-    if (p.a_kcontig && p.b_kcontig && p.epi == Epi::DLogits) return launch_fast_t<true, true, Epi::DLogits>(p, st);
-    if (p.a_kcontig && !p.b_kcontig && p.epi == Epi::AccumF32) return launch_fast_t<true, false, Epi::AccumF32>(p, st);
-    if (p.a_kcontig && !p.b_kcontig && p.epi == Epi::StoreF32) return launch_fast_t<true, false, Epi::StoreF32>(p, st);
-    if (!p.a_kcontig && !p.b_kcontig && p.epi == Epi::StoreF32) return launch_fast_t<false, false, Epi::StoreF32>(p, st);
+// Shard r of a group as a product of its own.
+static GemmBf16Params shard_params(const GemmBf16Group& g, int r) {
+    GemmBf16Params p = g.base;
+    const GemmBf16Shard& s = g.sh[r];
+    if (p.a_kcontig && p.b_kcontig) { p.B = s.B; p.N = s.rows; p.Y = (u16*)s.out; p.ldy = s.ld; }
+    else if (p.a_kcontig) { p.A = s.A; p.lda = s.ld; p.B = s.B; p.K = s.rows; }
+    else { p.A = s.A; p.lda = s.ld; p.M = s.rows; p.C = (float*)s.out; }
+    return p;
+}
+
+bool gemm_bf16_group_ok(const GemmBf16Group& g) {
+    if (g.n < 1 || g.n > GEMM_GROUP_MAX || gemm_bf16_generic_forced()) return false;
+    for (int r = 0; r < g.n; ++r) {
+        const GemmBf16Params p = shard_params(g, r);
+        if (p.M < 1 || p.N < 1 || p.K < 1 || !gemm_bf16_fast_ok(p) || !gemm_bf16_out_ok(p)) return false;
+    }
+    return true;
+}
+
+void gemm_bf16_group_finish(GemmBf16Group& g, int n) {
+    const int unit = g.base.a_kcontig ? (g.base.b_kcontig ? BN : BK) : BM;
+    g.n = n;
+    g.slices = g.slices > 1 ? g.slices : 1;
+    g.total = 0;
+    for (int r = 0; r < GEMM_GROUP_MAX; ++r) {
+        g.first[r] = r < n ? g.total : INT_MAX;
+        if (r < n) g.total += (int)ceil_div(g.sh[r].rows, unit);
+    }
+}
+
+hipError_t launch_gemm_bf16_group(const GemmBf16Group& g, hipStream_t st) {
+    const GemmBf16Params& p = g.base;
+    ProfScope prof(p.kernel_id, st);
+    if (p.a_kcontig && p.b_kcontig && p.epi == Epi::FwdStats) return launch_fast_t<true, true, Epi::FwdStats>(g, st);
+    if (p.a_kcontig && p.b_kcontig && p.epi == Epi::DLogits) return launch_fast_t<true, true, Epi::DLogits>(g, st);
+    if (p.a_kcontig && !p.b_kcontig && p.epi == Epi::AccumF32) return launch_fast_t<true, false, Epi::AccumF32>(g, st);
+    if (p.a_kcontig && !p.b_kcontig && p.epi == Epi::StoreF32) return launch_fast_t<true, false, Epi::StoreF32>(g, st);
+    if (!p.a_kcontig && !p.b_kcontig && p.epi == Epi::StoreF32) return launch_fast_t<false, false, Epi::StoreF32>(g, st);
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_gemm_bf16_fast(const GemmBf16Params& p, hipStream_t st) {
+    GemmBf16Group g{};
+    g.base = p;
+    GemmBf16Shard& s = g.sh[0];
+    s.A = p.A; s.B = p.B; s.offset = p.shard_offset;
+    if (p.a_kcontig && p.b_kcontig) { s.out = p.Y; s.rows = p.N; s.ld = p.ldy; }
+    else if (p.a_kcontig) { s.rows = p.K; s.ld = p.lda; }
+    else { s.out = p.C; s.rows = p.M; s.ld = p.lda; }
+    gemm_bf16_group_finish(g, 1);
+    return launch_gemm_bf16_group(g, st);
+}
+
+// A dH product has only N h / 65536 tiles but the whole vocabulary as K, so with few tokens most compute units would
+// idle (512 tokens, h = 2048: 16 tiles).  The k tiles are cut into S equal slices per output tile; the least estimated
+// time wins: rounds of 256 workgroups at 1.1 us per k tile (256 x 256 x 64 at 2400 cycles) and 5 us per tile for its
+// start and its stores, and for S > 1 the partial outputs written and read once at 4 TB/s and another launch.
+int gemm_bf16_slices(int64_t M, int64_t N, int64_t kt) {
+    const int64_t tiles = ceil_div(M, BM) * ceil_div(N, BN);
+    int best = 1;
+    double best_us = 0;
+    for (int64_t S = 1; S <= 32 && (S == 1 || S * 8 <= kt) && (S == 1 || S * M * N <= (int64_t)1 << 28); ++S) {
+        double us = (double)ceil_div(tiles * S, 256) * ((double)ceil_div(kt, S) * 1.1 + 5.0);
+        if (S > 1) us += (double)(S * M * N) * 8.0 / 4e6 + 5.0;
+        if (S == 1 || us < best_us) {
+            best = (int)S;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
+__global__ __launch_bounds__(256) void sum_slices_kernel(const floatx4* __restrict__ part, int S, int64_t quads, floatx4* C,
+                                                         int accumulate) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= quads) return;
+    floatx4 acc = part[t];
+    int z = 1;
+    for (; z + 4 <= S; z += 4) {        // four loads in flight, added in order
+        floatx4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = part[(int64_t)(z + u) * quads + t];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc += v[u];
+    }
+    for (; z < S; ++z) acc += part[(int64_t)z * quads + t];
+    C[t] = accumulate ? C[t] + acc : acc;
+}
+
+hipError_t launch_sum_slices(const float* part, int S, int64_t MN, float* C, bool accumulate, hipStream_t st) {
+    const int64_t quads = MN / 4;
+    hipLaunchKernelGGL(sum_slices_kernel, dim3((unsigned)ceil_div(quads, 256)), dim3(256), 0, st, (const floatx4*)part, S,
+                       quads, (floatx4*)C, accumulate ? 1 : 0);
+    return hipGetLastError();
 }
 
 }  // namespace vp

@@ -75,6 +75,39 @@ struct GemmBf16Params {
     int trace_cap;               // tiles per workgroup the trace buffer holds
 };
 
+// One product of the output layer over several shards on this device as ONE launch of the fast kernel.  The shards'
+// matrices are laid end to end in the dimension the vocabulary has in the product:
+//   logits (A, B K-contiguous)        along N: a tile column belongs to one shard,
+//   dW     (A, B K-strided)           along M: a tile row belongs to one shard,
+//   dH     (A K-contiguous, B K-str.) along K: a tile walks the k tiles of one shard after the other.
+// `base` holds what the shards share, sh[r] what they do not.
+constexpr int GEMM_GROUP_MAX = 16;     // shards per launch (they travel in the kernel arguments)
+struct GemmBf16Shard {
+    const u16* A;        // dW, dH: D_r
+    const u16* B;        // logits, dH: W_r
+    void* out;           // logits: Y_r or D_r (may be nullptr); dW: dW_r
+    int64_t offset;      // first vocabulary row
+    int rows;            // vocabulary rows of the shard
+    int ld;              // row stride of A (dW, dH) or of out (logits), elements
+};
+struct GemmBf16Group {
+    GemmBf16Params base;
+    int n;                         // shards
+    int slices;                    // dH: K slices, slice z writes base.C + z M ldc
+    int total;                     // tile columns / tile rows / k tiles of all shards
+    int first[GEMM_GROUP_MAX];     // the first of them that belongs to shard r (INT_MAX from n on)
+    GemmBf16Shard sh[GEMM_GROUP_MAX];
+};
+// Fills n, total and first from sh[].rows.
+void gemm_bf16_group_finish(GemmBf16Group& g, int n);
+// Whether every shard meets the fast kernel's preconditions (and the generic kernel has not been forced).
+bool gemm_bf16_group_ok(const GemmBf16Group& g);
+hipError_t launch_gemm_bf16_group(const GemmBf16Group& g, hipStream_t st);
+// K slices of a dH product [M, N] over kt k tiles (the slices' partial outputs take slices * M * N floats of scratch).
+int gemm_bf16_slices(int64_t M, int64_t N, int64_t kt);
+// C (+)= sum over S partial matrices of MN floats each, in ascending order (MN a multiple of 4)
+hipError_t launch_sum_slices(const float* part, int S, int64_t MN, float* C, bool accumulate, hipStream_t st);
+
 // Dispatches to the fast kernel when its preconditions hold (and the generic kernel has not been
 // forced through vp_profile_force_generic_gemm), else to the generic kernel.
 hipError_t launch_gemm_bf16(const GemmBf16Params& p, hipStream_t st);
@@ -82,6 +115,8 @@ void gemm_bf16_force_generic(bool on);
 // Measurement aid: device buffer into which the fast kernel's next launches write their phase stamps
 // (nullptr: off); kernel_id >= 0 restricts it to the launches timed under that kernel id.
 void gemm_bf16_set_trace(void* buf, size_t bytes, int kernel_id);
+bool gemm_bf16_generic_forced();
+bool gemm_bf16_out_ok(const GemmBf16Params& p);
 bool gemm_bf16_fast_ok(const GemmBf16Params& p);
 hipError_t launch_gemm_bf16_fast(const GemmBf16Params& p, hipStream_t st);
 
@@ -98,10 +133,22 @@ size_t gemm_f32_scratch_floats(int64_t M, int64_t N, int64_t K);
 hipError_t launch_row_stats_f32(const float* Y, int64_t ldy, const int64_t* labels, int64_t off,
                                 int N, int Vs, float* lmax, float* lsum, float* ltgt, hipStream_t st);
 
-// Fold the per-column-tile partial statistics written by the FwdStats epilogue.
-hipError_t launch_fold_partials(const float* part_max, const float* part_sum, const float* part_tgt,
-                                int tiles, int N, const int64_t* labels, int64_t off, int Vs,
-                                float* lmax, float* lsum, float* ltgt, hipStream_t st);
+// Per-shard arguments of the small kernels that serve all shards of a group in one launch.
+struct ShardList {
+    int n;
+    int rows[GEMM_GROUP_MAX];
+    int first[GEMM_GROUP_MAX + 1];     // fold: first column tile of shard r; first[n] = all of them
+    int64_t offset[GEMM_GROUP_MAX];
+    int64_t ldd[GEMM_GROUP_MAX];
+    const void* Y[GEMM_GROUP_MAX];
+    void* D[GEMM_GROUP_MAX];
+};
+
+// Fold the per-column-tile partial statistics written by the FwdStats epilogue: shard r's partials are the rows
+// first[r] .. first[r+1]-1 of part_max / part_sum, its target logits row r of part_tgt, its results row r of lmax, lsum
+// and ltgt (all rows of N).
+hipError_t launch_fold_partials(const float* part_max, const float* part_sum, const float* part_tgt, const ShardList& l,
+                                int N, const int64_t* labels, float* lmax, float* lsum, float* ltgt, hipStream_t st);
 
 hipError_t launch_combine(const float* lmax, const float* lsum, const float* ltgt, int p, int N,
                           float* gmax, float* gsum, float* loss_row, float* loss_mean, hipStream_t st);
@@ -119,8 +166,12 @@ hipError_t launch_dx_alg2(const float* A, const void* B, int b_is_bf16, const fl
                           const float* gmax, const float* gsum, int N, int h, float scale, bool overwrite, float* dH,
                           hipStream_t st);
 
-// Zeroes the padding columns Vs .. ldd-1 of the bf16 matrix D [N, ldd].
-hipError_t launch_zero_pad_columns(void* D, int N, int Vs, int64_t ldd, hipStream_t st);
+// The same in bf16 for all shards of a list (D_r from Y_r, whose row stride is rows[r]).
+hipError_t launch_dlogits_group(const ShardList& l, const int64_t* labels, const float* gmax, const float* gsum, float scale,
+                                int N, hipStream_t st);
+
+// Zeroes the padding columns rows[r] .. ldd[r]-1 of the bf16 matrices D_r [N, ldd[r]].
+hipError_t launch_zero_pad_columns(const ShardList& l, int N, hipStream_t st);
 
 // Input layer of p consecutive shards of Vs rows each, the first at row `off` of the vocabulary (host arrays of device
 // pointers, one per shard).

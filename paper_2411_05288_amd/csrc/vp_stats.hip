@@ -62,11 +62,20 @@ hipError_t launch_row_stats_f32(const float* Y, int64_t ldy, const int64_t* labe
 // Fold of the per-column-tile partial (max, sum-exp) pairs of one shard with the same online
 // rescaling as the cross-shard fold.  A workgroup folds 64 token rows; wavefront g takes the
 // tiles congruent to g mod 4 (independent loads, several in flight), and the four partial
-// results meet in LDS in the fixed order g = 0..3.
+// results meet in LDS in the fixed order g = 0..3.  blockIdx.y is the shard.
 __global__ __launch_bounds__(256) void fold_partials_kernel(const float* __restrict__ pm, const float* __restrict__ ps,
-                                                            const float* __restrict__ pt, int tiles, int N,
-                                                            const int64_t* __restrict__ labels, int64_t off, int Vs,
+                                                            const float* __restrict__ pt, ShardList l, int N,
+                                                            const int64_t* __restrict__ labels,
                                                             float* lmax, float* lsum, float* ltgt) {
+    const int sh = blockIdx.y;
+    const int tiles = l.first[sh + 1] - l.first[sh], Vs = l.rows[sh];
+    const int64_t off = l.offset[sh];
+    pm += (size_t)l.first[sh] * N;
+    ps += (size_t)l.first[sh] * N;
+    pt += (size_t)sh * N;
+    lmax += (size_t)sh * N;
+    lsum += (size_t)sh * N;
+    ltgt += (size_t)sh * N;
     __shared__ float xm[4][64], xs[4][64];
     const int g = threadIdx.x >> 6, r = threadIdx.x & 63;
     const int i = blockIdx.x * 64 + r;
@@ -108,12 +117,11 @@ __global__ __launch_bounds__(256) void fold_partials_kernel(const float* __restr
     }
 }
 
-hipError_t launch_fold_partials(const float* pm, const float* ps, const float* pt, int tiles, int N,
-                                const int64_t* labels, int64_t off, int Vs, float* lmax, float* lsum, float* ltgt,
-                                hipStream_t st) {
+hipError_t launch_fold_partials(const float* pm, const float* ps, const float* pt, const ShardList& l, int N,
+                                const int64_t* labels, float* lmax, float* lsum, float* ltgt, hipStream_t st) {
     ProfScope prof(K_FOLD, st);
-    hipLaunchKernelGGL(fold_partials_kernel, dim3((unsigned)ceil_div(N, 64)), dim3(256), 0, st, pm, ps, pt, tiles, N,
-                       labels, off, Vs, lmax, lsum, ltgt);
+    hipLaunchKernelGGL(fold_partials_kernel, dim3((unsigned)ceil_div(N, 64), l.n), dim3(256), 0, st, pm, ps, pt, l, N, labels,
+                       lmax, lsum, ltgt);
     return hipGetLastError();
 }
 
@@ -265,20 +273,76 @@ __global__ __launch_bounds__(256) void dlogits_vec_kernel(const T* Y, T* D,   //
     *reinterpret_cast<uint4*>(D + (int64_t)i * ldd + j0) = o;
 }
 
-// Zeroes columns Vs .. ldd-1 of every row of the bf16 matrix D (recompute mode: the GEMM
-// epilogue that writes D stops at column Vs).
-__global__ __launch_bounds__(256) void zero_pad_columns_kernel(u16* D, int N, int Vs, int64_t ldd) {
+// Zeroes columns rows .. ldd-1 of every row of the bf16 matrices D_r (recompute mode: the GEMM
+// epilogue that writes D stops at the shard's last column).  blockIdx.y is the shard.
+__global__ __launch_bounds__(256) void zero_pad_columns_kernel(ShardList l, int N) {
+    const int sh = blockIdx.y, Vs = l.rows[sh];
+    const int64_t ldd = l.ldd[sh];
     const int pad = (int)(ldd - Vs);
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= (int64_t)N * pad) return;
     const int i = (int)(t / pad), j = (int)(t - (int64_t)i * pad);
-    D[(int64_t)i * ldd + Vs + j] = 0;
+    ((u16*)l.D[sh])[(int64_t)i * ldd + Vs + j] = 0;
 }
 
-hipError_t launch_zero_pad_columns(void* D, int N, int Vs, int64_t ldd, hipStream_t st) {
-    if (ldd <= Vs) return hipSuccess;
-    hipLaunchKernelGGL(zero_pad_columns_kernel, dim3((unsigned)ceil_div((int64_t)N * (ldd - Vs), 256)), dim3(256), 0, st,
-                       (u16*)D, N, Vs, ldd);
+hipError_t launch_zero_pad_columns(const ShardList& l, int N, hipStream_t st) {
+    int64_t pad = 0;
+    for (int r = 0; r < l.n; ++r) pad = l.ldd[r] - l.rows[r] > pad ? l.ldd[r] - l.rows[r] : pad;
+    if (pad == 0) return hipSuccess;
+    hipLaunchKernelGGL(zero_pad_columns_kernel, dim3((unsigned)ceil_div((int64_t)N * pad, 256), l.n), dim3(256), 0, st, l, N);
+    return hipGetLastError();
+}
+
+// bf16 D of all shards of a list, any number of rows per shard: a thread forms 8 elements of a row of D (16-byte aligned:
+// ldd is a multiple of 64).  Rows of Y start 2 rows[r] bytes apart, so their 16 bytes may begin at any element: the load
+// is declared 2-byte aligned, which global memory takes on this hardware; the last chunk of a row is read by elements.
+// Bound by memory (Y in, D out).  Workgroup (x, y, z): row x, chunks 256 y .. + 255, shard z.
+__global__ __launch_bounds__(256) void dlogits_group_kernel(ShardList l, const int64_t* __restrict__ labels,
+                                                            const float* __restrict__ gmax, const float* __restrict__ gsum,
+                                                            float scale) {
+    typedef unsigned ua4 __attribute__((ext_vector_type(4), aligned(2)));
+    const int sh = blockIdx.z, Vs = l.rows[sh], i = blockIdx.x;
+    const int64_t ldd = l.ldd[sh];
+    const int j0 = (blockIdx.y * 256 + threadIdx.x) * 8;
+    if (j0 >= ldd) return;
+    const u16* y = (const u16*)l.Y[sh] + (int64_t)i * Vs + j0;
+    u16* d = (u16*)l.D[sh] + (int64_t)i * ldd + j0;
+    unsigned w[4] = {0u, 0u, 0u, 0u};
+    if (j0 + 8 <= Vs) {
+        const ua4 raw = *reinterpret_cast<const ua4*>(y);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = raw[e];
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (j0 + e < Vs) w[e >> 1] |= (unsigned)y[e] << (16 * (e & 1));
+    }
+    const float m = gmax[i];
+    const float inv = 1.0f / gsum[i];
+    const int64_t loc = labels[i] - l.offset[sh] - j0;
+    unsigned q[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float v[2] = {__uint_as_float(w[e] << 16), __uint_as_float(w[e] & 0xFFFF0000u)};
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            float pr = __expf(v[u] - m) * inv;
+            if (loc == (int64_t)(2 * e + u)) pr -= 1.0f;
+            v[u] = j0 + 2 * e + u < Vs ? pr * scale : 0.f;    // padding: zero, the dH product multiplies it by zero
+        }
+        const __bf16 a = (__bf16)v[0], b = (__bf16)v[1];
+        q[e] = (unsigned)__builtin_bit_cast(u16, a) | ((unsigned)__builtin_bit_cast(u16, b) << 16);
+    }
+    *reinterpret_cast<uint4*>(d) = make_uint4(q[0], q[1], q[2], q[3]);
+}
+
+hipError_t launch_dlogits_group(const ShardList& l, const int64_t* labels, const float* gmax, const float* gsum, float scale,
+                                int N, hipStream_t st) {
+    ProfScope prof(K_DLOGITS_EW, st);
+    int64_t ldd = 0;
+    for (int r = 0; r < l.n; ++r) ldd = l.ldd[r] > ldd ? l.ldd[r] : ldd;
+    hipLaunchKernelGGL(dlogits_group_kernel, dim3((unsigned)N, (unsigned)ceil_div(ldd, 2048), l.n), dim3(256), 0, st, l, labels,
+                       gmax, gsum, scale);
     return hipGetLastError();
 }
 

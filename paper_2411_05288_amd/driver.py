@@ -90,6 +90,16 @@ class OutputLayerPlan:
             if v > 0:
                 nbytes = max(nbytes, B.vp_workspace_bytes(fwd_call, N, h, v, self.dt, flags),
                              B.vp_workspace_bytes(B.VP_CALL_OUTPUT_BWD, N, h, v, self.dt, flags))
+        # All shards of the device go through one call when the ones with real rows come first (else one by one); that
+        # call's workspace is larger: the D matrices of all shards (at most 4 GiB) and the slices of a cut dH product.
+        self.live = sum(v > 0 for v in self.valid)
+        self.grouped = all(v > 0 for v in self.valid[:self.live])
+        if self.grouped:
+            live = self.valid[:self.live]
+            if algorithm == 1:
+                nbytes = max(nbytes, B.vp_output_group_workspace_bytes(B.VP_CALL_OUTPUT_FWD, N, h, live, self.dt, flags))
+            nbytes = max(nbytes, B.vp_output_group_workspace_bytes(B.VP_CALL_OUTPUT_BWD, N, h, live, self.dt,
+                                                                   flags | (B.VP_SKIP_DH if algorithm == 2 else 0)))
         # Algorithm 2 keeps A = softmax' W_r and B = G W_r of every shard until the barrier
         self.A = [torch.empty((N, h), **f32) for _ in range(p)] if algorithm == 2 else None
         self.Bm = [torch.empty((N, h), dtype=H.dtype, device=dev) for _ in range(p)] if algorithm == 2 else None
@@ -113,6 +123,8 @@ class OutputLayerPlan:
                     self.local_target[r].zero_()
                 continue
             lg = self.logits[r] if self.logits is not None else None
+            if self.algorithm == 1 and self.grouped:
+                continue
             if self.algorithm == 1:
                 B.vp_output_fwd(self.H, self.W[r][:v], self.labels, self.offsets[r],
                                 self.local_max[r], self.local_sumexp[r], self.local_target[r],
@@ -121,6 +133,11 @@ class OutputLayerPlan:
                 B.vp_output_fwd_alg2(self.H, self.W[r][:v], self.labels, self.offsets[r],
                                      self.local_max[r], self.local_sumexp[r], self.local_target[r],
                                      self.A[r], self.Bm[r], lg, self.workspace, stream)
+        if self.algorithm == 1 and self.grouped:
+            q = self.live
+            B.vp_output_fwd_group(self.H, [w[:v] for w, v in zip(self.W[:q], self.valid)], self.labels, self.offsets[:q],
+                                  self.local_max[:q], self.local_sumexp[:q], self.local_target[:q],
+                                  self.logits[:q] if self.logits is not None else None, self.workspace, stream)
         B.vp_combine_stats(self.local_max, self.local_sumexp, self.local_target,
                            self.global_max, self.global_sumexp, self.loss_rows, self.loss, stream)
         if self.algorithm == 2:
@@ -144,13 +161,19 @@ class OutputLayerPlan:
             if v < self.rows[r]:
                 with self._on(stream):
                     self.dW[r][v:].zero_()
-            if v == 0:
+            if v == 0 or self.grouped:
                 continue
             B.vp_output_bwd(self.H, self.W[r][:v], self.labels, self.offsets[r], self.global_max, self.global_sumexp,
                             self.logits[r] if self.logits is not None else None, self.grad_scale,
                             self.dH if self.algorithm == 1 else None, self.dW[r][:v], self.workspace, stream,
                             dh_overwrite=first)
             first = False
+        if self.grouped:
+            q = self.live
+            B.vp_output_bwd_group(self.H, [w[:v] for w, v in zip(self.W[:q], self.valid)], self.labels, self.offsets[:q],
+                                  self.global_max, self.global_sumexp, self.logits[:q] if self.logits is not None else None,
+                                  self.grad_scale, self.dH if self.algorithm == 1 else None,
+                                  [d[:v] for d, v in zip(self.dW[:q], self.valid)], self.workspace, stream, dh_overwrite=True)
 
     def step(self, stream=None) -> None:
         self.forward(stream)

@@ -1,0 +1,103 @@
+"""All shards of a device in one call (vp_output_fwd_group / vp_output_bwd_group) against the same shards one by one.
+
+The products of a group run over tiles of all shards, dH over the k tiles of all shards, cut into slices where its output
+has few tiles; the shapes sit at the edges of that: shards of unequal size, of less than a tile, of no multiple of
+anything; more shards than a launch takes; K slices that begin and end inside shards; the generic kernel's shapes.
+"""
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as si
+from gpu_util import to_dev
+
+pytestmark = pytest.mark.gpu
+
+GUARD = 1024
+
+
+def guarded(shape, dtype):
+    n = int(np.prod(shape))
+    big = torch.full((n + 2 * GUARD,), 7.0, dtype=dtype, device="cuda")
+    return big, big[GUARD:GUARD + n].view(*shape)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("save_logits", [True, False])
+@pytest.mark.parametrize("N,h,rows", [
+    (64, 128, [256, 256]),                    # one tile row, whole tiles
+    (300, 128, [1000, 1000, 936]),            # ragged in every direction, last shard shorter
+    (257, 64, [255, 1, 64, 513, 2]),          # shards of less than a tile, odd row counts (rows of the logits unaligned)
+    (130, 192, [700] * 19),                   # more shards than a launch takes; many k tiles per output tile: K slices
+    (513, 512, [1301, 1299]),                 # K slices that start and end inside a shard
+    (200, 72, [500, 500]),                    # h % 64 != 0: the logits product takes the generic kernel
+    (65, 30, [77, 130]),                      # rows not 16-byte aligned
+    (4400, 64, [4400, 300]),                  # more than 16 tile rows
+])
+def test_group_equals_single_shards(N, h, rows, save_logits, dtype):
+    import paper_2411_05288_amd as vp
+    p, V = len(rows), sum(rows)
+    print("output group", (N, h, rows, save_logits, dtype), flush=True)
+    offs = [int(x) for x in np.cumsum([0] + rows[:-1])]
+    H = to_dev(si.normal((N, h), 1.0, dtype, 31, si.STREAM_TABLE, 99))
+    W = [to_dev(si.normal((n, h), 0.05, dtype, 31, si.STREAM_TABLE, r)) for r, n in enumerate(rows)]
+    labels = si.zipf_ids(N, V, 1.1, 31)
+    labels[::9] = V + 3                       # owned by no shard
+    labels = to_dev(labels)
+    f32, dt, code = torch.float32, H.dtype, vp.VP_F32 if dtype == "f32" else vp.VP_BF16
+    flags = vp.VP_SAVE_LOGITS if save_logits else 0
+    scale = 1.0 / N
+
+    def run(group):
+        keep, out = [], {}
+        for name, shp, t in [("lm", (p, N), f32), ("ls", (p, N), f32), ("lt", (p, N), f32), ("dH", (N, h), f32)] + \
+                [("dW%d" % r, (n, h), f32) for r, n in enumerate(rows)] + \
+                [("y%d" % r, (N, n), dt) for r, n in enumerate(rows) if save_logits]:
+            big, out[name] = guarded(shp, t)
+            keep.append((name, big))
+        ys = [out["y%d" % r] for r in range(p)] if save_logits else None
+        dWs = [out["dW%d" % r] for r in range(p)]
+        gm, gs, lr, lo = (torch.empty((N,), device="cuda") for _ in range(4))
+        B = vp.binding
+        if group:
+            need = max(vp.vp_output_group_workspace_bytes(c, N, h, rows, code, flags) for c in (B.VP_CALL_OUTPUT_FWD, B.VP_CALL_OUTPUT_BWD))
+        else:
+            need = max(vp.vp_workspace_bytes(c, N, h, n, code, flags) for c in (B.VP_CALL_OUTPUT_FWD, B.VP_CALL_OUTPUT_BWD) for n in rows)
+        need = max(need, 256)
+        wsb = torch.full((need + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
+        ws = wsb[:need]
+        if group:
+            vp.vp_output_fwd_group(H, W, labels, offs, out["lm"], out["ls"], out["lt"], ys, ws)
+        else:
+            for r in range(p):
+                vp.vp_output_fwd(H, W[r], labels, offs[r], out["lm"][r], out["ls"][r], out["lt"][r], ys[r] if ys else None, ws)
+        vp.vp_combine_stats(out["lm"], out["ls"], out["lt"], gm, gs, lr, lo[:1])
+        ws.fill_(0xFF)
+        results = []
+        for over in (True, False):            # overwrite, then add to what is there
+            if group:
+                vp.vp_output_bwd_group(H, W, labels, offs, gm, gs, ys, scale, out["dH"], dWs, ws, dh_overwrite=over)
+            else:
+                for r in range(p):
+                    vp.vp_output_bwd(H, W[r], labels, offs[r], gm, gs, ys[r] if ys else None, scale, out["dH"], dWs[r], ws,
+                                     dh_overwrite=over and r == 0)
+            results.append(out["dH"].clone())
+        torch.cuda.synchronize()
+        for name, big in keep:
+            assert bool((big[:GUARD] == 7.0).all()) and bool((big[-GUARD:] == 7.0).all()), name + ": written outside"
+        assert bool((wsb[need:] == 0xFF).all()), "workspace written beyond its size"
+        out["dH"], out["dH twice"] = results
+        return out
+
+    a, b = run(True), run(False)
+    # fp32 sums of V terms in another order: each of the two differs from the exact sum by at most (adds in a chain) * 2^-24
+    # of the sum of magnitudes; sqrt(V) * 2^-22 of the largest element covers both many times over.  In fp32 the logits (and
+    # with them everything) may differ by a few ulp where the single call cut K, so there it holds for every tensor, with
+    # chains of max(V, h, N) terms and |Y| of order 1 in the exponent.
+    tol = 2.0 ** -22 * max(V, h, N) ** 0.5
+    for name in a:
+        x, y = a[name].float(), b[name].float()
+        if name.startswith("dH") or dtype == "f32":
+            assert float((x - y).abs().max()) <= tol * max(float(y.abs().max()), 1e-30), name
+        else:
+            assert torch.equal(x, y), name
