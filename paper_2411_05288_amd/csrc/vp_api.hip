@@ -42,48 +42,62 @@ size_t f32_bwd_scratch(int64_t N, int64_t h, int64_t Vs) {
 size_t f32_matrix_bytes(int64_t N, int64_t Vs) { return align_up((size_t)N * Vs * sizeof(float), 256); }
 
 // One shard as a list for the kernels that take several.
-ShardList one_shard(int64_t Vs, int64_t off) {
+ShardList one_shard(int64_t Vs, int64_t off, const void* Y = nullptr) {
     ShardList l{};
     l.n = 1;
     l.rows[0] = (int)Vs;
     l.first[1] = (int)fwd_tiles(Vs);
     l.offset[0] = off;
     l.ldd[0] = d_row_stride(Vs);
+    l.Y[0] = Y;
+    l.ldy[0] = Vs;
     return l;
 }
 
-// The bf16 shards of a group call are taken in parts of at most GEMM_GROUP_MAX shards whose D matrices (all kept until
-// the part's dH and dW products are done) take at most this much workspace together, or of one shard.
+// The shards of a group call are taken in parts of at most GEMM_GROUP_MAX shards whose D matrices (all kept until the
+// part's dH and dW products are done) take at most this much workspace together, or of one shard.
 constexpr size_t GROUP_D_BYTES = (size_t)4 << 30;
+// fp32: a part whose dH slices would take more scratch than this goes shard by shard.
+constexpr size_t GROUP_SLICE_BYTES = (size_t)1 << 30;
 
-size_t d_bytes(int64_t N, int64_t Vs) { return align_up((size_t)N * d_row_stride(Vs) * 2, 256); }
+int64_t d_ld(int64_t Vs, vp_dtype dt) { return dt == VP_BF16 ? d_row_stride(Vs) : (Vs + 3) / 4 * 4; }
+size_t d_bytes(int64_t N, int64_t Vs, vp_dtype dt) { return align_up((size_t)N * d_ld(Vs, dt) * (dt == VP_BF16 ? 2 : 4), 256); }
 
 // Shards of the part that begins at shard r0.
-int part_shards(const int64_t* rows, int p, int r0, int64_t N) {
-    size_t b = d_bytes(N, rows[r0]);
+int part_shards(const int64_t* rows, int p, int r0, int64_t N, vp_dtype dt) {
+    size_t b = d_bytes(N, rows[r0], dt);
     int n = 1;
-    while (r0 + n < p && n < GEMM_GROUP_MAX && b + d_bytes(N, rows[r0 + n]) <= GROUP_D_BYTES) b += d_bytes(N, rows[r0 + n++]);
+    while (r0 + n < p && n < GEMM_GROUP_MAX && b + d_bytes(N, rows[r0 + n], dt) <= GROUP_D_BYTES)
+        b += d_bytes(N, rows[r0 + n++], dt);
     return n;
 }
 
 struct PartSizes {
-    size_t d, slices, stats;     // bytes: D matrices, K-slice partials of dH, statistics partials of the forward pass
-    int64_t tiles;               // column tiles of the forward pass
-    int S;
+    size_t d, slices, stats;     // bytes: D matrices, K-slice partials of dH, statistics partials of the bf16 forward pass
+    int64_t tiles;               // bf16: column tiles of the forward pass
+    int S;                       // K slices of dH: bf16 over all shards, fp32 per shard
 };
-PartSizes part_sizes(const int64_t* rows, int r0, int n, int64_t N, int64_t h) {
+PartSizes part_sizes(const int64_t* rows, int r0, int n, int64_t N, int64_t h, vp_dtype dt) {
     PartSizes z{};
-    int64_t kt = 0;
+    int64_t kt = 0, longest = 0;
     for (int r = r0; r < r0 + n; ++r) {
-        z.d += d_bytes(N, rows[r]);
+        z.d += d_bytes(N, rows[r], dt);
         z.tiles += fwd_tiles(rows[r]);
         kt += ceil_div(rows[r], 64);
+        longest = rows[r] > longest ? rows[r] : longest;
     }
-    z.S = h % 8 == 0 ? gemm_bf16_slices(N, h, kt) : 1;
-    z.slices = z.S > 1 ? (size_t)z.S * N * h * sizeof(float) : 0;
-    z.stats = align_up((size_t)(2 * z.tiles + n) * N * sizeof(float), 256);
+    if (dt == VP_BF16) {
+        z.S = h % 8 == 0 ? gemm_bf16_slices(N, h, kt) : 1;
+        z.slices = z.S > 1 ? (size_t)z.S * N * h * sizeof(float) : 0;
+        z.stats = align_up((size_t)(2 * z.tiles + n) * N * sizeof(float), 256);
+    } else {
+        z.S = gemm_f32_dh_slices(N, h, longest, n);
+        z.slices = z.S * n > 1 ? (size_t)z.S * n * N * h * sizeof(float) : 0;
+    }
     return z;
 }
+// Whether a part of the fp32 path is computed as a group (a single shard has K slices in every product: launch_gemm_f32).
+bool f32_grouped(int n, const PartSizes& z, int64_t N) { return n > 1 && N <= MAX_ROW && z.slices <= GROUP_SLICE_BYTES; }
 
 GemmBf16Params logits_product(const void* H, const int64_t* labels, int64_t N, int64_t h, Epi epi) {
     GemmBf16Params g{};
@@ -218,8 +232,7 @@ vp_status vp_output_fwd(const void* H, const void* W_shard, const int64_t* label
     hipError_t e = launch_gemm_f32((const float*)H, h, 1, (const float*)W_shard, h, 1, Y, Vs, (int)N, (int)Vs, (int)h,
                                    false, scratch, st);
     if (e != hipSuccess) return VP_ERR_DEVICE;
-    return dev(launch_row_stats_f32(Y, Vs, labels, shard_offset, (int)N, (int)Vs, local_max, local_sumexp,
-                                    local_target, st));
+    return dev(launch_row_stats_f32(one_shard(Vs, shard_offset, Y), labels, (int)N, local_max, local_sumexp, local_target, st));
 }
 
 size_t vp_output_fwd_noalloc_max_scratch(void) { return NOALLOC_SCRATCH_BYTES; }
@@ -364,11 +377,13 @@ size_t vp_output_group_workspace_bytes(vp_call which, int32_t p, int64_t N, int6
         if (b == (size_t)-1) return b;
         need = b > need ? b : need;
     }
-    if (dt != VP_BF16 || h % 8) return need;
+    if (dt == VP_BF16 && h % 8) return need;
     for (int r = 0; r < p;) {
-        const int n = part_shards(rows, p, r, N);
-        const PartSizes z = part_sizes(rows, r, n, N, h);
-        const size_t b = which == VP_CALL_OUTPUT_FWD ? z.stats : z.d + ((flags & VP_SKIP_DH) ? 0 : align_up(z.slices, 256));
+        const int n = part_shards(rows, p, r, N, dt);
+        const PartSizes z = part_sizes(rows, r, n, N, h, dt);
+        size_t b = z.d + ((flags & VP_SKIP_DH) ? 0 : align_up(z.slices, 256));
+        if (dt == VP_F32 && !f32_grouped(n, z, N)) b = 0;
+        else if (which == VP_CALL_OUTPUT_FWD) b = dt == VP_BF16 ? z.stats : (flags & VP_SAVE_LOGITS) ? 0 : z.d;
         need = b > need ? b : need;
         r += n;
     }
@@ -394,9 +409,32 @@ vp_status vp_output_fwd_group(const void* H, const void* const* W_shards, const 
     if (need > 0 && (!workspace || workspace_bytes < need)) return VP_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     for (int r0 = 0; r0 < p;) {
-        int n = 1;
-        if (dt == VP_BF16 && (n = part_shards(rows, p, r0, N)) > 1) {
-            const PartSizes z = part_sizes(rows, r0, n, N, h);
+        const int n = part_shards(rows, p, r0, N, dt);
+        const PartSizes z = part_sizes(rows, r0, n, N, h, dt);
+        if (dt == VP_F32 && f32_grouped(n, z, N)) {
+            GemmF32Shard sh[GEMM_GROUP_MAX];
+            ShardList l{};
+            l.n = n;
+            char* d = (char*)workspace;
+            for (int k = 0; k < n; ++k) {
+                const int r = r0 + k;
+                const int ld = (int)(logits_out ? rows[r] : d_ld(rows[r], dt));
+                float* Y = logits_out ? (float*)logits_out[r] : (float*)d;
+                sh[k] = {nullptr, (const float*)W_shards[r], Y, (int)rows[r], ld};
+                l.rows[k] = (int)rows[r];
+                l.ldy[k] = ld;
+                l.offset[k] = shard_offsets[r];
+                l.Y[k] = Y;
+                d += d_bytes(N, rows[r], dt);
+            }
+            if (launch_gemm_f32_logits((const float*)H, N, h, sh, n, st) != hipSuccess ||
+                launch_row_stats_f32(l, labels, (int)N, local_max + r0 * N, local_sumexp + r0 * N, local_target + r0 * N, st) !=
+                    hipSuccess)
+                return VP_ERR_DEVICE;
+            r0 += n;
+            continue;
+        }
+        if (dt == VP_BF16 && n > 1) {
             float* pm = (float*)workspace;
             GemmBf16Group g{};
             ShardList l{};
@@ -460,10 +498,36 @@ vp_status vp_output_bwd_group(const void* H, const void* const* W_shards, const 
     const bool skip_dh = (flags & VP_SKIP_DH) != 0;
     for (int r0 = 0; r0 < p;) {
         const bool overwrite = (flags & VP_DH_OVERWRITE) != 0 && r0 == 0;
-        int n = 1;
+        const int n = part_shards(rows, p, r0, N, dt);
+        const PartSizes z = part_sizes(rows, r0, n, N, h, dt);
+        if (dt == VP_F32 && f32_grouped(n, z, N)) {
+            GemmF32Shard y[GEMM_GROUP_MAX], g[GEMM_GROUP_MAX];     // logits again; dH and dW
+            ShardList l{};
+            l.n = n;
+            char* d = (char*)workspace;
+            float* slices = (float*)(d + z.d);
+            for (int k = 0; k < n; ++k) {
+                const int r = r0 + k;
+                const int ld = (int)d_ld(rows[r], dt);
+                y[k] = {nullptr, (const float*)W_shards[r], (float*)d, (int)rows[r], ld};
+                g[k] = {(const float*)d, (const float*)W_shards[r], dW_shards[r], (int)rows[r], ld};
+                l.rows[k] = (int)rows[r];
+                l.offset[k] = shard_offsets[r];
+                l.Y[k] = logits_saved ? logits_saved[r] : d;       // (D is formed in place where the logits are formed again)
+                l.ldy[k] = logits_saved ? rows[r] : ld;
+                l.D[k] = d;
+                l.ldd[k] = ld;
+                d += d_bytes(N, rows[r], dt);
+            }
+            hipError_t e = logits_saved ? hipSuccess : launch_gemm_f32_logits((const float*)H, N, h, y, n, st);
+            if (e == hipSuccess) e = launch_dlogits_group(l, 0, labels, global_max, global_sumexp, grad_scale, (int)N, st);
+            if (e == hipSuccess && !skip_dh) e = launch_gemm_f32_dh(N, h, g, n, z.S, dH_accum, !overwrite, slices, st);
+            if (e == hipSuccess) e = launch_gemm_f32_dw((const float*)H, N, h, g, n, st);
+            if (e != hipSuccess) return VP_ERR_DEVICE;
+            r0 += n;
+            continue;
+        }
         if (dt == VP_BF16 && h % 8 == 0) {
-            n = part_shards(rows, p, r0, N);
-            const PartSizes z = part_sizes(rows, r0, n, N, h);
             GemmBf16Group y{}, gh{}, gw{};      // logits again, dH, dW
             ShardList l{};
             y.base = logits_product(H, labels, N, h, Epi::DLogits);
@@ -498,9 +562,10 @@ vp_status vp_output_bwd_group(const void* H, const void* const* W_shards, const 
                 y.sh[k].rows = gh.sh[k].rows = gw.sh[k].rows = l.rows[k] = (int)rows[r];
                 y.sh[k].offset = l.offset[k] = shard_offsets[r];
                 l.ldd[k] = ldd;
+                l.ldy[k] = rows[r];
                 l.Y[k] = logits_saved ? logits_saved[r] : nullptr;
                 l.D[k] = d;
-                d += d_bytes(N, rows[r]);
+                d += d_bytes(N, rows[r], dt);
             }
             gemm_bf16_group_finish(y, n);
             gemm_bf16_group_finish(gh, n);
@@ -509,7 +574,7 @@ vp_status vp_output_bwd_group(const void* H, const void* const* W_shards, const 
                 (skip_dh || gemm_bf16_group_ok(gh)) && gemm_bf16_group_ok(gw)) {
                 hipError_t e;
                 if (logits_saved) {
-                    e = launch_dlogits_group(l, labels, global_max, global_sumexp, grad_scale, (int)N, st);
+                    e = launch_dlogits_group(l, 1, labels, global_max, global_sumexp, grad_scale, (int)N, st);
                 } else {
                     e = launch_gemm_bf16_group(y, st);
                     if (e == hipSuccess) e = launch_zero_pad_columns(l, (int)N, st);
@@ -603,8 +668,7 @@ vp_status vp_output_fwd_alg2(const void* H, const void* W_shard, const int64_t* 
     if ((e = launch_gemm_f32((const float*)H, h, 1, (const float*)W_shard, h, 1, Y, Vs, (int)N, (int)Vs, (int)h, false,
                              scratch, st)) != hipSuccess)
         return VP_ERR_DEVICE;
-    if ((e = launch_row_stats_f32(Y, Vs, labels, shard_offset, (int)N, (int)Vs, local_max, local_sumexp, local_target,
-                                  st)) != hipSuccess)
+    if ((e = launch_row_stats_f32(one_shard(Vs, shard_offset, Y), labels, (int)N, local_max, local_sumexp, local_target, st)) != hipSuccess)
         return VP_ERR_DEVICE;
     if ((e = launch_dlogits(Y, Vs, P, Vs, 0, nullptr, shard_offset, local_max, local_sumexp, 1.0f, (int)N, (int)Vs,
                             st)) != hipSuccess)

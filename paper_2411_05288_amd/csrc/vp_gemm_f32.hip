@@ -25,6 +25,8 @@
 // occupy a handful of compute units.  With scratch memory the K range is cut into S slices
 // (grid.y); every slice writes its partial tile to scratch[z], and a second kernel adds the S
 // partials in ascending z (a fixed order: results repeat bit for bit).
+#include <climits>
+
 #include "vp_internal.h"
 
 namespace vp {
@@ -43,10 +45,16 @@ struct GemmF32Params {
     float* C;
     int64_t lda, ldb, ldc;
     int M, N, K;
-    int a_vec, b_vec;              // 1: 16-byte loads allowed (rows 16-byte aligned, and K % 4 == 0 if K-contiguous)
+    int a_vec, b_vec;              // not 0: 16-byte loads allowed (rows 16-byte aligned, and if K-contiguous K % 4 == 0
+                                   // or zeros behind the row's last element up to a multiple of 4)
     int accumulate;
-    int k_per_slice;
+    int k_per_slice, slices;       // of one shard
     int64_t slice_stride;          // floats between the partial outputs of consecutive slices
+    // shards: n of them; along N or M `first` is the first tile column / row of each (INT_MAX from n on) and `total` all of
+    // them, along K a slice belongs to one shard (slice z to shard z / slices)
+    int n, total;
+    int first[GEMM_GROUP_MAX];
+    GemmF32Shard sh[GEMM_GROUP_MAX];
 };
 
 template <bool KC, int ROWS>
@@ -124,18 +132,35 @@ __global__ __launch_bounds__(F_THREADS, TM == 128 ? 2 : 4) void gemm_f32_kernel(
 
     // Tiles in panels of 8 tile rows, column by column; workgroups are dealt to the 8 XCDs round-robin, so
     // every XCD takes a contiguous run of tiles and shares the operand panels of its run in its L2.
-    const int tiles_m = (g.M + TM - 1) / TM, tiles_n = (g.N + TN - 1) / TN;
+    constexpr bool CAT_N = A_KC && B_KC, CAT_M = !A_KC && !B_KC, CAT_K = A_KC && !B_KC;
+    const int tiles_m = CAT_M ? g.total : (g.M + TM - 1) / TM, tiles_n = CAT_N ? g.total : (g.N + TN - 1) / TN;
     const int total = tiles_m * tiles_n, b = blockIdx.x;
     const int x = b & 7, per = total >> 3, rem = total & 7;
     const int t = x * per + (x < rem ? x : rem) + (b >> 3);
     const int panel = t / (8 * tiles_n), in_panel = t - panel * 8 * tiles_n;
     const int prows = min(8, tiles_m - panel * 8);
-    const int m0 = (panel * 8 + in_panel % prows) * TM, n0 = (in_panel / prows) * TN;
+    int tile_m = panel * 8 + in_panel % prows, tile_n = in_panel / prows;
 
-    // slice y of the K range; with one slice this is all of K and C is the real output
-    const int k_begin = blockIdx.y * g.k_per_slice;
-    const int k_end = min(g.K, k_begin + g.k_per_slice);
-    float* C = g.C + (int64_t)blockIdx.y * g.slice_stride;
+    // the shard of this tile (or slice), its operands and its part of the output
+    int shard = CAT_K ? blockIdx.y / g.slices : 0;
+    const int slice = CAT_K ? blockIdx.y - shard * g.slices : blockIdx.y;
+    if (!CAT_K) {
+        const int tc = CAT_N ? tile_n : tile_m;
+#pragma unroll
+        for (int i = 1; i < GEMM_GROUP_MAX; ++i) shard += tc >= g.first[i] ? 1 : 0;
+        if (CAT_N) tile_n -= g.first[shard];
+        else tile_m -= g.first[shard];
+    }
+    const GemmF32Shard& s = g.sh[shard];
+    const float* A = CAT_N ? g.A : s.A;
+    const float* B = CAT_M ? g.B : s.B;
+    const int64_t lda = CAT_N ? g.lda : s.ld, ldc = CAT_N ? s.ld : g.ldc;
+    const int M = CAT_M ? s.rows : g.M, N = CAT_N ? s.rows : g.N, K = CAT_K ? s.rows : g.K;
+    const int m0 = tile_m * TM, n0 = tile_n * TN;
+    // slice of the K range; with one slice this is all of K and C is the real output (a short shard's last slices are empty)
+    const int k_begin = min(K, slice * g.k_per_slice);
+    const int k_end = min(K, k_begin + g.k_per_slice);
+    float* C = (CAT_K ? g.C : s.C) + (int64_t)blockIdx.y * g.slice_stride;
 
     floatx16 acc[MT][NT];
 #pragma unroll
@@ -146,8 +171,8 @@ __global__ __launch_bounds__(F_THREADS, TM == 128 ? 2 : 4) void gemm_f32_kernel(
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
     uintx4 ra[TA::CHUNKS], rb[TB::CHUNKS];
-    f32_load<A_KC, TM>(ra, g.A, g.lda, m0, k_begin, g.M, k_end, g.a_vec, tid);
-    f32_load<B_KC, TN>(rb, g.B, g.ldb, n0, k_begin, g.N, k_end, g.b_vec, tid);
+    f32_load<A_KC, TM>(ra, A, lda, m0, k_begin, M, k_end, g.a_vec, tid);
+    f32_load<B_KC, TN>(rb, B, g.ldb, n0, k_begin, N, k_end, g.b_vec, tid);
     f32_store<A_KC, TM>(ra, sA[0], tid);
     f32_store<B_KC, TN>(rb, sB[0], tid);
     __syncthreads();
@@ -155,8 +180,8 @@ __global__ __launch_bounds__(F_THREADS, TM == 128 ? 2 : 4) void gemm_f32_kernel(
     for (int k0 = k_begin; k0 < k_end; k0 += FK, cur ^= 1) {
         const bool more = k0 + FK < k_end;
         if (more) {
-            f32_load<A_KC, TM>(ra, g.A, g.lda, m0, k0 + FK, g.M, k_end, g.a_vec, tid);
-            f32_load<B_KC, TN>(rb, g.B, g.ldb, n0, k0 + FK, g.N, k_end, g.b_vec, tid);
+            f32_load<A_KC, TM>(ra, A, lda, m0, k0 + FK, M, k_end, g.a_vec, tid);
+            f32_load<B_KC, TN>(rb, B, g.ldb, n0, k0 + FK, N, k_end, g.b_vec, tid);
         }
 #pragma unroll
         for (int q = 0; q < FK / 8; ++q) {
@@ -187,19 +212,19 @@ __global__ __launch_bounds__(F_THREADS, TM == 128 ? 2 : 4) void gemm_f32_kernel(
         for (int j = 0; j < NT; ++j) {
             const int col = n0 + (wn * NT + j) * 32 + l32;
             const int row0 = m0 + (wm * MT + i) * 32 + 4 * hf;
-            if (col >= g.N) continue;
-            float* c = C + (int64_t)row0 * g.ldc + col;
+            if (col >= N) continue;
+            float* c = C + (int64_t)row0 * ldc + col;
             if (g.accumulate) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int dr = 8 * (r >> 2) + (r & 3);
-                    if (row0 + dr < g.M) acc[i][j][r] += c[(int64_t)dr * g.ldc];
+                    if (row0 + dr < M) acc[i][j][r] += c[(int64_t)dr * ldc];
                 }
             }
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int dr = 8 * (r >> 2) + (r & 3);
-                if (row0 + dr < g.M) c[(int64_t)dr * g.ldc] = acc[i][j][r];
+                if (row0 + dr < M) c[(int64_t)dr * ldc] = acc[i][j][r];
             }
         }
 }
@@ -230,12 +255,61 @@ size_t gemm_f32_scratch_floats(int64_t M, int64_t N, int64_t K) {
 }
 
 template <bool A_KC, bool B_KC>
-static void launch_f32_t(const GemmF32Params& g, int tile, int slices, hipStream_t st) {
-    const unsigned tiles = (unsigned)(ceil_div(g.M, tile) * ceil_div(g.N, tile));
+static void launch_f32_t(GemmF32Params& g, int tile, hipStream_t st) {
+    int64_t tm = ceil_div(g.M, tile), tn = ceil_div(g.N, tile), cat = 0;
+    for (int r = 0; r < GEMM_GROUP_MAX; ++r) {
+        g.first[r] = r < g.n ? (int)cat : INT_MAX;
+        if (r < g.n) cat += ceil_div(g.sh[r].rows, tile);
+    }
+    g.total = (int)cat;
+    int z = g.slices;
+    if (A_KC && B_KC) tn = cat;
+    else if (!A_KC) tm = cat;
+    else z *= g.n;
+    const dim3 grid((unsigned)(tm * tn), (unsigned)z);
     if (tile == 128)
-        hipLaunchKernelGGL((gemm_f32_kernel<A_KC, B_KC, 128, 128>), dim3(tiles, slices), dim3(F_THREADS), 0, st, g);
+        hipLaunchKernelGGL((gemm_f32_kernel<A_KC, B_KC, 128, 128>), grid, dim3(F_THREADS), 0, st, g);
     else
-        hipLaunchKernelGGL((gemm_f32_kernel<A_KC, B_KC, 64, 64>), dim3(tiles, slices), dim3(F_THREADS), 0, st, g);
+        hipLaunchKernelGGL((gemm_f32_kernel<A_KC, B_KC, 64, 64>), grid, dim3(F_THREADS), 0, st, g);
+}
+
+// Launches the product; C is [M, N] with row stride ldc where the shards share the output (dH).  With more than one K slice
+// (of all shards together) the partial outputs go through scratch.
+static hipError_t launch_f32(GemmF32Params g, bool a_kc, bool b_kc, float* C, int64_t ldc, bool accumulate, float* scratch,
+                             hipStream_t st) {
+    const bool cat_k = a_kc && !b_kc;
+    const int parts = g.slices * (cat_k ? g.n : 1);
+    // workgroups of 128 x 128 tiles; these (half the LDS and load traffic per flop) once every compute unit gets one
+    int64_t wg = 0;
+    for (int r = 0; r < g.n; ++r) {
+        if (a_kc && b_kc) wg += ceil_div(g.M, 128) * ceil_div(g.sh[r].rows, 128);
+        else if (a_kc) wg += ceil_div(g.M, 128) * ceil_div(g.N, 128);
+        else wg += ceil_div(g.sh[r].rows, 128) * ceil_div(g.N, 128);
+    }
+    const int tile = wg * g.slices >= 256 ? 128 : 64;
+    // parts > 1 without shared output happens for one shard only: its output is M x N as well
+    const int M = !a_kc ? g.sh[0].rows : g.M, N = a_kc && b_kc ? g.sh[0].rows : g.N;
+    const int64_t MN = (int64_t)M * N;
+    if (parts > 1) {
+        g.C = g.sh[0].C = scratch;
+        g.accumulate = 0;
+        g.slice_stride = MN;
+        if (a_kc && b_kc) g.sh[0].ld = N;
+        else g.ldc = N;
+    } else {
+        g.C = C;
+        g.accumulate = accumulate ? 1 : 0;
+        if (!(a_kc && b_kc)) g.ldc = ldc;
+    }
+    if (a_kc && b_kc) launch_f32_t<true, true>(g, tile, st);
+    else if (a_kc) launch_f32_t<true, false>(g, tile, st);
+    else if (!b_kc) launch_f32_t<false, false>(g, tile, st);
+    else return hipErrorInvalidValue;
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || parts == 1) return e;
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)ceil_div(MN, 256)), dim3(256), 0, st, scratch, parts, MN, N, C, ldc,
+                       accumulate ? 1 : 0);
+    return hipGetLastError();
 }
 
 hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float* B, int64_t sbn, int64_t sbk,
@@ -251,26 +325,76 @@ hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float
     g.M = M; g.N = N; g.K = K;
     const int S = scratch ? splitk_slices(M, N, K) : 1;
     g.k_per_slice = S > 1 ? (int)(ceil_div(ceil_div(K, S), FK) * FK) : K;     // multiple of the K step
-    const int slices = (int)ceil_div(K, g.k_per_slice);
+    g.slices = (int)ceil_div(K, g.k_per_slice);
     g.a_vec = g.lda % 4 == 0 && ((uintptr_t)A & 15u) == 0 && (!a_kc || K % 4 == 0);
     g.b_vec = g.ldb % 4 == 0 && ((uintptr_t)B & 15u) == 0 && (!b_kc || K % 4 == 0);
-    const int64_t MN = (int64_t)M * N;
-    if (slices > 1) {
-        g.C = scratch; g.ldc = N; g.accumulate = 0; g.slice_stride = MN;
-    } else {
-        g.C = C; g.ldc = ldc; g.accumulate = accumulate ? 1 : 0; g.slice_stride = 0;
+    g.n = 1;
+    GemmF32Shard& s = g.sh[0];
+    s.A = A; s.B = B; s.C = C;
+    s.rows = a_kc && b_kc ? N : a_kc ? K : M;
+    s.ld = (int)(a_kc && b_kc ? ldc : g.lda);
+    return launch_f32(g, a_kc, b_kc, C, ldc, accumulate, scratch, st);
+}
+
+// The three products over n shards (see GemmBf16Group for how they are laid end to end; here a K slice never crosses a
+// shard, so a sum runs over at most one shard's K before it meets the others in ascending order, as with one call per
+// shard).  D_r has rows of ld elements, zero behind the shard's columns, a multiple of four: 16-byte loads for any row count.
+hipError_t launch_gemm_f32_logits(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, hipStream_t st) {
+    ProfScope prof(K_GEMM_F32, st);
+    GemmF32Params g{};
+    g.A = H;
+    g.lda = g.ldb = h;
+    g.M = (int)N; g.K = (int)h;
+    g.a_vec = g.b_vec = h % 4 == 0 ? 1 : 0;
+    g.k_per_slice = g.K; g.slices = 1;
+    g.n = n;
+    for (int r = 0; r < n; ++r) g.sh[r] = sh[r];
+    return launch_f32(g, true, true, nullptr, 0, false, nullptr, st);
+}
+
+hipError_t launch_gemm_f32_dh(int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* dH, bool accumulate,
+                              float* scratch, hipStream_t st) {
+    ProfScope prof(K_GEMM_F32, st);
+    GemmF32Params g{};
+    g.ldb = h;
+    g.M = (int)N; g.N = (int)h;
+    int rows = 0;
+    for (int r = 0; r < n; ++r) {
+        g.sh[r] = sh[r];
+        rows = sh[r].rows > rows ? sh[r].rows : rows;
     }
-    // 128 x 128 tiles (half the LDS and load traffic per flop) once they give every compute unit a workgroup
-    const int tile = ceil_div(M, 128) * ceil_div(N, 128) * slices >= 256 ? 128 : 64;
-    if (a_kc && b_kc) launch_f32_t<true, true>(g, tile, slices, st);
-    else if (a_kc) launch_f32_t<true, false>(g, tile, slices, st);
-    else if (!b_kc) launch_f32_t<false, false>(g, tile, slices, st);
-    else return hipErrorInvalidValue;
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || slices == 1) return e;
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)ceil_div(MN, 256)), dim3(256), 0, st, scratch, slices, MN, N,
-                       C, ldc, accumulate ? 1 : 0);
-    return hipGetLastError();
+    g.a_vec = 1;
+    g.b_vec = h % 4 == 0 ? 1 : 0;
+    g.slices = slices;
+    g.k_per_slice = (int)(ceil_div(ceil_div(rows, slices), FK) * FK);
+    g.n = n;
+    return launch_f32(g, true, false, dH, h, accumulate, scratch, st);
+}
+
+hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, hipStream_t st) {
+    ProfScope prof(K_GEMM_F32, st);
+    GemmF32Params g{};
+    g.B = H;
+    g.ldb = h;
+    g.N = (int)h; g.K = (int)N;
+    g.a_vec = 1;
+    g.b_vec = h % 4 == 0 ? 1 : 0;
+    g.k_per_slice = g.K; g.slices = 1;
+    g.n = n;
+    for (int r = 0; r < n; ++r) g.sh[r] = sh[r];
+    return launch_f32(g, false, false, nullptr, h, false, nullptr, st);
+}
+
+// K slices per shard of a grouped dH product: one if 128 x 128 tiles of all shards fill the chip; else slices of at least
+// 512 k that make them do so; else 64 x 64 tiles, up to two workgroups per compute unit, slices of at least 64.
+int gemm_f32_dh_slices(int64_t N, int64_t h, int64_t rows, int n) {
+    const int64_t big = ceil_div(N, 128) * ceil_div(h, 128) * n, small = ceil_div(N, 64) * ceil_div(h, 64) * n;
+    const int64_t S = ceil_div(256, big);
+    if (rows / S >= 512 || S == 1) return (int)S;
+    int64_t S64 = 512 / small;
+    if (S64 > rows / 64) S64 = rows / 64;
+    if (S64 > 32) S64 = 32;
+    return S64 < 1 ? 1 : (int)S64;
 }
 
 }  // namespace vp

@@ -129,9 +129,20 @@ hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak,
 // Floats of scratch with which launch_gemm_f32 cuts K into slices for this shape (0: it would not).
 size_t gemm_f32_scratch_floats(int64_t M, int64_t N, int64_t K);
 
-// Row statistics of stored fp32 logits (fp32 path): m', sum', t'
-hipError_t launch_row_stats_f32(const float* Y, int64_t ldy, const int64_t* labels, int64_t off,
-                                int N, int Vs, float* lmax, float* lsum, float* ltgt, hipStream_t st);
+// The fp32 products over several shards in one launch (n <= GEMM_GROUP_MAX).
+struct GemmF32Shard {
+    const float* A;      // dH, dW: D_r
+    const float* B;      // logits, dH: W_r
+    float* C;            // logits: Y_r; dW: dW_r
+    int rows;            // vocabulary rows
+    int ld;              // row stride of Y_r or D_r
+};
+hipError_t launch_gemm_f32_logits(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, hipStream_t st);
+// scratch: n * slices * N * h floats unless n * slices == 1
+hipError_t launch_gemm_f32_dh(int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* dH, bool accumulate,
+                              float* scratch, hipStream_t st);
+hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, hipStream_t st);
+int gemm_f32_dh_slices(int64_t N, int64_t h, int64_t rows, int n);
 
 // Per-shard arguments of the small kernels that serve all shards of a group in one launch.
 struct ShardList {
@@ -139,10 +150,15 @@ struct ShardList {
     int rows[GEMM_GROUP_MAX];
     int first[GEMM_GROUP_MAX + 1];     // fold: first column tile of shard r; first[n] = all of them
     int64_t offset[GEMM_GROUP_MAX];
-    int64_t ldd[GEMM_GROUP_MAX];
+    int64_t ldy[GEMM_GROUP_MAX], ldd[GEMM_GROUP_MAX];
     const void* Y[GEMM_GROUP_MAX];
     void* D[GEMM_GROUP_MAX];
 };
+
+// Row statistics of stored fp32 logits (fp32 path): m', sum', t' of shard r from Y[r] (row stride ldd[r]) into row r of
+// lmax, lsum and ltgt.
+hipError_t launch_row_stats_f32(const ShardList& l, const int64_t* labels, int N, float* lmax, float* lsum, float* ltgt,
+                                hipStream_t st);
 
 // Fold the per-column-tile partial statistics written by the FwdStats epilogue: shard r's partials are the rows
 // first[r] .. first[r+1]-1 of part_max / part_sum, its target logits row r of part_tgt, its results row r of lmax, lsum
@@ -166,9 +182,9 @@ hipError_t launch_dx_alg2(const float* A, const void* B, int b_is_bf16, const fl
                           const float* gmax, const float* gsum, int N, int h, float scale, bool overwrite, float* dH,
                           hipStream_t st);
 
-// The same in bf16 for all shards of a list (D_r from Y_r, whose row stride is rows[r]).
-hipError_t launch_dlogits_group(const ShardList& l, const int64_t* labels, const float* gmax, const float* gsum, float scale,
-                                int N, hipStream_t st);
+// The same for all shards of a list (D_r from Y_r, whose row stride is ldy[r]).
+hipError_t launch_dlogits_group(const ShardList& l, int is_bf16, const int64_t* labels, const float* gmax, const float* gsum,
+                                float scale, int N, hipStream_t st);
 
 // Zeroes the padding columns rows[r] .. ldd[r]-1 of the bf16 matrices D_r [N, ldd[r]].
 hipError_t launch_zero_pad_columns(const ShardList& l, int N, hipStream_t st);

@@ -31,13 +31,12 @@ __device__ __forceinline__ float block_sum256(float v, float* sh) {
     return (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-// fp32 path, pass S statistics of one shard from its stored logits: one workgroup per row.
-__global__ __launch_bounds__(256) void row_stats_f32_kernel(const float* __restrict__ Y, int64_t ldy,
-                                                            const int64_t* __restrict__ labels, int64_t off,
-                                                            int Vs, float* lmax, float* lsum, float* ltgt) {
+// fp32 path, pass S statistics of the shards from their stored logits: one workgroup per row and shard (blockIdx.y).
+__global__ __launch_bounds__(256) void row_stats_f32_kernel(ShardList l, const int64_t* __restrict__ labels, int N,
+                                                            float* lmax, float* lsum, float* ltgt) {
     __shared__ float sh[4];
-    const int i = blockIdx.x;
-    const float* y = Y + (int64_t)i * ldy;
+    const int i = blockIdx.x, r = blockIdx.y, Vs = l.rows[r];
+    const float* __restrict__ y = (const float*)l.Y[r] + (int64_t)i * l.ldy[r];
     float m = -INFINITY;
     for (int j = threadIdx.x; j < Vs; j += 256) m = fmaxf(m, y[j]);
     m = block_max256(m, sh);
@@ -45,17 +44,18 @@ __global__ __launch_bounds__(256) void row_stats_f32_kernel(const float* __restr
     for (int j = threadIdx.x; j < Vs; j += 256) s += expf(y[j] - m);
     s = block_sum256(s, sh);
     if (threadIdx.x == 0) {
-        lmax[i] = m;
-        lsum[i] = s;
-        const int64_t loc = labels[i] - off;
-        ltgt[i] = (loc >= 0 && loc < Vs) ? y[loc] : 0.f;
+        const size_t o = (size_t)r * N + i;
+        lmax[o] = m;
+        lsum[o] = s;
+        const int64_t loc = labels[i] - l.offset[r];
+        ltgt[o] = (loc >= 0 && loc < Vs) ? y[loc] : 0.f;
     }
 }
 
-hipError_t launch_row_stats_f32(const float* Y, int64_t ldy, const int64_t* labels, int64_t off, int N, int Vs,
-                                float* lmax, float* lsum, float* ltgt, hipStream_t st) {
+hipError_t launch_row_stats_f32(const ShardList& l, const int64_t* labels, int N, float* lmax, float* lsum, float* ltgt,
+                                hipStream_t st) {
     ProfScope prof(K_ROWSTATS_F32, st);
-    hipLaunchKernelGGL(row_stats_f32_kernel, dim3(N), dim3(256), 0, st, Y, ldy, labels, off, Vs, lmax, lsum, ltgt);
+    hipLaunchKernelGGL(row_stats_f32_kernel, dim3(N, l.n), dim3(256), 0, st, l, labels, N, lmax, lsum, ltgt);
     return hipGetLastError();
 }
 
@@ -294,7 +294,7 @@ hipError_t launch_zero_pad_columns(const ShardList& l, int N, hipStream_t st) {
 }
 
 // bf16 D of all shards of a list, any number of rows per shard: a thread forms 8 elements of a row of D (16-byte aligned:
-// ldd is a multiple of 64).  Rows of Y start 2 rows[r] bytes apart, so their 16 bytes may begin at any element: the load
+// ldd is a multiple of 64).  Rows of Y start 2 ldy[r] bytes apart, so their 16 bytes may begin at any element: the load
 // is declared 2-byte aligned, which global memory takes on this hardware; the last chunk of a row is read by elements.
 // Bound by memory (Y in, D out).  Workgroup (x, y, z): row x, chunks 256 y .. + 255, shard z.
 __global__ __launch_bounds__(256) void dlogits_group_kernel(ShardList l, const int64_t* __restrict__ labels,
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(256) void dlogits_group_kernel(ShardList l, const i
     const int64_t ldd = l.ldd[sh];
     const int j0 = (blockIdx.y * 256 + threadIdx.x) * 8;
     if (j0 >= ldd) return;
-    const u16* y = (const u16*)l.Y[sh] + (int64_t)i * Vs + j0;
+    const u16* y = (const u16*)l.Y[sh] + (int64_t)i * l.ldy[sh] + j0;
     u16* d = (u16*)l.D[sh] + (int64_t)i * ldd + j0;
     unsigned w[4] = {0u, 0u, 0u, 0u};
     if (j0 + 8 <= Vs) {
@@ -336,13 +336,49 @@ __global__ __launch_bounds__(256) void dlogits_group_kernel(ShardList l, const i
     *reinterpret_cast<uint4*>(d) = make_uint4(q[0], q[1], q[2], q[3]);
 }
 
-hipError_t launch_dlogits_group(const ShardList& l, const int64_t* labels, const float* gmax, const float* gsum, float scale,
-                                int N, hipStream_t st) {
+// The same in fp32 (4 elements per thread, ldd a multiple of 4); D_r may be Y_r.
+__global__ __launch_bounds__(256) void dlogits_group_f32_kernel(ShardList l, const int64_t* __restrict__ labels,
+                                                                const float* __restrict__ gmax, const float* __restrict__ gsum,
+                                                                float scale) {
+    typedef float ua4 __attribute__((ext_vector_type(4), aligned(4)));
+    const int sh = blockIdx.z, Vs = l.rows[sh], i = blockIdx.x;
+    const int64_t ldd = l.ldd[sh];
+    const int j0 = (blockIdx.y * 256 + threadIdx.x) * 4;
+    if (j0 >= ldd) return;
+    const float* y = (const float*)l.Y[sh] + (int64_t)i * l.ldy[sh] + j0;
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (j0 + 4 <= Vs) {
+        const ua4 raw = *reinterpret_cast<const ua4*>(y);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = raw[e];
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (j0 + e < Vs) v[e] = y[e];
+    }
+    const float m = gmax[i];
+    const float inv = 1.0f / gsum[i];
+    const int64_t loc = labels[i] - l.offset[sh] - j0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float pr = expf(v[e] - m) * inv;
+        if (loc == (int64_t)e) pr -= 1.0f;
+        v[e] = j0 + e < Vs ? pr * scale : 0.f;
+    }
+    *reinterpret_cast<float4*>((float*)l.D[sh] + (int64_t)i * ldd + j0) = make_float4(v[0], v[1], v[2], v[3]);
+}
+
+hipError_t launch_dlogits_group(const ShardList& l, int is_bf16, const int64_t* labels, const float* gmax, const float* gsum,
+                                float scale, int N, hipStream_t st) {
     ProfScope prof(K_DLOGITS_EW, st);
     int64_t ldd = 0;
     for (int r = 0; r < l.n; ++r) ldd = l.ldd[r] > ldd ? l.ldd[r] : ldd;
-    hipLaunchKernelGGL(dlogits_group_kernel, dim3((unsigned)N, (unsigned)ceil_div(ldd, 2048), l.n), dim3(256), 0, st, l, labels,
-                       gmax, gsum, scale);
+    if (is_bf16)
+        hipLaunchKernelGGL(dlogits_group_kernel, dim3((unsigned)N, (unsigned)ceil_div(ldd, 2048), l.n), dim3(256), 0, st, l,
+                           labels, gmax, gsum, scale);
+    else
+        hipLaunchKernelGGL(dlogits_group_f32_kernel, dim3((unsigned)N, (unsigned)ceil_div(ldd, 1024), l.n), dim3(256), 0, st, l,
+                           labels, gmax, gsum, scale);
     return hipGetLastError();
 }
 
