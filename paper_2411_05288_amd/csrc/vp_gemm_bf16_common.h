@@ -154,19 +154,6 @@ __device__ __forceinline__ void store4_f32(float* row, int col, int n_cols, bool
             if (col + e < n_cols) row[col + e] = ACCUM ? row[col + e] + v[e] : v[e];
     }
 }
-// Stores eight consecutive bf16 values (bit patterns packed in a uint4) of a row at column `col`
-// (a multiple of 8), clipped to n_cols.
-__device__ __forceinline__ void store8_bf16(u16* row, int col, int n_cols, bool vec, const uint4& v) {
-    if (vec && col + 8 <= n_cols) {
-        *reinterpret_cast<uint4*>(row + col) = v;
-    } else {
-        const unsigned w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if (col + e < n_cols) row[col + e] = (u16)(w[e >> 1] >> (16 * (e & 1)));
-    }
-}
-
 // Orders a wavefront's own LDS writes before its following LDS reads (and the reverse).  The
 // LDS executes one wavefront's accesses in program order; this only pins the program order.
 __device__ __forceinline__ void wave_lds_fence() {
@@ -214,10 +201,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rows_rsrc(void* first_row
 }
 
 // Wavefront-private staging block -> global memory, bf16: 16 bytes per lane, row-contiguous.
-// `off` is the lane's byte offset of staged row `orow` (or beyond the buffer, see above).
+// `off` is the lane's byte offset of staged row `orow` (or beyond the buffer, see above).  Rows may start at any element:
+// vector memory takes 16-byte accesses at any address on this hardware (the forward product of N=1999, h=3072, V=50001 in
+// 8 shards: 737 us element by element, 659 us so).  tail: some lanes hold a chunk that the last column cuts; such a lane
+// stores n_tail elements at off_tail (n_tail = 0 in the others).
 template <typename St, bool STREAM>
 __device__ __forceinline__ void flush_stage_bf16(const char* region, __amdgpu_buffer_rsrc_t rs, unsigned off,
-                                                 unsigned row_bytes, int orow, int ochunk) {
+                                                 unsigned row_bytes, int orow, int ochunk, bool tail, unsigned off_tail,
+                                                 int n_tail) {
     // the staged rows are all fetched first, then stored back to back
     uintx4 v[St::STEPS];
 #pragma unroll
@@ -228,17 +219,14 @@ __device__ __forceinline__ void flush_stage_bf16(const char* region, __amdgpu_bu
 #pragma unroll
     for (int s = 0; s < St::STEPS; ++s)
         __builtin_amdgcn_raw_buffer_store_b128(v[s], rs, (int)(off + (unsigned)(s * St::RPI) * row_bytes), 0, STREAM ? 2 : 0);
-}
-
-// The same for outputs whose rows are not 16-byte aligned (or whose last column cuts a chunk).
-template <typename St>
-__device__ __forceinline__ void flush_stage_bf16_unaligned(const char* region, u16* Y, int ldy, int row_first, int M,
-                                                           int ocol, int N, bool aligned, int orow, int ochunk) {
+    if (tail) {      // uniform: the last column tile of a shard whose last column cuts a chunk
 #pragma unroll
-    for (int s = 0; s < St::STEPS; ++s) {
-        const int rr = s * St::RPI + orow;
-        const uint4 v = *reinterpret_cast<const uint4*>(region + rr * St::RS + ochunk * 16);
-        if (row_first + rr < M) store8_bf16(Y + (size_t)(row_first + rr) * ldy, ocol, N, aligned, v);
+        for (int s = 0; s < St::STEPS; ++s)
+#pragma unroll
+            for (int e = 0; e < 7; ++e)
+                __builtin_amdgcn_raw_buffer_store_b16(
+                    (short)(v[s][e >> 1] >> (16 * (e & 1))), rs,
+                    (int)(e < n_tail ? off_tail + (unsigned)(s * St::RPI) * row_bytes + 2u * e : OOB_OFFSET), 0, 0);
     }
 }
 
@@ -258,14 +246,14 @@ __device__ __forceinline__ void gemm_epilogue_f32(floatx16 (&acc)[4][NJ], const 
     const int wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int l32 = lane & 31, hf = lane >> 5;
-    const int m0 = tile_m * BM, n0 = tile_n * BN;
+    const int m0 = tile_m * BM, n0 = tile_n * (WN * WCOLS);
 
     typedef StageF32<WCOLS> St;
     constexpr bool ACCUM = (EPI == Epi::AccumF32);
     const bool vec = (g.ldc % 4 == 0) && (((uintptr_t)g.C & 15u) == 0);
     const int orow = lane / St::LPR, ochunk = lane % St::LPR;
     const int col = n0 + wn * WCOLS + ochunk * 4;
-    const bool interior = vec && (m0 + BM <= g.M) && (n0 + BN <= g.N);   // uniform over the workgroup
+    const bool interior = vec && (m0 + BM <= g.M) && (n0 + WN * WCOLS <= g.N);   // uniform over the workgroup
     // accumulators of row block i -> the wavefront's staging block
     auto stage = [&](int i) {
 #pragma unroll
@@ -358,9 +346,6 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
         // D = (softmax - G) * scale with the global statistics (pass T of Algorithm 1, with
         // the logits taken from the accumulators instead of memory)
         typedef StageBf16<WCOLS> St;
-        // uniform over the grid: rows are 16-byte aligned and chunks are never cut by the last column
-        const bool aligned = (g.ldy % 8 == 0) && (((uintptr_t)g.Y & 15u) == 0);
-        const bool vec = aligned && (g.N % 8 == 0);
         const int orow = lane / St::LPR, ochunk = lane % St::LPR;
         const int ocol = n0 + wn * WCOLS + ochunk * 8;
         const unsigned row_bytes = (unsigned)g.ldy * 2u;
@@ -368,6 +353,9 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
             tile_rows_rsrc(g.Y + (size_t)m0 * g.ldy, g.M - m0 < BM ? g.M - m0 : BM, row_bytes);
         const unsigned off0 =
             (ocol + 8 <= g.N) ? (unsigned)(wm * 128 + orow) * row_bytes + (unsigned)ocol * 2u : OOB_OFFSET;
+        const bool tail = n0 + WN * WCOLS > g.N && g.N % 8 != 0;
+        const int n_tail = ocol + 8 > g.N && ocol < g.N ? g.N - ocol : 0;
+        const unsigned off_tail = (unsigned)(wm * 128 + orow) * row_bytes + (unsigned)ocol * 2u;
         // all loads come before the first store (see the note on the labels in the FwdStats branch)
         float ml2_[4], f_[4];
         int lab_[4];
@@ -395,8 +383,7 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
             asm volatile("" : "+v"(ml2_[0]), "+v"(ml2_[1]), "+v"(ml2_[2]), "+v"(ml2_[3]));
             asm volatile("" : "+v"(f_[0]), "+v"(f_[1]), "+v"(f_[2]), "+v"(f_[3]));
         }
-        auto blocks = [&](auto vec_c) {
-            constexpr bool VEC = decltype(vec_c)::value;
+        {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 // One row block at a time: left alone, the scheduler uses every free register to overlap the
@@ -424,14 +411,11 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
                             make_uint2(pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3]));
                     }
                 wave_lds_fence();
-                if (VEC) flush_stage_bf16<St, STREAM>(region, rs, off0 + (unsigned)(i * 32) * row_bytes, row_bytes, orow, ochunk);
-                else flush_stage_bf16_unaligned<St>(region, g.Y, g.ldy, m0 + wm * 128 + i * 32, g.M, ocol, g.N, aligned, orow, ochunk);
+                const unsigned down = (unsigned)(i * 32) * row_bytes;
+                flush_stage_bf16<St, STREAM>(region, rs, off0 + down, row_bytes, orow, ochunk, tail, off_tail + down, n_tail);
                 wave_lds_fence();
             }
-        };
-        // (chosen once, outside the loop: see the fp32 branch above)
-        if (vec) blocks(std::true_type{});
-        else blocks(std::false_type{});
+        }
     }
 
     if (EPI == Epi::FwdStats) {
@@ -443,9 +427,6 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
         typedef StageBf16<WCOLS> St;
         float* xm = reinterpret_cast<float*>(xchg);          // [WN][256]
         float* xs = xm + WN * 256;                             // [WN][256]
-        // uniform over the grid: rows are 16-byte aligned and chunks are never cut by the last column
-        const bool aligned = g.Y && (g.ldy % 8 == 0) && (((uintptr_t)g.Y & 15u) == 0);
-        const bool vec = aligned && (g.N % 8 == 0);
         const int orow = lane / St::LPR, ochunk = lane % St::LPR;
         const int ocol = n0 + wn * WCOLS + ochunk * 8;
         const unsigned row_bytes = (unsigned)g.ldy * 2u;
@@ -453,6 +434,9 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
             tile_rows_rsrc(g.Y ? g.Y + (size_t)m0 * g.ldy : nullptr, g.Y ? (g.M - m0 < BM ? g.M - m0 : BM) : 0, row_bytes);
         const unsigned off0 =
             (ocol + 8 <= g.N) ? (unsigned)(wm * 128 + orow) * row_bytes + (unsigned)ocol * 2u : OOB_OFFSET;
+        const bool tail = n0 + WN * WCOLS > g.N && g.N % 8 != 0;
+        const int n_tail = ocol + 8 > g.N && ocol < g.N ? g.N - ocol : 0;
+        const unsigned off_tail = (unsigned)(wm * 128 + orow) * row_bytes + (unsigned)ocol * 2u;
         // The labels of the wavefront's four row blocks are fetched before the first store of
         // logits: the memory counter a load is waited on also counts the stores issued before it,
         // so a load inside the loop below would wait for the previous block's stores to be
@@ -463,9 +447,8 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
         // lab[i]: column of row block i's label relative to cbase if this lane holds it, else -1
         int lab[4];
         // (columns past the shard in the ragged last column tile hold -inf: see init_acc)
-        // MODE 0: the logits are not kept; 1: stored through the tile's buffer descriptor; 2: unaligned rows
-        auto blocks = [&](auto mode_c) {
-        constexpr int MODE = decltype(mode_c)::value;
+        auto blocks = [&](auto store_c) {
+        constexpr bool STORE = decltype(store_c)::value;       // whether the logits are kept
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             __builtin_amdgcn_sched_barrier(0);          // one row block at a time (see the DLogits branch)
@@ -509,7 +492,7 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
                         if (lab[i] == j * 32 + 8 * (r >> 2) + (r & 3)) t = acc[i][j][r];
                 if (lab[i] >= 0) g.part_tgt[rbase + i * 32] = t;
             }
-            if (MODE != 0) {
+            if (STORE) {
 #pragma unroll
                 for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -518,16 +501,15 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
                             make_uint2(pack_bf16x2(acc[i][j][4 * q], acc[i][j][4 * q + 1]),
                                        pack_bf16x2(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]));
                 wave_lds_fence();
-                if (MODE == 1) flush_stage_bf16<St, STREAM>(region, rs, off0 + (unsigned)(i * 32) * row_bytes, row_bytes, orow, ochunk);
-                else flush_stage_bf16_unaligned<St>(region, g.Y, g.ldy, m0 + wm * 128 + i * 32, g.M, ocol, g.N, aligned, orow, ochunk);
+                const unsigned down = (unsigned)(i * 32) * row_bytes;
+                flush_stage_bf16<St, STREAM>(region, rs, off0 + down, row_bytes, orow, ochunk, tail, off_tail + down, n_tail);
                 wave_lds_fence();
             }
         }
         };
         // (chosen once, outside the loop: see the fp32 branch above)
-        if (!g.Y) blocks(std::integral_constant<int, 0>{});
-        else if (vec) blocks(std::integral_constant<int, 1>{});
-        else blocks(std::integral_constant<int, 2>{});
+        if (!g.Y) blocks(std::false_type{});
+        else blocks(std::true_type{});
         __syncthreads();
         if (tid < 256) {
             const int row = m0 + tid;
