@@ -612,28 +612,4 @@ int gemm_bf16_slices(int64_t M, int64_t N, int64_t kt) {
     return best;
 }
 
-__global__ __launch_bounds__(256) void sum_slices_kernel(const floatx4* __restrict__ part, int S, int64_t quads, floatx4* C,
-                                                         int accumulate) {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= quads) return;
-    floatx4 acc = part[t];
-    int z = 1;
-    for (; z + 4 <= S; z += 4) {        // four loads in flight, added in order
-        floatx4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = part[(int64_t)(z + u) * quads + t];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc += v[u];
-    }
-    for (; z < S; ++z) acc += part[(int64_t)z * quads + t];
-    C[t] = accumulate ? C[t] + acc : acc;
-}
-
-hipError_t launch_sum_slices(const float* part, int S, int64_t MN, float* C, bool accumulate, hipStream_t st) {
-    const int64_t quads = MN / 4;
-    hipLaunchKernelGGL(sum_slices_kernel, dim3((unsigned)ceil_div(quads, 256)), dim3(256), 0, st, (const floatx4*)part, S,
-                       quads, (floatx4*)C, accumulate ? 1 : 0);
-    return hipGetLastError();
-}
-
 }  // namespace vp

@@ -24,7 +24,7 @@
 // Small outputs with a long K (dX of the tiny configuration: 128 x 256 outputs, K = 4096) would
 // occupy a handful of compute units.  With scratch memory the K range is cut into S slices
 // (grid.y); every slice writes its partial tile to scratch[z], and a second kernel adds the S
-// partials in ascending z (a fixed order: results repeat bit for bit).
+// partials in a fixed order (results repeat bit for bit).
 #include <climits>
 
 #include "vp_internal.h"
@@ -229,17 +229,6 @@ __global__ __launch_bounds__(F_THREADS, TM == 128 ? 2 : 4) void gemm_f32_kernel(
         }
 }
 
-// C (+)= sum over the S partial matrices [M, N] in scratch, ascending slice index
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ part, int S, int64_t MN, int N,
-                                                            float* __restrict__ C, int64_t ldc, int accumulate) {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= MN) return;
-    float acc = part[t];
-    for (int z = 1; z < S; ++z) acc += part[(int64_t)z * MN + t];
-    float* c = C + (t / N) * ldc + (t % N);
-    *c = accumulate ? (*c + acc) : acc;
-}
-
 // K slices for an [M, N] output: enough workgroups of 64 x 64 tiles to cover the chip, slices of at least 64.
 static int splitk_slices(int M, int N, int K) {
     const int64_t tiles = ceil_div(M, 64) * ceil_div(N, 64);
@@ -307,9 +296,7 @@ static hipError_t launch_f32(GemmF32Params g, bool a_kc, bool b_kc, float* C, in
     else return hipErrorInvalidValue;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || parts == 1) return e;
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)ceil_div(MN, 256)), dim3(256), 0, st, scratch, parts, MN, N, C, ldc,
-                       accumulate ? 1 : 0);
-    return hipGetLastError();
+    return launch_sum_slices(scratch, parts, MN, C, accumulate, st);        // (every such C has rows of N: ldc == N)
 }
 
 hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float* B, int64_t sbn, int64_t sbk,

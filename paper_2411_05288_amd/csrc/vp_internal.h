@@ -105,7 +105,7 @@ bool gemm_bf16_group_ok(const GemmBf16Group& g);
 hipError_t launch_gemm_bf16_group(const GemmBf16Group& g, hipStream_t st);
 // K slices of a dH product [M, N] over kt k tiles (the slices' partial outputs take slices * M * N floats of scratch).
 int gemm_bf16_slices(int64_t M, int64_t N, int64_t kt);
-// C (+)= sum over S partial matrices of MN floats each, in ascending order (MN a multiple of 4)
+// C (+)= sum over S partial matrices of MN floats each (in a fixed order)
 hipError_t launch_sum_slices(const float* part, int S, int64_t MN, float* C, bool accumulate, hipStream_t st);
 
 // Dispatches to the fast kernel when its preconditions hold (and the generic kernel has not been
