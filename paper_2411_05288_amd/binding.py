@@ -136,7 +136,7 @@ def _ptr(t: Optional[torch.Tensor], name: str, dtypes=None, shape=None) -> Optio
         raise VPError("%s must be contiguous" % name)
     if dtypes is not None and t.dtype not in dtypes:
         raise VPError("%s has dtype %s, expected one of %s" % (name, t.dtype, dtypes))
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise VPError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
     return t.data_ptr()
 

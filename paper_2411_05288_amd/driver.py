@@ -113,8 +113,13 @@ class OutputLayerPlan:
             stream = torch.cuda.ExternalStream(int(stream))
         return torch.cuda.stream(stream)
 
+    def _live(self, tensors):
+        """The real rows of the shards that have any (a view is made only of a shard with padding: on small workloads
+        the host's work is what bounds a step)."""
+        return [t if t.shape[0] == v else t[:v] for t, v in zip(tensors, self.valid[:self.live])]
+
     def forward(self, stream=None) -> None:
-        for r in range(self.p):
+        for r in range(self.live if self.algorithm == 1 and self.grouped else 0, self.p):
             v = self.valid[r]
             if v == 0:     # all padding: the neutral element of the combine (exp(-inf) = 0)
                 with self._on(stream):
@@ -123,8 +128,6 @@ class OutputLayerPlan:
                     self.local_target[r].zero_()
                 continue
             lg = self.logits[r] if self.logits is not None else None
-            if self.algorithm == 1 and self.grouped:
-                continue
             if self.algorithm == 1:
                 B.vp_output_fwd(self.H, self.W[r][:v], self.labels, self.offsets[r],
                                 self.local_max[r], self.local_sumexp[r], self.local_target[r],
@@ -135,8 +138,9 @@ class OutputLayerPlan:
                                      self.A[r], self.Bm[r], lg, self.workspace, stream)
         if self.algorithm == 1 and self.grouped:
             q = self.live
-            B.vp_output_fwd_group(self.H, [w[:v] for w, v in zip(self.W[:q], self.valid)], self.labels, self.offsets[:q],
-                                  self.local_max[:q], self.local_sumexp[:q], self.local_target[:q],
+            stats = (self.local_max, self.local_sumexp, self.local_target)
+            B.vp_output_fwd_group(self.H, self._live(self.W), self.labels, self.offsets[:q],
+                                  *(stats if q == self.p else (t[:q] for t in stats)),
                                   self.logits[:q] if self.logits is not None else None, self.workspace, stream)
         B.vp_combine_stats(self.local_max, self.local_sumexp, self.local_target,
                            self.global_max, self.global_sumexp, self.loss_rows, self.loss, stream)
@@ -170,10 +174,10 @@ class OutputLayerPlan:
             first = False
         if self.grouped:
             q = self.live
-            B.vp_output_bwd_group(self.H, [w[:v] for w, v in zip(self.W[:q], self.valid)], self.labels, self.offsets[:q],
+            B.vp_output_bwd_group(self.H, self._live(self.W), self.labels, self.offsets[:q],
                                   self.global_max, self.global_sumexp, self.logits[:q] if self.logits is not None else None,
                                   self.grad_scale, self.dH if self.algorithm == 1 else None,
-                                  [d[:v] for d, v in zip(self.dW[:q], self.valid)], self.workspace, stream, dh_overwrite=True)
+                                  self._live(self.dW), self.workspace, stream, dh_overwrite=True)
 
     def step(self, stream=None) -> None:
         self.forward(stream)
