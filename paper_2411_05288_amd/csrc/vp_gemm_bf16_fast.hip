@@ -7,17 +7,18 @@
 //
 // Preconditions (checked by gemm_bf16_fast_ok on the host; anything else takes the generic
 // kernel): rows of both operands 16-byte aligned, operands smaller than 4 GB with slack for
-// the offsets of the zero-filled tile overhang, and K a multiple of 64 when both operands
-// are K-contiguous.
+// the offsets of the zero-filled tile overhang.
 //
 // Out-of-range handling relies on the buffer descriptor: every operand is described by a raw
 // buffer of exactly its size, so a lane whose 16 bytes start at or beyond the end of the
 // matrix receives zeros.  Rows past the end of a K-contiguous operand and k-rows past the
 // end of a K-strided operand are therefore zero.  What is NOT zero is the overhang inside
 // the matrix (the k tail of a K-contiguous row runs into the next row, the column tail of a
-// K-strided row runs into the next k-row): that data is finite and either meets zeros of the
-// other operand (k tails; this is why K % 64 == 0 is required when no operand is K-strided)
-// or lands in output rows / columns that the epilogue never stores.
+// K-strided row runs into the next k-row): that data either meets zeros of the other operand
+// (k tails: D's rows are padded with zeros to a multiple of 64) or lands in output rows / columns
+// that the epilogue never stores.  Where no operand is K-strided and K is no multiple of 64, an
+// instantiation of its own (KTAIL) gives the lanes past the end of K in the last k tile an offset
+// beyond every buffer, in both operands.
 //
 // LDS layouts (a slot holds 32 of a k tile's 64 k for both operands, 16 KB each, written by 16
 // wave-wide loads of 1 KB per operand; a load writes lane i's 16 bytes at byte 16*i of its 1 KB
@@ -105,9 +106,9 @@ __device__ __forceinline__ void half_voffsets(unsigned (&voff)[4], int r0, int l
 // advance is applied to the descriptors (base += advance, size -= advance, clamped to the operand size:
 // a tile past the end of K yields empty descriptors, every lane reads zero and no access is made), so
 // the per-lane offsets are loop invariant and the range check still sees the true distance to the end.
-template <bool IS_B, int S0, int S1>
+template <bool IS_B, int S0, int S1, bool KTAIL>
 __device__ __forceinline__ void issue_operand_loads(const void* base, unsigned bytes, unsigned kadv, unsigned half_adv,
-                                                    const unsigned (&voff)[4], int wave) {
+                                                    const unsigned (&voff)[4], int wave, unsigned tail0, unsigned tail1) {
     const unsigned adv0 = kadv < bytes ? kadv : bytes;
     const unsigned adv1 = kadv + half_adv < bytes ? kadv + half_adv : bytes;
     const __amdgpu_buffer_rsrc_t rs0 = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + adv0), 0,
@@ -117,8 +118,8 @@ __device__ __forceinline__ void issue_operand_loads(const void* base, unsigned b
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {
         const int off = (IS_B ? HALF_OP_BYTES : 0) + (wave * 4 + jj) * 1024;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs0, (lds_ptr)(lds_slot<S0>() + off), 16, (int)voff[jj], 0, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs1, (lds_ptr)(lds_slot<S1>() + off), 16, (int)voff[jj], 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs0, (lds_ptr)(lds_slot<S0>() + off), 16, (int)(KTAIL ? voff[jj] | tail0 : voff[jj]), 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs1, (lds_ptr)(lds_slot<S1>() + off), 16, (int)(KTAIL ? voff[jj] | tail1 : voff[jj]), 0, 0, 0);
     }
 }
 
@@ -218,7 +219,7 @@ __device__ __forceinline__ int shard_of(const GemmBf16Group& gg, int t) {
 // have fewer tiles than there are compute units.  Whole steps, one launch per shard and product -> one per product:
 // N=512 h=2048 V=32000 p=4: 954 -> 290 us; N=1999 h=3072 V=50001 p=8: 3048 -> 1888; N=4096 h=4096 V=32000 p=8: 2940 -> 2692;
 // N=4096 h=8192 V=256000 p=16: 52.6 -> 51.5 ms; the loss alone, N=64 h=4096 V=128256 p=8: 653 -> 253 us.
-template <bool A_KC, bool B_KC, Epi EPI, bool STREAM, bool TRACE>
+template <bool A_KC, bool B_KC, Epi EPI, bool STREAM, bool TRACE, bool KTAIL>
 __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Group gg) {
     constexpr bool CAT_N = A_KC && B_KC, CAT_M = !A_KC && !B_KC, CAT_K = A_KC && !B_KC;
     const GemmBf16Params& g = gg.base;
@@ -237,6 +238,15 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Group gg) {
     int abase[4], bbase[4];
     frag_offsets<A_KC>(abase, wm, lane);
     frag_offsets<B_KC>(bbase, wn, lane);
+
+    // KTAIL: bits that put the offsets of this lane's chunk in the last k tile's two halves beyond every buffer (operands
+    // are smaller than 4 GB - 1 MB) where the chunk lies past the end of K (see half_voffsets; K is a multiple of 8)
+    unsigned tail0 = 0u, tail1 = 0u;
+    if constexpr (KTAIL) {
+        const int k = ((lane & 3) ^ ((lane >> 4) & 3)) * 8, left = g.K % BK;
+        tail0 = k >= left ? 0xFFFFFF00u : 0u;
+        tail1 = k + 32 >= left ? 0xFFFFFF00u : 0u;
+    }
 
     // Persistent workgroups: one per compute unit, each walking the tile list with stride
     // gridDim.x.  The stores of a tile's epilogue are fire-and-forget, so they drain while the
@@ -305,8 +315,9 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Group gg) {
     constexpr int DS_PER_STEP = (A_KC ? 4 : 8) + (B_KC ? 4 : 8);   // LDS reads per 16-wide k sub-step
 
     // Loads of k tile T into the slots (2T) % 5 and (2T + 1) % 5.
-#define VP_LOAD_A(T, S0, S1) issue_operand_loads<false, S0, S1>(opA, a_bytes, (unsigned)(kt_base + (T)) * a_kstep, a_half, avoff, wave)
-#define VP_LOAD_B(T, S0, S1) issue_operand_loads<true, S0, S1>(opB, b_bytes, (unsigned)(kt_base + (T)) * b_kstep, b_half, bvoff, wave)
+#define VP_TAIL(T, x) (KTAIL && (T) == nkt - 1 ? (x) : 0u)
+#define VP_LOAD_A(T, S0, S1) issue_operand_loads<false, S0, S1, KTAIL>(opA, a_bytes, (unsigned)(kt_base + (T)) * a_kstep, a_half, avoff, wave, VP_TAIL(T, tail0), VP_TAIL(T, tail1))
+#define VP_LOAD_B(T, S0, S1) issue_operand_loads<true, S0, S1, KTAIL>(opB, b_bytes, (unsigned)(kt_base + (T)) * b_kstep, b_half, bvoff, wave, VP_TAIL(T, tail0), VP_TAIL(T, tail1))
     // Waits (s_waitcnt immediates: vmcnt in bits 3:0 and 15:14, lgkmcnt in bits 11:8, expcnt 6:4 left at 7).
 #define VP_WAIT_LGKM0() __builtin_amdgcn_s_waitcnt(0xC07F)                 /* lgkmcnt(0), vmcnt(63) */
 #define VP_WAIT_VM16_LGKM0() __builtin_amdgcn_s_waitcnt(0x4070)            /* vmcnt(16) lgkmcnt(0) */
@@ -432,6 +443,7 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Group gg) {
 #undef VP_PROLOGUE
 #undef VP_TILE
 #undef VP_MIX_LOADS
+#undef VP_TAIL
 #undef VP_LOAD_A
 #undef VP_LOAD_B
 #undef VP_WAIT_LGKM0
@@ -645,6 +657,15 @@ static hipError_t launch_fast_t(const GemmBf16Group& p0, hipStream_t st) {
     const int tiles = (int)(tm * tn) * (A_KC && !B_KC ? p.slices : 1);
     const int cus = compute_unit_count();
     const int grid = tiles > cus ? cus : tiles;
+    if constexpr (A_KC && B_KC) {
+        if (p.base.K % BK) {      // (not traced)
+            if (tiles > cus)
+                hipLaunchKernelGGL((gemm_bf16_fast_kernel<A_KC, B_KC, EPI, true, false, true>), dim3(grid), dim3(NT), 0, st, p);
+            else
+                hipLaunchKernelGGL((gemm_bf16_fast_kernel<A_KC, B_KC, EPI, false, false, true>), dim3(grid), dim3(NT), 0, st, p);
+            return hipGetLastError();
+        }
+    }
     unsigned long long* tb = g_trace_buf.load();
     const int want = g_trace_kernel.load();
     if (tb && (want < 0 || want == p.base.kernel_id)) {   // measurement aid: the instrumented instantiation, if the buffer holds this launch's records
@@ -653,17 +674,17 @@ static hipError_t launch_fast_t(const GemmBf16Group& p0, hipStream_t st) {
             p.base.trace = tb;
             p.base.trace_cap = per_wg;
             if (tiles > cus)
-                hipLaunchKernelGGL((gemm_bf16_fast_kernel<A_KC, B_KC, EPI, true, true>), dim3(grid), dim3(NT), 0, st, p);
+                hipLaunchKernelGGL((gemm_bf16_fast_kernel<A_KC, B_KC, EPI, true, true, false>), dim3(grid), dim3(NT), 0, st, p);
             else
-                hipLaunchKernelGGL((gemm_bf16_fast_kernel<A_KC, B_KC, EPI, false, true>), dim3(grid), dim3(NT), 0, st, p);
+                hipLaunchKernelGGL((gemm_bf16_fast_kernel<A_KC, B_KC, EPI, false, true, false>), dim3(grid), dim3(NT), 0, st, p);
             return hipGetLastError();
         }
     }
     // more tiles than workgroups: outputs are streamed past the L2 (see gemm_epilogue)
     if (tiles > cus)
-        hipLaunchKernelGGL((gemm_bf16_fast_kernel<A_KC, B_KC, EPI, true, false>), dim3(grid), dim3(NT), 0, st, p);
+        hipLaunchKernelGGL((gemm_bf16_fast_kernel<A_KC, B_KC, EPI, true, false, false>), dim3(grid), dim3(NT), 0, st, p);
     else
-        hipLaunchKernelGGL((gemm_bf16_fast_kernel<A_KC, B_KC, EPI, false, false>), dim3(grid), dim3(NT), 0, st, p);
+        hipLaunchKernelGGL((gemm_bf16_fast_kernel<A_KC, B_KC, EPI, false, false, false>), dim3(grid), dim3(NT), 0, st, p);
     return hipGetLastError();
 }
 
@@ -683,7 +704,7 @@ bool gemm_bf16_fast_ok(const GemmBf16Params& p) {
     if (!p.vec_ok) return false;
     if (((uintptr_t)p.A | (uintptr_t)p.B) & 15u) return false;
     if ((p.lda % 8) || (p.ldb % 8)) return false;
-    if (p.a_kcontig && p.b_kcontig && (p.K % BK)) return false;
+    if (p.K % 8 && p.a_kcontig && p.b_kcontig) return false;
     // byte offsets are 32-bit: the furthest lane of the zero-filled overhang must still not wrap
     const uint64_t lim = ((uint64_t)1 << 32) - ((uint64_t)1 << 20);
     const uint64_t a_ext = p.a_kcontig ? ((uint64_t)p.M + BM) * p.lda * 2 + 2 * (uint64_t)p.K + 256

@@ -30,7 +30,8 @@ def guarded(shape, dtype):
     (257, 64, [255, 1, 64, 513, 2]),          # shards of less than a tile, odd row counts (rows of the logits unaligned)
     (130, 192, [700] * 19),                   # more shards than a launch takes; many k tiles per output tile: K slices
     (513, 512, [1301, 1299]),                 # K slices that start and end inside a shard
-    (200, 72, [500, 500]),                    # h % 64 != 0: the logits product takes the generic kernel
+    (200, 72, [500, 500]),                    # h % 64 != 0: masked k tail of the logits product
+    (70, 8, [300, 5]), (70, 32, [300, 6]), (300, 40, [512, 260]), (64, 376, [300, 300]),    # k tails of either half
     (65, 30, [77, 130]),                      # rows not 16-byte aligned
     (4400, 64, [4400, 300]),                  # more than 16 tile rows
 ])
