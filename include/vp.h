@@ -221,6 +221,15 @@ vp_status vp_output_bwd_group(const void* H, const void* const* W_shards, const 
                               float* const* dW_shards, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * vp_output_dx_alg2 for p shards that live on one device, added in ascending order: A and B are HOST arrays of p device
+ * pointers (read before the call returns), local_max and local_sumexp [p, N].  Equals p single calls bit for bit.
+ */
+vp_status vp_output_dx_alg2_group(const float* const* A, const void* const* B, int32_t p, const float* local_max,
+                                  const float* local_sumexp, const float* global_max, const float* global_sumexp,
+                                  int64_t N, int64_t h, vp_dtype dt, uint32_t flags, float grad_scale, float* dH_accum,
+                                  void* stream);
+
+/*
  * Input layer forward on one shard (appendix C): the full-size [N,h] output, row i being
  * table_shard[ids[i] - shard_offset] when the shard owns ids[i] and all +0 otherwise, so
  * that the sum over shards is the embedding lookup.  Pure data movement, bit exact.

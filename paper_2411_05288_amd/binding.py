@@ -78,6 +78,8 @@ def load_library() -> ctypes.CDLL:
     lib.vp_output_fwd_alg2.argtypes = [vp, vp, vp, i64, i64, i64, i64, c.c_int, u32, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.vp_output_dx_alg2.restype = c.c_int
     lib.vp_output_dx_alg2.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, c.c_int, u32, fl, vp, vp]
+    lib.vp_output_dx_alg2_group.restype = c.c_int
+    lib.vp_output_dx_alg2_group.argtypes = [vp, vp, i32, vp, vp, vp, vp, i64, i64, c.c_int, u32, fl, vp, vp]
     lib.vp_embed_fwd.restype = c.c_int
     lib.vp_embed_fwd.argtypes = [vp, vp, i64, i64, i64, i64, c.c_int, vp, vp]
     lib.vp_embed_bwd.restype = c.c_int
@@ -362,6 +364,20 @@ def vp_output_dx_alg2(A, B, local_max, local_sumexp, global_max, global_sumexp, 
         _ptr(global_sumexp, "global_sumexp", f, (N,)), N, h, dt, VP_DH_OVERWRITE if dh_overwrite else 0,
         float(grad_scale), _ptr(dH_accum, "dH_accum", f, (N, h)), _stream(stream))
     _check(st, "vp_output_dx_alg2")
+
+
+def vp_output_dx_alg2_group(A, B, local_max, local_sumexp, global_max, global_sumexp, grad_scale: float, dH_accum,
+                            stream=None, dh_overwrite: bool = False) -> None:
+    """vp_output_dx_alg2 for several shards in one call, in order; local_max and local_sumexp are [p, N]."""
+    N, h = A[0].shape
+    p = len(A)
+    f = (torch.float32,)
+    st = load_library().vp_output_dx_alg2_group(
+        _ptrs(A, "A", f, (N, h)), _each(B, "B", (B[0].dtype,), [(N, h)] * p), p, _ptr(local_max, "local_max", f, (p, N)),
+        _ptr(local_sumexp, "local_sumexp", f, (p, N)), _ptr(global_max, "global_max", f, (N,)),
+        _ptr(global_sumexp, "global_sumexp", f, (N,)), N, h, _dtype_code(B[0]), VP_DH_OVERWRITE if dh_overwrite else 0,
+        float(grad_scale), _ptr(dH_accum, "dH_accum", f, (N, h)), _stream(stream))
+    _check(st, "vp_output_dx_alg2_group")
 
 
 def vp_embed_fwd(table_shard, ids, shard_offset: int, out, stream=None) -> None:

@@ -680,16 +680,25 @@ vp_status vp_output_fwd_alg2(const void* H, const void* W_shard, const int64_t* 
     return dev(launch_embed_fwd(&W_shard, labels, 1, (int)N, (int)h, (int)Vs, shard_offset, 4, &B_out, st));
 }
 
+vp_status vp_output_dx_alg2_group(const float* const* A, const void* const* B, int32_t p, const float* local_max,
+                                  const float* local_sumexp, const float* global_max, const float* global_sumexp, int64_t N,
+                                  int64_t h, vp_dtype dt, uint32_t flags, float grad_scale, float* dH_accum, void* stream) {
+    if (!A || !B || p < 1 || !local_max || !local_sumexp || !global_max || !global_sumexp || !dH_accum)
+        return VP_ERR_INVALID_ARG;
+    if (N < 1 || h < 1 || !dtype_ok(dt) || (flags & ~(uint32_t)VP_DH_OVERWRITE)) return VP_ERR_INVALID_ARG;
+    if (!aligned16(dH_accum)) return VP_ERR_INVALID_ARG;
+    for (int32_t r = 0; r < p; ++r)
+        if (!A[r] || !B[r] || !aligned16(A[r]) || !aligned16(B[r])) return VP_ERR_INVALID_ARG;
+    if (N >= MAX_ELEMS || h >= MAX_ELEMS || N * h >= MAX_ELEMS) return VP_ERR_UNSUPPORTED;
+    return dev(launch_dx_alg2(A, B, p, dt == VP_BF16 ? 1 : 0, local_max, local_sumexp, global_max, global_sumexp, (int)N,
+                              (int)h, grad_scale, (flags & VP_DH_OVERWRITE) != 0, dH_accum, (hipStream_t)stream));
+}
+
 vp_status vp_output_dx_alg2(const float* A, const void* B, const float* local_max, const float* local_sumexp,
                             const float* global_max, const float* global_sumexp, int64_t N, int64_t h, vp_dtype dt,
                             uint32_t flags, float grad_scale, float* dH_accum, void* stream) {
-    if (!A || !B || !local_max || !local_sumexp || !global_max || !global_sumexp || !dH_accum)
-        return VP_ERR_INVALID_ARG;
-    if (N < 1 || h < 1 || !dtype_ok(dt) || (flags & ~(uint32_t)VP_DH_OVERWRITE)) return VP_ERR_INVALID_ARG;
-    if (!aligned16(A) || !aligned16(B) || !aligned16(dH_accum)) return VP_ERR_INVALID_ARG;
-    if (N >= MAX_ELEMS || h >= MAX_ELEMS || N * h >= MAX_ELEMS) return VP_ERR_UNSUPPORTED;
-    return dev(launch_dx_alg2(A, B, dt == VP_BF16 ? 1 : 0, local_max, local_sumexp, global_max, global_sumexp, (int)N,
-                              (int)h, grad_scale, (flags & VP_DH_OVERWRITE) != 0, dH_accum, (hipStream_t)stream));
+    return vp_output_dx_alg2_group(&A, &B, 1, local_max, local_sumexp, global_max, global_sumexp, N, h, dt, flags, grad_scale,
+                                   dH_accum, stream);
 }
 
 vp_status vp_embed_fwd_group(const void* const* table_shards, const int64_t* ids, int32_t p, int64_t N, int64_t h, int64_t Vs,

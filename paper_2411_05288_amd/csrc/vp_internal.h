@@ -176,11 +176,11 @@ hipError_t launch_dlogits(const void* Y, int64_t ldy, void* D, int64_t ldd, int 
                           int64_t off, const float* gmax, const float* gsum, float scale, int N, int Vs,
                           hipStream_t st);
 
-// dH += (A * c - B) * scale with c_i = lsum_i exp(lmax_i - gmax_i) / gsum_i  (Algorithm 2)
-// (overwrite: dH = ... instead of +=)
-hipError_t launch_dx_alg2(const float* A, const void* B, int b_is_bf16, const float* lmax, const float* lsum,
-                          const float* gmax, const float* gsum, int N, int h, float scale, bool overwrite, float* dH,
-                          hipStream_t st);
+// dH += (A_r * c_r - B_r) * scale over p shards, c_ri = lsum_ri exp(lmax_ri - gmax_i) / gsum_i  (Algorithm 2)
+// (overwrite: dH = ... instead of +=; A and B are host arrays, lmax and lsum [p, N])
+hipError_t launch_dx_alg2(const float* const* A, const void* const* B, int p, int b_is_bf16, const float* lmax,
+                          const float* lsum, const float* gmax, const float* gsum, int N, int h, float scale, bool overwrite,
+                          float* dH, hipStream_t st);
 
 // The same for all shards of a list (D_r from Y_r, whose row stride is ldy[r]).
 hipError_t launch_dlogits_group(const ShardList& l, int is_bf16, const int64_t* labels, const float* gmax, const float* gsum,

@@ -148,6 +148,12 @@ class OutputLayerPlan:
             # still inside the one barrier of Algorithm 2: the input gradient leaves here; the first shard
             # that contributes overwrites dH, so nothing is zero-filled
             first = True
+            if self.grouped:
+                q = self.live
+                B.vp_output_dx_alg2_group(self.A[:q], self.Bm[:q], self.local_max[:q], self.local_sumexp[:q],
+                                          self.global_max, self.global_sumexp, self.grad_scale, self.dH, stream,
+                                          dh_overwrite=True)
+                return
             for r in range(self.p):
                 if self.valid[r] > 0:
                     B.vp_output_dx_alg2(self.A[r], self.Bm[r], self.local_max[r], self.local_sumexp[r],

@@ -102,3 +102,21 @@ def test_group_equals_single_shards(N, h, rows, save_logits, dtype):
             assert float((x - y).abs().max()) <= tol * max(float(y.abs().max()), 1e-30), name
         else:
             assert torch.equal(x, y), name
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("N,h,p", [(70, 64, 3), (33, 30, 2), (16, 8, 17)])     # vector and element paths; more than one launch
+def test_dx_alg2_group_equals_single_calls(N, h, p, dtype):
+    import paper_2411_05288_amd as vp
+    A = [to_dev(si.normal((N, h), 1.0, "f32", 41, si.STREAM_TABLE, r)) for r in range(p)]
+    Bm = [to_dev(si.normal((N, h), 1.0, dtype, 42, si.STREAM_TABLE, r)) for r in range(p)]
+    lm = to_dev(si.normal((p, N), 1.0, "f32", 43, si.STREAM_TABLE, 0))
+    ls = to_dev(si.normal((p, N), 1.0, "f32", 44, si.STREAM_TABLE, 0)).abs() + 1
+    lm[p - 1].fill_(float("-inf"))             # a shard that is all padding
+    gm, gs = lm.max(0).values.contiguous(), ls.sum(0).contiguous()
+    for over in (True, False):
+        x = torch.full((N, h), 3.0, device="cuda")
+        y = x.clone()
+        vp.vp_output_dx_alg2_group(A, Bm, lm, ls, gm, gs, 0.25, x, dh_overwrite=over)
+        for r in range(p):
+            vp.vp_output_dx_alg2(A[r], Bm[r], lm[r], ls[r], gm, gs, 0.25, y, dh_overwrite=over and r == 0)
+        assert torch.equal(x, y)
