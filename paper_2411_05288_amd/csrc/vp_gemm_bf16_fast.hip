@@ -168,24 +168,25 @@ __device__ __forceinline__ bf16x8 read_operand(const char* half, const int (&bas
     }
 }
 
-template <bool A_KC, bool B_KC>
+// MI: row blocks of 32 of the wavefront's 128 rows that are multiplied (the others lie past the end of M).
+template <bool A_KC, bool B_KC, int MI>
 __device__ __forceinline__ void read_frags(bf16x8 (&af)[4], bf16x8 (&bf)[4], const char* slot, const int (&abase)[4],
                                            const int (&bbase)[4], int kk) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) af[t] = read_operand<A_KC>(slot, abase, t, kk);
+    for (int t = 0; t < MI; ++t) af[t] = read_operand<A_KC>(slot, abase, t, kk);
 #pragma unroll
     for (int t = 0; t < 4; ++t) bf[t] = read_operand<B_KC>(slot + HALF_OP_BYTES, bbase, t, kk);
 }
 
-template <Epi EPI>
+template <Epi EPI, int MI>
 __device__ __forceinline__ void mfma_step(floatx16 (&acc)[4][4], const bf16x8 (&af)[4], const bf16x8 (&bf)[4]) {
     // Column by column in a snake, so that only one of the two operands changes between
     // consecutive MFMAs (less switching on the operand paths; the kernel is power limited).
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-            const int i = (j & 1) ? 3 - ii : ii;
+        for (int ii = 0; ii < MI; ++ii) {
+            const int i = (j & 1) ? MI - 1 - ii : ii;
             mfma_tile<EPI>(acc[i][j], af[i], bf[j]);
         }
 }
@@ -219,7 +220,11 @@ __device__ __forceinline__ int shard_of(const GemmBf16Group& gg, int t) {
 // have fewer tiles than there are compute units.  Whole steps, one launch per shard and product -> one per product:
 // N=512 h=2048 V=32000 p=4: 954 -> 290 us; N=1999 h=3072 V=50001 p=8: 3048 -> 1888; N=4096 h=4096 V=32000 p=8: 2940 -> 2692;
 // N=4096 h=8192 V=256000 p=16: 52.6 -> 51.5 ms; the loss alone, N=64 h=4096 V=128256 p=8: 653 -> 253 us.
-template <bool A_KC, bool B_KC, Epi EPI, bool STREAM, bool TRACE, bool KTAIL>
+//
+// MI = 2: at most 64 rows (tokens): only the first two row blocks are multiplied, a quarter of the tile's rows.  The
+// products are then bound by reading W, and the loads of a k tile wait for the wavefront's matrix work no longer:
+// N=16 h=2048 V=32000: 48 -> 37 us (3.5 TB/s), N=64 h=4096 V=128256: 265 -> 224 us (4.7 TB/s).
+template <bool A_KC, bool B_KC, Epi EPI, bool STREAM, bool TRACE, bool KTAIL, int MI = 4>
 __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Group gg) {
     constexpr bool CAT_N = A_KC && B_KC, CAT_M = !A_KC && !B_KC, CAT_K = A_KC && !B_KC;
     const GemmBf16Params& g = gg.base;
@@ -312,7 +317,7 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Group gg) {
 #define VP_SCHED_MFMA(n) __builtin_amdgcn_sched_group_barrier(0x008, n, 0)
 #define VP_SCHED_DSRD(n) __builtin_amdgcn_sched_group_barrier(0x100, n, 0)
 #define VP_SCHED_VMEM(n) __builtin_amdgcn_sched_group_barrier(0x020, n, 0)
-    constexpr int DS_PER_STEP = (A_KC ? 4 : 8) + (B_KC ? 4 : 8);   // LDS reads per 16-wide k sub-step
+    constexpr int DS_PER_STEP = (A_KC ? MI : 2 * MI) + (B_KC ? 4 : 8);   // LDS reads per 16-wide k sub-step
 
     // Loads of k tile T into the slots (2T) % 5 and (2T + 1) % 5.
 #define VP_TAIL(T, x) (KTAIL && (T) == nkt - 1 ? (x) : 0u)
@@ -352,7 +357,7 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Group gg) {
     VP_BARRIER();
     if (first_pass) trace_stamp<TRACE>(g, tile_idx, 1);
     bf16x8 af0[4], bf0[4], af1[4], bf1[4];
-    read_frags<A_KC, B_KC>(af0, bf0, lds_slot<0>(), abase, bbase, 0);
+    read_frags<A_KC, B_KC, MI>(af0, bf0, lds_slot<0>(), abase, bbase, 0);
 
     // One k tile T = four 16-wide sub-steps, operands fetched one sub-step ahead into the other register
     // set.  M = T % 5 fixes the slots: first half H0 = 2M % 5, second half H1 = (2M+1) % 5, first half
@@ -366,7 +371,7 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Group gg) {
     //   sub-step 3: first operands of tile T + 1 from NX.
 #define VP_MIX_LOADS()   /* 16 MFMAs, the sub-step's operand reads and 8 global loads */              \
     _Pragma("unroll") for (int q = 0; q < 8; ++q) {                                                       \
-        VP_SCHED_MFMA(2);                                                                                \
+        VP_SCHED_MFMA(MI == 4 ? 2 : 1);                                                                                \
         VP_SCHED_DSRD((DS_PER_STEP + 7) / 8);                                                            \
         VP_SCHED_VMEM(1);                                                                                \
     }
@@ -375,29 +380,29 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Group gg) {
         constexpr int H0 = (2 * (M)) % 5, H1 = (2 * (M) + 1) % 5, NX = (2 * (M) + 2) % 5, L0 = (2 * (M) + 4) % 5; \
         opaque_offsets<A_KC>(abase);   /* keeps "slot address + lane offset" sums from being hoisted out of */ \
         opaque_offsets<B_KC>(bbase);   /* the loop for all five slots at once (they would spill)            */ \
-        read_frags<A_KC, B_KC>(af1, bf1, lds_slot<H0>(), abase, bbase, 1);                                \
-        mfma_step<EPI>(acc, af0, bf0);                                                                   \
+        read_frags<A_KC, B_KC, MI>(af1, bf1, lds_slot<H0>(), abase, bbase, 1);                                \
+        mfma_step<EPI, MI>(acc, af0, bf0);                                                                   \
         _Pragma("unroll") for (int q = 0; q < 4; ++q) {   /* operand reads early: they must have */     \
             VP_SCHED_MFMA(1);                               /* landed when the barrier is reached  */     \
             VP_SCHED_DSRD((DS_PER_STEP + 3) / 4);                                                        \
         }                                                                                                \
-        VP_SCHED_MFMA(12);                                                                               \
+        VP_SCHED_MFMA(MI == 4 ? 12 : 4);                                                                               \
         VP_WAIT_LGKM0();                                                                                 \
         VP_BARRIER();                                                                                    \
-        read_frags<A_KC, B_KC>(af0, bf0, lds_slot<H1>(), abase, bbase, 0);                                \
+        read_frags<A_KC, B_KC, MI>(af0, bf0, lds_slot<H1>(), abase, bbase, 0);                                \
         VP_LOAD_A((T) + 2, L0, H0);                                                                      \
-        mfma_step<EPI>(acc, af1, bf1);                                                                   \
+        mfma_step<EPI, MI>(acc, af1, bf1);                                                                   \
         VP_MIX_LOADS()                                                                                   \
-        read_frags<A_KC, B_KC>(af1, bf1, lds_slot<H1>(), abase, bbase, 1);                                \
+        read_frags<A_KC, B_KC, MI>(af1, bf1, lds_slot<H1>(), abase, bbase, 1);                                \
         VP_LOAD_B((T) + 2, L0, H0);                                                                      \
-        mfma_step<EPI>(acc, af0, bf0);                                                                   \
+        mfma_step<EPI, MI>(acc, af0, bf0);                                                                   \
         VP_MIX_LOADS()                                                                                   \
         VP_WAIT_VM16_LGKM0();                                                                            \
         VP_BARRIER();                                                                                    \
-        read_frags<A_KC, B_KC>(af0, bf0, lds_slot<NX>(), abase, bbase, 0);                                \
-        mfma_step<EPI>(acc, af1, bf1);                                                                   \
+        read_frags<A_KC, B_KC, MI>(af0, bf0, lds_slot<NX>(), abase, bbase, 0);                                \
+        mfma_step<EPI, MI>(acc, af1, bf1);                                                                   \
         _Pragma("unroll") for (int q = 0; q < 5; ++q) {                                                   \
-            VP_SCHED_MFMA(3);                                                                            \
+            VP_SCHED_MFMA(MI == 4 ? 3 : 1);                                                                            \
             VP_SCHED_DSRD((DS_PER_STEP + 4) / 5);                                                        \
         }                                                                                                \
         VP_SCHED_MFMA(1);                                                                                \
@@ -658,6 +663,13 @@ static hipError_t launch_fast_t(const GemmBf16Group& p0, hipStream_t st) {
     const int cus = compute_unit_count();
     const int grid = tiles > cus ? cus : tiles;
     if constexpr (A_KC && B_KC) {
+        if (p.base.M <= 64 && !g_trace_buf.load()) {
+            if (p.base.K % BK)
+                hipLaunchKernelGGL((gemm_bf16_fast_kernel<A_KC, B_KC, EPI, false, false, true, 2>), dim3(grid), dim3(NT), 0, st, p);
+            else
+                hipLaunchKernelGGL((gemm_bf16_fast_kernel<A_KC, B_KC, EPI, false, false, false, 2>), dim3(grid), dim3(NT), 0, st, p);
+            return hipGetLastError();
+        }
         if (p.base.K % BK) {      // (not traced)
             if (tiles > cus)
                 hipLaunchKernelGGL((gemm_bf16_fast_kernel<A_KC, B_KC, EPI, true, false, true>), dim3(grid), dim3(NT), 0, st, p);

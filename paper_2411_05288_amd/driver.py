@@ -1,4 +1,4 @@
-"""Host driver: runs the p shards of one configuration in sequence on one GPU.
+"""Host driver: runs the p shards of one configuration on one GPU, all of them in one call per pass.
 
 This is launch ordering and buffer ownership only.  It follows Algorithm 1 of the paper:
 pass S on every shard (vp_output_fwd), barrier C1 (vp_combine_stats, standing in for the two

@@ -33,6 +33,7 @@ def guarded(shape, dtype):
     (200, 72, [500, 500]),                    # h % 64 != 0: masked k tail of the logits product
     (70, 8, [300, 5]), (70, 32, [300, 6]), (300, 40, [512, 260]), (64, 376, [300, 300]),    # k tails of either half
     (65, 30, [77, 130]),                      # rows not 16-byte aligned
+    (63, 320, [300, 258]), (65, 320, [300, 258]), (64, 1000, [300] * 5), (1, 64, [256, 7]),    # at most 64 tokens and one more
     (4400, 64, [4400, 300]),                  # more than 16 tile rows
 ])
 def test_group_equals_single_shards(N, h, rows, save_logits, dtype):
