@@ -305,7 +305,9 @@ hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float
     if (M <= 0 || N <= 0 || K <= 0) return hipErrorInvalidValue;
     if ((sam != 1 && sak != 1) || (sbn != 1 && sbk != 1)) return hipErrorInvalidValue;
     ProfScope prof(K_GEMM_F32, st);
-    const bool a_kc = sak == 1, b_kc = sbk == 1;
+    // (a matrix of one column, or one row, is K-contiguous and K-strided at once: B is then taken as A is, because a
+    // K-strided A with a K-contiguous B is the one pair that is not instantiated - dW of hidden size 1)
+    const bool a_kc = sak == 1, b_kc = sbk == 1 && (a_kc || sbn != 1);
     GemmF32Params g{};
     g.A = A; g.B = B;
     g.lda = a_kc ? sam : sak; g.ldb = b_kc ? sbn : sbk;
