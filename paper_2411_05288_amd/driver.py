@@ -234,6 +234,12 @@ def embedding_forward(table_shards, ids):
     return plan.out
 
 
+def _disjoint(tensors) -> bool:
+    """Whether no two of the (contiguous) tensors share memory: one launch writes all of them in no order."""
+    spans = sorted((t.data_ptr(), t.data_ptr() + t.numel() * t.element_size()) for t in tensors)
+    return all(a[1] <= b[0] for a, b in zip(spans, spans[1:]))
+
+
 def embedding_backward(grad_out, ids, Vs: int, p: int, dtable: Optional[List[torch.Tensor]] = None):
     """Scatter-add into (optionally supplied, accumulate-into) fp32 shard gradients."""
     N, h = grad_out.shape
@@ -241,11 +247,12 @@ def embedding_backward(grad_out, ids, Vs: int, p: int, dtable: Optional[List[tor
     if dtable is None:
         dtable = [torch.zeros((Vs, h), dtype=torch.float32, device=dev) for _ in range(p)]
     dt = B.VP_F32 if grad_out.dtype == torch.float32 else B.VP_BF16
-    nbytes = max(B.vp_workspace_bytes(B.VP_CALL_EMBED_BWD, N, h, Vs, dt, 0), 256)
+    used = [dtable[r] for r in range(p)]
+    nbytes = max([256] + [B.vp_workspace_bytes(B.VP_CALL_EMBED_BWD, N, h, int(d.shape[0]), dt, 0) for d in used])
     ws = torch.empty((nbytes,), dtype=torch.uint8, device=dev)
-    if all(d.shape == dtable[0].shape for d in dtable[:p]) and dtable[0].shape[0] == Vs:
-        B.vp_embed_bwd_group(grad_out, ids, 0, dtable[:p], ws)
+    if used and all(d.shape[0] == Vs for d in used) and _disjoint(used):
+        B.vp_embed_bwd_group(grad_out, ids, 0, used, ws)
         return dtable
-    for r in range(p):
+    for r in range(p):       # gradients of other sizes, or that share memory: one after the other
         B.vp_embed_bwd(grad_out, ids, r * Vs, dtable[r], ws)
     return dtable

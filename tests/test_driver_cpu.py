@@ -1,0 +1,65 @@
+"""Host-side choices of the driver, on CPU tensors: which entry point a call goes to, and with how much workspace.  The
+entry points that would launch kernels are replaced by recorders."""
+import pytest
+import torch
+
+import paper_2411_05288_amd as vp
+from paper_2411_05288_amd import binding as B, driver
+
+
+@pytest.fixture
+def embed_calls(monkeypatch):
+    calls = []
+    monkeypatch.setattr(B, "vp_embed_bwd_group",
+                        lambda g, ids, off, dt, ws, stream=None: calls.append(("group", [d.data_ptr() for d in dt], ws.numel())))
+    monkeypatch.setattr(B, "vp_embed_bwd",
+                        lambda g, ids, off, d, ws, stream=None: calls.append(("one", off, d.data_ptr(), ws.numel())))
+    return calls
+
+
+def grads(p, Vs=6, h=8):
+    return [torch.zeros(Vs, h) for _ in range(p)]
+
+
+def test_embedding_backward_takes_one_call_for_shards_of_their_own(embed_calls):
+    g, ids, d = torch.zeros(5, 8), torch.zeros(5, dtype=torch.int64), grads(3)
+    assert driver.embedding_backward(g, ids, 6, 3, d) is d
+    assert [c[0] for c in embed_calls] == ["group"] and embed_calls[0][1] == [t.data_ptr() for t in d]
+    # more gradients than shards: the others are left alone
+    embed_calls.clear()
+    driver.embedding_backward(g, ids, 6, 2, d)
+    assert embed_calls[0][1] == [t.data_ptr() for t in d[:2]]
+    # one tensor [p, Vs, h] instead of a list, and shards that touch without overlapping
+    embed_calls.clear()
+    driver.embedding_backward(g, ids, 6, 3, torch.zeros(3, 6, 8))
+    assert [c[0] for c in embed_calls] == ["group"]
+
+
+def test_embedding_backward_refuses_too_few_gradients(embed_calls):
+    # a shard without a gradient must not be passed over in silence
+    with pytest.raises(IndexError):
+        driver.embedding_backward(torch.zeros(5, 8), torch.zeros(5, dtype=torch.int64), 6, 4, grads(2))
+    assert embed_calls == []
+
+
+def test_embedding_backward_of_no_shards(embed_calls):
+    assert driver.embedding_backward(torch.zeros(5, 8), torch.zeros(5, dtype=torch.int64), 6, 0) == []
+    assert embed_calls == []
+
+
+@pytest.mark.parametrize("overlap", ["same", "shifted"])
+def test_embedding_backward_of_gradients_that_share_memory_goes_in_order(embed_calls, overlap):
+    # one launch would add to the same rows from several workgroups at once
+    base = torch.zeros(9, 8)
+    d = [base[:6], base[:6]] if overlap == "same" else [base[3:9], base[:6]]
+    driver.embedding_backward(torch.zeros(5, 8), torch.zeros(5, dtype=torch.int64), 6, 2, d)
+    assert [c[:3] for c in embed_calls] == [("one", 0, d[0].data_ptr()), ("one", 6, d[1].data_ptr())]
+
+
+def test_embedding_backward_workspace_covers_every_gradient(embed_calls):
+    # gradients with more rows than Vs go one by one; above 2^19 - 1 rows a call needs the larger workspace
+    N, h, rows = 5000, 8, 2 ** 19
+    d = [torch.empty(rows, h), torch.empty(6, h)]
+    driver.embedding_backward(torch.zeros(N, h), torch.zeros(N, dtype=torch.int64), 6, 2, d)
+    assert [c[0] for c in embed_calls] == ["one", "one"]
+    assert embed_calls[0][3] >= vp.vp_workspace_bytes(B.VP_CALL_EMBED_BWD, N, h, rows, vp.VP_F32, 0)
