@@ -214,7 +214,9 @@ class EmbeddingPlan:
         self.dt = B.VP_F32 if table_shards[0].dtype == torch.float32 else B.VP_BF16
         self.out = [torch.empty((self.N, self.h), dtype=table_shards[0].dtype, device=dev) for _ in range(self.p)]
         self.dtable = [torch.zeros((self.Vs, self.h), dtype=torch.float32, device=dev) for _ in range(self.p)]
-        nbytes = max(B.vp_workspace_bytes(B.VP_CALL_EMBED_BWD, self.N, self.h, self.Vs, self.dt, 0), 256)
+        # the gradient may be of the other type than the tables, and the size depends on it
+        nbytes = max([256] + [B.vp_workspace_bytes(B.VP_CALL_EMBED_BWD, self.N, self.h, self.Vs, dt, 0)
+                              for dt in (B.VP_F32, B.VP_BF16)])
         self.workspace = torch.empty((nbytes,), dtype=torch.uint8, device=dev)
 
     def forward(self, stream=None) -> None:

@@ -63,3 +63,12 @@ def test_embedding_backward_workspace_covers_every_gradient(embed_calls):
     driver.embedding_backward(torch.zeros(N, h), torch.zeros(N, dtype=torch.int64), 6, 2, d)
     assert [c[0] for c in embed_calls] == ["one", "one"]
     assert embed_calls[0][3] >= vp.vp_workspace_bytes(B.VP_CALL_EMBED_BWD, N, h, rows, vp.VP_F32, 0)
+
+
+@pytest.mark.parametrize("table,grad", [(torch.bfloat16, torch.float32), (torch.float32, torch.bfloat16)])
+def test_embedding_plan_workspace_fits_a_gradient_of_the_other_type(table, grad):
+    # at 4 GB of fp32 gradients the scatter-add takes another path than at 2 GB of bf16 ones, with a larger workspace
+    N, h = 8192, (1 << 17) + 8
+    plan = driver.EmbeddingPlan([torch.empty(2, h, dtype=table)], torch.zeros(N, dtype=torch.int64), None)
+    code = vp.VP_F32 if grad == torch.float32 else vp.VP_BF16
+    assert plan.workspace.numel() >= vp.vp_workspace_bytes(B.VP_CALL_EMBED_BWD, N, h, 2, code, 0)
