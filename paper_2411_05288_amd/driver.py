@@ -41,11 +41,16 @@ class OutputLayerPlan:
     vocabulary when the table was padded to split evenly (the paper pads V to a multiple of
     2p): rows at or beyond it are padding.  Padding never reaches the kernels -- a shard is
     passed as its valid prefix, which is the same as giving the padded logits -inf -- and
-    the padding rows of dW are zero."""
+    the padding rows of dW are zero.
+
+    All shards go through one call per pass, which keeps the D matrices of all of them (at most
+    4 GiB) and up to 1 GiB of partial sums in ``workspace``; one shard at a time needs the largest
+    D alone.  ``workspace_limit`` (bytes) makes the plan go shard by shard where the workspace
+    would be larger than that, and so does a device without room for it."""
 
     def __init__(self, H: torch.Tensor, W_shards: List[torch.Tensor], labels: torch.Tensor,
                  save_logits: bool = True, grad_scale: Optional[float] = None, vocab_size: Optional[int] = None,
-                 algorithm: int = 1):
+                 algorithm: int = 1, workspace_limit: Optional[int] = None):
         if algorithm not in (1, 2):
             raise B.VPError("algorithm must be 1 (two barriers) or 2 (one barrier)")
         self.algorithm = algorithm
@@ -96,14 +101,22 @@ class OutputLayerPlan:
         self.grouped = all(v > 0 for v in self.valid[:self.live])
         if self.grouped:
             live = self.valid[:self.live]
+            group_bytes = max(nbytes, B.vp_output_group_workspace_bytes(B.VP_CALL_OUTPUT_BWD, N, h, live, self.dt,
+                                                                        flags | (B.VP_SKIP_DH if algorithm == 2 else 0)))
             if algorithm == 1:
-                nbytes = max(nbytes, B.vp_output_group_workspace_bytes(B.VP_CALL_OUTPUT_FWD, N, h, live, self.dt, flags))
-            nbytes = max(nbytes, B.vp_output_group_workspace_bytes(B.VP_CALL_OUTPUT_BWD, N, h, live, self.dt,
-                                                                   flags | (B.VP_SKIP_DH if algorithm == 2 else 0)))
+                group_bytes = max(group_bytes, B.vp_output_group_workspace_bytes(B.VP_CALL_OUTPUT_FWD, N, h, live, self.dt,
+                                                                                 flags))
+            self.grouped = workspace_limit is None or group_bytes <= max(nbytes, workspace_limit)
         # Algorithm 2 keeps A = softmax' W_r and B = G W_r of every shard until the barrier
         self.A = [torch.empty((N, h), **f32) for _ in range(p)] if algorithm == 2 else None
         self.Bm = [torch.empty((N, h), dtype=H.dtype, device=dev) for _ in range(p)] if algorithm == 2 else None
-        self.workspace = torch.empty((nbytes,), dtype=torch.uint8, device=dev)
+        if self.grouped:
+            try:
+                self.workspace = torch.empty((group_bytes,), dtype=torch.uint8, device=dev)
+            except torch.OutOfMemoryError:
+                self.grouped = False
+        if not self.grouped:
+            self.workspace = torch.empty((nbytes,), dtype=torch.uint8, device=dev)
 
     def _on(self, stream):
         """Context in which torch-side fills run on the same stream as the library's kernels."""

@@ -72,3 +72,40 @@ def test_embedding_plan_workspace_fits_a_gradient_of_the_other_type(table, grad)
     plan = driver.EmbeddingPlan([torch.empty(2, h, dtype=table)], torch.zeros(N, dtype=torch.int64), None)
     code = vp.VP_F32 if grad == torch.float32 else vp.VP_BF16
     assert plan.workspace.numel() >= vp.vp_workspace_bytes(B.VP_CALL_EMBED_BWD, N, h, 2, code, 0)
+
+
+def output_plan(algorithm=1, **kw):
+    N, h, p, rows = 300, 64, 4, 1000
+    return driver.OutputLayerPlan(torch.zeros(N, h, dtype=torch.bfloat16),
+                                  [torch.zeros(rows, h, dtype=torch.bfloat16) for _ in range(p)],
+                                  torch.zeros(N, dtype=torch.int64), algorithm=algorithm, **kw)
+
+
+def one_shard_bytes(algorithm):
+    fwd = B.VP_CALL_OUTPUT_FWD if algorithm == 1 else B.VP_CALL_OUTPUT_FWD_ALG2
+    return max(B.vp_workspace_bytes(c, 300, 64, 1000, vp.VP_BF16, B.VP_SAVE_LOGITS) for c in (fwd, B.VP_CALL_OUTPUT_BWD))
+
+
+@pytest.mark.parametrize("algorithm", [1, 2])
+def test_output_plan_workspace_limit(algorithm):
+    full = output_plan(algorithm)
+    assert full.grouped and full.workspace.numel() > one_shard_bytes(algorithm)
+    assert output_plan(algorithm, workspace_limit=full.workspace.numel()).grouped
+    for limit in (full.workspace.numel() - 1, 0):
+        small = output_plan(algorithm, workspace_limit=limit)
+        assert not small.grouped and small.workspace.numel() == one_shard_bytes(algorithm)
+
+
+@pytest.mark.parametrize("algorithm", [1, 2])
+def test_output_plan_on_a_device_without_room_for_all_shards(monkeypatch, algorithm):
+    # what one shard at a time had room for still runs
+    limit, empty = one_shard_bytes(algorithm), torch.empty
+
+    def full_device(shape, *a, dtype=None, **kw):
+        if dtype == torch.uint8 and shape[0] > limit:
+            raise torch.OutOfMemoryError("no room")
+        return empty(shape, *a, dtype=dtype, **kw)
+
+    monkeypatch.setattr(torch, "empty", full_device)
+    plan = output_plan(algorithm)
+    assert not plan.grouped and plan.workspace.numel() == limit

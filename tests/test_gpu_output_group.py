@@ -121,3 +121,27 @@ def test_dx_alg2_group_equals_single_calls(N, h, p, dtype):
         for r in range(p):
             vp.vp_output_dx_alg2(A[r], Bm[r], lm[r], ls[r], gm, gs, 0.25, y, dh_overwrite=over and r == 0)
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("algorithm", [1, 2])
+@pytest.mark.parametrize("save_logits", [True, False])
+def test_plan_with_a_workspace_limit(save_logits, algorithm):
+    # shard by shard, with a short shard and one of padding alone; same numbers as in one call per pass
+    import paper_2411_05288_amd as vp
+    N, h, p, rows, V = 300, 128, 4, 520, 1300
+    H, Ws, labels = si.small_output_case(N, h, rows * p, p, "bf16", seed=71, w_std=0.08)
+    H, Ws, labels = to_dev(H), [to_dev(w) for w in Ws], to_dev(labels % V)
+    plans = []
+    for limit in (None, 0):
+        plans.append(vp.OutputLayerPlan(H, Ws, labels, save_logits, vocab_size=V, algorithm=algorithm, workspace_limit=limit))
+        plans[-1].workspace.fill_(0xFF)
+        plans[-1].step()
+    torch.cuda.synchronize()
+    a, b = plans
+    assert a.grouped and not b.grouped and b.workspace.numel() < a.workspace.numel()
+    for name in ("loss", "local_max", "local_sumexp", "local_target", "global_max", "global_sumexp"):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
+    for x, y in zip(a.dW, b.dW):
+        assert torch.equal(x, y)
+    # (orders of the sums: see the bound above)
+    assert float((a.dH - b.dH).abs().max()) <= 2.0 ** -22 * V ** 0.5 * float(b.dH.abs().max())
