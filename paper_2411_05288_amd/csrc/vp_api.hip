@@ -76,12 +76,16 @@ struct PartSizes {
     size_t d, slices, stats;     // bytes: D matrices, K-slice partials of dH, statistics partials of the bf16 forward pass
     int64_t tiles;               // bf16: column tiles of the forward pass
     int S;                       // K slices of dH: bf16 over all shards, fp32 per shard
+    int S_logits, S_dw;          // fp32: K slices of the logits and of dW
+    size_t logits_slices, dw_slices;     // fp32: bytes of their partials
 };
 PartSizes part_sizes(const int64_t* rows, int r0, int n, int64_t N, int64_t h, vp_dtype dt) {
     PartSizes z{};
     int64_t kt = 0, longest = 0;
+    size_t dw = 0;
     for (int r = r0; r < r0 + n; ++r) {
         z.d += d_bytes(N, rows[r], dt);
+        dw += align_up((size_t)rows[r] * h * sizeof(float), 256);
         z.tiles += fwd_tiles(rows[r]);
         kt += ceil_div(rows[r], 64);
         longest = rows[r] > longest ? rows[r] : longest;
@@ -93,6 +97,10 @@ PartSizes part_sizes(const int64_t* rows, int r0, int n, int64_t N, int64_t h, v
     } else {
         z.S = gemm_f32_dh_slices(N, h, longest, n);
         z.slices = z.S * n > 1 ? (size_t)z.S * n * N * h * sizeof(float) : 0;
+        z.S_logits = gemm_f32_group_slices(ceil_div(N, 64) * kt, h);
+        z.S_dw = gemm_f32_group_slices(ceil_div(h, 64) * kt, N);
+        z.logits_slices = z.S_logits > 1 ? z.S_logits * z.d : 0;
+        z.dw_slices = z.S_dw > 1 ? z.S_dw * dw : 0;
     }
     return z;
 }
@@ -381,9 +389,11 @@ size_t vp_output_group_workspace_bytes(vp_call which, int32_t p, int64_t N, int6
     for (int r = 0; r < p;) {
         const int n = part_shards(rows, p, r, N, dt);
         const PartSizes z = part_sizes(rows, r, n, N, h, dt);
-        size_t b = z.d + ((flags & VP_SKIP_DH) ? 0 : align_up(z.slices, 256));
+        // the slices' partials of one product at a time
+        const size_t logits = which == VP_CALL_OUTPUT_BWD && (flags & VP_SAVE_LOGITS) ? 0 : z.logits_slices;
+        size_t b = z.d + max3((flags & VP_SKIP_DH) ? 0 : align_up(z.slices, 256), logits, z.dw_slices);
         if (dt == VP_F32 && !f32_grouped(n, z, N)) b = 0;
-        else if (which == VP_CALL_OUTPUT_FWD) b = dt == VP_BF16 ? z.stats : (flags & VP_SAVE_LOGITS) ? 0 : z.d;
+        else if (which == VP_CALL_OUTPUT_FWD) b = dt == VP_BF16 ? z.stats : ((flags & VP_SAVE_LOGITS) ? 0 : z.d) + logits;
         need = b > need ? b : need;
         r += n;
     }
@@ -425,9 +435,9 @@ vp_status vp_output_fwd_group(const void* H, const void* const* W_shards, const 
                 l.ldy[k] = ld;
                 l.offset[k] = shard_offsets[r];
                 l.Y[k] = Y;
-                d += d_bytes(N, rows[r], dt);
+                d += logits_out ? 0 : d_bytes(N, rows[r], dt);
             }
-            if (launch_gemm_f32_logits((const float*)H, N, h, sh, n, st) != hipSuccess ||
+            if (launch_gemm_f32_logits((const float*)H, N, h, sh, n, z.S_logits, (float*)d, st) != hipSuccess ||
                 launch_row_stats_f32(l, labels, (int)N, local_max + r0 * N, local_sumexp + r0 * N, local_target + r0 * N, st) !=
                     hipSuccess)
                 return VP_ERR_DEVICE;
@@ -519,10 +529,10 @@ vp_status vp_output_bwd_group(const void* H, const void* const* W_shards, const 
                 l.ldd[k] = ld;
                 d += d_bytes(N, rows[r], dt);
             }
-            hipError_t e = logits_saved ? hipSuccess : launch_gemm_f32_logits((const float*)H, N, h, y, n, st);
+            hipError_t e = logits_saved ? hipSuccess : launch_gemm_f32_logits((const float*)H, N, h, y, n, z.S_logits, slices, st);
             if (e == hipSuccess) e = launch_dlogits_group(l, 0, labels, global_max, global_sumexp, grad_scale, (int)N, st);
             if (e == hipSuccess && !skip_dh) e = launch_gemm_f32_dh(N, h, g, n, z.S, dH_accum, !overwrite, slices, st);
-            if (e == hipSuccess) e = launch_gemm_f32_dw((const float*)H, N, h, g, n, st);
+            if (e == hipSuccess) e = launch_gemm_f32_dw((const float*)H, N, h, g, n, z.S_dw, slices, st);
             if (e != hipSuccess) return VP_ERR_DEVICE;
             r0 += n;
             continue;

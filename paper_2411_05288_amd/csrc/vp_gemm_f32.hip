@@ -229,17 +229,23 @@ __global__ __launch_bounds__(F_THREADS, TM == 128 ? 2 : 4) void gemm_f32_kernel(
         }
 }
 
-// K slices for an [M, N] output: enough workgroups of 64 x 64 tiles to cover the chip, slices of at least 64.
-static int splitk_slices(int M, int N, int K) {
-    const int64_t tiles = ceil_div(M, 64) * ceil_div(N, 64);
+// K slices for an output of this many 64 x 64 tiles: enough workgroups to cover the chip, slices of at least min_k.
+static int slices_for(int64_t tiles, int64_t K, int64_t min_k) {
     int64_t S = 256 / tiles;
     if (S > 32) S = 32;
-    if (S > K / 64) S = K / 64;
+    if (S > K / min_k) S = K / min_k;
     return S < 2 ? 1 : (int)S;
 }
+static int splitk_slices(int64_t M, int64_t N, int64_t K) { return slices_for(ceil_div(M, 64) * ceil_div(N, 64), K, 64); }
+// Logits and dW of a group.  A K step of 32 takes 0.55 us where a workgroup has a compute unit to itself, the sum of the
+// slices 4 us and a launch, so a K that is not cut into two slices of 256 is not cut (N=500 h=128 V=2000 p=4, forward pass,
+// K = 128: 29 us whole, 34 in two slices).
+int gemm_f32_group_slices(int64_t tiles, int64_t K) { return slices_for(tiles, K, 256); }
+// A product cut in S slices advances in steps of FK.
+static int slice_length(int64_t K, int S) { return S > 1 ? (int)(ceil_div(ceil_div(K, S), FK) * FK) : (int)K; }
 
 size_t gemm_f32_scratch_floats(int64_t M, int64_t N, int64_t K) {
-    const int S = splitk_slices((int)M, (int)N, (int)K);
+    const int S = splitk_slices(M, N, K);
     return S > 1 ? (size_t)S * (size_t)M * (size_t)N : 0;
 }
 
@@ -263,40 +269,45 @@ static void launch_f32_t(GemmF32Params& g, int tile, hipStream_t st) {
 }
 
 // Launches the product; C is [M, N] with row stride ldc where the shards share the output (dH).  With more than one K slice
-// (of all shards together) the partial outputs go through scratch.
+// (dH: of all shards together) the partial outputs go through scratch, every slice laid out like the output, or like the
+// outputs of the shards one behind the other.
 static hipError_t launch_f32(GemmF32Params g, bool a_kc, bool b_kc, float* C, int64_t ldc, bool accumulate, float* scratch,
                              hipStream_t st) {
-    const bool cat_k = a_kc && !b_kc;
+    const bool cat_n = a_kc && b_kc, cat_k = a_kc && !b_kc;
     const int parts = g.slices * (cat_k ? g.n : 1);
     // workgroups of 128 x 128 tiles; these (half the LDS and load traffic per flop) once every compute unit gets one
     int64_t wg = 0;
     for (int r = 0; r < g.n; ++r) {
-        if (a_kc && b_kc) wg += ceil_div(g.M, 128) * ceil_div(g.sh[r].rows, 128);
-        else if (a_kc) wg += ceil_div(g.M, 128) * ceil_div(g.N, 128);
+        if (cat_n) wg += ceil_div(g.M, 128) * ceil_div(g.sh[r].rows, 128);
+        else if (cat_k) wg += ceil_div(g.M, 128) * ceil_div(g.N, 128);
         else wg += ceil_div(g.sh[r].rows, 128) * ceil_div(g.N, 128);
     }
-    const int tile = wg * g.slices >= 256 ? 128 : 64;
-    // parts > 1 without shared output happens for one shard only: its output is M x N as well
-    const int M = !a_kc ? g.sh[0].rows : g.M, N = a_kc && b_kc ? g.sh[0].rows : g.N;
-    const int64_t MN = (int64_t)M * N;
+    // (slices of logits and dW are counted in 64 x 64 tiles: gemm_f32_group_slices)
+    const int tile = wg * g.slices >= 256 && (cat_k || g.slices == 1) ? 128 : 64;
+    g.C = C;
+    if (!cat_n) g.ldc = ldc;
+    g.accumulate = accumulate ? 1 : 0;
+    SumList l{};
     if (parts > 1) {
-        g.C = g.sh[0].C = scratch;
+        l.n = cat_k ? 1 : g.n;
+        for (int r = 0; r < l.n; ++r) {
+            GemmF32Shard& s = g.sh[r];
+            l.first[r] = g.slice_stride;
+            l.count[r] = cat_n ? (int64_t)g.M * s.ld : cat_k ? (int64_t)g.M * ldc : (int64_t)s.rows * ldc;
+            l.C[r] = cat_k ? C : s.C;
+            if (!cat_k) s.C = scratch + l.first[r];
+            g.slice_stride += l.n == 1 ? l.count[r] : (l.count[r] + 3) / 4 * 4;
+        }
+        g.C = scratch;
         g.accumulate = 0;
-        g.slice_stride = MN;
-        if (a_kc && b_kc) g.sh[0].ld = N;
-        else g.ldc = N;
-    } else {
-        g.C = C;
-        g.accumulate = accumulate ? 1 : 0;
-        if (!(a_kc && b_kc)) g.ldc = ldc;
     }
-    if (a_kc && b_kc) launch_f32_t<true, true>(g, tile, st);
-    else if (a_kc) launch_f32_t<true, false>(g, tile, st);
+    if (cat_n) launch_f32_t<true, true>(g, tile, st);
+    else if (cat_k) launch_f32_t<true, false>(g, tile, st);
     else if (!b_kc) launch_f32_t<false, false>(g, tile, st);
     else return hipErrorInvalidValue;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || parts == 1) return e;
-    return launch_sum_slices(scratch, parts, MN, C, accumulate, st);        // (every such C has rows of N: ldc == N)
+    return launch_sum_slices(scratch, parts, g.slice_stride, l, accumulate, st);
 }
 
 hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float* B, int64_t sbn, int64_t sbk,
@@ -312,8 +323,7 @@ hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float
     g.A = A; g.B = B;
     g.lda = a_kc ? sam : sak; g.ldb = b_kc ? sbn : sbk;
     g.M = M; g.N = N; g.K = K;
-    const int S = scratch ? splitk_slices(M, N, K) : 1;
-    g.k_per_slice = S > 1 ? (int)(ceil_div(ceil_div(K, S), FK) * FK) : K;     // multiple of the K step
+    g.k_per_slice = slice_length(K, scratch ? splitk_slices(M, N, K) : 1);
     g.slices = (int)ceil_div(K, g.k_per_slice);
     g.a_vec = g.lda % 4 == 0 && ((uintptr_t)A & 15u) == 0 && (!a_kc || K % 4 == 0);
     g.b_vec = g.ldb % 4 == 0 && ((uintptr_t)B & 15u) == 0 && (!b_kc || K % 4 == 0);
@@ -328,17 +338,22 @@ hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float
 // The three products over n shards (see GemmBf16Group for how they are laid end to end; here a K slice never crosses a
 // shard, so a sum runs over at most one shard's K before it meets the others in ascending order, as with one call per
 // shard).  D_r has rows of ld elements, zero behind the shard's columns, a multiple of four: 16-byte loads for any row count.
-hipError_t launch_gemm_f32_logits(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, hipStream_t st) {
+// Logits and dW are cut into K slices where the tiles of all shards leave compute units idle, as in a call per shard.  One
+// launch for all shards with a single chain over K, and with slices: forward pass of N=16 h=2048 V=2000 p=2: 62 -> 31 us,
+// N=64 h=2048 V=1024 p=2: 62 -> 31, backward pass of N=2048 h=64 V=2000 p=16: 93 -> 56.
+hipError_t launch_gemm_f32_logits(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* scratch,
+                                  hipStream_t st) {
     ProfScope prof(K_GEMM_F32, st);
     GemmF32Params g{};
     g.A = H;
     g.lda = g.ldb = h;
     g.M = (int)N; g.K = (int)h;
     g.a_vec = g.b_vec = h % 4 == 0 ? 1 : 0;
-    g.k_per_slice = g.K; g.slices = 1;
+    g.k_per_slice = slice_length(h, slices);
+    g.slices = (int)ceil_div(h, g.k_per_slice);
     g.n = n;
     for (int r = 0; r < n; ++r) g.sh[r] = sh[r];
-    return launch_f32(g, true, true, nullptr, 0, false, nullptr, st);
+    return launch_f32(g, true, true, nullptr, 0, false, scratch, st);
 }
 
 hipError_t launch_gemm_f32_dh(int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* dH, bool accumulate,
@@ -360,7 +375,8 @@ hipError_t launch_gemm_f32_dh(int64_t N, int64_t h, const GemmF32Shard* sh, int 
     return launch_f32(g, true, false, dH, h, accumulate, scratch, st);
 }
 
-hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, hipStream_t st) {
+hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* scratch,
+                              hipStream_t st) {
     ProfScope prof(K_GEMM_F32, st);
     GemmF32Params g{};
     g.B = H;
@@ -368,10 +384,11 @@ hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF3
     g.N = (int)h; g.K = (int)N;
     g.a_vec = 1;
     g.b_vec = h % 4 == 0 ? 1 : 0;
-    g.k_per_slice = g.K; g.slices = 1;
+    g.k_per_slice = slice_length(N, slices);
+    g.slices = (int)ceil_div(N, g.k_per_slice);
     g.n = n;
     for (int r = 0; r < n; ++r) g.sh[r] = sh[r];
-    return launch_f32(g, false, false, nullptr, h, false, nullptr, st);
+    return launch_f32(g, false, false, nullptr, h, false, scratch, st);
 }
 
 // K slices per shard of a grouped dH product: one if 128 x 128 tiles of all shards fill the chip; else slices of at least

@@ -105,7 +105,15 @@ bool gemm_bf16_group_ok(const GemmBf16Group& g);
 hipError_t launch_gemm_bf16_group(const GemmBf16Group& g, hipStream_t st);
 // K slices of a dH product [M, N] over kt k tiles (the slices' partial outputs take slices * M * N floats of scratch).
 int gemm_bf16_slices(int64_t M, int64_t N, int64_t kt);
-// C (+)= sum over S partial matrices of MN floats each (in a fixed order)
+// Outputs of a sum over partial matrices: output r of count[r] floats, whose partials start at float first[r] of each slice.
+struct SumList {
+    int n;
+    int64_t first[GEMM_GROUP_MAX], count[GEMM_GROUP_MAX];
+    float* C[GEMM_GROUP_MAX];
+};
+// C_r (+)= sum over S slices (in a fixed order), consecutive slices `stride` floats apart
+hipError_t launch_sum_slices(const float* part, int S, int64_t stride, const SumList& l, bool accumulate, hipStream_t st);
+// the same for one output of MN floats
 hipError_t launch_sum_slices(const float* part, int S, int64_t MN, float* C, bool accumulate, hipStream_t st);
 
 // Dispatches to the fast kernel when its preconditions hold (and the generic kernel has not been
@@ -137,11 +145,17 @@ struct GemmF32Shard {
     int rows;            // vocabulary rows
     int ld;              // row stride of Y_r or D_r
 };
-hipError_t launch_gemm_f32_logits(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, hipStream_t st);
+// K slices of a logits or dW product with this many 64 x 64 tiles (of all its shards)
+int gemm_f32_group_slices(int64_t tiles, int64_t K);
+// scratch, if slices > 1: slices * (N * ld of every shard, each rounded up to 4) floats
+hipError_t launch_gemm_f32_logits(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* scratch,
+                                  hipStream_t st);
 // scratch: n * slices * N * h floats unless n * slices == 1
 hipError_t launch_gemm_f32_dh(int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* dH, bool accumulate,
                               float* scratch, hipStream_t st);
-hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, hipStream_t st);
+// scratch, if slices > 1: slices * (rows * h of every shard, each rounded up to 4) floats
+hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* scratch,
+                              hipStream_t st);
 int gemm_f32_dh_slices(int64_t N, int64_t h, int64_t rows, int n);
 
 // Per-shard arguments of the small kernels that serve all shards of a group in one launch.

@@ -1,5 +1,7 @@
 // Small bandwidth/latency-bound kernels around the GEMMs: softmax statistics, their folds
 // (barrier C1 of Algorithm 1), and the D = softmax - G matrix of pass T from stored logits.
+#include <type_traits>
+
 #include "vp_internal.h"
 
 namespace vp {
@@ -125,14 +127,32 @@ hipError_t launch_fold_partials(const float* pm, const float* ps, const float* p
     return hipGetLastError();
 }
 
-// C (+)= the sum of S partial matrices of n elements V each.  Bound by reading them.  A small matrix has few threads, so a
-// long list of slices would be a serial chain of loads: G groups of 256 / G threads take an equal share of the slices each,
-// in ascending order and four loads at a time, and the groups' sums are added in ascending order.  64 slices of 128 x 256:
-// 16.8 us with one thread per element, 4.1 us with G = 4; with a thread for every lane of the chip (8 slices and more of
-// 512 x 2048) G = 1 is the better one, 12.3 against 15.6 us.
-template <typename V, int G>
-__global__ __launch_bounds__(256) void sum_slices_kernel(const V* __restrict__ part, int S, int64_t n, V* C, int accumulate) {
+// C_r (+)= the sum of the S partials of output r (blockIdx.y; elements V).  Bound by reading them.  A small matrix has few
+// threads, so a long list of slices would be a serial chain of loads: G groups of 256 / G threads take an equal share of the
+// slices each, in ascending order and four loads at a time, and the groups' sums are added in ascending order.  64 slices of
+// 128 x 256: 16.8 us with one thread per element, 4.1 us with G = 4; with a thread for every lane of the chip (8 slices and
+// more of 512 x 2048) G = 1 is the better one, 12.3 against 15.6 us.  One output alone (List = SumOne) needs no second read
+// of the argument block at an address that hangs on blockIdx: 0.8 us of a step of N=128 h=256 V=8192.
+struct SumOne {
+    int64_t count;
+    float* C;
+};
+template <typename V, int G, typename List>
+__global__ __launch_bounds__(256) void sum_slices_kernel(const V* __restrict__ part, int S, int64_t stride, List list,
+                                                         int accumulate) {
     constexpr int W = 256 / G;
+    constexpr int E = sizeof(V) / sizeof(float);
+    int64_t n;
+    V* C;
+    if constexpr (std::is_same<List, SumOne>::value) {
+        n = list.count / E;
+        C = (V*)list.C;
+    } else {
+        n = list.count[blockIdx.y] / E;
+        C = (V*)list.C[blockIdx.y];
+        part += list.first[blockIdx.y] / E;
+    }
+    stride /= E;
     const int g = threadIdx.x / W, l = threadIdx.x % W;
     const int64_t t = (int64_t)blockIdx.x * W + l;
     const int q = (S + G - 1) / G, z1 = min(S, (g + 1) * q);
@@ -142,11 +162,11 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(const V* __restrict__ p
         for (; z + 4 <= z1; z += 4) {
             V v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = part[(int64_t)(z + u) * n + t];
+            for (int u = 0; u < 4; ++u) v[u] = part[(int64_t)(z + u) * stride + t];
 #pragma unroll
             for (int u = 0; u < 4; ++u) acc += v[u];
         }
-        for (; z < z1; ++z) acc += part[(int64_t)z * n + t];
+        for (; z < z1; ++z) acc += part[(int64_t)z * stride + t];
     }
     if constexpr (G > 1) {
         __shared__ V sh[G - 1][W];
@@ -158,23 +178,39 @@ __global__ __launch_bounds__(256) void sum_slices_kernel(const V* __restrict__ p
     if (t < n) C[t] = accumulate ? C[t] + acc : acc;
 }
 
-template <typename V>
-static void launch_sum_slices_t(const float* part, int S, int64_t n, float* C, bool accumulate, hipStream_t st) {
-    if (n >= 65536)
-        hipLaunchKernelGGL((sum_slices_kernel<V, 1>), dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, (const V*)part, S, n,
-                           (V*)C, accumulate ? 1 : 0);
+template <typename V, typename List>
+static hipError_t launch_sum_slices_t(const float* part, int S, int64_t stride, const List& l, int n, int64_t longest,
+                                      int64_t all, bool accumulate, hipStream_t st) {
+    const int64_t E = sizeof(V) / sizeof(float);
+    if (all / E >= 65536)
+        hipLaunchKernelGGL((sum_slices_kernel<V, 1, List>), dim3((unsigned)ceil_div(longest / E, 256), n), dim3(256), 0, st,
+                           (const V*)part, S, stride, l, accumulate ? 1 : 0);
     else
-        hipLaunchKernelGGL((sum_slices_kernel<V, 4>), dim3((unsigned)ceil_div(n, 64)), dim3(256), 0, st, (const V*)part, S, n,
-                           (V*)C, accumulate ? 1 : 0);
+        hipLaunchKernelGGL((sum_slices_kernel<V, 4, List>), dim3((unsigned)ceil_div(longest / E, 64), n), dim3(256), 0, st,
+                           (const V*)part, S, stride, l, accumulate ? 1 : 0);
+    return hipGetLastError();
+}
+
+typedef float sum4 __attribute__((ext_vector_type(4)));
+
+hipError_t launch_sum_slices(const float* part, int S, int64_t stride, const SumList& l, bool accumulate, hipStream_t st) {
+    if (l.n == 1 && l.first[0] == 0 && l.count[0] == stride) return launch_sum_slices(part, S, stride, l.C[0], accumulate, st);
+    bool vec = stride % 4 == 0 && ((uintptr_t)part & 15u) == 0;
+    int64_t longest = 0, all = 0;
+    for (int r = 0; r < l.n; ++r) {
+        vec = vec && l.first[r] % 4 == 0 && l.count[r] % 4 == 0 && ((uintptr_t)l.C[r] & 15u) == 0;
+        longest = l.count[r] > longest ? l.count[r] : longest;
+        all += l.count[r];
+    }
+    return vec ? launch_sum_slices_t<sum4>(part, S, stride, l, l.n, longest, all, accumulate, st)
+               : launch_sum_slices_t<float>(part, S, stride, l, l.n, longest, all, accumulate, st);
 }
 
 hipError_t launch_sum_slices(const float* part, int S, int64_t MN, float* C, bool accumulate, hipStream_t st) {
-    typedef float floatx4 __attribute__((ext_vector_type(4)));
-    if (MN % 4 == 0 && ((((uintptr_t)part) | ((uintptr_t)C)) & 15u) == 0)
-        launch_sum_slices_t<floatx4>(part, S, MN / 4, C, accumulate, st);
-    else
-        launch_sum_slices_t<float>(part, S, MN, C, accumulate, st);
-    return hipGetLastError();
+    const SumOne l{MN, C};
+    return MN % 4 == 0 && ((((uintptr_t)part) | ((uintptr_t)C)) & 15u) == 0
+               ? launch_sum_slices_t<sum4>(part, S, MN, l, 1, MN, MN, accumulate, st)
+               : launch_sum_slices_t<float>(part, S, MN, l, 1, MN, MN, accumulate, st);
 }
 
 // Barrier C1 of one token row: global max, rescaled sum, loss.

@@ -74,6 +74,18 @@ def test_workspace_sizes(lib):
     assert ws(2, 8, (1 << 20) + 8, 8, 1, 0) == bad
 
 
+def test_group_workspace_covers_the_slices_of_fp32_products(lib):
+    # outputs with few tiles are cut into K slices for a group as for a single shard: partial sums behind the D matrices
+    def ws(which, N, h, rows, flags):
+        return lib.vp_output_group_workspace_bytes(which, len(rows), N, h, (ctypes.c_int64 * len(rows))(*rows), 0, flags)
+    one = 16 * 1000 * 4                                               # logits of a shard, a multiple of 256
+    assert ws(0, 16, 2048, [1000, 1000], 0) == 2 * one + 8 * 2 * one  # 32 tiles of 64 x 64: 8 slices
+    d, dw = 2048 * 128 * 4, 125 * 64 * 4                              # D with rows padded to 4; dW, 125 * 256 bytes
+    assert ws(2, 2048, 64, [125] * 16, 1 | 2) == 16 * d + 8 * 16 * dw # (no dH) 32 tiles: 8 slices
+    # enough tiles: no slices, and what a single shard needs for its own is more
+    assert ws(2, 128, 256, [4096] * 2, 1 | 2) == lib.vp_workspace_bytes(2, 128, 256, 4096, 0, 1 | 2)
+
+
 def test_argument_validation_launches_nothing(lib):
     # every call below must be rejected on the host; fake non-null pointers are never touched
     P = 0x1000

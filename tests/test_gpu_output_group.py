@@ -145,3 +145,18 @@ def test_plan_with_a_workspace_limit(save_logits, algorithm):
         assert torch.equal(x, y)
     # (orders of the sums: see the bound above)
     assert float((a.dH - b.dH).abs().max()) <= 2.0 ** -22 * V ** 0.5 * float(b.dH.abs().max())
+
+
+@pytest.mark.parametrize("save_logits", [True, False])
+@pytest.mark.parametrize("N,h,rows", [
+    (16, 2048, [1000, 999]),                  # logits in 8 slices; rows of Y of no multiple of four, so sums element by element
+    (16, 1028, [500, 500]),                   # slices of unequal length, 16-byte sums
+    (2048, 64, [125] * 16),                   # dW in 8 slices
+    (1030, 37, [70, 65, 1]),                  # dW in slices of an odd K, rows of H not 16-byte aligned
+    (20, 511, [64] * 3), (20, 512, [64] * 3), # the last K that is not cut and the first that is
+    (64, 4096, [64] * 16),                    # shards of one tile: 256 workgroups with either size of tile
+    (200, 1024, [70] * 19),                   # more shards than a launch takes
+])
+def test_fp32_group_with_k_slices(N, h, rows, save_logits):
+    # outputs with few tiles and a long K: the logits and dW of all shards are cut into K slices
+    test_group_equals_single_shards(N, h, rows, save_logits, "f32")
