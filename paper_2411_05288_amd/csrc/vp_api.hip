@@ -591,7 +591,10 @@ vp_status vp_output_bwd_group(const void* H, const void* const* W_shards, const 
                 }
                 if (e == hipSuccess && !skip_dh) {
                     e = launch_gemm_bf16_group(gh, st);
-                    if (e == hipSuccess && z.S > 1) e = launch_sum_slices(slices, z.S, N * h, dH_accum, !overwrite, st);
+                    if (e == hipSuccess && z.S > 1) {
+                        ProfScope prof(K_SUM_SLICES, st);
+                        e = launch_sum_slices(slices, z.S, N * h, dH_accum, !overwrite, st);
+                    }
                 }
                 if (e == hipSuccess) e = launch_gemm_bf16_group(gw, st);
                 if (e != hipSuccess) return VP_ERR_DEVICE;

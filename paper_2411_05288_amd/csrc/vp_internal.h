@@ -18,7 +18,7 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 // Kernel ids for the optional per-kernel timing (names in vp_profile.hip, same order).
 enum KernelId : int {
     K_GEMM_FWD_STATS = 0, K_GEMM_DLOGITS, K_GEMM_DH, K_GEMM_DW, K_FOLD, K_COMBINE, K_DLOGITS_EW, K_GEMM_F32,
-    K_ROWSTATS_F32, K_EMBED_FWD, K_EMBED_SORT, K_EMBED_ACCUM, K_GEMM_A_ALG2, K_DX_ALG2, K_COUNT
+    K_ROWSTATS_F32, K_EMBED_FWD, K_EMBED_SORT, K_EMBED_ACCUM, K_GEMM_A_ALG2, K_DX_ALG2, K_SUM_SLICES, K_ZERO_PAD, K_COUNT
 };
 
 // Brackets the launches made during its lifetime with two events when timing is enabled;
@@ -111,7 +111,8 @@ struct SumList {
     int64_t first[GEMM_GROUP_MAX], count[GEMM_GROUP_MAX];
     float* C[GEMM_GROUP_MAX];
 };
-// C_r (+)= sum over S slices (in a fixed order), consecutive slices `stride` floats apart
+// C_r (+)= sum over S slices (in a fixed order), consecutive slices `stride` floats apart.  Timed by the caller: alone, or
+// with the product it ends.
 hipError_t launch_sum_slices(const float* part, int S, int64_t stride, const SumList& l, bool accumulate, hipStream_t st);
 // the same for one output of MN floats
 hipError_t launch_sum_slices(const float* part, int S, int64_t MN, float* C, bool accumulate, hipStream_t st);

@@ -410,6 +410,7 @@ hipError_t launch_zero_pad_columns(const ShardList& l, int N, hipStream_t st) {
     int64_t pad = 0;
     for (int r = 0; r < l.n; ++r) pad = l.ldd[r] - l.rows[r] > pad ? l.ldd[r] - l.rows[r] : pad;
     if (pad == 0) return hipSuccess;
+    ProfScope prof(K_ZERO_PAD, st);
     hipLaunchKernelGGL(zero_pad_columns_kernel, dim3((unsigned)ceil_div((int64_t)N * pad, 256), l.n), dim3(256), 0, st, l, N);
     return hipGetLastError();
 }

@@ -160,3 +160,21 @@ def test_plan_with_a_workspace_limit(save_logits, algorithm):
 def test_fp32_group_with_k_slices(N, h, rows, save_logits):
     # outputs with few tiles and a long K: the logits and dW of all shards are cut into K slices
     test_group_equals_single_shards(N, h, rows, save_logits, "f32")
+
+
+def test_every_launch_of_a_step_is_timed():
+    # dH in K slices, recomputed logits with rows of D to pad: the sum and the fill are launches of their own
+    import paper_2411_05288_amd as vp
+    H, Ws, labels = si.small_output_case(300, 512, 2600, 2, "bf16", seed=73, w_std=0.08)
+    plan = vp.OutputLayerPlan(to_dev(H), [to_dev(w) for w in Ws], to_dev(labels), False)
+    plan.step()
+    torch.cuda.synchronize()
+    vp.vp_profile_enable(True)
+    try:
+        plan.step()
+        torch.cuda.synchronize()
+        launches = {k: n for k, (_, n) in vp.vp_profile_read().items()}
+    finally:
+        vp.vp_profile_enable(False)
+    assert launches == {"gemm_bf16_fwd_stats": 1, "fold_partials": 1, "combine_stats": 1, "gemm_bf16_dlogits": 1,
+                        "zero_pad_columns": 1, "gemm_bf16_dH": 1, "sum_slices": 1, "gemm_bf16_dW": 1}
