@@ -70,3 +70,23 @@ def run_output_layer_keep_D(H, Ws, labels, save_logits=True, grad_scale=None):
         assert (full[:, Vs:] == 0).all(), "row padding of D must be zero"
         Ds.append(np.ascontiguousarray(full[:, :Vs]))
     return plan, Ds
+
+
+def run_output_layer_group_keep_D(H, Ws, labels, save_logits=True, grad_scale=None):
+    """A step of the plan (all shards in one call per pass), reading the D matrices vp_output_bwd_group leaves at the start
+    of its workspace: one behind the other, each rounded up to 256 bytes, rows padded to 64 elements (bf16) or 4 (fp32).
+    Returns (plan, [D_r]) as run_output_layer_keep_D does."""
+    import paper_2411_05288_amd as vp
+    plan = run_output_layer(H, Ws, labels, save_logits, grad_scale)
+    assert plan.grouped and plan.p > 1
+    Ds, at = [], 0
+    bf16 = plan.dt == vp.VP_BF16
+    for Vs in plan.rows:
+        ld = vp.vp_dlogits_row_stride(Vs, plan.dt) if bf16 else (Vs + 3) // 4 * 4
+        nbytes = plan.N * ld * (2 if bf16 else 4)
+        D = plan.workspace[at:at + nbytes].view(torch.bfloat16 if bf16 else torch.float32).view(plan.N, ld)
+        full = to_host_f64(D)
+        assert (full[:, Vs:] == 0).all(), "row padding of D must be zero"
+        Ds.append(np.ascontiguousarray(full[:, :Vs]))
+        at += (nbytes + 255) // 256 * 256
+    return plan, Ds

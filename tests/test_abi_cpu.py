@@ -86,6 +86,35 @@ def test_group_workspace_covers_the_slices_of_fp32_products(lib):
     assert ws(2, 128, 256, [4096] * 2, 1 | 2) == lib.vp_workspace_bytes(2, 128, 256, 4096, 0, 1 | 2)
 
 
+def test_group_workspace_is_bounded(lib):
+    def ws(which, N, h, rows, dt, flags):
+        return lib.vp_output_group_workspace_bytes(which, len(rows), N, h, (ctypes.c_int64 * len(rows))(*rows), dt, flags)
+    gib = 1 << 30
+    for dt, rows in ((1, 65536), (0, 32768)):                         # D of 2 GiB per shard: two shards at a time
+        assert ws(2, 16384, 64, [rows] * 2, dt, 2) == 4 * gib == ws(2, 16384, 64, [rows] * 3, dt, 2)
+    # 2 GiB of fp32 partial sums of dH: shard by shard, with what one shard needs
+    assert ws(2, 16384, 2048, [64] * 16, 0, 0) == lib.vp_workspace_bytes(2, 16384, 2048, 64, 0, 0)
+    assert ws(2, 16384, 1024, [64] * 16, 0, 0) >= gib
+    bad = ctypes.c_size_t(-1).value
+    assert ws(2, 64, 64, [64, 0], 1, 0) == bad and ws(1, 64, 64, [64], 1, 0) == bad and ws(2, 64, 64, [], 1, 0) == bad
+
+
+def test_group_calls_validate_their_arguments(lib):
+    P, arr, i64 = 0x1000, ctypes.c_void_p * 2, ctypes.c_int64 * 2
+    ptrs, rows, offs = arr(P, P), i64(8, 8), i64(0, 8)
+    fwd = lambda W=ptrs, r=rows, o=offs, p=2, flags=0, ws=P, wb=1 << 20: lib.vp_output_fwd_group(
+        P, W, r, o, p, P, 8, 8, 1, flags, P, P, P, None, ws, wb, None)
+    assert fwd(W=arr(P, None)) == VP_ERR_INVALID_ARG and fwd(W=arr(P, P + 2)) == VP_ERR_INVALID_ARG
+    assert fwd(r=i64(8, 0)) == VP_ERR_INVALID_ARG and fwd(o=i64(0, -1)) == VP_ERR_INVALID_ARG and fwd(p=0) == VP_ERR_INVALID_ARG
+    assert fwd(flags=1) == VP_ERR_INVALID_ARG and fwd(ws=None, wb=0) == VP_ERR_WORKSPACE and fwd(wb=16) == VP_ERR_WORKSPACE
+    assert fwd(r=i64(8, (1 << 20) + 8)) == VP_ERR_UNSUPPORTED
+    bwd = lambda dW=ptrs, dH=P, flags=0, wb=1 << 20: lib.vp_output_bwd_group(
+        P, ptrs, rows, offs, 2, P, 8, 8, 1, flags, P, P, None, 1.0, dH, dW, P, wb, None)
+    assert bwd(dW=arr(P, None)) == VP_ERR_INVALID_ARG and bwd(dW=arr(P + 4, P)) == VP_ERR_INVALID_ARG
+    assert bwd(dH=None) == VP_ERR_INVALID_ARG and bwd(flags=6) == VP_ERR_INVALID_ARG and bwd(flags=1) == VP_ERR_INVALID_ARG
+    assert bwd(dH=None, flags=2, wb=8) == VP_ERR_WORKSPACE and bwd(wb=8) == VP_ERR_WORKSPACE
+
+
 def test_argument_validation_launches_nothing(lib):
     # every call below must be rejected on the host; fake non-null pointers are never touched
     P = 0x1000

@@ -16,14 +16,14 @@ import pytest
 import synth_inputs as si
 from oracle import vp_oracle as oc
 import parity_metrics as pm
-from gpu_util import GRAD_TOL, run_output_layer_keep_D, to_host
+from gpu_util import GRAD_TOL, run_output_layer_group_keep_D, run_output_layer_keep_D, to_host
 
 pytestmark = pytest.mark.gpu
 
 
-def check_D_and_softmax_half(H, Ws, labels, save_logits, tag, grad_scale=None):
+def check_D_and_softmax_half(H, Ws, labels, save_logits, tag, grad_scale=None, run=run_output_layer_keep_D):
     dtype = "bf16" if H.dtype == np.uint16 else "f32"
-    plan, Ds = run_output_layer_keep_D(H, Ws, labels, save_logits, grad_scale)
+    plan, Ds = run(H, Ws, labels, save_logits, grad_scale)
     X = si.as_f64(H)
     W64 = [si.as_f64(w) for w in Ws]
     ref = oc.output_layer_alg1(X, W64, labels, grad_scale)
@@ -106,3 +106,24 @@ def test_unscaled_form_and_zipf_labels():
     H, Ws, labels = si.small_output_case(700, 128, 2048, 4, "bf16", seed=55, labels="zipf", w_std=0.08)
     check_D_and_softmax_half(H, Ws, labels, True, "zipf stored scale=1", grad_scale=1.0)
     check_D_and_softmax_half(H, Ws, labels, False, "zipf recompute scale=1", grad_scale=1.0)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("save_logits", [True, False])
+@pytest.mark.parametrize("labelled", [True, False])
+@pytest.mark.parametrize("shape", [
+    (300, 136, 1040, 2),     # ragged tiles, masked k tail of the logits product
+    (513, 72, 500, 2),       # rows of Y not 16-byte aligned: the last chunk of a row by elements
+    (64, 200, 1530, 3), (33, 72, 303, 3),     # at most 64 tokens: two row blocks; odd rows
+    (1540, 64, 606, 2),      # the first dW of more than 1536 tokens
+    (16, 2048, 999, 3),      # fp32 logits in K slices
+    (1100, 40, 130, 2),      # fp32 dW in K slices
+])
+def test_D_of_all_shards_in_one_call(shape, labelled, save_logits, dtype):
+    # the kernels the plan runs: D of every shard against the definition, dH and dW against the oracle, without labels too
+    N, h, V, p = shape
+    H, Ws, labels = si.small_output_case(N, h, V, p, dtype, seed=501 + N, w_std=0.08 if h < 1000 else 0.02)
+    if not labelled:
+        labels = np.where(np.arange(N) % 2 == 0, V + 5, -3).astype(np.int64)
+    check_D_and_softmax_half(H, Ws, labels, save_logits, "group D %s labelled=%s stored=%s %s" % (
+        shape, labelled, save_logits, dtype), run=run_output_layer_group_keep_D)

@@ -146,3 +146,28 @@ def test_embed_groups_of_shards(shape):
     ids[3::11] = -2
     print("embed group", shape, flush=True)
     check_embed(N, h, V, p, "bf16" if N % 2 else "f32", seed=400 + N, ids=ids, preload=True)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("shape", [(700, 40, 96, 3), (9000, 24, 96, 3), (3000, 37, 64, 2)])    # one kernel, general path, one column per lane
+def test_embed_infinities_nan_and_negative_zeros(shape, dtype):
+    # bit for bit the in-order sum (any NaN equal to any other), nothing in rows whose tokens are finite
+    N, h, V, p = shape
+    Vs = V // p
+    tables = [si.normal((Vs, h), 0.02, dtype, 81, si.STREAM_TABLE, r) for r in range(p)]
+    ids = si.zipf_ids(N, V, 1.1, 81)
+    g = si.as_f32(si.normal((N, h), 1.0, dtype, 81, si.STREAM_GRAD)).copy()
+    g[3, 0], g[50, 1], g[60, 1], g[70, 2], g[11, :] = np.inf, np.inf, -np.inf, np.nan, -0.0
+    for t in tables:
+        t[Vs // 2] = -t[Vs // 2] if t.dtype != np.uint16 else t[Vs // 2] ^ 0x8000
+    gout = g if dtype == "f32" else (g.view(np.uint32) >> 16).astype(np.uint16)      # (values that are bf16 already)
+    print("embed non-finite", shape, dtype, flush=True)
+    plan = run_embed(tables, ids, gout)
+    for r in range(p):
+        assert np.array_equal(to_host(plan.out[r]), oc.embed_fwd(tables[r], ids, r * Vs))
+        with np.errstate(invalid="ignore"):
+            ref = oc.embed_bwd(g, ids, r * Vs, Vs, np.zeros((Vs, h), dtype=np.float32))
+        got = to_host(plan.dtable[r])
+        nan = np.isnan(ref)
+        assert np.array_equal(np.isnan(got), nan)
+        assert np.array_equal(got.view(np.uint32)[~nan], ref.view(np.uint32)[~nan])

@@ -178,3 +178,62 @@ def test_every_launch_of_a_step_is_timed():
         vp.vp_profile_enable(False)
     assert launches == {"gemm_bf16_fwd_stats": 1, "fold_partials": 1, "combine_stats": 1, "gemm_bf16_dlogits": 1,
                         "zero_pad_columns": 1, "gemm_bf16_dH": 1, "sum_slices": 1, "gemm_bf16_dW": 1}
+
+
+@pytest.mark.parametrize("N,h,rows,dtype", [
+    (16384, 64, [65536] * 3, "bf16"),         # 2 GiB of D per shard: parts of two shards and of one
+    (16384, 64, [32768] * 3, "f32"),          # the same
+    (16384, 2048, [64] * 16, "f32"),          # 2 GiB of partial sums of dH: shard by shard
+])
+def test_parts_by_bytes(N, h, rows, dtype):
+    # dH is overwritten by the first part and added to by the second
+    test_group_equals_single_shards(N, h, rows, False, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("N,h,rows", [
+    (70, 72, [300, 131]), (64, 72, [300, 131]), (64, 136, [257, 64]),     # masked k tails, two and four row blocks
+    (300, 128, [300, 131]), (40, 37, [66, 70]),
+])
+def test_infinities_and_nan_stay_where_they_are(N, h, rows, dtype):
+    # A token row (or vocabulary row) with infinities and NaN: nothing of it reaches another row's logits, statistics or dH
+    # through a tile's overhang, where it would meet a zero.  Without it the same sums in the same order: equal bits.
+    import paper_2411_05288_amd as vp
+    p, V = len(rows), sum(rows)
+    print("non-finite", (N, h, rows, dtype), flush=True)
+    H = to_dev(si.normal((N, h), 1.0, dtype, 51, si.STREAM_TABLE, 99))
+    W = [to_dev(si.normal((n, h), 0.05, dtype, 51, si.STREAM_TABLE, r)) for r, n in enumerate(rows)]
+    labels = to_dev(si.zipf_ids(N, V, 1.1, 51))
+
+    def step(H, W):
+        plan = vp.OutputLayerPlan(H, W, labels, True)
+        plan.workspace.fill_(0xFF)
+        plan.step()
+        torch.cuda.synchronize()
+        return plan
+
+    clean = step(H, W)
+    bad = [0, 5, N - 1]
+    H2 = H.clone()
+    H2[0, :3] = float("inf")
+    H2[5, h // 2] = float("nan")
+    H2[N - 1, -1] = float("-inf")
+    got = step(H2, W)
+    good = torch.ones(N, dtype=torch.bool, device="cuda")
+    good[bad] = False
+    for name in ("local_max", "local_sumexp", "local_target"):
+        assert torch.equal(getattr(got, name)[:, good], getattr(clean, name)[:, good]), name
+    for name in ("global_max", "global_sumexp", "loss_rows", "dH"):
+        assert torch.equal(getattr(got, name)[good], getattr(clean, name)[good]), name
+    for y, y0 in zip(got.logits, clean.logits):
+        assert torch.equal(y[good], y0[good])
+    assert not bool(torch.isfinite(got.loss_rows[bad]).any())
+    # the last vocabulary row of the first shard
+    W2 = [w.clone() for w in W]
+    W2[0][-1, :2] = float("inf")
+    W2[0][-1, -1] = float("nan")
+    got = step(H, W2)
+    assert torch.equal(got.logits[0][:, :-1], clean.logits[0][:, :-1]) and torch.equal(got.logits[1], clean.logits[1])
+    assert bool(torch.isnan(got.logits[0][:, -1]).all())
+    for name in ("local_max", "local_sumexp", "local_target"):
+        assert torch.equal(getattr(got, name)[1], getattr(clean, name)[1]), name
