@@ -2,8 +2,8 @@
 """Benchmark of the vocabulary-layer hot path on one MI355X.
 
 A step is one pass of the whole path over one batch of synthetic input:
-p x vp_output_fwd, vp_combine_stats, p x vp_output_bwd (all p shards of the configuration run
-in sequence on the one GPU).  The headline workload is the largest configuration, cfg4
+vp_output_fwd_group, vp_combine_stats, vp_output_bwd_group (all p shards of the configuration on
+the one GPU, one launch per product for all of them).  The headline workload is the largest configuration, cfg4
 (N=4096, h=8192, V=256000, p=16, bf16, logits recomputed in the backward pass); the other
 configurations are timed briefly as well and reported under "per_config", each with its own
 roofline entry.  Inputs are resident in HBM before the timed region starts.
@@ -30,18 +30,28 @@ BF16_MFMA_PEAK_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 HBM_PEAK_GBS = 8000.0            # MI355X HBM3E
 # L2-miss / fabric traffic per launch of the GEMM kernels: what leaves the eight L2s towards the memory-side
 # cache and HBM.  NOT measured by this run (counters cannot be read from inside the process): the figures
-# are copied from the committed rocprofv3 --pmc summaries (FETCH_SIZE, WRITE_SIZE in KiB per dispatch;
-# profiles/output_layer_<config>.txt, which state the command).  A plain 256 MiB copy in the same counter
+# are copied from the committed rocprofv3 --pmc summary (FETCH_SIZE, WRITE_SIZE in KiB per dispatch, a
+# dispatch being one product over all shards; profiles/group_launches_counters.txt, which states the command).  A plain 256 MiB copy in the same counter
 # runs reads 0.5x its size on FETCH_SIZE and 1.0x on WRITE_SIZE, hence the factors.
 PMC_FETCH_FACTOR, PMC_WRITE_FACTOR = 2.0, 1.0
-PMC_KIB = {   # kernel -> (FETCH_SIZE, WRITE_SIZE); dH is the accumulating launch (all shards but the first)
-    "cfg2_llama": {"gemm_bf16_fwd_stats": (106407.0, 46354.1), "gemm_bf16_dH": (132114.7, 80896.0),
-                   "gemm_bf16_dW": (99353.0, 80384.0)},
-    "cfg3_large_vocab": {"gemm_bf16_fwd_stats": (443979.2, 189183.5), "gemm_bf16_dH": (420997.1, 80896.0),
-                         "gemm_bf16_dW": (404757.8, 309940.4)},
-    "cfg4_very_large_vocab": {"gemm_bf16_fwd_stats": (859749.0, 51943.3), "gemm_bf16_dlogits": (856499.4, 177420.7),
-                              "gemm_bf16_dH": (837983.0, 158828.7), "gemm_bf16_dW": (945260.4, 615018.7)},
+PMC_KIB = {   # kernel -> (FETCH_SIZE, WRITE_SIZE) of the launch of all shards
+    "cfg2_llama": {"gemm_bf16_fwd_stats": (835032.8, 375269.2), "gemm_bf16_dH": (788832.1, 65536.0),
+                   "gemm_bf16_dW": (936644.8, 615517.3)},
+    "cfg3_large_vocab": {"gemm_bf16_fwd_stats": (3333393.3, 1489916.6), "gemm_bf16_dH": (3114406.7, 65536.0),
+                         "gemm_bf16_dW": (3660926.7, 2450387.8)},
+    "cfg4_very_large_vocab": {"gemm_bf16_fwd_stats": (12778888.0, 807796.6), "gemm_bf16_dlogits": (12600491.1, 2823198.8),
+                              "gemm_bf16_dH": (14812445.1, 131076.0), "gemm_bf16_dW": (13320595.9, 9777529.9)},
+    "cfg5_embedding": {"embed_fwd": (16524.4, 524711.6)},
 }
+PMC_SOURCE = "not measured by this run: copied from the committed counter summary profiles/group_launches_counters.txt"
+
+
+def pmc_traffic(config, kernel, launches_per_step):
+    """Counter traffic (bytes) of a kernel's launch over all shards, None where it is not known."""
+    pmc = PMC_KIB.get(config, {}).get(kernel) if launches_per_step == 1 else None
+    return None if pmc is None else (PMC_FETCH_FACTOR * pmc[0] + PMC_WRITE_FACTOR * pmc[1]) * 1024.0
+
+
 METRIC = "vocab-layer fwd+bwd TFLOP/s and tokens/s per GPU; % of bf16 MFMA peak"
 
 
@@ -131,9 +141,8 @@ def gemm_roofline(cfg, kernels):
     shards = cfg.p / kernels[dom]["launches_per_step"]
     flops_per_launch = 2.0 * cfg.N * cfg.h * cfg.Vs * shards
     ach = flops_per_launch / (kernels[dom]["ms_per_launch"] * 1e-3) / 1e12
-    pmc = PMC_KIB.get(cfg.name, {}).get(dom) if shards == 1 else None       # counters of launches of one shard
-    traffic = None if pmc is None else (PMC_FETCH_FACTOR * pmc[0] + PMC_WRITE_FACTOR * pmc[1]) * 1024.0
-    # algorithmic bytes of one launch: both operands read once, the output written once (dH += also reads it)
+    traffic = pmc_traffic(cfg.name, dom, kernels[dom]["launches_per_step"])
+    # algorithmic bytes of one launch: both operands read once, the output written once
     N, h, V = cfg.N, cfg.h, cfg.Vs * shards
     ab = {"gemm_bf16_fwd_stats": 2.0 * (N * h + V * h) + (2.0 * N * V if cfg.save_logits else 0.0),
           "gemm_bf16_dlogits": 2.0 * (N * h + V * h) + 2.0 * N * V,
@@ -143,8 +152,7 @@ def gemm_roofline(cfg, kernels):
             "frac": ach / BF16_MFMA_PEAK_TFLOPS, "flops_per_launch": flops_per_launch,
             "avg_launch_ms": kernels[dom]["ms_per_launch"], "traffic": traffic, "traffic_unit": "bytes per launch",
             "traffic_kind": "L2-miss / fabric bytes (2.0 x FETCH_SIZE + WRITE_SIZE)",
-            "traffic_source": None if pmc is None else
-            "not measured by this run: copied from the committed counter summary profiles/output_layer_%s.txt" % cfg.name,
+            "traffic_source": None if traffic is None else PMC_SOURCE,
             "algorithmic_bytes_per_launch": ab}
 
 
@@ -207,17 +215,16 @@ def bench_embedding(vp, cfg, steps, warmup):
         "bwd_frac_hbm_peak": bwd_bytes / (bwd_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
         "tokens_per_s_fwd_bwd": cfg.N / ((fwd_ms + bwd_ms) * 1e-3),
         "unique_ids": uniq, "kernels": kern,
-        # dominant kernel of the input layer: the gather (algorithmic bytes of one shard over its launch time)
+        # dominant kernel of the input layer: the gather (algorithmic bytes of all shards over the time of its launches)
         "roofline": {"bound": "hbm", "kernel": "embed_fwd",
                      "achieved": fwd_bytes / (kern["embed_fwd"]["ms_per_step"] * 1e-3) / 1e9,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": fwd_bytes / (kern["embed_fwd"]["ms_per_step"] * 1e-3) / 1e9 / HBM_PEAK_GBS,
                      "bytes_per_launch": fwd_bytes / kern["embed_fwd"]["launches_per_step"], "avg_launch_ms": kern["embed_fwd"]["ms_per_launch"],
-                     # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 per launch (profiles/input_layer_cfg5_embedding.txt)
-                     "traffic": (2.0 * 2524.4 + 65564.3) * 1024.0, "traffic_unit": "bytes per launch",
+                     "traffic": pmc_traffic(cfg.name, "embed_fwd", kern["embed_fwd"]["launches_per_step"]),
+                     "traffic_unit": "bytes per launch",
                      "traffic_kind": "L2-miss / fabric bytes (2.0 x FETCH_SIZE + WRITE_SIZE)",
-                     "traffic_source": "not measured by this run: copied from the committed counter summary "
-                                       "profiles/input_layer_cfg5_embedding.txt"},
+                     "traffic_source": PMC_SOURCE},
     }
 
 
@@ -260,7 +267,7 @@ def mfma_sustained(vp, cfg):
 
 
 def gemm_timeline(vp, cfg, reps=3):
-    """Itemised time budget of the fast GEMM launches of the last shard's passes S and T, from the phase stamps the
+    """Itemised time budget of the fast GEMM launches of passes S and T (one launch takes all shards), from the phase stamps the
     kernel writes when its timeline is switched on (vp_profile_gemm_trace): per workgroup and output tile, the
     100 MHz counter and the shader clock at tile start, first operands landed, main loop done, epilogue done.
     All figures in microseconds per launch, averaged over workgroups (and over `reps` launches)."""
@@ -313,7 +320,7 @@ def gemm_timeline(vp, cfg, reps=3):
             for x in range(8):
                 acc[-1]["busy_us_xcd%d" % x] = busy[x::8].mean()
         out[name] = {k: float(np.mean([a[k] for a in acc])) for k in acc[0]}
-        flops = 2.0 * cfg.N * cfg.h * cfg.Vs
+        flops = 2.0 * cfg.N * cfg.h * cfg.Vs * cfg.p
         out[name]["main_loop_tflops"] = flops / (out[name]["main_loop_us"] * 1e-6) / 1e12 * (
             out[name]["tiles"] / (out[name]["workgroups"] * out[name]["tiles_per_workgroup_max"]))
         out[name]["span_tflops"] = flops / (out[name]["span_us"] * 1e-6) / 1e12
@@ -382,8 +389,8 @@ def main():
                          "the GEMM kernels of --config, from the kernel's own phase stamps")
     args = ap.parse_args()
     if args.gpus != 1:
-        print("bench.py: this build runs on one GPU only (the p shards of a configuration run in sequence "
-              "on it); --gpus %d is not supported" % args.gpus, file=sys.stderr)
+        print("bench.py: this build runs on one GPU only (the p shards of a configuration share it); "
+              "--gpus %d is not supported" % args.gpus, file=sys.stderr)
         sys.exit(2)
 
     import torch
@@ -440,7 +447,7 @@ def main():
             per_config[name] = dict(output_numbers(c, w_ms), kernels=kern, roofline=gemm_roofline(c, kern))
             del pl
             torch.cuda.empty_cache()
-        # the Llama-like workload through Algorithm 2 (one barrier; same three products per shard), and the
+        # the Llama-like workload through Algorithm 2 (one barrier; a launch per shard in pass S), and the
         # barrier on a side stream next to a pass S of that workload
         c2 = si.CONFIGS["cfg2_llama"]
         pl = make_output_plan(vp, c2, seeded_numpy=False, algorithm=2)
@@ -479,7 +486,7 @@ def main():
         "pct_bf16_mfma_peak_hardware_flops": 100.0 * nums["hardware_tflops"] / BF16_MFMA_PEAK_TFLOPS,
         "loss": loss,
         "config": {"workload": "%s: N=%d h=%d V=%d p=%d Vs=%d %s, logits %s; fwd + combine + bwd of all p shards "
-                               "in sequence on one GPU" % (cfg.name, cfg.N, cfg.h, cfg.V, cfg.p, cfg.Vs, cfg.dtype,
+                               "on one GPU" % (cfg.name, cfg.N, cfg.h, cfg.V, cfg.p, cfg.Vs, cfg.dtype,
                                                            "stored" if cfg.save_logits else "recomputed"),
                    "N": cfg.N, "h": cfg.h, "V": cfg.V, "p": cfg.p, "Vs": cfg.Vs,
                    "model_flops_per_step": cfg.model_flops},
