@@ -204,9 +204,13 @@ vp_status vp_output_dx_alg2(const float* A, const void* B,
  * rows[r] >= 1 vocabulary rows from shard_offsets[r] on.  W_shards, logits_out, logits_saved and dW_shards are HOST arrays
  * of p device pointers, rows and shard_offsets HOST arrays; all are read before the call returns.  The statistics are
  * [p, N].  vp_output_bwd_group adds every shard's term to dH_accum in ascending order of the vocabulary (with
- * VP_DH_OVERWRITE: writes their sum).  Checks, statistics, logits and dW are those of p single calls; dH may differ from
- * theirs in the order of its fp32 sums.  The workspace is that of vp_output_group_workspace_bytes (VP_CALL_OUTPUT_FWD or
- * VP_CALL_OUTPUT_BWD; (size_t)-1 on invalid arguments).
+ * VP_DH_OVERWRITE: writes their sum).  No two outputs may share memory.  The checks are those of p single calls.  With
+ * VP_BF16 so are statistics, logits and dW, bit for bit; dH may differ in the order of its fp32 sums, and a sum may run
+ * over all shards in one chain, where p single calls round each shard's sum apart before they add it.  With VP_F32 every
+ * result may differ from theirs in the order of its sums (K is cut into slices by the tiles of all shards together), but
+ * no chain of a sum is longer than a shard.  The workspace is that of vp_output_group_workspace_bytes
+ * (VP_CALL_OUTPUT_FWD or VP_CALL_OUTPUT_BWD; (size_t)-1 on invalid arguments).  vp_output_bwd_group makes no promise of D
+ * in its workspace.
  */
 size_t vp_output_group_workspace_bytes(vp_call which, int32_t p, int64_t N, int64_t h, const int64_t* rows, vp_dtype dt,
                                        uint32_t flags);
@@ -255,7 +259,8 @@ vp_status vp_embed_bwd(const void* grad_out, const int64_t* ids,
 /*
  * The same for p consecutive shards of Vs rows each that live on one device, in as few launches as
  * possible: shard r owns rows [shard_offset + r Vs, shard_offset + (r + 1) Vs).  table_shards, outs and
- * dtable_shards are HOST arrays of p device pointers; the arrays are read before the call returns.
+ * dtable_shards are HOST arrays of p device pointers; the arrays are read before the call returns.  No two outputs may
+ * share memory.
  * Results equal those of p single calls bit for bit.  The workspace is that of the single call.
  */
 vp_status vp_embed_fwd_group(const void* const* table_shards, const int64_t* ids, int32_t p, int64_t N, int64_t h,
@@ -266,7 +271,8 @@ vp_status vp_embed_bwd_group(const void* grad_out, const int64_t* ids, int32_t p
 
 /*
  * Measurement aid, not part of the method.  While enabled, every kernel launch made by the
- * entry points above is bracketed by two HIP events on the launch stream (events are created
+ * entry points above is bracketed by two HIP events on the launch stream, the few launches of one step (an fp32 product and
+ * the sum of its K slices, the barrier, the sort of the input layer) by one pair (events are created
  * on demand and pooled; this is the only state the library ever holds, and none exists while
  * timing is off, the default).  vp_profile_read waits for the recorded events, writes the
  * summed elapsed milliseconds and the launch count per kernel id into the two host arrays

@@ -221,9 +221,11 @@ __device__ __forceinline__ int shard_of(const GemmBf16Group& gg, int t) {
 // N=512 h=2048 V=32000 p=4: 954 -> 290 us; N=1999 h=3072 V=50001 p=8: 3048 -> 1888; N=4096 h=4096 V=32000 p=8: 2940 -> 2692;
 // N=4096 h=8192 V=256000 p=16: 52.6 -> 51.5 ms; the loss alone, N=64 h=4096 V=128256 p=8: 653 -> 253 us.
 //
-// MI = 2: at most 64 rows (tokens): only the first two row blocks are multiplied, a quarter of the tile's rows.  The
-// products are then bound by reading W, and the loads of a k tile wait for the wavefront's matrix work no longer:
-// N=16 h=2048 V=32000: 48 -> 37 us (3.5 TB/s), N=64 h=4096 V=128256: 265 -> 224 us (4.7 TB/s).
+// MI = 2: at most 64 rows (tokens): every wavefront multiplies the first two of its four row blocks, so half the tile (the
+// half of it that the lower two wavefronts have are rows past the end).  The products are then bound by reading W, and the
+// loads of a k tile wait for the wavefront's matrix work no longer: N=16 h=2048 V=32000: 46 -> 36 us (3.7 TB/s), N=64 h=4096
+// V=128256 p=8: 230 -> 198 us (5.3 TB/s).  A third row block would be the next step: 65 and 96 tokens take 231 and 228 us
+// with the whole tile, 128 take 248.
 template <bool A_KC, bool B_KC, Epi EPI, bool STREAM, bool TRACE, bool KTAIL, int MI = 4>
 __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Group gg) {
     constexpr bool CAT_N = A_KC && B_KC, CAT_M = !A_KC && !B_KC, CAT_K = A_KC && !B_KC;

@@ -170,7 +170,7 @@ struct ShardList {
     void* D[GEMM_GROUP_MAX];
 };
 
-// Row statistics of stored fp32 logits (fp32 path): m', sum', t' of shard r from Y[r] (row stride ldd[r]) into row r of
+// Row statistics of stored fp32 logits (fp32 path): m', sum', t' of shard r from Y[r] (row stride ldy[r]) into row r of
 // lmax, lsum and ltgt.
 hipError_t launch_row_stats_f32(const ShardList& l, const int64_t* labels, int N, float* lmax, float* lsum, float* ltgt,
                                 hipStream_t st);
@@ -184,22 +184,22 @@ hipError_t launch_fold_partials(const float* part_max, const float* part_sum, co
 hipError_t launch_combine(const float* lmax, const float* lsum, const float* ltgt, int p, int N,
                           float* gmax, float* gsum, float* loss_row, float* loss_mean, hipStream_t st);
 
-// D = (exp(Y - m)/sum - onehot) * scale from stored logits; is_bf16 selects the type of Y and D.
+// D = (exp(Y - m)/sum - onehot) * scale from stored logits of one shard; is_bf16 selects the type of Y and D.
 // Y has row stride ldy, D row stride ldd (elements); columns Vs..ldd-1 of D are zeroed.
 // labels == nullptr: no one-hot term (softmax' of Algorithm 2 with the local statistics).
 hipError_t launch_dlogits(const void* Y, int64_t ldy, void* D, int64_t ldd, int is_bf16, const int64_t* labels,
                           int64_t off, const float* gmax, const float* gsum, float scale, int N, int Vs,
                           hipStream_t st);
 
+// The same for all shards of a list (D_r from Y_r, whose row stride is ldy[r]).
+hipError_t launch_dlogits_group(const ShardList& l, int is_bf16, const int64_t* labels, const float* gmax, const float* gsum,
+                                float scale, int N, hipStream_t st);
+
 // dH += (A_r * c_r - B_r) * scale over p shards, c_ri = lsum_ri exp(lmax_ri - gmax_i) / gsum_i  (Algorithm 2)
 // (overwrite: dH = ... instead of +=; A and B are host arrays, lmax and lsum [p, N])
 hipError_t launch_dx_alg2(const float* const* A, const void* const* B, int p, int b_is_bf16, const float* lmax,
                           const float* lsum, const float* gmax, const float* gsum, int N, int h, float scale, bool overwrite,
                           float* dH, hipStream_t st);
-
-// The same for all shards of a list (D_r from Y_r, whose row stride is ldy[r]).
-hipError_t launch_dlogits_group(const ShardList& l, int is_bf16, const int64_t* labels, const float* gmax, const float* gsum,
-                                float scale, int N, hipStream_t st);
 
 // Zeroes the padding columns rows[r] .. ldd[r]-1 of the bf16 matrices D_r [N, ldd[r]].
 hipError_t launch_zero_pad_columns(const ShardList& l, int N, hipStream_t st);

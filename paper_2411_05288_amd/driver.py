@@ -1,12 +1,14 @@
-"""Host driver: runs the p shards of one configuration on one GPU, all of them in one call per pass.
+"""Host driver: runs the p shards of one configuration on one GPU, all of them in one call per pass where it can.
 
 This is launch ordering and buffer ownership only.  It follows Algorithm 1 of the paper:
-pass S on every shard (vp_output_fwd), barrier C1 (vp_combine_stats, standing in for the two
-all-reduces), pass T on every shard (vp_output_bwd) with the reduce C2 realised as fp32
-accumulation into one dH buffer in ascending shard order.  With algorithm=2 it follows
-Algorithm 2: pass S also forms A and B (vp_output_fwd_alg2), the input gradient is
-accumulated inside the single barrier (vp_output_dx_alg2), and pass T is dW alone.  All device buffers are allocated
-once, when the plan is built; a step allocates nothing.
+pass S on all shards (vp_output_fwd_group), barrier C1 (vp_combine_stats, standing in for the two
+all-reduces), pass T on all shards (vp_output_bwd_group) with the reduce C2 realised as fp32
+accumulation into one dH buffer in ascending order of the vocabulary.  With algorithm=2 it follows
+Algorithm 2: pass S, shard by shard, also forms A and B (vp_output_fwd_alg2), the input gradient is
+accumulated inside the single barrier (vp_output_dx_alg2_group), and pass T is dW alone.  The calls of a single
+shard (vp_output_fwd, vp_output_bwd) serve plans whose shards without real rows are not the last ones, and plans
+without the workspace for all shards.  All device buffers are allocated once, when the plan is built; a step
+allocates nothing.
 """
 from __future__ import annotations
 
