@@ -237,10 +237,11 @@ static int slices_for(int64_t tiles, int64_t K, int64_t min_k) {
     return S < 2 ? 1 : (int)S;
 }
 static int splitk_slices(int64_t M, int64_t N, int64_t K) { return slices_for(ceil_div(M, 64) * ceil_div(N, 64), K, 64); }
-// Logits and dW of a group.  A K step of 32 takes 0.55 us where a workgroup has a compute unit to itself, the sum of the
-// slices 4 us and a launch, so a K that is not cut into two slices of 256 is not cut (N=500 h=128 V=2000 p=4, forward pass,
-// K = 128: 29 us whole, 34 in two slices).
-int gemm_f32_group_slices(int64_t tiles, int64_t K) { return slices_for(tiles, K, 256); }
+// Logits and dW of a group.  A K step of 32 takes 0.55 us where a workgroup has a compute unit to itself; the sum of the
+// slices is another launch, 3 us of host time in passes that the host bounds.  So slices of at least 256, from K = 1024 on.
+// 32 tiles, product and forward pass, us, in one chain -> in slices: K = 512: 19.3 -> 15.4 and 28.0 -> 31.2; 640: 22.4 ->
+// 17.2 and 27.8 -> 30.6; 800: 26.5 -> 16.5 and 30.6 -> 31.0; 1024: 32.4 -> 15.9 and 36.9 -> 30.5; 2048: 58 -> 17 and 63 -> 30.
+int gemm_f32_group_slices(int64_t tiles, int64_t K) { return K < 1024 ? 1 : slices_for(tiles, K, 256); }
 // A product cut in S slices advances in steps of FK.
 static int slice_length(int64_t K, int S) { return S > 1 ? (int)(ceil_div(ceil_div(K, S), FK) * FK) : (int)K; }
 

@@ -153,7 +153,7 @@ def test_plan_with_a_workspace_limit(save_logits, algorithm):
     (16, 1028, [500, 500]),                   # slices of unequal length, 16-byte sums
     (2048, 64, [125] * 16),                   # dW in 8 slices
     (1030, 37, [70, 65, 1]),                  # dW in slices of an odd K, rows of H not 16-byte aligned
-    (20, 511, [64] * 3), (20, 512, [64] * 3), # the last K that is not cut and the first that is
+    (20, 1023, [64] * 3), (20, 1024, [64] * 3),     # the last K that is not cut and the first that is
     (64, 4096, [64] * 16),                    # shards of one tile: 256 workgroups with either size of tile
     (200, 1024, [70] * 19),                   # more shards than a launch takes
 ])
