@@ -25,13 +25,39 @@ struct EmbedBwdGroup {
 };
 
 // ------------------------------------------------------------------------- forward
-// Bound by the stores: p full-size outputs leave, at most N table rows come in.  Workgroup (x, s) writes rows_per_wg
-// consecutive rows of shard s's output, one wavefront per row and 64 * V bytes per store, so that a workgroup's
-// stores cover one contiguous range of about 32 KB whatever the row length.  Measured: 8 shards, N = 8192, h = 4096,
-// bf16: 102 us (5.3 TB/s) in one launch, 103 us in eight; N = 512, h = 1024, fp32: 5 us for 8 launches of 2.7 us.
+// Bound by the stores: p full-size outputs leave, at most N table rows come in.  The output is written once and read much
+// later (by the reduce over shards): streaming stores.  Two maps of threads to rows, both with the shard in blockIdx.y:
+//  * a workgroup per row: its four wavefronts write neighbouring KB of one row at a time;
+//  * a wavefront per row, rows_per_wg consecutive rows (about 32 KB) per workgroup: for short rows, of which one leaves most
+//    lanes of a workgroup idle.
+// Wavefront -> workgroup per row, us in one launch (V=32000): 65536 tokens, 8 shards, bf16, h = 128: 26 -> 114, 512: 101 ->
+// 114, 640: 131 -> 123, 768: 157 -> 124, 1024: 202 -> 149, 2048: 394 -> 321; one shard, 640: 26 -> 28, 1024: 40 -> 38;
+// 8192 tokens, 8 shards, h = 4096: 101 -> 96 (5.6 TB/s).  Rows that are not 16-byte aligned (4 shards, 30000 tokens): 261
+// bf16: 34 -> 36, 511: 62 -> 42, 1001: 120 -> 58; 131 fp32: 31 -> 33, 251: 51 -> 37.
+constexpr int64_t FWD_WAVE_BYTES = 1280, FWD_WAVE_BYTES_UNALIGNED = 640;     // the longest row of a wavefront
+
 template <typename V>
-__global__ __launch_bounds__(256) void embed_fwd_kernel(EmbedFwdGroup g, const int64_t* __restrict__ ids, int N,
-                                                        int row_vecs, int Vs, int64_t off, int rows_per_wg) {
+__device__ __forceinline__ void embed_row(V* o, const V* __restrict__ table, int64_t loc, int Vs, int row_vecs, int first, int step) {
+    if (loc >= 0 && loc < Vs) {
+        const V* __restrict__ t = table + (size_t)loc * row_vecs;
+        for (int c = first; c < row_vecs; c += step) __builtin_nontemporal_store(t[c], o + c);
+    } else {
+        const V z = V(0);
+        for (int c = first; c < row_vecs; c += step) __builtin_nontemporal_store(z, o + c);
+    }
+}
+
+template <typename V>
+__global__ __launch_bounds__(256) void embed_fwd_wg_kernel(EmbedFwdGroup g, const int64_t* __restrict__ ids, int row_vecs, int Vs,
+                                                           int64_t off) {
+    const int s = blockIdx.y, i = blockIdx.x;
+    embed_row<V>((V*)g.out[s] + (size_t)i * row_vecs, (const V*)g.table[s], ids[i] - (off + (int64_t)s * Vs), Vs, row_vecs,
+                 threadIdx.x, 256);
+}
+
+template <typename V>
+__global__ __launch_bounds__(256) void embed_fwd_wave_kernel(EmbedFwdGroup g, const int64_t* __restrict__ ids, int N, int row_vecs,
+                                                             int Vs, int64_t off, int rows_per_wg) {
     const int s = blockIdx.y;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -39,53 +65,43 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(EmbedFwdGroup g, const i
     V* __restrict__ out = (V*)g.out[s];
     const int64_t first = off + (int64_t)s * Vs;
     const int end = min(N, (int)(blockIdx.x + 1) * rows_per_wg);
-    // the output is written once and read much later (by the reduce over shards): streaming stores
-    for (int i = blockIdx.x * rows_per_wg + wave; i < end; i += 4) {
-        const int64_t loc = ids[i] - first;
-        V* o = out + (size_t)i * row_vecs;
-        if (loc >= 0 && loc < Vs) {
-            const V* t = table + (size_t)loc * row_vecs;
-            int c = lane;
-            for (; c + 192 < row_vecs; c += 256) {
-                const V a = t[c], b = t[c + 64], d = t[c + 128], e = t[c + 192];
-                __builtin_nontemporal_store(a, o + c);
-                __builtin_nontemporal_store(b, o + c + 64);
-                __builtin_nontemporal_store(d, o + c + 128);
-                __builtin_nontemporal_store(e, o + c + 192);
-            }
-            for (; c < row_vecs; c += 64) __builtin_nontemporal_store(t[c], o + c);
-        } else {
-            const V z = V(0);
-            for (int c = lane; c < row_vecs; c += 64) __builtin_nontemporal_store(z, o + c);
-        }
-    }
+    for (int i = blockIdx.x * rows_per_wg + wave; i < end; i += 4)
+        embed_row<V>(out + (size_t)i * row_vecs, table, ids[i] - first, Vs, row_vecs, lane, 64);
+}
+
+template <typename V>
+static void launch_embed_fwd_t(const EmbedFwdGroup& g, int n, const int64_t* ids, int N, int row_vecs, int Vs, int64_t off,
+                               int rows, hipStream_t st) {
+    if (rows == 0)
+        hipLaunchKernelGGL((embed_fwd_wg_kernel<V>), dim3((unsigned)N, (unsigned)n), dim3(256), 0, st, g, ids, row_vecs, Vs, off);
+    else
+        hipLaunchKernelGGL((embed_fwd_wave_kernel<V>), dim3((unsigned)ceil_div(N, rows), (unsigned)n), dim3(256), 0, st, g, ids, N,
+                           row_vecs, Vs, off, rows);
 }
 
 hipError_t launch_embed_fwd(const void* const* tables, const int64_t* ids, int p, int N, int h, int Vs, int64_t off,
                             int elem_bytes, void* const* outs, hipStream_t st) {
     const int64_t row_bytes = (int64_t)h * elem_bytes;
     ProfScope prof(K_EMBED_FWD, st);
-    int rows = (int)(32768 / row_bytes) / 4 * 4;
-    if (rows < 4) rows = 4;
-    if (rows > 64) rows = 64;
-    // fewer rows per workgroup while the grid would leave compute units without one
-    while (rows > 4 && ceil_div(N, rows) * p < 1024) rows -= 4;
+    const bool vec = row_bytes % 16 == 0;
+    int rows = 0;              // of a workgroup with a wavefront per row; 0: a workgroup per row (N h < 2^31: below 2^23 rows)
+    if (row_bytes <= (vec ? FWD_WAVE_BYTES : FWD_WAVE_BYTES_UNALIGNED)) {
+        rows = (int)(32768 / row_bytes) / 4 * 4;
+        if (rows > 64) rows = 64;
+        // fewer rows per workgroup while the grid would leave compute units without one
+        while (rows > 4 && ceil_div(N, rows) * p < 1024) rows -= 4;
+    }
     for (int s0 = 0; s0 < p; s0 += EMBED_GROUP_MAX) {
         const int n = p - s0 < EMBED_GROUP_MAX ? p - s0 : EMBED_GROUP_MAX;
         EmbedFwdGroup g{};
-        bool vec = row_bytes % 16 == 0;
         for (int s = 0; s < n; ++s) {
             g.table[s] = tables[s0 + s];
             g.out[s] = outs[s0 + s];
         }
-        const dim3 grid((unsigned)ceil_div(N, rows), (unsigned)n);
         const int64_t first = off + (int64_t)s0 * Vs;
-        if (vec)
-            hipLaunchKernelGGL((embed_fwd_kernel<uintx4>), grid, dim3(256), 0, st, g, ids, N, (int)(row_bytes / 16), Vs, first, rows);
-        else if (elem_bytes == 4)
-            hipLaunchKernelGGL((embed_fwd_kernel<unsigned>), grid, dim3(256), 0, st, g, ids, N, h, Vs, first, rows);
-        else
-            hipLaunchKernelGGL((embed_fwd_kernel<u16>), grid, dim3(256), 0, st, g, ids, N, h, Vs, first, rows);
+        if (vec) launch_embed_fwd_t<uintx4>(g, n, ids, N, (int)(row_bytes / 16), Vs, first, rows, st);
+        else if (elem_bytes == 4) launch_embed_fwd_t<unsigned>(g, n, ids, N, h, Vs, first, rows, st);
+        else launch_embed_fwd_t<u16>(g, n, ids, N, h, Vs, first, rows, st);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

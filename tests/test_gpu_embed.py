@@ -171,3 +171,16 @@ def test_embed_infinities_nan_and_negative_zeros(shape, dtype):
         nan = np.isnan(ref)
         assert np.array_equal(np.isnan(got), nan)
         assert np.array_equal(got.view(np.uint32)[~nan], ref.view(np.uint32)[~nan])
+
+
+@pytest.mark.parametrize("dtype,widths", [
+    ("bf16", (640, 648, 320, 321)),        # the longest row of a wavefront and the next one: 16-byte vectors, elements
+    ("f32", (320, 324, 160, 161, 159)),
+])
+@pytest.mark.parametrize("N,p", [(1, 1), (263, 3), (1030, 33)])
+def test_embed_row_lengths_at_the_change_of_kernel(N, p, dtype, widths):
+    for h in widths:
+        ids = si.zipf_ids(N, 4 * p, 1.1, 500 + h)
+        ids[::7] = 4 * p + 5
+        print("embed widths", (N, h, p, dtype), flush=True)
+        check_embed(N, h, 4 * p, p, dtype, seed=500 + h, ids=ids)
