@@ -109,6 +109,9 @@ class OutputLayerPlan:
                 group_bytes = max(group_bytes, B.vp_output_group_workspace_bytes(B.VP_CALL_OUTPUT_FWD, N, h, live, self.dt,
                                                                                  flags))
             self.grouped = workspace_limit is None or group_bytes <= max(nbytes, workspace_limit)
+            # a single shard gains from the group call only the K slices of dH, which need workspace
+            if self.live == 1 and group_bytes == nbytes:
+                self.grouped = False
         # Algorithm 2 keeps A = softmax' W_r and B = G W_r of every shard until the barrier
         self.A = [torch.empty((N, h), **f32) for _ in range(p)] if algorithm == 2 else None
         self.Bm = [torch.empty((N, h), dtype=H.dtype, device=dev) for _ in range(p)] if algorithm == 2 else None
@@ -128,10 +131,15 @@ class OutputLayerPlan:
             stream = torch.cuda.ExternalStream(int(stream))
         return torch.cuda.stream(stream)
 
+    def _real(self, tensors, r):
+        """The real rows of shard r (a view is made only of a shard with padding: on small workloads the host's work is
+        what bounds a step)."""
+        t, v = tensors[r], self.valid[r]
+        return t if t.shape[0] == v else t[:v]
+
     def _live(self, tensors):
-        """The real rows of the shards that have any (a view is made only of a shard with padding: on small workloads
-        the host's work is what bounds a step)."""
-        return [t if t.shape[0] == v else t[:v] for t, v in zip(tensors, self.valid[:self.live])]
+        """The real rows of the shards that have any."""
+        return [self._real(tensors, r) for r in range(self.live)]
 
     def forward(self, stream=None) -> None:
         for r in range(self.live if self.algorithm == 1 and self.grouped else 0, self.p):
@@ -144,11 +152,11 @@ class OutputLayerPlan:
                 continue
             lg = self.logits[r] if self.logits is not None else None
             if self.algorithm == 1:
-                B.vp_output_fwd(self.H, self.W[r][:v], self.labels, self.offsets[r],
+                B.vp_output_fwd(self.H, self._real(self.W, r), self.labels, self.offsets[r],
                                 self.local_max[r], self.local_sumexp[r], self.local_target[r],
                                 lg, self.workspace, stream)
             else:
-                B.vp_output_fwd_alg2(self.H, self.W[r][:v], self.labels, self.offsets[r],
+                B.vp_output_fwd_alg2(self.H, self._real(self.W, r), self.labels, self.offsets[r],
                                      self.local_max[r], self.local_sumexp[r], self.local_target[r],
                                      self.A[r], self.Bm[r], lg, self.workspace, stream)
         if self.algorithm == 1 and self.grouped:
@@ -188,9 +196,9 @@ class OutputLayerPlan:
                     self.dW[r][v:].zero_()
             if v == 0 or self.grouped:
                 continue
-            B.vp_output_bwd(self.H, self.W[r][:v], self.labels, self.offsets[r], self.global_max, self.global_sumexp,
+            B.vp_output_bwd(self.H, self._real(self.W, r), self.labels, self.offsets[r], self.global_max, self.global_sumexp,
                             self.logits[r] if self.logits is not None else None, self.grad_scale,
-                            self.dH if self.algorithm == 1 else None, self.dW[r][:v], self.workspace, stream,
+                            self.dH if self.algorithm == 1 else None, self._real(self.dW, r), self.workspace, stream,
                             dh_overwrite=first)
             first = False
         if self.grouped:
@@ -235,13 +243,16 @@ class EmbeddingPlan:
         self.workspace = torch.empty((nbytes,), dtype=torch.uint8, device=dev)
 
     def forward(self, stream=None) -> None:
-        if all(t.shape == self.tables[0].shape for t in self.tables):
+        if self.p > 1 and all(t.shape == self.tables[0].shape for t in self.tables):
             B.vp_embed_fwd_group(self.tables, self.ids, 0, self.out, stream)
             return
-        for r in range(self.p):       # shards of different sizes
+        for r in range(self.p):       # a single shard (the group call costs the host 1 us more), shards of different sizes
             B.vp_embed_fwd(self.tables[r], self.ids, r * self.Vs, self.out[r], stream)
 
     def backward(self, stream=None) -> None:
+        if self.p == 1:
+            B.vp_embed_bwd(self.grad_out, self.ids, 0, self.dtable[0], self.workspace, stream)
+            return
         B.vp_embed_bwd_group(self.grad_out, self.ids, 0, self.dtable, self.workspace, stream)
 
 

@@ -109,3 +109,23 @@ def test_output_plan_on_a_device_without_room_for_all_shards(monkeypatch, algori
     monkeypatch.setattr(torch, "empty", full_device)
     plan = output_plan(algorithm)
     assert not plan.grouped and plan.workspace.numel() == limit
+
+
+def test_a_single_shard_takes_the_single_calls(monkeypatch, embed_calls):
+    fwd = []
+    monkeypatch.setattr(B, "vp_embed_fwd", lambda *a: fwd.append("one"))
+    monkeypatch.setattr(B, "vp_embed_fwd_group", lambda *a: fwd.append("group"))
+    for p in (1, 2):
+        plan = driver.EmbeddingPlan([torch.zeros(6, 8) for _ in range(p)], torch.zeros(5, dtype=torch.int64), torch.zeros(5, 8))
+        plan.forward()
+        plan.backward()
+    assert fwd == ["one", "group"] and [c[0] for c in embed_calls] == ["one", "group"]
+
+    def plan(N, h, rows, dtype, p=1, **kw):
+        return driver.OutputLayerPlan(torch.zeros(N, h, dtype=dtype), [torch.zeros(rows, h, dtype=dtype) for _ in range(p)],
+                                      torch.zeros(N, dtype=torch.int64), **kw)
+    assert plan(512, 2048, 8000, torch.bfloat16).grouped              # dH in K slices: the group call alone has them
+    assert not plan(512, 64, 256, torch.bfloat16).grouped             # no slices: nothing to gain
+    assert not plan(128, 256, 4096, torch.float32).grouped            # fp32: the single call cuts K itself
+    assert not plan(512, 64, 256, torch.bfloat16, 2, vocab_size=200).grouped      # the other shard is padding
+    assert plan(512, 64, 256, torch.bfloat16, 2).grouped
