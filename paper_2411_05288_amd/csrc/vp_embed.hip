@@ -150,7 +150,7 @@ __device__ __forceinline__ void add_batch(float (&acc)[VEC], const GV (&v)[D], i
 // threads, one per compute unit) builds and sorts the keys in its own LDS - the same few microseconds in all of them,
 // instead of a sort kernel, a round trip of the keys through memory and a second launch - numbers the runs of equal
 // rows, and then takes its share of the sums: workgroup (slab, group) covers 64 * VEC columns; its 16 wavefronts take
-// the runs group * 16 + w, + groups * 16, ... but for the long ones (sum_short_runs, sum_mid_run), which the 16 share
+// the runs group * 16 + w, + groups * 16, ... (sum_short_runs, sum_mid_run) but for the long ones, which the 16 share
 // (sum_long_run).  Measured: 8192 Zipf tokens, h = 4096, bf16, 8 shards of 32000 rows: 81 us in one launch, 162 us in
 // eight; N = 512, h = 1024, fp32: 12 us for 8 launches of 9 us.
 constexpr int FUSED_MAX_N = 8192;
@@ -354,8 +354,8 @@ __device__ __forceinline__ void load_batch(GV (&v)[D], const Rows& rows, unsigne
 constexpr int SHORT_Q = 4, SHORT_TINY = 4;      // runs of up to SHORT_TINY tokens go SHORT_Q at a time
 
 // One wavefront, SHORT_Q runs of at most B tokens (len 0: none): lane u of tok[q] holds the u-th token of run q, d[q] is
-// the lane's element of the run's row in the table gradient (any element of it if the lane is not active).  All loads of the runs of up to SHORT_TINY tokens, and of
-// the first longer one, are in flight before the first add.
+// the lane's element of the run's row in the table gradient (any element of it if the lane is not active).  All loads of the
+// runs of up to SHORT_TINY tokens, and of the first longer one, are in flight before the first add.
 template <typename T, int VEC, typename Rows>
 __device__ __forceinline__ void sum_short_runs(const int (&len)[SHORT_Q], const unsigned (&tok)[SHORT_Q],
                                                float* const (&d)[SHORT_Q], bool active, const Rows& rows) {
@@ -405,9 +405,10 @@ __device__ __forceinline__ void sum_short_runs(const int (&len)[SHORT_Q], const 
 }
 
 // One wavefront, one run: batches of B tokens, the rows of the next batch in flight during the adds of this one.  For runs
-// of B + 1 .. MID_BATCHES B tokens: a workgroup's chain (below) pays a few microseconds of latency per run whatever its
-// length, which 16 wavefronts with a run each hide from one another.
+// of B + 1 .. MID_BATCHES B tokens where there are many: a workgroup's chain (below) pays a few microseconds of latency per
+// run whatever its length, which 16 wavefronts with a run each hide from one another.
 constexpr int MID_BATCHES = 8;
+constexpr int MID_PER_GROUP = 3;     // more of them per workgroup go to its wavefronts (embed_bwd_fused_kernel)
 template <typename T, int VEC, typename Rows, typename TokenAt>
 __device__ __forceinline__ void sum_mid_run(int len, float* d, bool active, int lane, const Rows& rows,
                                             const TokenAt& token_at) {
@@ -527,8 +528,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(EmbedBwd
     __shared__ unsigned short run_start[FUSED_MAX_N + 2];   // position of the first key of run r; [n_runs] = owned
     __shared__ int wave_cnt[FUSED_MAX_N / 64];
     __shared__ float xchg[64 * VEC];
-    __shared__ int s_owned, s_runs;
-    if (threadIdx.x == 0) { s_owned = 0; s_runs = 0; }
+    __shared__ int s_owned, s_runs, s_mids;
+    if (threadIdx.x == 0) { s_owned = 0; s_runs = 0; s_mids = 0; }
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -605,6 +606,31 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(EmbedBwd
     __syncthreads();
     const int n_runs = s_runs;
 
+    // Runs of B + 1 .. MID_BATCHES B tokens: a wavefront each, or all 16 of a workgroup as the longer ones.  A wavefront alone
+    // waits for memory once per batch, a workgroup once per 16 of them, so it is the quicker way until the workgroups of a
+    // slab have several such runs each to take in turn.  us, a wavefront each -> a workgroup each (N tokens in V rows, h):
+    //   runs per workgroup below 1:  1000, 10, 1024, bf16: 17.8 -> 12.5;  4000, 40, 256: 25.6 -> 19.0
+    //   2.5: 8192, 40, 2048: 46.6 -> 37.7;  4 (two shards): 8192, 128, 1024: 35.4 -> 36.6;  6: 8192, 100, 2048: 38.1 -> 44.1
+    // Runs of up to 2 B tokens always to a wavefront: 8192, 400, 2048: 37.6 -> 34.5, but 3203, 79, 152: 29.3 -> 32.8 and
+    // 7000, 8000, 256 (four shards): 38.7 -> 42.5, because the long runs then start later.
+    // (owned - n_runs) / B bounds their number, so that they are seldom counted.
+    int mid_max = B;
+    if ((owned - n_runs) / B > MID_PER_GROUP * n_groups) {
+        int mids = 0;
+        for (int r0 = 0; r0 < n_runs; r0 += FUSED_THREADS) {
+            const int r = r0 + (int)threadIdx.x;
+            bool is_mid = false;
+            if (r < n_runs) {
+                const int len = (int)run_start[r + 1] - (int)run_start[r];
+                is_mid = len > B && len <= MID_BATCHES * B;
+            }
+            mids += __builtin_popcountll(__builtin_amdgcn_ballot_w64(is_mid));
+        }
+        if (lane == 0 && mids) atomicAdd(&s_mids, mids);
+        __syncthreads();
+        if (s_mids > MID_PER_GROUP * n_groups) mid_max = MID_BATCHES * B;
+    }
+
     const int slab = blockIdx.x % n_slabs, group = blockIdx.x / n_slabs;
     const bool active = (slab * 64 + lane) * VEC < h;
     const int c0 = active ? (slab * 64 + lane) * VEC : 0;
@@ -615,8 +641,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(EmbedBwd
     // short runs: one wavefront each, Q of them per turn
     const int stride = n_groups * FUSED_WAVES;
     for (int r0 = group * FUSED_WAVES + wave; r0 < n_runs; r0 += Q * stride) {
-        int len[Q], first[Q], mid[Q];
-        unsigned tok[Q];
+        int len[Q];
+        unsigned tok[Q], row[Q];
         float* d[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -629,24 +655,41 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(EmbedBwd
             }
             s = __builtin_amdgcn_readfirstlane(s);
             len[q] = __builtin_amdgcn_readfirstlane(len[q]);
-            first[q] = s;
-            mid[q] = len[q] > B && len[q] <= MID_BATCHES * B ? len[q] : 0;
             if (len[q] > B) len[q] = 0;
             tok[q] = lane < len[q] ? key_token(sh[s + lane]) : 0u;
-            d[q] = dtable_row(g, __builtin_amdgcn_readfirstlane(key_row(sh[s])), (unsigned)Vs, h) + c0;
+            row[q] = __builtin_amdgcn_readfirstlane(key_row(sh[s]));
         }
+        #pragma unroll
+        for (int q = 0; q < Q; ++q) d[q] = dtable_row(g, row[q], (unsigned)Vs, h) + c0;
         sum_short_runs<T, VEC>(len, tok, d, active, rows);
-        for (int q = 0; q < Q; ++q)
-            if (mid[q] > 0)
-                sum_mid_run<T, VEC>(mid[q], d[q], active, lane, rows, [&](int j) { return key_token(sh[first[q] + j]); });
     }
+    // mid runs: the wavefront looks through its run numbers 64 at a time (a loop of its own: kept over the one above, the
+    // positions of mid runs cost it registers)
+    if (mid_max > B)
+        for (int base = group * FUSED_WAVES + wave; base < n_runs; base += 64 * stride) {
+            const int cand = base + lane * stride;
+            bool is_mid = false;
+            if (cand < n_runs) {
+                const int len = (int)run_start[cand + 1] - (int)run_start[cand];
+                is_mid = len > B && len <= mid_max;
+            }
+            u64 todo = __builtin_amdgcn_ballot_w64(is_mid);
+            while (todo) {
+                const int r = base + __builtin_ctzll(todo) * stride;
+                todo &= todo - 1;
+                const int s = __builtin_amdgcn_readfirstlane((int)run_start[r]);
+                const int len = __builtin_amdgcn_readfirstlane((int)run_start[r + 1]) - s;
+                float* const d = dtable_row(g, __builtin_amdgcn_readfirstlane(key_row(sh[s])), (unsigned)Vs, h) + c0;
+                sum_mid_run<T, VEC>(len, d, active, lane, rows, [&](int j) { return key_token(sh[s + j]); });
+            }
+        }
     // long runs: run r belongs to group r % n_groups, all 16 wavefronts of it.  Each wavefront looks through that
     // group's run numbers 64 at a time; LDS holds the same in all of them, so they agree on which runs are long
     // and meet at the same barriers.
     for (int base = 0; base < n_runs; base += 64 * n_groups) {
         const int cand = base + lane * n_groups + group;
         bool is_long = false;
-        if (cand < n_runs) is_long = (int)run_start[cand + 1] - (int)run_start[cand] > MID_BATCHES * B;
+        if (cand < n_runs) is_long = (int)run_start[cand + 1] - (int)run_start[cand] > mid_max;
         u64 todo = __builtin_amdgcn_ballot_w64(is_long);
         while (todo) {
             const int r = base + __builtin_ctzll(todo) * n_groups + group;
@@ -862,7 +905,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwd
         for (int q0 = 0; q0 < DRAW && at + q0 < n_short; q0 += Q) {
             u64 key[Q];
             int len[Q];
-            unsigned tok[Q];
+            unsigned tok[Q], row[Q];
             float* d[Q];
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
@@ -871,12 +914,13 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwd
             }
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
-                const unsigned row = __builtin_amdgcn_readfirstlane((unsigned)(key[q] >> 32));
-                const u64 m = __builtin_amdgcn_ballot_w64((unsigned)(key[q] >> 32) == row);
+                row[q] = __builtin_amdgcn_readfirstlane((unsigned)(key[q] >> 32));
+                const u64 m = __builtin_amdgcn_ballot_w64((unsigned)(key[q] >> 32) == row[q]);
                 tok[q] = (unsigned)key[q];
                 len[q] = at + q0 + q < n_short ? __builtin_ctzll(~m) : 0;
-                d[q] = dtable_row(g, row, (unsigned)Vs, h) + c0;
             }
+            #pragma unroll
+        for (int q = 0; q < Q; ++q) d[q] = dtable_row(g, row[q], (unsigned)Vs, h) + c0;
             sum_short_runs<T, VEC>(len, tok, d, active, rows);
         }
         at = __builtin_amdgcn_readfirstlane(at_next);

@@ -184,3 +184,26 @@ def test_embed_row_lengths_at_the_change_of_kernel(N, p, dtype, widths):
         ids[::7] = 4 * p + 5
         print("embed widths", (N, h, p, dtype), flush=True)
         check_embed(N, h, 4 * p, p, dtype, seed=500 + h, ids=ids)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("N,h,rows,per_row", [
+    (1000, 128, 10, 100),     # few runs of a middle length: a workgroup each
+    (8000, 640, 200, 40),     # many of them: a wavefront each
+    (8192, 640, 32, 256),     # the longest a wavefront takes
+    (8192, 640, 31, 257),     # (and one token more)
+    (3072, 36, 96, 32),       # the longest short run (bf16)
+    (3168, 36, 96, 33),       # and the next length
+    (1600, 2052, 100, 16),    # the longest short run of fp32 pairs; a workgroup per slab
+    (1700, 2052, 100, 17),
+])
+@pytest.mark.parametrize("p", [1, 2])
+def test_embed_runs_of_a_middle_length(N, h, rows, per_row, p, dtype):
+    # every row has the same number of tokens, in an order that mixes the rows: bit for bit the in-order sum either way
+    ids = (np.arange(N, dtype=np.int64) * 7) % rows
+    if rows % 7 == 0:
+        ids = (np.arange(N, dtype=np.int64) * 11) % rows
+    V = (rows + p - 1) // p * p
+    assert np.bincount(ids).max() >= per_row
+    print("embed runs", (N, h, rows, per_row, p, dtype), flush=True)
+    check_embed(N, h, V, p, dtype, seed=600 + N, ids=ids, preload=True)
