@@ -16,9 +16,11 @@ namespace vp {
 typedef unsigned long long u64;
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
+// (P = 1 or EMBED_GROUP_MAX: a launch of one shard carries one shard's arguments)
+template <int P>
 struct EmbedFwdGroup {
-    const void* table[EMBED_GROUP_MAX];
-    void* out[EMBED_GROUP_MAX];
+    const void* table[P];
+    void* out[P];
 };
 struct EmbedBwdGroup {
     float* dtable[EMBED_GROUP_MAX];
@@ -27,13 +29,17 @@ struct EmbedBwdGroup {
 // ------------------------------------------------------------------------- forward
 // Bound by the stores: p full-size outputs leave, at most N table rows come in.  The output is written once and read much
 // later (by the reduce over shards): streaming stores.  Two maps of threads to rows, both with the shard in blockIdx.y:
-//  * a workgroup per row: its four wavefronts write neighbouring KB of one row at a time;
+//  * a workgroup per row: its four wavefronts write neighbouring KB of one row at a time.  Workgroups are dealt to the 8 XCDs
+//    round-robin and every XCD has its own L2, so each XCD takes a contiguous run of rows: a cache line that two rows share
+//    is then completed in one L2.  Row i in workgroup i -> so, us in one launch: 34340 tokens, h = 728, bf16, 24 shards:
+//    324 -> 231 (a launch per shard: 271), 20741, 1808, 16: 263 -> 218, 39694, 557, fp32, 8: 213 -> 163; rows of whole lines,
+//    8192, 4096, bf16, 8: 95 -> 88, 65536, 2048, 8: 322 -> 337;
 //  * a wavefront per row, rows_per_wg consecutive rows (about 32 KB) per workgroup: for short rows, of which one leaves most
 //    lanes of a workgroup idle.
-// Wavefront -> workgroup per row, us in one launch (V=32000): 65536 tokens, 8 shards, bf16, h = 128: 26 -> 114, 512: 101 ->
-// 114, 640: 131 -> 123, 768: 157 -> 124, 1024: 202 -> 149, 2048: 394 -> 321; one shard, 640: 26 -> 28, 1024: 40 -> 38;
-// 8192 tokens, 8 shards, h = 4096: 101 -> 96 (5.6 TB/s).  Rows that are not 16-byte aligned (4 shards, 30000 tokens): 261
-// bf16: 34 -> 36, 511: 62 -> 42, 1001: 120 -> 58; 131 fp32: 31 -> 33, 251: 51 -> 37.
+// Wavefront per row -> row i in workgroup i, us in one launch (V=32000): 65536 tokens, 8 shards, bf16, h = 128: 26 -> 114,
+// 512: 101 -> 114, 640: 131 -> 123, 768: 157 -> 124, 1024: 202 -> 149, 2048: 394 -> 321; one shard, 640: 26 -> 28, 1024:
+// 40 -> 38.  Rows that are not 16-byte aligned (4 shards, 30000 tokens): 261 bf16: 34 -> 36, 511: 62 -> 42, 1001: 120 -> 58;
+// 131 fp32: 31 -> 33, 251: 51 -> 37.
 constexpr int64_t FWD_WAVE_BYTES = 1280, FWD_WAVE_BYTES_UNALIGNED = 640;     // the longest row of a wavefront
 
 template <typename V>
@@ -47,17 +53,19 @@ __device__ __forceinline__ void embed_row(V* o, const V* __restrict__ table, int
     }
 }
 
-template <typename V>
-__global__ __launch_bounds__(256) void embed_fwd_wg_kernel(EmbedFwdGroup g, const int64_t* __restrict__ ids, int row_vecs, int Vs,
-                                                           int64_t off) {
-    const int s = blockIdx.y, i = blockIdx.x;
+template <typename V, int P>
+__global__ __launch_bounds__(256) void embed_fwd_wg_kernel(EmbedFwdGroup<P> g, const int64_t* __restrict__ ids, int row_vecs,
+                                                           int Vs, int64_t off) {
+    const int s = blockIdx.y, b = blockIdx.x, N = gridDim.x;
+    const int x = b & 7, per = N >> 3, rem = N & 7;
+    const int i = x * per + (x < rem ? x : rem) + (b >> 3);
     embed_row<V>((V*)g.out[s] + (size_t)i * row_vecs, (const V*)g.table[s], ids[i] - (off + (int64_t)s * Vs), Vs, row_vecs,
                  threadIdx.x, 256);
 }
 
-template <typename V>
-__global__ __launch_bounds__(256) void embed_fwd_wave_kernel(EmbedFwdGroup g, const int64_t* __restrict__ ids, int N, int row_vecs,
-                                                             int Vs, int64_t off, int rows_per_wg) {
+template <typename V, int P>
+__global__ __launch_bounds__(256) void embed_fwd_wave_kernel(EmbedFwdGroup<P> g, const int64_t* __restrict__ ids, int N,
+                                                             int row_vecs, int Vs, int64_t off, int rows_per_wg) {
     const int s = blockIdx.y;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -69,14 +77,25 @@ __global__ __launch_bounds__(256) void embed_fwd_wave_kernel(EmbedFwdGroup g, co
         embed_row<V>(out + (size_t)i * row_vecs, table, ids[i] - first, Vs, row_vecs, lane, 64);
 }
 
-template <typename V>
-static void launch_embed_fwd_t(const EmbedFwdGroup& g, int n, const int64_t* ids, int N, int row_vecs, int Vs, int64_t off,
-                               int rows, hipStream_t st) {
+template <typename V, int P>
+static void launch_embed_fwd_p(const void* const* tables, void* const* outs, int n, const int64_t* ids, int N, int row_vecs, int Vs,
+                               int64_t off, int rows, hipStream_t st) {
+    EmbedFwdGroup<P> g{};
+    for (int s = 0; s < n; ++s) {
+        g.table[s] = tables[s];
+        g.out[s] = outs[s];
+    }
     if (rows == 0)
-        hipLaunchKernelGGL((embed_fwd_wg_kernel<V>), dim3((unsigned)N, (unsigned)n), dim3(256), 0, st, g, ids, row_vecs, Vs, off);
+        hipLaunchKernelGGL((embed_fwd_wg_kernel<V, P>), dim3((unsigned)N, (unsigned)n), dim3(256), 0, st, g, ids, row_vecs, Vs, off);
     else
-        hipLaunchKernelGGL((embed_fwd_wave_kernel<V>), dim3((unsigned)ceil_div(N, rows), (unsigned)n), dim3(256), 0, st, g, ids, N,
-                           row_vecs, Vs, off, rows);
+        hipLaunchKernelGGL((embed_fwd_wave_kernel<V, P>), dim3((unsigned)ceil_div(N, rows), (unsigned)n), dim3(256), 0, st, g, ids,
+                           N, row_vecs, Vs, off, rows);
+}
+template <typename V>
+static void launch_embed_fwd_t(const void* const* tables, void* const* outs, int n, const int64_t* ids, int N, int row_vecs, int Vs,
+                               int64_t off, int rows, hipStream_t st) {
+    if (n == 1) launch_embed_fwd_p<V, 1>(tables, outs, n, ids, N, row_vecs, Vs, off, rows, st);
+    else launch_embed_fwd_p<V, EMBED_GROUP_MAX>(tables, outs, n, ids, N, row_vecs, Vs, off, rows, st);
 }
 
 hipError_t launch_embed_fwd(const void* const* tables, const int64_t* ids, int p, int N, int h, int Vs, int64_t off,
@@ -93,15 +112,10 @@ hipError_t launch_embed_fwd(const void* const* tables, const int64_t* ids, int p
     }
     for (int s0 = 0; s0 < p; s0 += EMBED_GROUP_MAX) {
         const int n = p - s0 < EMBED_GROUP_MAX ? p - s0 : EMBED_GROUP_MAX;
-        EmbedFwdGroup g{};
-        for (int s = 0; s < n; ++s) {
-            g.table[s] = tables[s0 + s];
-            g.out[s] = outs[s0 + s];
-        }
         const int64_t first = off + (int64_t)s0 * Vs;
-        if (vec) launch_embed_fwd_t<uintx4>(g, n, ids, N, (int)(row_bytes / 16), Vs, first, rows, st);
-        else if (elem_bytes == 4) launch_embed_fwd_t<unsigned>(g, n, ids, N, h, Vs, first, rows, st);
-        else launch_embed_fwd_t<u16>(g, n, ids, N, h, Vs, first, rows, st);
+        if (vec) launch_embed_fwd_t<uintx4>(tables + s0, outs + s0, n, ids, N, (int)(row_bytes / 16), Vs, first, rows, st);
+        else if (elem_bytes == 4) launch_embed_fwd_t<unsigned>(tables + s0, outs + s0, n, ids, N, h, Vs, first, rows, st);
+        else launch_embed_fwd_t<u16>(tables + s0, outs + s0, n, ids, N, h, Vs, first, rows, st);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
