@@ -22,8 +22,9 @@ struct EmbedFwdGroup {
     const void* table[P];
     void* out[P];
 };
+template <int P>
 struct EmbedBwdGroup {
-    float* dtable[EMBED_GROUP_MAX];
+    float* dtable[P];
 };
 
 // ------------------------------------------------------------------------- forward
@@ -524,28 +525,18 @@ __device__ __forceinline__ void sum_long_run(int len, float* d, bool active, int
     }
 }
 
-// Row of the group -> row of its shard's table gradient.  One shard (known to the host, so the same for the launch) needs
-// neither the division nor the read of the argument block that hangs on it, both in the chain of latencies that a turn of
-// the short runs is: 6958 uniform tokens, h = 3664, bf16, one shard: 83.5 us with both, 78.4 without; 8192 Zipf-like tokens, h = 4096: 84.7 and 81.9.
-__device__ __forceinline__ float* dtable_row(const EmbedBwdGroup& g, unsigned row, unsigned Vs, int h, bool one) {
-    if (one) return g.dtable[0] + (size_t)row * h;
+// Row of the group -> row of its shard's table gradient.  One shard needs neither the division nor the read of the argument
+// block that hangs on it, both in the chain of latencies that a turn of the short runs is: 6958 uniform tokens, h = 3664,
+// bf16, one shard: 80.7 us with both, 77.0 without; 8192 Zipf-like tokens, h = 4096: 85.1 and 79.5.
+template <int P>
+__device__ __forceinline__ float* dtable_row(const EmbedBwdGroup<P>& g, unsigned row, unsigned Vs, int h) {
+    if constexpr (P == 1) return g.dtable[0] + (size_t)row * h;
     const unsigned s = row / Vs;
     return g.dtable[s] + (size_t)(row - s * Vs) * h;
 }
-// (one branch for all runs of a turn: with one per run their LDS reads would wait for one another)
-__device__ __forceinline__ void dtable_rows(float* (&d)[SHORT_Q], const EmbedBwdGroup& g, const unsigned (&row)[SHORT_Q],
-                                            unsigned Vs, int h, int c0, bool one) {
-    if (one) {
-#pragma unroll
-        for (int q = 0; q < SHORT_Q; ++q) d[q] = dtable_row(g, row[q], Vs, h, true) + c0;
-    } else {
-#pragma unroll
-        for (int q = 0; q < SHORT_Q; ++q) d[q] = dtable_row(g, row[q], Vs, h, false) + c0;
-    }
-}
 
-template <typename T, int VEC>
-__global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(EmbedBwdGroup g, const int64_t* __restrict__ ids,
+template <typename T, int VEC, int P>
+__global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(EmbedBwdGroup<P> g, const int64_t* __restrict__ ids,
                                                                         int N, int Vs, int n_rows, int64_t off,
                                                                         const T* __restrict__ gout,
                                                                         unsigned grad_bytes, int h, int n_slabs,
@@ -660,7 +651,6 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(EmbedBwd
     }
 
     const int slab = blockIdx.x % n_slabs, group = blockIdx.x / n_slabs;
-    const bool one = n_rows == Vs;
     const bool active = (slab * 64 + lane) * VEC < h;
     const int c0 = active ? (slab * 64 + lane) * VEC : 0;
     const unsigned row_bytes = (unsigned)h * (unsigned)sizeof(T);
@@ -688,7 +678,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(EmbedBwd
             tok[q] = lane < len[q] ? key_token(sh[s + lane]) : 0u;
             row[q] = __builtin_amdgcn_readfirstlane(key_row(sh[s]));
         }
-        dtable_rows(d, g, row, (unsigned)Vs, h, c0, one);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) d[q] = dtable_row(g, row[q], (unsigned)Vs, h) + c0;
         sum_short_runs<T, VEC>(len, tok, d, active, rows);
     }
     // mid runs: the wavefront looks through its run numbers 64 at a time (a loop of its own: kept over the one above, the
@@ -707,7 +698,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(EmbedBwd
                 todo &= todo - 1;
                 const int s = __builtin_amdgcn_readfirstlane((int)run_start[r]);
                 const int len = __builtin_amdgcn_readfirstlane((int)run_start[r + 1]) - s;
-                float* const d = dtable_row(g, __builtin_amdgcn_readfirstlane(key_row(sh[s])), (unsigned)Vs, h, one) + c0;
+                float* const d = dtable_row(g, __builtin_amdgcn_readfirstlane(key_row(sh[s])), (unsigned)Vs, h) + c0;
                 sum_mid_run<T, VEC>(len, d, active, lane, rows, [&](int j) { return key_token(sh[s + j]); });
             }
         }
@@ -724,7 +715,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(EmbedBwd
             todo &= todo - 1;
             const int s = __builtin_amdgcn_readfirstlane((int)run_start[r]);
             const int len = __builtin_amdgcn_readfirstlane((int)run_start[r + 1]) - s;
-            float* const d = dtable_row(g, __builtin_amdgcn_readfirstlane(key_row(sh[s])), (unsigned)Vs, h, one) + c0;
+            float* const d = dtable_row(g, __builtin_amdgcn_readfirstlane(key_row(sh[s])), (unsigned)Vs, h) + c0;
             sum_long_run<T, VEC>(len, d, active, lane, wave, xchg, rows,
                                  [&](int j) { return key_token(sh[s + j]); });
         }
@@ -865,10 +856,10 @@ __global__ __launch_bounds__(256) void embed_find_runs_kernel(const u64* __restr
 }
 
 // Workgroup (slab, any): 64 * VEC columns.
-template <typename T, int VEC>
-__global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwdGroup g, const u64* __restrict__ keys, int n,
+template <typename T, int VEC, int P>
+__global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwdGroup<P> g, const u64* __restrict__ keys, int n,
                                                                         RunLists runs, const T* __restrict__ gout, int h,
-                                                                        int Vs, bool one, int n_slabs) {
+                                                                        int Vs, int n_slabs) {
     typedef typename FusedVec<T, VEC>::type GV;
     constexpr int B = FusedVec<T, VEC>::BATCH, Q = SHORT_Q;
     __shared__ float xchg[64 * VEC];
@@ -891,7 +882,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwd
         const int s = __builtin_amdgcn_readfirstlane((int)(unsigned)run);
         const int len = __builtin_amdgcn_readfirstlane((int)(run >> 32));
         const unsigned row = __builtin_amdgcn_readfirstlane((unsigned)(keys[s] >> 32));
-        float* const d = dtable_row(g, row, (unsigned)Vs, h, one) + c0;
+        float* const d = dtable_row(g, row, (unsigned)Vs, h) + c0;
         sum_long_run<T, VEC>(len, d, active, lane, wave, xchg, rows,
                              [&](int j) { return (unsigned)keys[s + j]; });
     }
@@ -915,7 +906,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwd
             len += c;
             if (c < 64) break;
         }
-        sum_mid_run<T, VEC>(len, dtable_row(g, row, (unsigned)Vs, h, one) + c0, active, lane, rows,
+        sum_mid_run<T, VEC>(len, dtable_row(g, row, (unsigned)Vs, h) + c0, active, lane, rows,
                             [&](int j) { return (unsigned)keys[s + j]; });
         at = __builtin_amdgcn_readfirstlane(at_next);
     }
@@ -947,7 +938,8 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwd
                 tok[q] = (unsigned)key[q];
                 len[q] = at + q0 + q < n_short ? __builtin_ctzll(~m) : 0;
             }
-            dtable_rows(d, g, row, (unsigned)Vs, h, c0, one);
+#pragma unroll
+            for (int q = 0; q < Q; ++q) d[q] = dtable_row(g, row[q], (unsigned)Vs, h) + c0;
             sum_short_runs<T, VEC>(len, tok, d, active, rows);
         }
         at = __builtin_amdgcn_readfirstlane(at_next);
@@ -980,8 +972,8 @@ size_t embed_bwd_workspace(int64_t N, int64_t h, int64_t Vs, int elem_bytes) {
     return n * (8 + 8 + 4) + n / 16 * (8 + 4) + (3 + 3 * (size_t)ceil_div(h, 64)) * 4;
 }
 
-template <typename T, int VEC>
-static hipError_t launch_fused(const EmbedBwdGroup& g, const int64_t* ids, int N, int Vs, int n_rows, int64_t off, const T* gout,
+template <typename T, int VEC, int P>
+static hipError_t launch_fused(const EmbedBwdGroup<P>& g, const int64_t* ids, int N, int Vs, int n_rows, int64_t off, const T* gout,
                                int h, hipStream_t st) {
     ProfScope prof(K_EMBED_ACCUM, st);
     const int n_slabs = (int)ceil_div(h, 64 * VEC);
@@ -990,13 +982,13 @@ static hipError_t launch_fused(const EmbedBwdGroup& g, const int64_t* ids, int N
     if (n_groups > want) n_groups = want;
     if (n_groups < 1) n_groups = 1;
     const unsigned grad_bytes = (unsigned)((size_t)N * h * sizeof(T));
-    hipLaunchKernelGGL((embed_bwd_fused_kernel<T, VEC>), dim3((unsigned)(n_slabs * n_groups)), dim3(FUSED_THREADS), 0, st, g, ids,
+    hipLaunchKernelGGL((embed_bwd_fused_kernel<T, VEC, P>), dim3((unsigned)(n_slabs * n_groups)), dim3(FUSED_THREADS), 0, st, g, ids,
                        N, Vs, n_rows, off, gout, grad_bytes, h, n_slabs, n_groups);
     return hipGetLastError();
 }
 
-template <typename T, int VEC>
-static hipError_t launch_general(const EmbedBwdGroup& g, const int64_t* ids, int N, int Vs, int n_rows, int64_t off,
+template <typename T, int VEC, int P>
+static hipError_t launch_general(const EmbedBwdGroup<P>& g, const int64_t* ids, int N, int Vs, int n_rows, int64_t off,
                                  const T* gout, int h, void* ws, hipStream_t st) {
     const int n = (int)padded_tokens(N);
     const int n_slabs = (int)ceil_div(h, 64 * VEC);
@@ -1028,9 +1020,18 @@ static hipError_t launch_general(const EmbedBwdGroup& g, const int64_t* ids, int
     const int want = (int)ceil_div(N, 64);
     if (n_groups > want) n_groups = want;
     if (n_groups < 1) n_groups = 1;
-    hipLaunchKernelGGL((embed_bwd_accum_kernel<T, VEC>), dim3((unsigned)(n_slabs * n_groups)), dim3(FUSED_THREADS), 0, st, g, a,
-                       n, runs, gout, h, Vs, n_rows == Vs, n_slabs);
+    hipLaunchKernelGGL((embed_bwd_accum_kernel<T, VEC, P>), dim3((unsigned)(n_slabs * n_groups)), dim3(FUSED_THREADS), 0, st, g, a,
+                       n, runs, gout, h, Vs, n_slabs);
     return hipGetLastError();
+}
+
+template <typename T, int VEC, int P>
+static hipError_t launch_bwd_part(float* const* dtables, const int64_t* ids, int n, int N, int Vs, int64_t off, const T* gout, int h,
+                                  bool fused, void* ws, hipStream_t st) {
+    EmbedBwdGroup<P> g{};
+    for (int s = 0; s < n; ++s) g.dtable[s] = dtables[s];
+    return fused ? launch_fused<T, VEC, P>(g, ids, N, Vs, n * Vs, off, gout, h, st)
+                 : launch_general<T, VEC, P>(g, ids, N, Vs, n * Vs, off, gout, h, ws, st);
 }
 
 template <typename T, int VEC>
@@ -1042,11 +1043,10 @@ static hipError_t launch_bwd_group(float* const* dtables, const int64_t* ids, in
     if (per > EMBED_GROUP_MAX) per = EMBED_GROUP_MAX;
     for (int s0 = 0; s0 < p; s0 += per) {
         const int n = p - s0 < per ? p - s0 : per;
-        EmbedBwdGroup g{};
-        for (int s = 0; s < n; ++s) g.dtable[s] = dtables[s0 + s];
         const int64_t first = off + (int64_t)s0 * Vs;
-        const hipError_t e = fused ? launch_fused<T, VEC>(g, ids, N, Vs, n * Vs, first, gout, h, st)
-                                   : launch_general<T, VEC>(g, ids, N, Vs, n * Vs, first, gout, h, ws, st);
+        const hipError_t e =
+            n == 1 ? launch_bwd_part<T, VEC, 1>(dtables + s0, ids, n, N, Vs, first, gout, h, fused, ws, st)
+                   : launch_bwd_part<T, VEC, EMBED_GROUP_MAX>(dtables + s0, ids, n, N, Vs, first, gout, h, fused, ws, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
