@@ -731,21 +731,21 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(EmbedBwd
 //      MERGE_WAYS of them cost the time of one).  One pass up to 32768 tokens, two up to 2^19, ...
 //   3. embed_find_runs: where runs of equal rows start, in three lists: up to `batch` tokens, up to MID_BATCHES times
 //      that, and above (with the length).
-//   4. embed_bwd_accum: the sums; workgroups of a column slab draw runs from the lists, the long ones first.
+//   4. embed_bwd_accum: the sums; the workgroups of a column slab share the runs of the lists out, the long ones first.
 // Bound by gradient and table rows in step 4; steps 1 to 3 are latency.  Measured for 32768 Zipf tokens, h = 4096, bf16,
 // 8 shards of 16032 rows: 9 + 19 + 7 + 200 us (0.6 GB).  A sort and an accumulation per shard (16384-key bitonic chunks,
 // one workgroup per long run) took 8 x 213 us.
 constexpr int SORT_CHUNK = 2048, CHUNK_BITS = 11, MERGE_WAYS = 16;
 constexpr int MAX_GROUP_ROWS = (1 << (32 - CHUNK_BITS)) - 1;      // rows of a group: no key equals KEY32_NONE
 constexpr unsigned NO_ROW = 0xFFFFFFFFu;
-constexpr int DRAW = 16;                                          // short runs a wavefront draws at a time
+constexpr unsigned MAX_SHORT = 16;                                // short runs of a wavefront in one share
 
 struct RunLists {
     u64* longs;           // length << 32 | start position
     unsigned* shorts;     // start positions
     unsigned* mids;       // start positions
     unsigned* count;      // [3]: shorts, mids, longs
-    unsigned* next;       // [3 * n_slabs]: next short, mid, long run of a slab
+    unsigned* next;       // [3 * n_slabs]: what has been drawn of the short, mid, long runs beyond the first shares, per slab
 };
 
 __global__ __launch_bounds__(FUSED_THREADS) void embed_sort_chunks_kernel(const int64_t* __restrict__ ids, int N, int n_rows,
@@ -855,7 +855,12 @@ __global__ __launch_bounds__(256) void embed_find_runs_kernel(const u64* __restr
     }
 }
 
-// Workgroup (slab, any): 64 * VEC columns.
+// Workgroup (slab, group): 64 * VEC columns.  A draw from a counter that all XCDs add to takes about 50 ns of that counter's
+// time, so that a draw per wavefront and list took longer than the sums where a row is few slabs and a slab many
+// workgroups.  So a workgroup draws for its 16 wavefronts, its first share of every list is fixed, and without long runs
+// (which are what makes workgroups late) all shares are.  us of this kernel, a draw per wavefront -> so: 12000 uniform tokens,
+// h = 512, V = 50000, bf16: 150 -> 16; 60000, 1024, 32000: 257 -> 76; 8193 skewed tokens, h = 256: 127 -> 18; 16384 of which
+// the shard owns 2048, h = 1024: 101 -> 9.6; 32768 Zipf tokens, h = 4096, 8 shards (with steps 1 to 3): 230 -> 170.
 template <typename T, int VEC, int P>
 __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwdGroup<P> g, const u64* __restrict__ keys, int n,
                                                                         RunLists runs, const T* __restrict__ gout, int h,
@@ -866,18 +871,27 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwd
     __shared__ unsigned s_next;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int slab = blockIdx.x % n_slabs;
+    const int slab = blockIdx.x % n_slabs, group = blockIdx.x / n_slabs;
+    const unsigned n_groups = gridDim.x / n_slabs;
     const bool active = (slab * 64 + lane) * VEC < h;
     const int c0 = active ? (slab * 64 + lane) * VEC : 0;
     const PointerRows<GV> rows{(const char*)gout, (unsigned)c0 * (unsigned)sizeof(T), (size_t)h * sizeof(T)};
     const unsigned n_short = runs.count[0], n_mid = runs.count[1], n_long = runs.count[2];
 
-    for (;;) {
+    // Thread 0 draws for the workgroup (start_draw; the others do nothing), all learn the result (end_draw).  (The address is
+    // one that the compiler takes for a different one per lane: it would otherwise wait for the result on the spot.)
+    auto start_draw = [&](unsigned* counter, unsigned n) {
+        asm volatile("" : "+v"(counter));
+        return threadIdx.x == 0 ? atomicAdd(counter, n) : 0u;
+    };
+    auto end_draw = [&](unsigned drawn) {
         __syncthreads();
-        if (threadIdx.x == 0) s_next = atomicAdd(runs.next + 2 * n_slabs + slab, 1u);
+        if (threadIdx.x == 0) s_next = drawn;
         __syncthreads();
-        const unsigned r = __builtin_amdgcn_readfirstlane(s_next);
-        if (r >= n_long) break;
+        return (unsigned)__builtin_amdgcn_readfirstlane(s_next);
+    };
+
+    for (unsigned r = group; r < n_long;) {
         const u64 run = runs.longs[r];
         const int s = __builtin_amdgcn_readfirstlane((int)(unsigned)run);
         const int len = __builtin_amdgcn_readfirstlane((int)(run >> 32));
@@ -885,18 +899,29 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwd
         float* const d = dtable_row(g, row, (unsigned)Vs, h) + c0;
         sum_long_run<T, VEC>(len, d, active, lane, wave, xchg, rows,
                              [&](int j) { return (unsigned)keys[s + j]; });
+        if (n_long <= n_groups) break;
+        r = n_groups + end_draw(start_draw(runs.next + 2 * n_slabs + slab, 1u));
     }
 
-    // (an address the compiler takes for a different one per lane: it would otherwise wait for the result on the spot)
-    unsigned* next = runs.next + n_slabs + slab;
-    asm volatile("" : "+v"(next));
-    unsigned at = 0;
-    if (lane == 0) at = atomicAdd(next, 1u);
-    at = __builtin_amdgcn_readfirstlane(at);
-    while (at < n_mid) {
-        unsigned at_next = 0;                    // the next draw is under way while these are summed
-        if (lane == 0) at_next = atomicAdd(next, 1u);
-        const int s = __builtin_amdgcn_readfirstlane((int)runs.mids[at]);
+    // Workgroup `worker` begins with share `worker` of the mid and of the short runs.  Those that have just had a long run are
+    // left out, if they are less than half.  No long runs: the shares that follow are fixed as well; else they are drawn.
+    const unsigned busy = 2 * n_long < n_groups ? n_long : 0u, workers = n_groups - busy;
+    const bool fixed = n_long == 0;
+    auto shares = [&](unsigned n, unsigned share, unsigned* counter, const auto& sum_share) {
+        const unsigned drawn_from = workers * share;         // what is beyond the first shares
+        const bool draws = !fixed && drawn_from < n;
+        unsigned at = (unsigned)group >= busy ? (group - busy) * share
+                                              : draws ? drawn_from + end_draw(start_draw(counter, share)) : n;
+        while (at < n) {
+            const unsigned drawn = draws ? start_draw(counter, share) : 0u;     // (under way while this share is summed)
+            sum_share(at);
+            at = fixed ? at + drawn_from : draws ? drawn_from + end_draw(drawn) : n;
+        }
+    };
+
+    shares(n_mid, FUSED_WAVES, runs.next + n_slabs + slab, [&](unsigned at) {
+        if (at + wave >= n_mid) return;
+        const int s = __builtin_amdgcn_readfirstlane((int)runs.mids[at + wave]);
         const unsigned row = __builtin_amdgcn_readfirstlane((unsigned)(keys[s] >> 32));
         int len = 0;
         for (;;) {
@@ -908,27 +933,24 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwd
         }
         sum_mid_run<T, VEC>(len, dtable_row(g, row, (unsigned)Vs, h) + c0, active, lane, rows,
                             [&](int j) { return (unsigned)keys[s + j]; });
-        at = __builtin_amdgcn_readfirstlane(at_next);
-    }
+    });
 
-    next = runs.next + slab;
-    asm volatile("" : "+v"(next));
-    at = 0;
-    if (lane == 0) at = atomicAdd(next, (unsigned)DRAW);
-    at = __builtin_amdgcn_readfirstlane(at);
-    while (at < n_short) {
-        unsigned at_next = 0;
-        if (lane == 0) at_next = atomicAdd(next, (unsigned)DRAW);
-        const unsigned starts = lane < DRAW && at + lane < n_short ? runs.shorts[at + lane] : 0u;
+    // short runs per wavefront and share: all of them in one share each if that is no more than MAX_SHORT
+    unsigned per_wave = (n_short + workers * FUSED_WAVES - 1) / (workers * FUSED_WAVES);
+    per_wave = per_wave > MAX_SHORT ? MAX_SHORT : (per_wave + Q - 1) / Q * Q;
+    per_wave = per_wave < Q ? Q : per_wave;
+    shares(n_short, per_wave * FUSED_WAVES, runs.next + slab, [&](unsigned at) {
+        const unsigned first = at + wave * per_wave;
+        const unsigned starts = lane < (int)per_wave && first + lane < n_short ? runs.shorts[first + lane] : 0u;
 #pragma unroll 1
-        for (int q0 = 0; q0 < DRAW && at + q0 < n_short; q0 += Q) {
+        for (unsigned q0 = 0; q0 < per_wave && first + q0 < n_short; q0 += Q) {
             u64 key[Q];
             int len[Q];
             unsigned tok[Q], row[Q];
             float* d[Q];
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
-                const int s = __builtin_amdgcn_readlane((int)starts, q0 + q);
+                const int s = __builtin_amdgcn_readlane((int)starts, (int)q0 + q);
                 key[q] = s + lane < n && lane <= B ? keys[s + lane] : ~0ull;
             }
 #pragma unroll
@@ -936,14 +958,13 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwd
                 row[q] = __builtin_amdgcn_readfirstlane((unsigned)(key[q] >> 32));
                 const u64 m = __builtin_amdgcn_ballot_w64((unsigned)(key[q] >> 32) == row[q]);
                 tok[q] = (unsigned)key[q];
-                len[q] = at + q0 + q < n_short ? __builtin_ctzll(~m) : 0;
+                len[q] = first + q0 + q < n_short ? __builtin_ctzll(~m) : 0;
             }
 #pragma unroll
             for (int q = 0; q < Q; ++q) d[q] = dtable_row(g, row[q], (unsigned)Vs, h) + c0;
             sum_short_runs<T, VEC>(len, tok, d, active, rows);
         }
-        at = __builtin_amdgcn_readfirstlane(at_next);
-    }
+    });
 }
 
 static int compute_units() {

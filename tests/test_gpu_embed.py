@@ -207,3 +207,26 @@ def test_embed_runs_of_a_middle_length(N, h, rows, per_row, p, dtype):
     assert np.bincount(ids).max() >= per_row
     print("embed runs", (N, h, rows, per_row, p, dtype), flush=True)
     check_embed(N, h, V, p, dtype, seed=600 + N, ids=ids, preload=True)
+
+
+@pytest.mark.parametrize("h", [64, 1026])                   # one slab, 256 workgroups of it; nine slabs
+@pytest.mark.parametrize("kind", ["none owned", "unique", "one long", "many long", "many mid", "mixed"])
+@pytest.mark.parametrize("p", [1, 3])
+def test_embed_general_path_shares(kind, p, h):
+    # more than 8192 tokens: how the runs are shared out depends on whether there are long ones, and on how many of each
+    N, V = 9001, 12000
+    if kind == "none owned":
+        ids = np.full(N, V + 7, dtype=np.int64)
+    elif kind == "unique":
+        ids = np.arange(N, dtype=np.int64) + 1500
+    elif kind == "one long":
+        ids = np.arange(N, dtype=np.int64)
+        ids[::5] = 17
+    elif kind == "many long":
+        ids = np.arange(N, dtype=np.int64) % 30
+    elif kind == "many mid":
+        ids = np.arange(N, dtype=np.int64) % 150
+    else:
+        ids = si.zipf_ids(N, V, 1.1, 700)
+    print("embed shares", kind, p, h, flush=True)
+    check_embed(N, h, V, p, "bf16", seed=700, ids=ids, preload=True)
