@@ -733,7 +733,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(EmbedBwd
 //      that, and above (with the length).
 //   4. embed_bwd_accum: the sums; the workgroups of a column slab share the runs of the lists out, the long ones first.
 // Bound by gradient and table rows in step 4; steps 1 to 3 are latency.  Measured for 32768 Zipf tokens, h = 4096, bf16,
-// 8 shards of 16032 rows: 9 + 19 + 7 + 200 us (0.6 GB).  A sort and an accumulation per shard (16384-key bitonic chunks,
+// 8 shards of 16032 rows: 9 + 19 + 7 + 144 us (0.5 GB).  A sort and an accumulation per shard (16384-key bitonic chunks,
 // one workgroup per long run) took 8 x 213 us.
 constexpr int SORT_CHUNK = 2048, CHUNK_BITS = 11, MERGE_WAYS = 16;
 constexpr int MAX_GROUP_ROWS = (1 << (32 - CHUNK_BITS)) - 1;      // rows of a group: no key equals KEY32_NONE
@@ -860,7 +860,7 @@ __global__ __launch_bounds__(256) void embed_find_runs_kernel(const u64* __restr
 // workgroups.  So a workgroup draws for its 16 wavefronts, its first share of every list is fixed, and without long runs
 // (which are what makes workgroups late) all shares are.  us of this kernel, a draw per wavefront -> so: 12000 uniform tokens,
 // h = 512, V = 50000, bf16: 150 -> 16; 60000, 1024, 32000: 257 -> 76; 8193 skewed tokens, h = 256: 127 -> 18; 16384 of which
-// the shard owns 2048, h = 1024: 101 -> 9.6; 32768 Zipf tokens, h = 4096, 8 shards (with steps 1 to 3): 230 -> 170.
+// the shard owns 2048, h = 1024: 101 -> 9.6; 32768 Zipf tokens, h = 4096, 8 shards: 196 -> 144.
 template <typename T, int VEC, int P>
 __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwdGroup<P> g, const u64* __restrict__ keys, int n,
                                                                         RunLists runs, const T* __restrict__ gout, int h,

@@ -131,15 +131,16 @@ class OutputLayerPlan:
             stream = torch.cuda.ExternalStream(int(stream))
         return torch.cuda.stream(stream)
 
+    # A view is made only of a shard with padding, and without a call per shard: on small workloads the host's work is what
+    # bounds a step.
     def _real(self, tensors, r):
-        """The real rows of shard r (a view is made only of a shard with padding: on small workloads the host's work is
-        what bounds a step)."""
+        """The real rows of shard r."""
         t, v = tensors[r], self.valid[r]
         return t if t.shape[0] == v else t[:v]
 
     def _live(self, tensors):
         """The real rows of the shards that have any."""
-        return [self._real(tensors, r) for r in range(self.live)]
+        return [t if t.shape[0] == v else t[:v] for t, v in zip(tensors, self.valid[:self.live])]
 
     def forward(self, stream=None) -> None:
         for r in range(self.live if self.algorithm == 1 and self.grouped else 0, self.p):
