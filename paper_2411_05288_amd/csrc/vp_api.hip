@@ -36,7 +36,9 @@ size_t max3(size_t a, size_t b, size_t c) { return a > b ? (a > c ? a : c) : (b 
 // fp32 path: bytes of K-slice scratch behind the [N, Vs] matrix at the start of the workspace
 size_t f32_fwd_scratch(int64_t N, int64_t h, int64_t Vs) { return gemm_f32_scratch_floats(N, Vs, h) * sizeof(float); }
 size_t f32_bwd_scratch(int64_t N, int64_t h, int64_t Vs) {
-    return max3(gemm_f32_scratch_floats(N, Vs, h), gemm_f32_scratch_floats(N, h, Vs), gemm_f32_scratch_floats(Vs, h, N)) *
+    const int dh = gemm_f32_dh_slices(N, h, Vs, 1);
+    return max3(gemm_f32_scratch_floats(N, Vs, h), dh > 1 ? (size_t)dh * (size_t)N * (size_t)h : 0,
+                gemm_f32_scratch_floats(Vs, h, N)) *
            sizeof(float);
 }
 size_t f32_matrix_bytes(int64_t N, int64_t Vs) { return align_up((size_t)N * Vs * sizeof(float), 256); }

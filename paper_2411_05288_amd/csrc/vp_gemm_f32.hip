@@ -1,25 +1,28 @@
-// fp32 path of the output layer: fp32 products on the matrix cores (v_mfma_f32_32x32x2_f32: fp32
-// operands, fp32 products and accumulation) with arbitrary operand layouts.  It serves the three
+// fp32 path of the output layer: fp32 products on the bf16 matrix cores, with arbitrary operand layouts.  It serves the three
 // products of section 4.2 for fp32 storage:  Y = X W^T,  dX += D W,  dW = D^T X.
 //
-// C[m, n] (+)= sum_k A(m, k) * B(n, k), each operand stored K-contiguous ([rows][K]) or K-strided
-// ([K][rows]).
+// C[m, n] (+)= sum_k A(m, k) * B(n, k), each operand stored K-contiguous ([rows][K]) or K-strided ([K][rows]).
 //
-// What bounds it: the fp32 matrix rate (157 TFLOP/s dense; one MFMA keeps a SIMD's matrix core busy
-// for 64 cycles and needs one operand register per side, so LDS and load traffic are light).  A
-// vector-ALU version of this kernel (64 x 64 tiles, no double buffering) took 411 us per product of
-// N=1000, h=1024, Vs=4000 (20 TFLOP/s); this one takes 88 us on the outputs of 256 tiles of 128 x 128
-// (one workgroup per compute unit, 94 TFLOP/s) and 120 us on the 1000 x 1024 output.
+// What bounds it: the matrix cores.  v_mfma_f32_32x32x2_f32 gives 157 TFLOP/s, the bf16 instruction sixteen times as much, so
+// every operand is split exactly into three bf16 parts, x = x0 + x1 + x2 (8 significant bits each, 24 together), and of
+// the nine products of parts the six down to 2^-18 of the whole are summed in fp32 accumulators: x0 y0, x0 y1, x1 y0, x1 y1,
+// x0 y2, x2 y0.  What is left out is below 2^-26 of a product, a quarter of the rounding of one fp32 addition; and one bf16 MFMA
+// adds 16 products at once, so that a sum is rounded six times per 16 k instead of eight.  Error of the results against float64
+// (2-norm, relative; fp32 MFMA -> this kernel): N=1000 h=1024 V=32000 p=8: logits 5.7e-7 -> 4.9e-7, dH 1.1e-6 -> 5.0e-7, dW
+// 5.7e-7 -> 3.6e-7; N=128 h=256 V=8192: 2.9e-7 -> 2.4e-7, 2.1e-7 -> 1.9e-7, 2.0e-7 -> 1.4e-7; N=2000 h=2048 V=8000: 8.1e-7 ->
+// 7.0e-7, 1.1e-6 -> 5.0e-7, 8.0e-7 -> 5.1e-7.  Time of a product at the first of these sizes: 520-560 us -> 330-350 us
+// (200 TFLOP/s of fp32 work, 1.2 PFLOP/s of the matrix cores'); whole step 1700 -> 1100 us.
 //
-// Workgroup: 4 wavefronts (2 x 2) on a TM x TN tile, TM = TN = 128 (64 x 64 per wavefront) or 64.
-// K advances 32 at a time through two LDS stages; the global loads of step k + 1 are in flight in
-// registers while step k is multiplied (4096 cycles at 128 x 128), one barrier per step; two
-// workgroups share a compute unit and fill each other's barriers.
+// Workgroup: 4 wavefronts (2 x 2) on tiles of 256 x 128 (dW: vocabulary rows first) or 128 x 256 (tokens first), 128 x 128 or
+// 64 x 64.  Operands go global -> registers (fp32) -> split -> LDS (three bf16 planes), K advances 16 (small tiles: 32) at a
+// time through two LDS stages with one barrier each: while stage q is multiplied, stage q + 1 is split between its products
+// (about 6 vector instructions per value, which issue while the matrix cores work; left to the compiler they came in
+// one block, 363 instead of 328 us) and stage q + 2 is on its way into the freed registers.  Two workgroups of the large
+// tiles (three of the others) share a compute unit and fill each other's barriers.  The split happens once per workgroup and
+// value: with every wavefront splitting what it loads, without LDS, small launches took as long and large ones 1.3 times.
 //
-// LDS: K-contiguous tile [rows][32 + 4]: one ds_read_b128 gives four k of one row, and lanes 32-63
-// take the next four, so MFMA step j of a group multiplies k = j and k = 4 + j (the order of the k
-// does not matter as long as both operands use it).  K-strided tile [32][rows + 8]: one ds_read_b32
-// per step; 4 * (rows + 8) words are 32 banks apart, so both lane halves fall into different banks.
+// LDS planes: K-contiguous tile [rows][16 or 32 k], one ds_read_b128 per MFMA operand; K-strided tile [k][rows], two
+// transposing reads (ds_read_b64_tr_b16) per operand.
 //
 // Small outputs with a long K (dX of the tiny configuration: 128 x 256 outputs, K = 4096) would
 // occupy a handful of compute units.  With scratch memory the K range is cut into S slices
@@ -32,12 +35,21 @@
 namespace vp {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short short4v __attribute__((ext_vector_type(4)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
-constexpr int FK = 32;             // K step
+// D is scaled by this before it is split and the sums by its inverse (exact): |D| is at most the gradient's scale, and
+// without it the lowest parts of softmax values below 2^-110 would be lost in bf16's smallest numbers.
+constexpr float D_SCALE = 0x1p64f;
+
+__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
+    const __bf16 a = (__bf16)lo, b = (__bf16)hi;   // round to nearest even
+    return (unsigned)__builtin_bit_cast(u16, a) | ((unsigned)__builtin_bit_cast(u16, b) << 16);
+}
+
 constexpr int F_THREADS = 256;
-constexpr unsigned F_OOB = 0x80000000u;   // beyond every buffer descriptor below (each covers at most 2^29 bytes)
+constexpr unsigned F_OOB = 0x80000000u;   // beyond every buffer descriptor below (each covers at most 2^30 bytes)
 
 struct GemmF32Params {
     const float* A;
@@ -57,82 +69,107 @@ struct GemmF32Params {
     GemmF32Shard sh[GEMM_GROUP_MAX];
 };
 
-template <bool KC, int ROWS>
+// One operand's part of a tile: ROWS rows by SK of the K dimension.
+template <bool KC, int ROWS, int SK>
 struct F32Tile {
-    static constexpr int RS = KC ? FK + 4 : ROWS + 8;                // row stride in floats
-    static constexpr int FLOATS = KC ? ROWS * RS : FK * RS;
-    static constexpr int CHUNKS = ROWS * FK / 4 / F_THREADS;         // 16-byte chunks per thread
+    static constexpr int RB = KC ? 2 * SK : 2 * ROWS;                // bytes per stored row of a plane
+    static constexpr int PLANE = 2 * ROWS * SK;                      // bytes per bf16 plane; three planes
+    static constexpr int CHUNKS = ROWS * SK / 4 / F_THREADS;         // 16-byte chunks of fp32 per thread
+    static constexpr int CPR = KC ? SK / 4 : ROWS / 4;               // chunks per stored row
+
+    // K-contiguous: position of the 16-byte chunk c (eight k) of row r within its row of SK * 2 bytes, so that the 16 rows
+    // that a pass of ds_read_b128 serves fall into different banks
+    static __device__ __forceinline__ int chunk_at(int r, int c) { return SK == 16 ? c ^ ((r >> 3) & 1) : SK == 32 ? c ^ ((r >> 2) & 3) : c ^ ((r >> 1) & 7); }
+    // K-strided: position of the 32-byte segment s (16 rows) of k-row k, so that the four k-rows by two segments that a
+    // pass of the transposing read serves fall into different banks
+    static __device__ __forceinline__ int seg_at(int k, int s) {
+        return ROWS == 64 ? s ^ (k & 2) : s ^ ((k & 3) ^ ((k & 1) << 2));
+    }
 };
 
-template <bool KC, int ROWS>
-using F32Chunks = uintx4[F32Tile<KC, ROWS>::CHUNKS];
-
-// Global -> registers for one ROWS x FK operand tile.  Out-of-range elements come back as zeros: the
+// Global -> registers for chunk i of this thread of one operand's ROWS x SK.  Out-of-range elements come back as zeros: the
 // descriptor covers exactly the rows of this tile that exist (K-contiguous) or the k-rows that exist
 // (K-strided), and elements past the end of a K-contiguous row get an offset beyond it.  (Rows past the
-// end of a K-strided operand read the neighbouring k-row: finite values for outputs never stored.)
-template <bool KC, int ROWS>
-__device__ __forceinline__ void f32_load(F32Chunks<KC, ROWS>& r, const float* p, int64_t ld, int r0,
-                                         int k0, int rows, int k_end, int vec, int tid) {
-    constexpr int CPR = KC ? FK / 4 : ROWS / 4;     // chunks per stored row of the tile
+// end of a K-strided operand read the neighbouring k-row: values for outputs never stored.)
+template <bool KC, int ROWS, int SK, bool VEC>
+__device__ __forceinline__ uintx4 f32_load(const float* p, int64_t ld, int r0, int k0, int rows, int k_end, int tid, int i) {
+    typedef F32Tile<KC, ROWS, SK> T;
     const float* base = KC ? p + (int64_t)r0 * ld + k0 : p + (int64_t)k0 * ld + r0;
     const int left = KC ? rows - r0 : k_end - k0;   // stored rows that exist from here on
-    const int have = left < 0 ? 0 : (left < (KC ? ROWS : FK) ? left : (KC ? ROWS : FK));
+    const int have = left < 0 ? 0 : (left < (KC ? ROWS : SK) ? left : (KC ? ROWS : SK));
     // bytes from `base` to the end of the last existing stored row
     const int64_t in_row = KC ? (int64_t)k_end - k0 : (int64_t)rows - r0;
     const int64_t bytes = have > 0 && in_row > 0 ? (((int64_t)have - 1) * ld + in_row) * 4 : 0;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000);
+    const int q = tid + F_THREADS * i;
+    const int row = q / T::CPR, c = (q % T::CPR) * 4;
+    const unsigned off = ((unsigned)row * (unsigned)ld + (unsigned)c) * 4u;
+    uintx4 r;
+    if (VEC) {
+        r = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(KC && k0 + c >= k_end ? F_OOB : off), 0, 0);
+    } else {
 #pragma unroll
-    for (int i = 0; i < F32Tile<KC, ROWS>::CHUNKS; ++i) {
-        const int q = tid + F_THREADS * i;
-        const int row = q / CPR, c = (q % CPR) * 4;
-        const unsigned off = ((unsigned)row * (unsigned)ld + (unsigned)c) * 4u;
-        if (vec) {
-            r[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(KC && k0 + c >= k_end ? F_OOB : off), 0, 0);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                r[i][e] = __builtin_amdgcn_raw_buffer_load_b32(
-                    rs, (int)(KC && k0 + c + e >= k_end ? F_OOB : off + 4u * e), 0, 0);
-        }
+        for (int e = 0; e < 4; ++e)
+            r[e] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(KC && k0 + c + e >= k_end ? F_OOB : off + 4u * e), 0, 0);
     }
+    return r;
 }
 
-template <bool KC, int ROWS>
-__device__ __forceinline__ void f32_store(const F32Chunks<KC, ROWS>& r, float* s, int tid) {
-    constexpr int CPR = KC ? FK / 4 : ROWS / 4;
-#pragma unroll
-    for (int i = 0; i < F32Tile<KC, ROWS>::CHUNKS; ++i) {
-        const int q = tid + F_THREADS * i;
-        *reinterpret_cast<uintx4*>(s + (q / CPR) * F32Tile<KC, ROWS>::RS + (q % CPR) * 4) = r[i];
-    }
+// x = p0 + p1 + p2 with bf16 p (round to nearest: |x - p0| <= 2^-9 |x|, |x - p0 - p1| <= 2^-18 |x|, and the third holds
+// what is left exactly).  Two values at a time, packed.
+__device__ __forceinline__ void split2(float x0, float x1, unsigned& p0, unsigned& p1, unsigned& p2) {
+    p0 = pack_bf16(x0, x1);
+    x0 -= __builtin_bit_cast(float, p0 << 16);
+    x1 -= __builtin_bit_cast(float, p0 & 0xFFFF0000u);
+    p1 = pack_bf16(x0, x1);
+    x0 -= __builtin_bit_cast(float, p1 << 16);
+    x1 -= __builtin_bit_cast(float, p1 & 0xFFFF0000u);
+    p2 = pack_bf16(x0, x1);
 }
 
-// The four k values (8q + 4 hf .. + 3) of tile row `row`
-template <bool KC, int ROWS>
-__device__ __forceinline__ floatx4 f32_frag(const float* s, int row, int q, int hf) {
-    constexpr int RS = F32Tile<KC, ROWS>::RS;
-    if (KC) return *reinterpret_cast<const floatx4*>(s + row * RS + 8 * q + 4 * hf);
-    floatx4 v;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = s[(8 * q + 4 * hf + j) * RS + row];
-    return v;
+// Byte offset of chunk i of this thread in a plane
+template <bool KC, int ROWS, int SK>
+__device__ __forceinline__ int f32_chunk_at(int tid, int i) {
+    typedef F32Tile<KC, ROWS, SK> T;
+    const int q = tid + F_THREADS * i;
+    const int row = q / T::CPR, c = q % T::CPR;
+    return KC ? row * T::RB + T::chunk_at(row, c >> 1) * 16 + (c & 1) * 8
+              : row * T::RB + T::seg_at(row, c >> 2) * 32 + (c & 3) * 8;
 }
+
+// This lane's MFMA operand from a plane: tile t of the wavefront's ROWS / 2 rows, sub-step kk of 16 k.
+template <bool KC, int ROWS, int SK>
+__device__ __forceinline__ bf16x8 f32_frag(const char* plane, int wt, int t, int kk, int lane) {
+    typedef F32Tile<KC, ROWS, SK> T;
+    if (KC) {
+        const int l32 = lane & 31, hf = lane >> 5;
+        return *reinterpret_cast<const bf16x8*>(plane + (wt * (ROWS / 2) + t * 32 + l32) * T::RB +
+                                                T::chunk_at(l32, 2 * kk + hf) * 16);
+    }
+    // lane s of a group of 16 points at k-row kb + s / 4, rows 4 (s % 4) .. + 3 and receives row s of four k-rows
+    const int b = lane >> 4, s = lane & 15;
+    const char* p = plane + (16 * kk + 8 * (b >> 1) + (s >> 2)) * T::RB +
+                    T::seg_at(s >> 2, wt * (ROWS / 32) + t * 2 + (b & 1)) * 32 + 8 * (s & 3);
+    union { short4v h[2]; bf16x8 v; } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(p));
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(p + 4 * T::RB));
+    return u.v;
+}
+
+// The work of one workgroup: its tile of TM x TN, the shard it belongs to and the range of K.
+struct F32Work {
+    const float* A;
+    const float* B;
+    float* C;
+    int64_t lda, ldb, ldc;
+    int M, N, m0, n0, k_begin, k_end;
+};
 
 template <bool A_KC, bool B_KC, int TM, int TN>
-__global__ __launch_bounds__(F_THREADS, TM == 128 ? 2 : 4) void gemm_f32_kernel(GemmF32Params g) {
-    constexpr int MT = TM / 64, NT = TN / 64;            // 32 x 32 MFMA tiles per wavefront and direction
-    typedef F32Tile<A_KC, TM> TA;
-    typedef F32Tile<B_KC, TN> TB;
-    __shared__ __attribute__((aligned(16))) float sA[2][TA::FLOATS];
-    __shared__ __attribute__((aligned(16))) float sB[2][TB::FLOATS];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, hf = lane >> 5;
-
+__device__ __forceinline__ F32Work f32_work(const GemmF32Params& g) {
+    constexpr bool CAT_N = A_KC && B_KC, CAT_M = !A_KC && !B_KC, CAT_K = A_KC && !B_KC;
     // Tiles in panels of 8 tile rows, column by column; workgroups are dealt to the 8 XCDs round-robin, so
     // every XCD takes a contiguous run of tiles and shares the operand panels of its run in its L2.
-    constexpr bool CAT_N = A_KC && B_KC, CAT_M = !A_KC && !B_KC, CAT_K = A_KC && !B_KC;
     const int tiles_m = CAT_M ? g.total : (g.M + TM - 1) / TM, tiles_n = CAT_N ? g.total : (g.N + TN - 1) / TN;
     const int total = tiles_m * tiles_n, b = blockIdx.x;
     const int x = b & 7, per = total >> 3, rem = total & 7;
@@ -152,81 +189,220 @@ __global__ __launch_bounds__(F_THREADS, TM == 128 ? 2 : 4) void gemm_f32_kernel(
         else tile_m -= g.first[shard];
     }
     const GemmF32Shard& s = g.sh[shard];
-    const float* A = CAT_N ? g.A : s.A;
-    const float* B = CAT_M ? g.B : s.B;
-    const int64_t lda = CAT_N ? g.lda : s.ld, ldc = CAT_N ? s.ld : g.ldc;
-    const int M = CAT_M ? s.rows : g.M, N = CAT_N ? s.rows : g.N, K = CAT_K ? s.rows : g.K;
-    const int m0 = tile_m * TM, n0 = tile_n * TN;
+    F32Work w;
+    w.A = CAT_N ? g.A : s.A;
+    w.B = CAT_M ? g.B : s.B;
+    w.lda = CAT_N ? g.lda : s.ld;
+    w.ldb = g.ldb;
+    w.ldc = CAT_N ? s.ld : g.ldc;
+    w.M = CAT_M ? s.rows : g.M;
+    w.N = CAT_N ? s.rows : g.N;
+    w.m0 = tile_m * TM;
+    w.n0 = tile_n * TN;
     // slice of the K range; with one slice this is all of K and C is the real output (a short shard's last slices are empty)
-    const int k_begin = min(K, slice * g.k_per_slice);
-    const int k_end = min(K, k_begin + g.k_per_slice);
-    float* C = (CAT_K ? g.C : s.C) + (int64_t)blockIdx.y * g.slice_stride;
+    const int K = CAT_K ? s.rows : g.K;
+    w.k_begin = min(K, slice * g.k_per_slice);
+    w.k_end = min(K, w.k_begin + g.k_per_slice);
+    w.C = (CAT_K ? g.C : s.C) + (int64_t)blockIdx.y * g.slice_stride;
+    return w;
+}
 
-    floatx16 acc[MT][NT];
+// Ends the 32 x 32 block at (row0, col0): register r of lane l holds C[8 (r/4) + 4 (l/32) + r%4][l%32], 128 contiguous bytes
+// per row and store.
+template <bool A_KC, bool B_KC>
+__device__ __forceinline__ void f32_finish(floatx16 v, const F32Work& w, int row0, int col0, bool accumulate, int lane) {
+    constexpr bool SCALE = !(A_KC && B_KC);
+    const int l32 = lane & 31, hf = lane >> 5;
+    // A non-finite operand (or one that rounds to a bf16 infinity, or an overflow) makes the parts of the split
+    // cancel to NaN.  Elements that are not finite are computed again from the operands as they are, in fp32.
+    float nf = 0.f;
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+    for (int r = 0; r < 16; ++r) nf = fmaf(v[r], 0.f, nf);
+    if (SCALE) {
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+        for (int r = 0; r < 16; ++r) v[r] *= 1.f / D_SCALE;
+    }
+    if (__builtin_amdgcn_ballot_w64(!(nf == 0.f)) != 0) {
+        const int ar = min(row0 + l32, w.M - 1), br = min(col0 + l32, w.N - 1);
+        const float* ap = w.A + (A_KC ? (int64_t)ar * w.lda : (int64_t)ar);
+        const float* bp = w.B + (B_KC ? (int64_t)br * w.ldb : (int64_t)br);
+        floatx16 c;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int r = 0; r < 16; ++r) c[r] = 0.f;
+        for (int k = w.k_begin + hf; k < w.k_end + hf; k += 2) {
+            const int kc = k < w.k_end ? k : w.k_begin;
+            float av = ap[A_KC ? (int64_t)kc : (int64_t)kc * w.lda], bv = bp[B_KC ? (int64_t)kc : (int64_t)kc * w.ldb];
+            if (k >= w.k_end) av = bv = 0.f;
+            c = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, c, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (!(fabsf(v[r]) < INFINITY)) v[r] = c[r];
+    }
+    const int col = col0 + l32, row = row0 + 4 * hf;
+    if (col >= w.N) return;
+    float* c = w.C + (int64_t)row * w.ldc + col;
+    if (accumulate) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int dr = 8 * (r >> 2) + (r & 3);
+            if (row + dr < w.M) v[r] += c[(int64_t)dr * w.ldc];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int dr = 8 * (r >> 2) + (r & 3);
+        if (row + dr < w.M) c[(int64_t)dr * w.ldc] = v[r];
+    }
+}
 
-    uintx4 ra[TA::CHUNKS], rb[TB::CHUNKS];
-    f32_load<A_KC, TM>(ra, A, lda, m0, k_begin, M, k_end, g.a_vec, tid);
-    f32_load<B_KC, TN>(rb, B, g.ldb, n0, k_begin, N, k_end, g.b_vec, tid);
-    f32_store<A_KC, TM>(ra, sA[0], tid);
-    f32_store<B_KC, TN>(rb, sB[0], tid);
+// MT x NT MFMA tiles of 32 x 32 per wavefront, SK of K per LDS stage, PD stages of global loads in flight in registers,
+// WPC workgroups per compute unit.
+template <bool A_KC, bool B_KC, int MT, int NT, int SK, int PD, int WPC, bool VEC>
+__global__ __launch_bounds__(F_THREADS, WPC) void gemm_f32_kernel(GemmF32Params g) {
+    constexpr int TM = 64 * MT, TN = 64 * NT;
+    constexpr bool SCALE = !(A_KC && B_KC);      // A is D
+    typedef F32Tile<A_KC, TM, SK> TA;
+    typedef F32Tile<B_KC, TN, SK> TB;
+    constexpr int STAGE = 3 * (TA::PLANE + TB::PLANE);
+    __shared__ __attribute__((aligned(16))) char lds[2 * STAGE];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const F32Work w = f32_work<A_KC, B_KC, TM, TN>(g);
+    constexpr int KS = SK / 16;
+    static_assert(MT * NT == 8 || MT * NT == 4 ? KS == 1 : MT * NT == 1 && KS == 2, "tile");
+    floatx16 acc[KS][MT][NT];
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[kk][i][j][r] = 0.f;
+
+    // Stage q waits in registers from its request until it is split into LDS buffer q & 1 while stage q - 1 is multiplied;
+    // stages past the end of K are zeros that nothing multiplies.
+    constexpr int CA = TA::CHUNKS, CB = TB::CHUNKS;
+    uintx4 raw[PD][CA + CB];
+    auto load = [&](int u, int c, int q) {
+        const int k0 = w.k_begin + q * SK;
+        raw[u][c] = c < CA ? f32_load<A_KC, TM, SK, VEC>(w.A, w.lda, w.m0, k0, w.M, w.k_end, tid, c)
+                           : f32_load<B_KC, TN, SK, VEC>(w.B, w.ldb, w.n0, k0, w.N, w.k_end, tid, c - CA);
+    };
+    // Splits two of the values of chunk c (first: the lower two); with the upper two the chunk's parts go to LDS.
+    uint2 parts[3];
+    auto split = [&](int u, int c, bool first, char* stage) {
+        float x0 = __builtin_bit_cast(float, (unsigned)raw[u][c][first ? 0 : 2]);
+        float x1 = __builtin_bit_cast(float, (unsigned)raw[u][c][first ? 1 : 3]);
+        if (SCALE && c < CA) { x0 *= D_SCALE; x1 *= D_SCALE; }
+        if (first) {
+            split2(x0, x1, parts[0].x, parts[1].x, parts[2].x);
+            return;
+        }
+        split2(x0, x1, parts[0].y, parts[1].y, parts[2].y);
+        char* at = c < CA ? stage + f32_chunk_at<A_KC, TM, SK>(tid, c)
+                          : stage + 3 * TA::PLANE + f32_chunk_at<B_KC, TN, SK>(tid, c - CA);
+#pragma unroll
+        for (int l = 0; l < 3; ++l) *reinterpret_cast<uint2*>(at + l * (c < CA ? TA::PLANE : TB::PLANE)) = parts[l];
+    };
+    const int stages = (w.k_end - w.k_begin + SK - 1) / SK;
+#pragma unroll
+    for (int u = 0; u < PD; ++u)
+#pragma unroll
+        for (int c = 0; c < CA + CB; ++c) load(u, c, u);
+#pragma unroll
+    for (int c = 0; c < CA + CB; ++c) {
+        split(0, c, true, lds);
+        split(0, c, false, lds);
+        load(0, c, PD);
+    }
     __syncthreads();
-    int cur = 0;
-    for (int k0 = k_begin; k0 < k_end; k0 += FK, cur ^= 1) {
-        const bool more = k0 + FK < k_end;
-        if (more) {
-            f32_load<A_KC, TM>(ra, A, lda, m0, k0 + FK, M, k_end, g.a_vec, tid);
-            f32_load<B_KC, TN>(rb, B, g.ldb, n0, k0 + FK, N, k_end, g.b_vec, tid);
+    for (int q0 = 0; q0 < stages; q0 += PD) {
+#pragma unroll
+        for (int u = 0; u < PD; ++u) {
+            const int q = q0 + u;
+            if (q >= stages) break;
+            const char* sa = lds + (q & 1) * STAGE;
+            const char* sb = sa + 3 * TA::PLANE;
+            char* next = lds + ((q + 1) & 1) * STAGE;      // last read before the previous barrier
+            // MFMAs that follow one another are independent (one waits for the sum it adds to): four tiles, of the 2 x 4 or
+            // 4 x 2 ones those of one column / row at a time, or where a wavefront has a single tile two sums over k.
+            constexpr int PASSES = MT * NT == 8 ? 2 : 1;
+            bf16x8 a[KS][3][MT], b[KS][3][NT];
+#pragma unroll
+            for (int f = 0; f < 3; ++f) {      // in the order of their first use
+                const int la = (f + 2) % 3, lb = (3 - f) % 3;
+#pragma unroll
+                for (int kk = 0; kk < KS; ++kk) {
+#pragma unroll
+                    for (int i = 0; i < (NT > MT ? MT / PASSES : MT); ++i)
+                        a[kk][la][i] = f32_frag<A_KC, TM, SK>(sa + la * TA::PLANE, wm, i, kk, lane);
+#pragma unroll
+                    for (int j = 0; j < (NT > MT ? NT : NT / PASSES); ++j)
+                        b[kk][lb][j] = f32_frag<B_KC, TN, SK>(sb + lb * TB::PLANE, wn, j, kk, lane);
+                }
+            }
+#pragma unroll
+            for (int o = 0; o < PASSES; ++o) {
+                // the six products down to 2^-18 of the whole, the small ones first; after each of them a share of the next
+                // stage's split, whose vector instructions issue while the matrix cores work
+                constexpr int LA[6] = {2, 0, 1, 1, 0, 0}, LB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+                for (int e = 0; e < 6; ++e) {
+                    if (e == 3 && o + 1 < PASSES) {
+#pragma unroll
+                        for (int l = 0; l < 3; ++l) {
+                            if (NT > MT) a[0][l][1] = f32_frag<A_KC, TM, SK>(sa + l * TA::PLANE, wm, 1, 0, lane);
+                            else b[0][l][1] = f32_frag<B_KC, TN, SK>(sb + l * TB::PLANE, wn, 1, 0, lane);
+                        }
+                    }
+                    constexpr int INNER = PASSES == 2 ? 4 : KS * MT * NT;
+#pragma unroll
+                    for (int xx = 0; xx < INNER; ++xx) {
+                        const int y = (e & 1) ? INNER - 1 - xx : xx;
+                        const int kk = KS == 2 ? y : 0;
+                        const int i = PASSES == 2 ? (NT > MT ? o : y) : KS == 2 ? 0 : y >> 1;
+                        const int j = PASSES == 2 ? (NT > MT ? y : o) : KS == 2 ? 0 : (y ^ (y >> 1)) & 1;
+                        acc[kk][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][LA[e]][i], b[kk][LB[e]][j], acc[kk][i][j], 0, 0, 0);
+                    }
+                    constexpr int PAIRS = 2 * (CA + CB), PER = (PAIRS + 6 * PASSES - 1) / (6 * PASSES);
+#pragma unroll
+                    for (int z = 0; z < PER; ++z) {
+                        const int pair = (o * 6 + e) * PER + z;
+                        if (pair < PAIRS) {
+                            split((u + 1) % PD, pair >> 1, (pair & 1) == 0, next);
+                            if (pair & 1) load((u + 1) % PD, pair >> 1, q + 1 + PD);
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __syncthreads();
         }
-#pragma unroll
-        for (int q = 0; q < FK / 8; ++q) {
-            floatx4 a[MT], bb[NT];
-#pragma unroll
-            for (int i = 0; i < MT; ++i) a[i] = f32_frag<A_KC, TM>(sA[cur], (wm * MT + i) * 32 + l32, q, hf);
-#pragma unroll
-            for (int j = 0; j < NT; ++j) bb[j] = f32_frag<B_KC, TN>(sB[cur], (wn * NT + j) * 32 + l32, q, hf);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int i = 0; i < MT; ++i)
-#pragma unroll
-                    for (int j = 0; j < NT; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], bb[j][e], acc[i][j], 0, 0, 0);
-        }
-        if (more) {     // the other stage was last read before the previous barrier
-            f32_store<A_KC, TM>(ra, sA[cur ^ 1], tid);
-            f32_store<B_KC, TN>(rb, sB[cur ^ 1], tid);
-        }
-        __syncthreads();
     }
 
-    // register r of lane l of a tile holds C[8 (r/4) + 4 (l/32) + r%4][l%32]: 128 contiguous bytes per row and store
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
-            const int col = n0 + (wn * NT + j) * 32 + l32;
-            const int row0 = m0 + (wm * MT + i) * 32 + 4 * hf;
-            if (col >= N) continue;
-            float* c = C + (int64_t)row0 * ldc + col;
-            if (g.accumulate) {
+            floatx16 v = acc[0][i][j];
+            if constexpr (KS == 2) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int dr = 8 * (r >> 2) + (r & 3);
-                    if (row0 + dr < M) acc[i][j][r] += c[(int64_t)dr * ldc];
-                }
+                for (int r = 0; r < 16; ++r) v[r] += acc[1][i][j][r];
             }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int dr = 8 * (r >> 2) + (r & 3);
-                if (row0 + dr < M) c[(int64_t)dr * ldc] = acc[i][j][r];
-            }
+            f32_finish<A_KC, B_KC>(v, w, w.m0 + (wm * MT + i) * 32, w.n0 + (wn * NT + j) * 32, g.accumulate != 0, lane);
         }
+}
+
+// Estimated time of `wg` workgroups over k steps of K each.  A workgroup alone on a compute unit takes `alone` us per 16 k
+// (a chain of load, split, LDS and products); several share the unit at `each` us (K = 1024: 256 tiles of 64 x 64 28 us, 1024 of
+// them 88; 64 tiles of 128 x 128 61; 512 of the largest 170).
+static double product_us(int tile, int64_t wg, int64_t k) {
+    const double alone = tile == 64 ? 0.42 : tile == 128 ? 0.95 : 1.6, each = tile == 64 ? 0.34 : tile == 128 ? 0.72 : 1.28;
+    const double n = (double)ceil_div(wg, 256) * each;
+    return (double)ceil_div(k, 16) * (n > alone ? n : alone);
 }
 
 // K slices for an output of this many 64 x 64 tiles: enough workgroups to cover the chip, slices of at least min_k.
@@ -237,13 +413,13 @@ static int slices_for(int64_t tiles, int64_t K, int64_t min_k) {
     return S < 2 ? 1 : (int)S;
 }
 static int splitk_slices(int64_t M, int64_t N, int64_t K) { return slices_for(ceil_div(M, 64) * ceil_div(N, 64), K, 64); }
-// Logits and dW of a group.  A K step of 32 takes 0.55 us where a workgroup has a compute unit to itself; the sum of the
+// Logits and dW of a group.  A K step of 32 takes 0.55-0.85 us where a workgroup has a compute unit to itself; the sum of the
 // slices is another launch, 3 us of host time in passes that the host bounds.  So slices of at least 256, from K = 1024 on.
 // 32 tiles, product and forward pass, us, in one chain -> in slices: K = 512: 19.3 -> 15.4 and 28.0 -> 31.2; 640: 22.4 ->
 // 17.2 and 27.8 -> 30.6; 800: 26.5 -> 16.5 and 30.6 -> 31.0; 1024: 32.4 -> 15.9 and 36.9 -> 30.5; 2048: 58 -> 17 and 63 -> 30.
 int gemm_f32_group_slices(int64_t tiles, int64_t K) { return K < 1024 ? 1 : slices_for(tiles, K, 256); }
-// A product cut in S slices advances in steps of FK.
-static int slice_length(int64_t K, int S) { return S > 1 ? (int)(ceil_div(ceil_div(K, S), FK) * FK) : (int)K; }
+// Slices are multiples of 32 k long, the step of the small tiles.
+static int slice_length(int64_t K, int S) { return S > 1 ? (int)(ceil_div(ceil_div(K, S), 32) * 32) : (int)K; }
 
 size_t gemm_f32_scratch_floats(int64_t M, int64_t N, int64_t K) {
     const int S = splitk_slices(M, N, K);
@@ -252,10 +428,12 @@ size_t gemm_f32_scratch_floats(int64_t M, int64_t N, int64_t K) {
 
 template <bool A_KC, bool B_KC>
 static void launch_f32_t(GemmF32Params& g, int tile, hipStream_t st) {
-    int64_t tm = ceil_div(g.M, tile), tn = ceil_div(g.N, tile), cat = 0;
+    constexpr bool DW = !A_KC;
+    const int tile_m = tile == 256 && !DW ? 128 : tile, tile_n = tile == 256 && DW ? 128 : tile;
+    int64_t tm = ceil_div(g.M, tile_m), tn = ceil_div(g.N, tile_n), cat = 0;
     for (int r = 0; r < GEMM_GROUP_MAX; ++r) {
         g.first[r] = r < g.n ? (int)cat : INT_MAX;
-        if (r < g.n) cat += ceil_div(g.sh[r].rows, tile);
+        if (r < g.n) cat += ceil_div(g.sh[r].rows, A_KC ? tile_n : tile_m);
     }
     g.total = (int)cat;
     int z = g.slices;
@@ -263,10 +441,14 @@ static void launch_f32_t(GemmF32Params& g, int tile, hipStream_t st) {
     else if (!A_KC) tm = cat;
     else z *= g.n;
     const dim3 grid((unsigned)(tm * tn), (unsigned)z);
-    if (tile == 128)
-        hipLaunchKernelGGL((gemm_f32_kernel<A_KC, B_KC, 128, 128>), grid, dim3(F_THREADS), 0, st, g);
-    else
-        hipLaunchKernelGGL((gemm_f32_kernel<A_KC, B_KC, 64, 64>), grid, dim3(F_THREADS), 0, st, g);
+    const bool vec = g.a_vec && g.b_vec;
+#define VP_LAUNCH(...) hipLaunchKernelGGL((gemm_f32_kernel<A_KC, B_KC, __VA_ARGS__>), grid, dim3(F_THREADS), 0, st, g)
+    if (tile == 256) VP_LAUNCH((DW ? 4 : 2), (DW ? 2 : 4), 16, 1, 2, true);
+    else if (tile == 128 && vec) VP_LAUNCH(2, 2, 16, 2, 3, true);
+    else if (tile == 128) VP_LAUNCH(2, 2, 16, 2, 2, false);
+    else if (vec) VP_LAUNCH(1, 1, 32, 1, 3, true);
+    else VP_LAUNCH(1, 1, 32, 1, 3, false);
+#undef VP_LAUNCH
 }
 
 // Launches the product; C is [M, N] with row stride ldc where the shards share the output (dH).  With more than one K slice
@@ -276,15 +458,23 @@ static hipError_t launch_f32(GemmF32Params g, bool a_kc, bool b_kc, float* C, in
                              hipStream_t st) {
     const bool cat_n = a_kc && b_kc, cat_k = a_kc && !b_kc;
     const int parts = g.slices * (cat_k ? g.n : 1);
-    // workgroups of 128 x 128 tiles; these (half the LDS and load traffic per flop) once every compute unit gets one
-    int64_t wg = 0;
-    for (int r = 0; r < g.n; ++r) {
-        if (cat_n) wg += ceil_div(g.M, 128) * ceil_div(g.sh[r].rows, 128);
-        else if (cat_k) wg += ceil_div(g.M, 128) * ceil_div(g.N, 128);
-        else wg += ceil_div(g.sh[r].rows, 128) * ceil_div(g.N, 128);
+    int tile = 64;
+    if (cat_k || g.slices == 1) {      // (slices of logits and dW are counted in 64 x 64 tiles: gemm_f32_group_slices)
+        double best = 0;
+        for (int t : {64, 128, 256}) {
+            if (t == 256 && !(g.a_vec && g.b_vec)) continue;
+            const int tm = t == 256 && a_kc ? 128 : t, tn = t == 256 && !a_kc ? 128 : t;
+            int64_t wg = 0;
+            for (int r = 0; r < g.n; ++r)
+                wg += cat_n ? ceil_div(g.M, tm) * ceil_div(g.sh[r].rows, tn)
+                            : ceil_div(cat_k ? g.M : g.sh[r].rows, tm) * ceil_div(g.N, tn);
+            const double us = product_us(t, wg * g.slices, g.k_per_slice);
+            if (t == 64 || us < best) {
+                best = us;
+                tile = t;
+            }
+        }
     }
-    // (slices of logits and dW are counted in 64 x 64 tiles: gemm_f32_group_slices)
-    const int tile = wg * g.slices >= 256 && (cat_k || g.slices == 1) ? 128 : 64;
     g.C = C;
     if (!cat_n) g.ldc = ldc;
     g.accumulate = accumulate ? 1 : 0;
@@ -324,7 +514,7 @@ hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float
     g.A = A; g.B = B;
     g.lda = a_kc ? sam : sak; g.ldb = b_kc ? sbn : sbk;
     g.M = M; g.N = N; g.K = K;
-    g.k_per_slice = slice_length(K, scratch ? splitk_slices(M, N, K) : 1);
+    g.k_per_slice = slice_length(K, !scratch ? 1 : a_kc && !b_kc ? gemm_f32_dh_slices(M, N, K, 1) : splitk_slices(M, N, K));
     g.slices = (int)ceil_div(K, g.k_per_slice);
     g.a_vec = g.lda % 4 == 0 && ((uintptr_t)A & 15u) == 0 && (!a_kc || K % 4 == 0);
     g.b_vec = g.ldb % 4 == 0 && ((uintptr_t)B & 15u) == 0 && (!b_kc || K % 4 == 0);
@@ -371,7 +561,7 @@ hipError_t launch_gemm_f32_dh(int64_t N, int64_t h, const GemmF32Shard* sh, int 
     g.a_vec = 1;
     g.b_vec = h % 4 == 0 ? 1 : 0;
     g.slices = slices;
-    g.k_per_slice = (int)(ceil_div(ceil_div(rows, slices), FK) * FK);
+    g.k_per_slice = (int)(ceil_div(ceil_div(rows, slices), 32) * 32);
     g.n = n;
     return launch_f32(g, true, false, dH, h, accumulate, scratch, st);
 }
@@ -392,16 +582,22 @@ hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF3
     return launch_f32(g, false, false, nullptr, h, false, scratch, st);
 }
 
-// K slices per shard of a grouped dH product: one if 128 x 128 tiles of all shards fill the chip; else slices of at least
-// 512 k that make them do so; else 64 x 64 tiles, up to two workgroups per compute unit, slices of at least 64.
+// K slices per shard of the dH product of n shards with at most `rows` rows each: the least estimated time; the partial
+// outputs are written and read once (4 TB/s), by another launch.
 int gemm_f32_dh_slices(int64_t N, int64_t h, int64_t rows, int n) {
-    const int64_t big = ceil_div(N, 128) * ceil_div(h, 128) * n, small = ceil_div(N, 64) * ceil_div(h, 64) * n;
-    const int64_t S = ceil_div(256, big);
-    if (rows / S >= 512 || S == 1) return (int)S;
-    int64_t S64 = 512 / small;
-    if (S64 > rows / 64) S64 = rows / 64;
-    if (S64 > 32) S64 = 32;
-    return S64 < 1 ? 1 : (int)S64;
+    int best = 1;
+    double best_us = 0;
+    for (int64_t S = 1; S <= 64 && (S == 1 || (rows >= 64 * S && n * S * N * h <= (int64_t)1 << 26)); ++S) {
+        const double sum = n * S > 1 ? (double)(n * S) * (double)(N * h) * 8.0 / 4e6 + 4.0 : 0.0;
+        for (int t : {64, 128, 256}) {
+            const double us = sum + product_us(t, ceil_div(N, t == 256 ? 128 : t) * ceil_div(h, t) * n * S, ceil_div(rows, S));
+            if ((S == 1 && t == 64) || us < best_us) {
+                best = (int)S;
+                best_us = us;
+            }
+        }
+    }
+    return best;
 }
 
 }  // namespace vp

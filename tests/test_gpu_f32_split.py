@@ -1,0 +1,83 @@
+"""fp32 products from bf16 parts: precision of an fp32 sum, the whole range of exponents, infinities where fp32 has them."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+# (N, h, rows per shard): tiles of 64 x 64 (with K slices of dH), 128 x 128, 256 x 128; remainders in every direction, rows
+# that are not 16-byte aligned
+SHAPES = [(70, 72, [300, 131]), (33, 257, [129]), (300, 200, [2500, 2400]), (601, 1100, [2053, 2049]), (520, 68, [9000, 8001])]
+
+
+def plan_of(N, h, rows, seed, grad_scale=None):
+    import paper_2411_05288_amd as vp
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    H = torch.randn((N, h), generator=g, device="cuda")
+    W = [torch.randn((n, h), generator=g, device="cuda") * 0.05 for n in rows]
+    labels = torch.randint(0, sum(rows), (N,), generator=g, device="cuda")
+    plan = vp.OutputLayerPlan(H, W, labels, True, grad_scale)
+    plan.workspace.fill_(0xFF)
+    return plan
+
+
+def step(plan):
+    plan.step()
+    torch.cuda.synchronize()
+    return plan
+
+
+@pytest.mark.parametrize("N,h,rows", SHAPES)
+def test_products_have_the_error_of_an_fp32_sum(N, h, rows):
+    print("split", N, h, rows, flush=True)
+    plan = step(plan_of(N, h, rows, 5))
+    H, W = plan.H.double(), torch.cat(plan.W).double()
+    Y = H @ W.t()
+    D = torch.softmax(Y, 1)
+    D[torch.arange(N, device="cuda"), plan.labels] -= 1.0
+    D /= N
+
+    def check(got, A, B, D_error):
+        # a sum is rounded at most 6 times per 16 k, each time by 2^-23 of a partial sum, itself at most sum |a b|; a random
+        # walk of them for the 2-norm.  D_error: relative error of the elements of D that the kernel formed (fp32 statistics and
+        # logits), which its products inherit.
+        ref, mag = A @ B, A.abs() @ B.abs()
+        n = 6 * (A.shape[1] / 16 + 1)
+        err = (got.double() - ref).abs()
+        assert bool((err <= (n * 2.0 ** -23 + D_error) * mag).all())
+        assert float(err.norm() / ref.norm()) <= n ** 0.5 * 2.0 ** -23 + D_error
+
+    check(torch.cat(plan.logits, 1), H, W.t(), 0.0)
+    # |Y| stays below 16: logits and statistics that are off by 4 ulp of 8..16 move D by 8 ulp, 2^-17 of it
+    assert float(Y.abs().max()) < 16
+    check(plan.dH, D, W, 2.0 ** -17)
+    check(torch.cat(plan.dW), D.t(), H, 2.0 ** -17)
+
+
+@pytest.mark.parametrize("N,h,rows", SHAPES)
+def test_small_gradients_keep_all_bits(N, h, rows):
+    # powers of two pass through every product and sum unchanged: the same bits, though softmax * 2^-100 ends in parts far
+    # below the smallest bf16
+    print("small", N, h, rows, flush=True)
+    one, small = step(plan_of(N, h, rows, 6, 1.0)), step(plan_of(N, h, rows, 6, 2.0 ** -100))
+    assert torch.equal(small.dH * 2.0 ** 100, one.dH)
+    for a, b in zip(small.dW, one.dW):
+        assert torch.equal(a * 2.0 ** 100, b)
+
+
+@pytest.mark.parametrize("N,h,rows", SHAPES)
+def test_infinities_and_the_largest_values(N, h, rows):
+    print("inf", N, h, rows, flush=True)
+    plan = plan_of(N, h, rows, 7)
+    clean = torch.cat(step(plan).logits, 1).clone()
+    j, k, t = rows[0] - 1, h - 1, N - 1
+    plan.W[0][j, k] = float("inf")              # an infinity that fp32 keeps: its column is +-inf by the sign of H
+    plan.H[t, 0] = 3.4e38                       # rounds to an infinity in bf16; its row stays finite
+    plan.H[t, 1:] = 0.0
+    plan.forward()
+    torch.cuda.synchronize()
+    got = torch.cat(plan.logits, 1)
+    others = torch.arange(got.shape[1], device="cuda") != j
+    assert torch.equal(got[:t, others], clean[:t, others])
+    assert torch.equal(got[:t, j], torch.where(plan.H[:t, k] > 0, float("inf"), float("-inf")))
+    want = 3.4e38 * torch.cat(plan.W)[:, 0].double()
+    assert bool(((got[t].double() - want).abs() <= 2.0 ** -23 * want.abs())[others].all())
