@@ -225,6 +225,26 @@ vp_status vp_output_bwd_group(const void* H, const void* const* W_shards, const 
                               float* const* dW_shards, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * vp_output_fwd_alg2 for p shards that live on one device: A_out is [p, N, h], B_out a HOST array of p device pointers;
+ * arguments otherwise as for vp_output_fwd_group, results as there.  The workspace is that of
+ * vp_output_group_workspace_bytes(VP_CALL_OUTPUT_FWD_ALG2, ...), which is (size_t)-1 for more than 16 shards or more than
+ * 4 GiB of softmax' matrices: such shards go one by one.
+ *
+ * vp_output_dx_alg2_gather is vp_output_dx_alg2_group for at most 16 shards with A [p, N, h] and the rows of B_r taken from the
+ * shards (row labels[i] of the shard that owns it) in place of the matrices B_r: the same result bit for bit.
+ */
+vp_status vp_output_fwd_alg2_group(const void* H, const void* const* W_shards, const int64_t* rows,
+                                   const int64_t* shard_offsets, int32_t p, const int64_t* labels, int64_t N, int64_t h,
+                                   vp_dtype dt, uint32_t flags, float* local_max, float* local_sumexp, float* local_target,
+                                   void* const* logits_out, float* A_out, void* const* B_out, void* workspace,
+                                   size_t workspace_bytes, void* stream);
+vp_status vp_output_dx_alg2_gather(const float* A, const void* const* W_shards, const int64_t* rows,
+                                   const int64_t* shard_offsets, int32_t p, const int64_t* labels, const float* local_max,
+                                   const float* local_sumexp, const float* global_max, const float* global_sumexp,
+                                   int64_t N, int64_t h, vp_dtype dt, uint32_t flags, float grad_scale, float* dH_accum,
+                                   void* stream);
+
+/*
  * vp_output_dx_alg2 for p shards that live on one device, added in ascending order: A and B are HOST arrays of p device
  * pointers (read before the call returns), local_max and local_sumexp [p, N].  Equals p single calls bit for bit.
  */

@@ -78,6 +78,10 @@ def load_library() -> ctypes.CDLL:
     lib.vp_output_fwd_alg2.argtypes = [vp, vp, vp, i64, i64, i64, i64, c.c_int, u32, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.vp_output_dx_alg2.restype = c.c_int
     lib.vp_output_dx_alg2.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, c.c_int, u32, fl, vp, vp]
+    lib.vp_output_fwd_alg2_group.restype = c.c_int
+    lib.vp_output_fwd_alg2_group.argtypes = [vp, vp, vp, vp, i32, vp, i64, i64, c.c_int, u32, vp, vp, vp, vp, vp, vp, vp, sz, vp]
+    lib.vp_output_dx_alg2_gather.restype = c.c_int
+    lib.vp_output_dx_alg2_gather.argtypes = [vp, vp, vp, vp, i32, vp, vp, vp, vp, vp, i64, i64, c.c_int, u32, fl, vp, vp]
     lib.vp_output_dx_alg2_group.restype = c.c_int
     lib.vp_output_dx_alg2_group.argtypes = [vp, vp, i32, vp, vp, vp, vp, i64, i64, c.c_int, u32, fl, vp, vp]
     lib.vp_embed_fwd.restype = c.c_int
@@ -364,6 +368,41 @@ def vp_output_dx_alg2(A, B, local_max, local_sumexp, global_max, global_sumexp, 
         _ptr(global_sumexp, "global_sumexp", f, (N,)), N, h, dt, VP_DH_OVERWRITE if dh_overwrite else 0,
         float(grad_scale), _ptr(dH_accum, "dH_accum", f, (N, h)), _stream(stream))
     _check(st, "vp_output_dx_alg2")
+
+
+def vp_output_fwd_alg2_group(H, W_shards, labels, shard_offsets, local_max, local_sumexp, local_target, A_out, B_out,
+                             logits_out=None, workspace=None, stream=None) -> None:
+    """vp_output_fwd_alg2 for several shards on this device in one call: the statistics are [p, N], A_out is [p, N, h]."""
+    N, h = H.shape
+    dt, rows = _shards(H, W_shards, shard_offsets)
+    p = len(rows)
+    same = (torch.float32,) if dt == VP_F32 else _BF16_LIKE
+    f = (torch.float32,)
+    wp, wb = _ws(workspace)
+    st = load_library().vp_output_fwd_alg2_group(
+        _ptr(H, "H"), _each(W_shards, "W_shards", None, [(n, h) for n in rows]), _i64s(rows), _i64s(shard_offsets), p,
+        _ptr(labels, "labels", (torch.int64,), (N,)), N, h, dt, VP_SAVE_LOGITS if logits_out is not None else 0,
+        _ptr(local_max, "local_max", f, (p, N)), _ptr(local_sumexp, "local_sumexp", f, (p, N)),
+        _ptr(local_target, "local_target", f, (p, N)), _each(logits_out, "logits_out", same, [(N, n) for n in rows]),
+        _ptr(A_out, "A_out", f, (p, N, h)), _each(B_out, "B_out", same, [(N, h)] * p), wp, wb, _stream(stream))
+    _check(st, "vp_output_fwd_alg2_group")
+
+
+def vp_output_dx_alg2_gather(A, W_shards, labels, shard_offsets, local_max, local_sumexp, global_max, global_sumexp,
+                             grad_scale: float, dH_accum, stream=None, dh_overwrite: bool = False) -> None:
+    """vp_output_dx_alg2_group with A [p, N, h] and the rows of B taken from the shards."""
+    p, N, h = A.shape
+    f = (torch.float32,)
+    rows = [int(w.shape[0]) for w in W_shards]
+    if len(shard_offsets) != p or len(rows) != p:
+        raise VPError("one offset and one matrix per shard")
+    st = load_library().vp_output_dx_alg2_gather(
+        _ptr(A, "A", f, (p, N, h)), _each(W_shards, "W_shards", (W_shards[0].dtype,), [(n, h) for n in rows]), _i64s(rows),
+        _i64s(shard_offsets), p, _ptr(labels, "labels", (torch.int64,), (N,)), _ptr(local_max, "local_max", f, (p, N)),
+        _ptr(local_sumexp, "local_sumexp", f, (p, N)), _ptr(global_max, "global_max", f, (N,)),
+        _ptr(global_sumexp, "global_sumexp", f, (N,)), N, h, _dtype_code(W_shards[0]), VP_DH_OVERWRITE if dh_overwrite else 0,
+        float(grad_scale), _ptr(dH_accum, "dH_accum", f, (N, h)), _stream(stream))
+    _check(st, "vp_output_dx_alg2_gather")
 
 
 def vp_output_dx_alg2_group(A, B, local_max, local_sumexp, global_max, global_sumexp, grad_scale: float, dH_accum,

@@ -106,6 +106,13 @@ PartSizes part_sizes(const int64_t* rows, int r0, int n, int64_t N, int64_t h, v
     }
     return z;
 }
+// K slices of each product A_r = softmax'_r W_r of a group.
+int each_slices(const int64_t* rows, int p, int64_t N, int64_t h, vp_dtype dt) {
+    int64_t longest = 0;
+    for (int r = 0; r < p; ++r) longest = rows[r] > longest ? rows[r] : longest;
+    if (dt == VP_F32) return gemm_f32_each_slices(N, h, longest, p);
+    return h % 8 == 0 ? gemm_bf16_slices_each(N, h, ceil_div(longest, 64), p) : 1;
+}
 // Whether a part of the fp32 path is computed as a group (a single shard has K slices in every product: launch_gemm_f32).
 bool f32_grouped(int n, const PartSizes& z, int64_t N) { return n > 1 && N <= MAX_ROW && z.slices <= GROUP_SLICE_BYTES; }
 
@@ -380,12 +387,21 @@ vp_status vp_output_bwd(const void* H, const void* W_shard, const int64_t* label
 
 size_t vp_output_group_workspace_bytes(vp_call which, int32_t p, int64_t N, int64_t h, const int64_t* rows, vp_dtype dt,
                                        uint32_t flags) {
-    if ((which != VP_CALL_OUTPUT_FWD && which != VP_CALL_OUTPUT_BWD) || p < 1 || !rows) return (size_t)-1;
+    const bool alg2 = which == VP_CALL_OUTPUT_FWD_ALG2;
+    if ((which != VP_CALL_OUTPUT_FWD && which != VP_CALL_OUTPUT_BWD && !alg2) || p < 1 || !rows) return (size_t)-1;
     size_t need = 0;
     for (int32_t r = 0; r < p; ++r) {       // what the shards need one by one (paths that are not grouped)
         const size_t b = vp_workspace_bytes(which, N, h, rows[r], dt, flags);
         if (b == (size_t)-1) return b;
         need = b > need ? b : need;
+    }
+    if (alg2) {      // one part: its softmax' matrices stay until A = softmax' W is done
+        if (part_shards(rows, p, 0, N, dt) < p) return (size_t)-1;
+        const PartSizes z = part_sizes(rows, 0, p, N, h, dt);
+        const int S = each_slices(rows, p, N, h, dt);
+        const size_t slices = S > 1 ? (size_t)S * p * N * h * sizeof(float) : 0;
+        const size_t b = (dt == VP_BF16 ? z.stats : 0) + z.d + max3(align_up(slices, 256), z.logits_slices, 0);
+        return b > need ? b : need;
     }
     if (dt == VP_BF16 && h % 8) return need;
     for (int r = 0; r < p;) {
@@ -532,7 +548,7 @@ vp_status vp_output_bwd_group(const void* H, const void* const* W_shards, const 
                 d += d_bytes(N, rows[r], dt);
             }
             hipError_t e = logits_saved ? hipSuccess : launch_gemm_f32_logits((const float*)H, N, h, y, n, z.S_logits, slices, st);
-            if (e == hipSuccess) e = launch_dlogits_group(l, 0, labels, global_max, global_sumexp, grad_scale, (int)N, st);
+            if (e == hipSuccess) e = launch_dlogits_group(l, 0, labels, global_max, global_sumexp, 0, grad_scale, (int)N, st);
             if (e == hipSuccess && !skip_dh) e = launch_gemm_f32_dh(N, h, g, n, z.S, dH_accum, !overwrite, slices, st);
             if (e == hipSuccess) e = launch_gemm_f32_dw((const float*)H, N, h, g, n, z.S_dw, slices, st);
             if (e != hipSuccess) return VP_ERR_DEVICE;
@@ -586,7 +602,7 @@ vp_status vp_output_bwd_group(const void* H, const void* const* W_shards, const 
                 (skip_dh || gemm_bf16_group_ok(gh)) && gemm_bf16_group_ok(gw)) {
                 hipError_t e;
                 if (logits_saved) {
-                    e = launch_dlogits_group(l, 1, labels, global_max, global_sumexp, grad_scale, (int)N, st);
+                    e = launch_dlogits_group(l, 1, labels, global_max, global_sumexp, 0, grad_scale, (int)N, st);
                 } else {
                     e = launch_gemm_bf16_group(y, st);
                     if (e == hipSuccess) e = launch_zero_pad_columns(l, (int)N, st);
@@ -693,6 +709,150 @@ vp_status vp_output_fwd_alg2(const void* H, const void* W_shard, const int64_t* 
         hipSuccess)
         return VP_ERR_DEVICE;
     return dev(launch_embed_fwd(&W_shard, labels, 1, (int)N, (int)h, (int)Vs, shard_offset, 4, &B_out, st));
+}
+
+vp_status vp_output_fwd_alg2_group(const void* H, const void* const* W_shards, const int64_t* rows,
+                                   const int64_t* shard_offsets, int32_t p, const int64_t* labels, int64_t N, int64_t h,
+                                   vp_dtype dt, uint32_t flags, float* local_max, float* local_sumexp, float* local_target,
+                                   void* const* logits_out, float* A_out, void* const* B_out, void* workspace,
+                                   size_t workspace_bytes, void* stream) {
+    if (!H || !W_shards || !rows || !shard_offsets || p < 1 || !labels || !local_max || !local_sumexp || !local_target ||
+        !A_out || !B_out)
+        return VP_ERR_INVALID_ARG;
+    if (!dtype_ok(dt) || (flags & ~(uint32_t)VP_SAVE_LOGITS)) return VP_ERR_INVALID_ARG;
+    if (((flags & VP_SAVE_LOGITS) != 0) != (logits_out != nullptr)) return VP_ERR_INVALID_ARG;
+    if (!aligned16(H) || !aligned16(workspace) || !aligned16(A_out)) return VP_ERR_INVALID_ARG;
+    for (int32_t r = 0; r < p; ++r) {
+        if (!W_shards[r] || !aligned16(W_shards[r]) || !sizes_ok(N, h, rows[r]) || shard_offsets[r] < 0) return VP_ERR_INVALID_ARG;
+        if (logits_out && (!logits_out[r] || !aligned16(logits_out[r]))) return VP_ERR_INVALID_ARG;
+        if (!B_out[r] || !aligned16(B_out[r])) return VP_ERR_INVALID_ARG;
+        if (!sizes_supported(N, h, rows[r])) return VP_ERR_UNSUPPORTED;
+    }
+    const size_t need = vp_output_group_workspace_bytes(VP_CALL_OUTPUT_FWD_ALG2, p, N, h, rows, dt, flags);
+    if (need == (size_t)-1) return VP_ERR_UNSUPPORTED;
+    if (!workspace || workspace_bytes < need) return VP_ERR_WORKSPACE;
+    hipStream_t st = (hipStream_t)stream;
+    const PartSizes z = part_sizes(rows, 0, p, N, h, dt);
+    const int S = each_slices(rows, p, N, h, dt);
+    const bool bf16 = dt == VP_BF16;
+
+    // the logits go to the caller's buffers when it keeps them, else into the softmax' buffers (in place)
+    ShardList l{};
+    l.n = p;
+    char* d = (char*)workspace + (bf16 ? z.stats : 0);
+    for (int r = 0; r < p; ++r) {
+        l.rows[r] = (int)rows[r];
+        l.first[r + 1] = l.first[r] + (int)fwd_tiles(rows[r]);
+        l.offset[r] = shard_offsets[r];
+        l.D[r] = d;
+        l.ldd[r] = d_ld(rows[r], dt);
+        l.Y[r] = logits_out ? logits_out[r] : d;
+        l.ldy[r] = logits_out ? rows[r] : l.ldd[r];
+        d += d_bytes(N, rows[r], dt);
+    }
+    float* slices = (float*)d;
+    hipError_t e = hipSuccess;
+
+    if (bf16) {
+        GemmBf16Group y{}, a{};
+        y.base = logits_product(H, labels, N, h, Epi::FwdStats);
+        y.base.part_max = (float*)workspace;
+        y.base.part_sum = y.base.part_max + z.tiles * N;
+        y.base.part_tgt = y.base.part_max + 2 * z.tiles * N;
+        a.base.M = (int)N; a.base.N = (int)h;      // A_r = softmax'_r W_r : K = rows, W_r is stored [K][N]
+        a.base.ldb = a.base.ldc = (int)h;
+        a.base.a_kcontig = 1;
+        a.base.vec_ok = h % 8 == 0 ? 1 : 0;
+        a.base.epi = Epi::StoreF32;
+        a.base.kernel_id = K_GEMM_A_ALG2;
+        a.base.C = S > 1 ? slices : A_out;
+        a.slices = S;
+        a.each = 1;
+        for (int r = 0; r < p; ++r) {
+            y.sh[r].B = a.sh[r].B = (const u16*)W_shards[r];
+            y.sh[r].out = (void*)l.Y[r];
+            y.sh[r].ld = (int)l.ldy[r];
+            y.sh[r].offset = shard_offsets[r];
+            a.sh[r].A = (const u16*)l.D[r];
+            a.sh[r].ld = (int)l.ldd[r];
+            y.sh[r].rows = a.sh[r].rows = (int)rows[r];
+        }
+        gemm_bf16_group_finish(y, p);
+        gemm_bf16_group_finish(a, p);
+        if (gemm_bf16_group_ok(y)) {
+            e = launch_gemm_bf16_group(y, st);
+        } else {      // shapes that the fast kernel does not take
+            for (int r = 0; r < p && e == hipSuccess; ++r) {
+                GemmBf16Params g = y.base;
+                g.B = y.sh[r].B;
+                g.N = y.sh[r].rows;
+                g.Y = (u16*)y.sh[r].out; g.ldy = y.sh[r].ld;
+                g.shard_offset = shard_offsets[r];
+                g.part_max += (int64_t)l.first[r] * N;
+                g.part_sum += (int64_t)l.first[r] * N;
+                g.part_tgt += r * N;
+                e = launch_gemm_bf16(g, st);
+            }
+        }
+        if (e == hipSuccess)
+            e = launch_fold_partials(y.base.part_max, y.base.part_sum, y.base.part_tgt, l, (int)N, labels, local_max,
+                                     local_sumexp, local_target, st);
+        // softmax' with the shards' own statistics (no one-hot term, scale 1), rows padded and zero-filled
+        if (e == hipSuccess) e = launch_dlogits_group(l, 1, nullptr, local_max, local_sumexp, N, 1.0f, (int)N, st);
+        if (e != hipSuccess) return VP_ERR_DEVICE;
+        if (gemm_bf16_group_ok(a)) {
+            e = launch_gemm_bf16_group(a, st);
+            if (e == hipSuccess && S > 1) {
+                ProfScope prof(K_SUM_SLICES, st);
+                e = launch_sum_slices(slices, S, (int64_t)p * N * h, A_out, false, st);
+            }
+        } else {
+            for (int r = 0; r < p && e == hipSuccess; ++r) {
+                GemmBf16Params g = a.base;
+                g.A = a.sh[r].A; g.lda = a.sh[r].ld;
+                g.B = a.sh[r].B;
+                g.K = a.sh[r].rows;
+                g.C = A_out + (int64_t)r * N * h;
+                e = launch_gemm_bf16(g, st);
+            }
+        }
+    } else {
+        GemmF32Shard y[GEMM_GROUP_MAX], a[GEMM_GROUP_MAX];
+        for (int r = 0; r < p; ++r) {
+            y[r] = {nullptr, (const float*)W_shards[r], (float*)l.Y[r], (int)rows[r], (int)l.ldy[r]};
+            a[r] = {(const float*)l.D[r], (const float*)W_shards[r], nullptr, (int)rows[r], (int)l.ldd[r]};
+        }
+        e = launch_gemm_f32_logits((const float*)H, N, h, y, p, z.S_logits, slices, st);
+        if (e == hipSuccess) e = launch_row_stats_f32(l, labels, (int)N, local_max, local_sumexp, local_target, st);
+        if (e == hipSuccess) e = launch_dlogits_group(l, 0, nullptr, local_max, local_sumexp, N, 1.0f, (int)N, st);
+        if (e == hipSuccess) e = launch_gemm_f32_each(N, h, a, p, S, A_out, slices, st);
+    }
+    // B_r = G W_r, the gather of the labels' rows: shards of one size that follow one another in one launch
+    for (int r = 0; r < p && e == hipSuccess;) {
+        int n = 1;
+        while (r + n < p && rows[r + n] == rows[r] && shard_offsets[r + n] == shard_offsets[r] + n * rows[r]) ++n;
+        e = launch_embed_fwd(W_shards + r, labels, n, (int)N, (int)h, (int)rows[r], shard_offsets[r], bf16 ? 2 : 4, B_out + r, st);
+        r += n;
+    }
+    return dev(e);
+}
+
+vp_status vp_output_dx_alg2_gather(const float* A, const void* const* W_shards, const int64_t* rows,
+                                   const int64_t* shard_offsets, int32_t p, const int64_t* labels, const float* local_max,
+                                   const float* local_sumexp, const float* global_max, const float* global_sumexp, int64_t N,
+                                   int64_t h, vp_dtype dt, uint32_t flags, float grad_scale, float* dH_accum, void* stream) {
+    if (!A || !W_shards || !rows || !shard_offsets || p < 1 || !labels || !local_max || !local_sumexp || !global_max ||
+        !global_sumexp || !dH_accum)
+        return VP_ERR_INVALID_ARG;
+    if (!dtype_ok(dt) || (flags & ~(uint32_t)VP_DH_OVERWRITE) || !aligned16(A) || !aligned16(dH_accum)) return VP_ERR_INVALID_ARG;
+    for (int32_t r = 0; r < p; ++r) {
+        if (!W_shards[r] || !aligned16(W_shards[r]) || !sizes_ok(N, h, rows[r]) || shard_offsets[r] < 0) return VP_ERR_INVALID_ARG;
+        if (!sizes_supported(N, h, rows[r])) return VP_ERR_UNSUPPORTED;
+    }
+    if (p > GEMM_GROUP_MAX) return VP_ERR_UNSUPPORTED;
+    return dev(launch_dx_alg2_gather(A, W_shards, rows, shard_offsets, p, dt == VP_BF16 ? 1 : 0, labels, local_max, local_sumexp,
+                                     global_max, global_sumexp, (int)N, (int)h, grad_scale, (flags & VP_DH_OVERWRITE) != 0,
+                                     dH_accum, (hipStream_t)stream));
 }
 
 vp_status vp_output_dx_alg2_group(const float* const* A, const void* const* B, int32_t p, const float* local_max,

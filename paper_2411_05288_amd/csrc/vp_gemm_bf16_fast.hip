@@ -238,7 +238,8 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Group gg) {
     const int tiles_m = CAT_M ? gg.total : (g.M + BM - 1) / BM;
     const int tiles_n = CAT_N ? gg.total : (g.N + BN - 1) / BN;
     const int plane = tiles_m * tiles_n;
-    const int total_tiles = CAT_K ? plane * gg.slices : plane;
+    const int pieces = CAT_K ? gg.slices * (gg.each ? gg.n : 1) : 1;      // of K
+    const int total_tiles = plane * pieces;
 
     const unsigned a_row = CAT_K || CAT_M ? 0u : (unsigned)g.lda;      // row stride of A if the shards share it
 
@@ -266,14 +267,21 @@ __global__ __launch_bounds__(NT) void gemm_bf16_fast_kernel(GemmBf16Group gg) {
     for (int v = blockIdx.x; v < total_tiles; v += gridDim.x, ++tile_idx) {
     trace_stamp<TRACE>(g, tile_idx, 0);
     int tile_m, tile_n, slice = 0;      // tile_m / tile_n: within the shard
-    if (CAT_K && gg.slices > 1) sliced_tile_of_block(v, gridDim.x, plane, gg.slices, tiles_m, tiles_n, tile_m, tile_n, slice);
+    if (pieces > 1) sliced_tile_of_block(v, gridDim.x, plane, pieces, tiles_m, tiles_n, tile_m, tile_n, slice);
     else tile_of_block(v, gridDim.x, total_tiles, tiles_m, tiles_n, tile_m, tile_n);
 
     // the shard, and for dH the range [kt_at, kt_end) of k tiles of this work item (over all shards)
     int shard, kt_at = 0, kt_end = 0;
     if constexpr (CAT_K) {
-        kt_at = (int)((long long)gg.total * slice / gg.slices);
-        kt_end = (int)((long long)gg.total * (slice + 1) / gg.slices);
+        int from = 0, count = gg.total, part = slice;
+        if (gg.each) {
+            const int r = slice % gg.n;
+            part = slice / gg.n;
+            from = gg.first[r];
+            count = (r + 1 < gg.n ? gg.first[r + 1] : gg.total) - from;
+        }
+        kt_at = from + (int)((long long)count * part / gg.slices);
+        kt_end = from + (int)((long long)count * (part + 1) / gg.slices);
         shard = shard_of(gg, kt_at);
     } else {
         shard = shard_of(gg, CAT_N ? tile_n : tile_m);
@@ -661,7 +669,7 @@ template <bool A_KC, bool B_KC, Epi EPI>
 static hipError_t launch_fast_t(const GemmBf16Group& p0, hipStream_t st) {
     GemmBf16Group p = p0;
     const int64_t tm = !A_KC && !B_KC ? p.total : ceil_div(p.base.M, BM), tn = A_KC && B_KC ? p.total : ceil_div(p.base.N, BN);
-    const int tiles = (int)(tm * tn) * (A_KC && !B_KC ? p.slices : 1);
+    const int tiles = (int)(tm * tn) * (A_KC && !B_KC ? p.slices * (p.each ? p.n : 1) : 1);
     const int cus = compute_unit_count();
     const int grid = tiles > cus ? cus : tiles;
     if constexpr (A_KC && B_KC) {
@@ -784,14 +792,16 @@ hipError_t launch_gemm_bf16_fast(const GemmBf16Params& p, hipStream_t st) {
 // A dH product has only N h / 65536 tiles but the whole vocabulary as K, so with few tokens most compute units would
 // idle (512 tokens, h = 2048: 16 tiles).  The k tiles are cut into S equal slices per output tile; the least estimated
 // time wins: rounds of 256 workgroups at 1.1 us per k tile (256 x 256 x 64 at 2400 cycles) and 5 us per tile for its
-// start and its stores, and for S > 1 the partial outputs written and read once at 4 TB/s and another launch.
-int gemm_bf16_slices(int64_t M, int64_t N, int64_t kt) {
-    const int64_t tiles = ceil_div(M, BM) * ceil_div(N, BN);
+// start and its stores, and for S > 1 the partial outputs written and read once at 4 TB/s and another launch.  The products
+// A_r = softmax'_r W_r of Algorithm 2 are n outputs of kt k tiles each in one launch: N=71 h=896 V=14003 p=8, step 619 -> 121 us
+// (with the logits of all shards in one launch too), N=136 h=7040 V=79658 p=2 2356 -> 1369, N=4096 h=4096 V=32000 p=8 3132 -> 2947.
+static int slices_of(int64_t M, int64_t N, int64_t kt, int n) {
+    const int64_t tiles = ceil_div(M, BM) * ceil_div(N, BN) * n;
     int best = 1;
     double best_us = 0;
-    for (int64_t S = 1; S <= 32 && (S == 1 || S * 8 <= kt) && (S == 1 || S * M * N <= (int64_t)1 << 28); ++S) {
+    for (int64_t S = 1; S <= 32 && (S == 1 || S * 8 <= kt) && (S == 1 || S * n * M * N <= (int64_t)1 << 28); ++S) {
         double us = (double)ceil_div(tiles * S, 256) * ((double)ceil_div(kt, S) * 1.1 + 5.0);
-        if (S > 1) us += (double)(S * M * N) * 8.0 / 4e6 + 5.0;
+        if (S > 1) us += (double)(S * n * M * N) * 8.0 / 4e6 + 5.0;
         if (S == 1 || us < best_us) {
             best = (int)S;
             best_us = us;
@@ -799,5 +809,7 @@ int gemm_bf16_slices(int64_t M, int64_t N, int64_t kt) {
     }
     return best;
 }
+int gemm_bf16_slices(int64_t M, int64_t N, int64_t kt) { return slices_of(M, N, kt, 1); }
+int gemm_bf16_slices_each(int64_t M, int64_t N, int64_t kt, int n) { return slices_of(M, N, kt, n); }
 
 }  // namespace vp

@@ -451,6 +451,28 @@ static void launch_f32_t(GemmF32Params& g, int tile, hipStream_t st) {
 #undef VP_LAUNCH
 }
 
+// Tile of the least estimated time.
+static int tile_for(const GemmF32Params& g, bool a_kc, bool b_kc) {
+    const bool cat_n = a_kc && b_kc, cat_k = a_kc && !b_kc;
+    if (!cat_k && g.slices > 1) return 64;      // (slices of logits and dW are counted in 64 x 64 tiles: gemm_f32_group_slices)
+    int tile = 64;
+    double best = 0;
+    for (int t : {64, 128, 256}) {
+        if (t == 256 && !(g.a_vec && g.b_vec)) continue;
+        const int tm = t == 256 && a_kc ? 128 : t, tn = t == 256 && !a_kc ? 128 : t;
+        int64_t wg = 0;
+        for (int r = 0; r < g.n; ++r)
+            wg += cat_n ? ceil_div(g.M, tm) * ceil_div(g.sh[r].rows, tn)
+                        : ceil_div(cat_k ? g.M : g.sh[r].rows, tm) * ceil_div(g.N, tn);
+        const double us = product_us(t, wg * g.slices, g.k_per_slice);
+        if (t == 64 || us < best) {
+            best = us;
+            tile = t;
+        }
+    }
+    return tile;
+}
+
 // Launches the product; C is [M, N] with row stride ldc where the shards share the output (dH).  With more than one K slice
 // (dH: of all shards together) the partial outputs go through scratch, every slice laid out like the output, or like the
 // outputs of the shards one behind the other.
@@ -458,23 +480,7 @@ static hipError_t launch_f32(GemmF32Params g, bool a_kc, bool b_kc, float* C, in
                              hipStream_t st) {
     const bool cat_n = a_kc && b_kc, cat_k = a_kc && !b_kc;
     const int parts = g.slices * (cat_k ? g.n : 1);
-    int tile = 64;
-    if (cat_k || g.slices == 1) {      // (slices of logits and dW are counted in 64 x 64 tiles: gemm_f32_group_slices)
-        double best = 0;
-        for (int t : {64, 128, 256}) {
-            if (t == 256 && !(g.a_vec && g.b_vec)) continue;
-            const int tm = t == 256 && a_kc ? 128 : t, tn = t == 256 && !a_kc ? 128 : t;
-            int64_t wg = 0;
-            for (int r = 0; r < g.n; ++r)
-                wg += cat_n ? ceil_div(g.M, tm) * ceil_div(g.sh[r].rows, tn)
-                            : ceil_div(cat_k ? g.M : g.sh[r].rows, tm) * ceil_div(g.N, tn);
-            const double us = product_us(t, wg * g.slices, g.k_per_slice);
-            if (t == 64 || us < best) {
-                best = us;
-                tile = t;
-            }
-        }
-    }
+    const int tile = tile_for(g, a_kc, b_kc);
     g.C = C;
     if (!cat_n) g.ldc = ldc;
     g.accumulate = accumulate ? 1 : 0;
@@ -547,9 +553,7 @@ hipError_t launch_gemm_f32_logits(const float* H, int64_t N, int64_t h, const Ge
     return launch_f32(g, true, true, nullptr, 0, false, scratch, st);
 }
 
-hipError_t launch_gemm_f32_dh(int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* dH, bool accumulate,
-                              float* scratch, hipStream_t st) {
-    ProfScope prof(K_GEMM_F32, st);
+static GemmF32Params dh_params(int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices) {
     GemmF32Params g{};
     g.ldb = h;
     g.M = (int)N; g.N = (int)h;
@@ -563,7 +567,13 @@ hipError_t launch_gemm_f32_dh(int64_t N, int64_t h, const GemmF32Shard* sh, int 
     g.slices = slices;
     g.k_per_slice = (int)(ceil_div(ceil_div(rows, slices), 32) * 32);
     g.n = n;
-    return launch_f32(g, true, false, dH, h, accumulate, scratch, st);
+    return g;
+}
+
+hipError_t launch_gemm_f32_dh(int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* dH, bool accumulate,
+                              float* scratch, hipStream_t st) {
+    ProfScope prof(K_GEMM_F32, st);
+    return launch_f32(dh_params(N, h, sh, n, slices), true, false, dH, h, accumulate, scratch, st);
 }
 
 hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* scratch,
@@ -582,13 +592,33 @@ hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF3
     return launch_f32(g, false, false, nullptr, h, false, scratch, st);
 }
 
+hipError_t launch_gemm_f32_each(int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* out, float* scratch,
+                                hipStream_t st) {
+    ProfScope prof(K_GEMM_F32, st);
+    GemmF32Params g = dh_params(N, h, sh, n, slices);
+    g.C = slices > 1 ? scratch : out;
+    g.ldc = h;
+    g.slice_stride = N * h;
+    launch_f32_t<true, false>(g, tile_for(g, true, false), st);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || slices == 1) return e;
+    SumList l{};
+    l.n = n;
+    for (int r = 0; r < n; ++r) {
+        l.first[r] = (int64_t)r * slices * N * h;
+        l.count[r] = N * h;
+        l.C[r] = out + (int64_t)r * N * h;
+    }
+    return launch_sum_slices(scratch, slices, N * h, l, false, st);
+}
+
 // K slices per shard of the dH product of n shards with at most `rows` rows each: the least estimated time; the partial
-// outputs are written and read once (4 TB/s), by another launch.
-int gemm_f32_dh_slices(int64_t N, int64_t h, int64_t rows, int n) {
+// outputs are written and read once (4 TB/s), by another launch (one: they are summed even with one slice per shard).
+static int dh_slices(int64_t N, int64_t h, int64_t rows, int n, bool one) {
     int best = 1;
     double best_us = 0;
     for (int64_t S = 1; S <= 64 && (S == 1 || (rows >= 64 * S && n * S * N * h <= (int64_t)1 << 26)); ++S) {
-        const double sum = n * S > 1 ? (double)(n * S) * (double)(N * h) * 8.0 / 4e6 + 4.0 : 0.0;
+        const double sum = (one ? n * S : S) > 1 ? (double)(n * S) * (double)(N * h) * 8.0 / 4e6 + 4.0 : 0.0;
         for (int t : {64, 128, 256}) {
             const double us = sum + product_us(t, ceil_div(N, t == 256 ? 128 : t) * ceil_div(h, t) * n * S, ceil_div(rows, S));
             if ((S == 1 && t == 64) || us < best_us) {
@@ -599,5 +629,7 @@ int gemm_f32_dh_slices(int64_t N, int64_t h, int64_t rows, int n) {
     }
     return best;
 }
+int gemm_f32_dh_slices(int64_t N, int64_t h, int64_t rows, int n) { return dh_slices(N, h, rows, n, true); }
+int gemm_f32_each_slices(int64_t N, int64_t h, int64_t rows, int n) { return dh_slices(N, h, rows, n, false); }
 
 }  // namespace vp

@@ -94,6 +94,8 @@ struct GemmBf16Group {
     GemmBf16Params base;
     int n;                         // shards
     int slices;                    // dH: K slices, slice z writes base.C + z M ldc
+    int each;                      // not 0: a product per shard in place of their sum over the shards, every one in `slices`
+                                   // slices; slice z of shard r writes base.C + (z n + r) M ldc
     int total;                     // tile columns / tile rows / k tiles of all shards
     int first[GEMM_GROUP_MAX];     // the first of them that belongs to shard r (INT_MAX from n on)
     GemmBf16Shard sh[GEMM_GROUP_MAX];
@@ -105,6 +107,8 @@ bool gemm_bf16_group_ok(const GemmBf16Group& g);
 hipError_t launch_gemm_bf16_group(const GemmBf16Group& g, hipStream_t st);
 // K slices of a dH product [M, N] over kt k tiles (the slices' partial outputs take slices * M * N floats of scratch).
 int gemm_bf16_slices(int64_t M, int64_t N, int64_t kt);
+// The same for n products of at most kt k tiles each (n * slices * M * N floats of scratch).
+int gemm_bf16_slices_each(int64_t M, int64_t N, int64_t kt, int n);
 // Outputs of a sum over partial matrices: output r of count[r] floats, whose partials start at float first[r] of each slice.
 struct SumList {
     int n;
@@ -158,6 +162,10 @@ hipError_t launch_gemm_f32_dh(int64_t N, int64_t h, const GemmF32Shard* sh, int 
 hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* scratch,
                               hipStream_t st);
 int gemm_f32_dh_slices(int64_t N, int64_t h, int64_t rows, int n);
+// A_r = P_r W_r of every shard (A in sh[].A), out [n, N, h]; scratch, if slices > 1: n * slices * N * h floats
+hipError_t launch_gemm_f32_each(int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* out, float* scratch,
+                                hipStream_t st);
+int gemm_f32_each_slices(int64_t N, int64_t h, int64_t rows, int n);
 
 // Per-shard arguments of the small kernels that serve all shards of a group in one launch.
 struct ShardList {
@@ -191,15 +199,21 @@ hipError_t launch_dlogits(const void* Y, int64_t ldy, void* D, int64_t ldd, int 
                           int64_t off, const float* gmax, const float* gsum, float scale, int N, int Vs,
                           hipStream_t st);
 
-// The same for all shards of a list (D_r from Y_r, whose row stride is ldy[r]).
+// The same for all shards of a list (D_r from Y_r, whose row stride is ldy[r]; D_r may be Y_r).  Shard r takes its
+// statistics r * shard_stats floats on (0: all the same).
 hipError_t launch_dlogits_group(const ShardList& l, int is_bf16, const int64_t* labels, const float* gmax, const float* gsum,
-                                float scale, int N, hipStream_t st);
+                                int64_t shard_stats, float scale, int N, hipStream_t st);
 
 // dH += (A_r * c_r - B_r) * scale over p shards, c_ri = lsum_ri exp(lmax_ri - gmax_i) / gsum_i  (Algorithm 2)
 // (overwrite: dH = ... instead of +=; A and B are host arrays, lmax and lsum [p, N])
 hipError_t launch_dx_alg2(const float* const* A, const void* const* B, int p, int b_is_bf16, const float* lmax,
                           const float* lsum, const float* gmax, const float* gsum, int N, int h, float scale, bool overwrite,
                           float* dH, hipStream_t st);
+
+// The same for p <= GEMM_GROUP_MAX shards with A [p, N, h] and the rows of B taken from the shards: row labels[i] of W.
+hipError_t launch_dx_alg2_gather(const float* A, const void* const* W, const int64_t* rows, const int64_t* offsets, int p,
+                                 int is_bf16, const int64_t* labels, const float* lmax, const float* lsum, const float* gmax,
+                                 const float* gsum, int N, int h, float scale, bool overwrite, float* dH, hipStream_t st);
 
 // Zeroes the padding columns rows[r] .. ldd[r]-1 of the bf16 matrices D_r [N, ldd[r]].
 hipError_t launch_zero_pad_columns(const ShardList& l, int N, hipStream_t st);

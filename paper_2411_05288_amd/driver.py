@@ -4,8 +4,8 @@ This is launch ordering and buffer ownership only.  It follows Algorithm 1 of th
 pass S on all shards (vp_output_fwd_group), barrier C1 (vp_combine_stats, standing in for the two
 all-reduces), pass T on all shards (vp_output_bwd_group) with the reduce C2 realised as fp32
 accumulation into one dH buffer in ascending order of the vocabulary.  With algorithm=2 it follows
-Algorithm 2: pass S, shard by shard, also forms A and B (vp_output_fwd_alg2), the input gradient is
-accumulated inside the single barrier (vp_output_dx_alg2_group), and pass T is dW alone.  The calls of a single
+Algorithm 2: pass S also forms A and B (vp_output_fwd_alg2_group), the input gradient is accumulated inside the single
+barrier (vp_output_dx_alg2_gather), and pass T is dW alone.  The calls of a single
 shard (vp_output_fwd, vp_output_bwd) serve plans whose shards without real rows are not the last ones, and plans
 without the workspace for all shards.  All device buffers are allocated once, when the plan is built; a step
 allocates nothing.
@@ -101,6 +101,7 @@ class OutputLayerPlan:
         # call's workspace is larger: the D matrices of all shards (at most 4 GiB) and the slices of a cut dH product.
         self.live = sum(v > 0 for v in self.valid)
         self.grouped = all(v > 0 for v in self.valid[:self.live])
+        self.grouped_S = False
         if self.grouped:
             live = self.valid[:self.live]
             group_bytes = max(nbytes, B.vp_output_group_workspace_bytes(B.VP_CALL_OUTPUT_BWD, N, h, live, self.dt,
@@ -108,13 +109,16 @@ class OutputLayerPlan:
             if algorithm == 1:
                 group_bytes = max(group_bytes, B.vp_output_group_workspace_bytes(B.VP_CALL_OUTPUT_FWD, N, h, live, self.dt,
                                                                                  flags))
+            else:
+                try:
+                    group_bytes = max(group_bytes, B.vp_output_group_workspace_bytes(fwd_call, N, h, live, self.dt, flags))
+                    self.grouped_S = True
+                except B.VPError:      # more shards or larger ones than one call takes
+                    pass
             self.grouped = workspace_limit is None or group_bytes <= max(nbytes, workspace_limit)
             # a single shard gains from the group call only the K slices of dH, which need workspace
             if self.live == 1 and group_bytes == nbytes:
                 self.grouped = False
-        # Algorithm 2 keeps A = softmax' W_r and B = G W_r of every shard until the barrier
-        self.A = [torch.empty((N, h), **f32) for _ in range(p)] if algorithm == 2 else None
-        self.Bm = [torch.empty((N, h), dtype=H.dtype, device=dev) for _ in range(p)] if algorithm == 2 else None
         if self.grouped:
             try:
                 self.workspace = torch.empty((group_bytes,), dtype=torch.uint8, device=dev)
@@ -122,6 +126,13 @@ class OutputLayerPlan:
                 self.grouped = False
         if not self.grouped:
             self.workspace = torch.empty((nbytes,), dtype=torch.uint8, device=dev)
+        # Algorithm 2 keeps A = softmax' W_r and B = G W_r of every shard until the barrier
+        self.grouped_S = self.grouped_S and self.grouped
+        # (apart from one another where the calls of a single shard, which take 16-byte aligned matrices, write them)
+        self.A = None
+        if algorithm == 2:
+            self.A = torch.empty((p, N, h), **f32) if self.grouped_S else [torch.empty((N, h), **f32) for _ in range(p)]
+        self.Bm = [torch.empty((N, h), dtype=H.dtype, device=dev) for _ in range(p)] if algorithm == 2 else None
 
     def _on(self, stream):
         """Context in which torch-side fills run on the same stream as the library's kernels."""
@@ -143,7 +154,8 @@ class OutputLayerPlan:
         return [t if t.shape[0] == v else t[:v] for t, v in zip(tensors, self.valid[:self.live])]
 
     def forward(self, stream=None) -> None:
-        for r in range(self.live if self.algorithm == 1 and self.grouped else 0, self.p):
+        in_one_call = self.grouped if self.algorithm == 1 else self.grouped_S
+        for r in range(self.live if in_one_call else 0, self.p):
             v = self.valid[r]
             if v == 0:     # all padding: the neutral element of the combine (exp(-inf) = 0)
                 with self._on(stream):
@@ -160,18 +172,29 @@ class OutputLayerPlan:
                 B.vp_output_fwd_alg2(self.H, self._real(self.W, r), self.labels, self.offsets[r],
                                      self.local_max[r], self.local_sumexp[r], self.local_target[r],
                                      self.A[r], self.Bm[r], lg, self.workspace, stream)
-        if self.algorithm == 1 and self.grouped:
+        if in_one_call:
             q = self.live
             stats = (self.local_max, self.local_sumexp, self.local_target)
-            B.vp_output_fwd_group(self.H, self._live(self.W), self.labels, self.offsets[:q],
-                                  *(stats if q == self.p else (t[:q] for t in stats)),
-                                  self.logits[:q] if self.logits is not None else None, self.workspace, stream)
+            stats = stats if q == self.p else tuple(t[:q] for t in stats)
+            lg = self.logits[:q] if self.logits is not None else None
+            if self.algorithm == 1:
+                B.vp_output_fwd_group(self.H, self._live(self.W), self.labels, self.offsets[:q], *stats, lg, self.workspace,
+                                      stream)
+            else:
+                B.vp_output_fwd_alg2_group(self.H, self._live(self.W), self.labels, self.offsets[:q], *stats, self.A[:q],
+                                           self.Bm[:q], lg, self.workspace, stream)
         B.vp_combine_stats(self.local_max, self.local_sumexp, self.local_target,
                            self.global_max, self.global_sumexp, self.loss_rows, self.loss, stream)
         if self.algorithm == 2:
             # still inside the one barrier of Algorithm 2: the input gradient leaves here; the first shard
             # that contributes overwrites dH, so nothing is zero-filled
             first = True
+            if self.grouped_S:
+                q = self.live
+                B.vp_output_dx_alg2_gather(self.A[:q], self._live(self.W), self.labels, self.offsets[:q], self.local_max[:q],
+                                           self.local_sumexp[:q], self.global_max, self.global_sumexp, self.grad_scale,
+                                           self.dH, stream, dh_overwrite=True)
+                return
             if self.grouped:
                 q = self.live
                 B.vp_output_dx_alg2_group(self.A[:q], self.Bm[:q], self.local_max[:q], self.local_sumexp[:q],
