@@ -51,8 +51,8 @@ __device__ __forceinline__ void mfma_tile(floatx16& c, const bf16x8& a, const bf
 // W past the end are read as zeros), so they stay -inf: they leave the row maximum alone and add
 // exp(-inf) = 0 to the sum, with no masking pass over the accumulators in the epilogue.  Written
 // straight into the AGPR half of the register file, like the zeros.
-template <int NJ, int WN>
-__device__ __forceinline__ void init_acc_ragged(floatx16 (&acc)[4][NJ], int n_cols, int tile_n) {
+template <int NJ, int WN, int MI>
+__device__ __forceinline__ void init_acc_ragged(floatx16 (&acc)[MI][NJ], int n_cols, int tile_n) {
     const int lane = threadIdx.x & 63;
     const int wn = (threadIdx.x >> 6) % WN;
     // this lane holds columns cbase + j*32 + 8*(r/4) + r%4; those below nvalid exist
@@ -63,7 +63,7 @@ __device__ __forceinline__ void init_acc_ragged(floatx16 (&acc)[4][NJ], int n_co
         for (int r = 0; r < 16; ++r) {
             const float z = (j * 32 + 8 * (r >> 2) + (r & 3) < nvalid) ? 0.f : -INFINITY;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { float t; asm volatile("v_accvgpr_write_b32 %0, %1" : "=a"(t) : "v"(z)); acc[i][j][r] = t; }
+            for (int i = 0; i < MI; ++i) { float t; asm volatile("v_accvgpr_write_b32 %0, %1" : "=a"(t) : "v"(z)); acc[i][j][r] = t; }
         }
 }
 
@@ -240,8 +240,8 @@ __device__ __forceinline__ void flush_stage_bf16(const char* region, __amdgpu_bu
 // panels the workgroup's next tile re-reads out of the L2 (measured: +6..10 % per launch with
 // four tiles per workgroup, -1.6 % with one; the launcher picks by tiles per workgroup).  A
 // compile-time choice: two stores that differ only in that hint get merged into a plain one.
-template <Epi EPI, int NJ, int WN, bool STREAM>
-__device__ __forceinline__ void gemm_epilogue_f32(floatx16 (&acc)[4][NJ], const GemmBf16Params& g, int tile_m, int tile_n,
+template <Epi EPI, int NJ, int WN, bool STREAM, int MI>
+__device__ __forceinline__ void gemm_epilogue_f32(floatx16 (&acc)[MI][NJ], const GemmBf16Params& g, int tile_m, int tile_n,
                                                   char* region) {
     constexpr int WCOLS = NJ * 32;            // columns owned by one wavefront
     const int tid = threadIdx.x;
@@ -249,14 +249,15 @@ __device__ __forceinline__ void gemm_epilogue_f32(floatx16 (&acc)[4][NJ], const 
     const int wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int l32 = lane & 31, hf = lane >> 5;
-    const int m0 = tile_m * BM, n0 = tile_n * (WN * WCOLS);
+    constexpr int TM = 64 * MI;               // rows of the tile
+    const int m0 = tile_m * TM, n0 = tile_n * (WN * WCOLS);
 
     typedef StageF32<WCOLS> St;
     constexpr bool ACCUM = (EPI == Epi::AccumF32);
     const bool vec = (g.ldc % 4 == 0) && (((uintptr_t)g.C & 15u) == 0);
     const int orow = lane / St::LPR, ochunk = lane % St::LPR;
     const int col = n0 + wn * WCOLS + ochunk * 4;
-    const bool interior = vec && (m0 + BM <= g.M) && (n0 + WN * WCOLS <= g.N);   // uniform over the workgroup
+    const bool interior = vec && (m0 + TM <= g.M) && (n0 + WN * WCOLS <= g.N);   // uniform over the workgroup
     // accumulators of row block i -> the wavefront's staging block
     auto stage = [&](int i) {
 #pragma unroll
@@ -272,7 +273,7 @@ __device__ __forceinline__ void gemm_epilogue_f32(floatx16 (&acc)[4][NJ], const 
         // block ahead, before the previous block's stores: the memory counter a load is waited on also
         // counts the stores issued before it, so waiting for loads issued after a block's stores would
         // mean waiting for those stores to be acknowledged.
-        float* c0 = g.C + (size_t)(m0 + wm * 128 + orow) * g.ldc + col;
+        float* c0 = g.C + (size_t)(m0 + wm * (32 * MI) + orow) * g.ldc + col;
         auto c_at = [&](int i, int s) { return reinterpret_cast<floatx4*>(c0 + (size_t)(i * 32 + s * St::RPI) * g.ldc); };
         floatx4 cv[St::STEPS];
         if (ACCUM) {
@@ -280,7 +281,7 @@ __device__ __forceinline__ void gemm_epilogue_f32(floatx16 (&acc)[4][NJ], const 
             for (int s = 0; s < St::STEPS; ++s) cv[s] = STREAM ? __builtin_nontemporal_load(c_at(0, s)) : *c_at(0, s);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < MI; ++i) {
             stage(i);
             wave_lds_fence();
             // all staged rows are fetched first, then stored
@@ -293,7 +294,7 @@ __device__ __forceinline__ void gemm_epilogue_f32(floatx16 (&acc)[4][NJ], const 
             if (ACCUM) {
 #pragma unroll
                 for (int s = 0; s < St::STEPS; ++s) v[s] += cv[s];
-                if (i < 3) {
+                if (i < MI - 1) {
 #pragma unroll
                     for (int s = 0; s < St::STEPS; ++s)
                         cv[s] = STREAM ? __builtin_nontemporal_load(c_at(i + 1, s)) : *c_at(i + 1, s);
@@ -308,8 +309,8 @@ __device__ __forceinline__ void gemm_epilogue_f32(floatx16 (&acc)[4][NJ], const 
         }
     } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row0 = m0 + wm * 128 + i * 32 + orow;
+        for (int i = 0; i < MI; ++i) {
+            const int row0 = m0 + wm * (32 * MI) + i * 32 + orow;
             stage(i);
             wave_lds_fence();
 #pragma unroll
@@ -325,8 +326,8 @@ __device__ __forceinline__ void gemm_epilogue_f32(floatx16 (&acc)[4][NJ], const 
 }
 
 // The epilogues of pass S (FwdStats) and of the fused pass T (DLogits): bf16 outputs.
-template <Epi EPI, int NJ, int WN, bool STREAM>
-__device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const GemmBf16Params& g, int tile_m, int tile_n,
+template <Epi EPI, int NJ, int WN, bool STREAM, int MI>
+__device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[MI][NJ], const GemmBf16Params& g, int tile_m, int tile_n,
                                                    char* xchg, char* region) {
     constexpr int WCOLS = NJ * 32;            // columns owned by one wavefront
     // Arithmetic on threadIdx does not depend on the tile, so it is hoisted above the caller's tile
@@ -340,9 +341,10 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
     const int tid = wave * 64 + lane;
     const int wm = wave / WN, wn = wave % WN;
     const int l32 = lane & 31, hf = lane >> 5;
-    const int m0 = tile_m * BM, n0 = tile_n * BN;
+    constexpr int TM = 64 * MI;               // rows of the tile
+    const int m0 = tile_m * TM, n0 = tile_n * BN;
     // element (i, j, r) of this lane: row = rbase + i*32, col = cbase + j*32 + 8*(r/4) + (r%4)
-    const int rbase = m0 + wm * 128 + l32;
+    const int rbase = m0 + wm * (32 * MI) + l32;
     const int cbase = n0 + wn * WCOLS + 4 * hf;
 
     if (EPI == Epi::DLogits) {
@@ -353,20 +355,20 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
         const int ocol = n0 + wn * WCOLS + ochunk * 8;
         const unsigned row_bytes = (unsigned)g.ldy * 2u;
         const __amdgpu_buffer_rsrc_t rs =
-            tile_rows_rsrc(g.Y + (size_t)m0 * g.ldy, g.M - m0 < BM ? g.M - m0 : BM, row_bytes);
+            tile_rows_rsrc(g.Y + (size_t)m0 * g.ldy, g.M - m0 < TM ? g.M - m0 : TM, row_bytes);
         const unsigned off0 =
-            (ocol + 8 <= g.N) ? (unsigned)(wm * 128 + orow) * row_bytes + (unsigned)ocol * 2u : OOB_OFFSET;
+            (ocol + 8 <= g.N) ? (unsigned)(wm * (32 * MI) + orow) * row_bytes + (unsigned)ocol * 2u : OOB_OFFSET;
         const bool tail = n0 + WN * WCOLS > g.N && g.N % 8 != 0;
         const int n_tail = ocol + 8 > g.N && ocol < g.N ? g.N - ocol : 0;
-        const unsigned off_tail = (unsigned)(wm * 128 + orow) * row_bytes + (unsigned)ocol * 2u;
+        const unsigned off_tail = (unsigned)(wm * (32 * MI) + orow) * row_bytes + (unsigned)ocol * 2u;
         // all loads come before the first store (see the note on the labels in the FwdStats branch)
-        float ml2_[4], f_[4];
-        int lab_[4];
+        float ml2_[MI], f_[MI];
+        int lab_[MI];
         {
-            float gm[4], gs[4];
-            int64_t lraw[4];
+            float gm[MI], gs[MI];
+            int64_t lraw[MI];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < MI; ++i) {
                 const int row = rbase + i * 32;
                 const int rowc = row < g.M ? row : g.M - 1;      // rows past the end compute on a copy, store nothing
                 gm[i] = g.gmax[rowc];
@@ -374,7 +376,7 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
                 lraw[i] = g.labels[rowc];
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < MI; ++i) {
                 const int64_t lab64 = lraw[i] - g.shard_offset - cbase;
                 // column of the label relative to cbase, or -1 when it is not in this lane's range
                 lab_[i] = (lab64 >= 0 && lab64 < WCOLS) ? (int)lab64 : -1;
@@ -382,13 +384,12 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
                 f_[i] = (1.0f / gs[i]) * g.scale;
             }
             // keep the derived values, not the inputs
-            asm volatile("" : "+v"(lab_[0]), "+v"(lab_[1]), "+v"(lab_[2]), "+v"(lab_[3]));
-            asm volatile("" : "+v"(ml2_[0]), "+v"(ml2_[1]), "+v"(ml2_[2]), "+v"(ml2_[3]));
-            asm volatile("" : "+v"(f_[0]), "+v"(f_[1]), "+v"(f_[2]), "+v"(f_[3]));
+#pragma unroll
+            for (int i = 0; i < MI; ++i) asm volatile("" : "+v"(lab_[i]), "+v"(ml2_[i]), "+v"(f_[i]));
         }
         {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < MI; ++i) {
                 // One row block at a time: left alone, the scheduler uses every free register to overlap the
                 // blocks and then spills, and a reload after the first stores waits for them (a reload is a load).
                 __builtin_amdgcn_sched_barrier(0);
@@ -416,7 +417,7 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
                 wave_lds_fence();
                 const unsigned down = (unsigned)(i * 32) * row_bytes;
                 flush_stage_bf16<St, STREAM>(region, rs, off0 + down, row_bytes, orow, ochunk, tail, off_tail + down, n_tail,
-                                             g.M - (m0 + wm * 128 + i * 32));
+                                             g.M - (m0 + wm * (32 * MI) + i * 32));
                 wave_lds_fence();
             }
         }
@@ -435,26 +436,26 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
         const int ocol = n0 + wn * WCOLS + ochunk * 8;
         const unsigned row_bytes = (unsigned)g.ldy * 2u;
         const __amdgpu_buffer_rsrc_t rs =
-            tile_rows_rsrc(g.Y ? g.Y + (size_t)m0 * g.ldy : nullptr, g.Y ? (g.M - m0 < BM ? g.M - m0 : BM) : 0, row_bytes);
+            tile_rows_rsrc(g.Y ? g.Y + (size_t)m0 * g.ldy : nullptr, g.Y ? (g.M - m0 < TM ? g.M - m0 : TM) : 0, row_bytes);
         const unsigned off0 =
-            (ocol + 8 <= g.N) ? (unsigned)(wm * 128 + orow) * row_bytes + (unsigned)ocol * 2u : OOB_OFFSET;
+            (ocol + 8 <= g.N) ? (unsigned)(wm * (32 * MI) + orow) * row_bytes + (unsigned)ocol * 2u : OOB_OFFSET;
         const bool tail = n0 + WN * WCOLS > g.N && g.N % 8 != 0;
         const int n_tail = ocol + 8 > g.N && ocol < g.N ? g.N - ocol : 0;
-        const unsigned off_tail = (unsigned)(wm * 128 + orow) * row_bytes + (unsigned)ocol * 2u;
+        const unsigned off_tail = (unsigned)(wm * (32 * MI) + orow) * row_bytes + (unsigned)ocol * 2u;
         // The labels of the wavefront's four row blocks are fetched before the first store of
         // logits: the memory counter a load is waited on also counts the stores issued before it,
         // so a load inside the loop below would wait for the previous block's stores to be
         // acknowledged and serialise the epilogue.
-        int64_t lraw[4];
+        int64_t lraw[MI];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) lraw[i] = (rbase + i * 32 < g.M) ? g.labels[rbase + i * 32] : (int64_t)-1;
+        for (int i = 0; i < MI; ++i) lraw[i] = (rbase + i * 32 < g.M) ? g.labels[rbase + i * 32] : (int64_t)-1;
         // lab[i]: column of row block i's label relative to cbase if this lane holds it, else -1
-        int lab[4];
+        int lab[MI];
         // (columns past the shard in the ragged last column tile hold -inf: see init_acc)
         auto blocks = [&](auto store_c) {
         constexpr bool STORE = decltype(store_c)::value;       // whether the logits are kept
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < MI; ++i) {
             __builtin_amdgcn_sched_barrier(0);          // one row block at a time (see the DLogits branch)
             float v = acc[i][0][0];
 #pragma unroll
@@ -472,19 +473,20 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
                 for (int r = 0; r < 16; ++r) s += exp2_fast(fmaf(acc[i][j][r], LOG2E, -ml2));
             s += __shfl_xor(s, 32, 64);
             if (hf == 0) {
-                const int lr = wm * 128 + i * 32 + l32;
+                const int lr = wm * (32 * MI) + i * 32 + l32;
                 xm[wn * 256 + lr] = m;
                 xs[wn * 256 + lr] = s;
             }
             if (i == 0) {
-                // the four loads have had the first block's arithmetic to arrive
+                // the loads have had the first block's arithmetic to arrive
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
+                for (int k = 0; k < MI; ++k) {
                     const int64_t lab64 = lraw[k] - g.shard_offset - cbase;
                     const bool mine = lraw[k] >= 0 && lab64 >= 0 && lab64 < WCOLS && (lab64 & 4) == 0 && lab64 + cbase < g.N;
                     lab[k] = mine ? (int)lab64 : -1;
                 }
-                asm volatile("" : "+v"(lab[0]), "+v"(lab[1]), "+v"(lab[2]), "+v"(lab[3]));   // narrowed here, not at the use
+#pragma unroll
+                for (int k = 0; k < MI; ++k) asm volatile("" : "+v"(lab[k]));      // narrowed here, not at the use
             }
             // at most one element per row is a target logit: wavefront-uniform branch
             if (__builtin_amdgcn_ballot_w64(lab[i] >= 0) != 0) {
@@ -507,7 +509,7 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
                 wave_lds_fence();
                 const unsigned down = (unsigned)(i * 32) * row_bytes;
                 flush_stage_bf16<St, STREAM>(region, rs, off0 + down, row_bytes, orow, ochunk, tail, off_tail + down, n_tail,
-                                             g.M - (m0 + wm * 128 + i * 32));
+                                             g.M - (m0 + wm * (32 * MI) + i * 32));
                 wave_lds_fence();
             }
         }
@@ -516,7 +518,7 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
         if (!g.Y) blocks(std::false_type{});
         else blocks(std::true_type{});
         __syncthreads();
-        if (tid < 256) {
+        if (tid < TM) {
             const int row = m0 + tid;
             if (row < g.M) {
                 float m = -INFINITY;
@@ -535,13 +537,13 @@ __device__ __forceinline__ void gemm_epilogue_bf16(floatx16 (&acc)[4][NJ], const
     }
 }
 
-template <Epi EPI, int NJ, int WN, bool STREAM>
-__device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[4][NJ], const GemmBf16Params& g, int tile_m, int tile_n,
+template <Epi EPI, int NJ, int WN, bool STREAM, int MI>
+__device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[MI][NJ], const GemmBf16Params& g, int tile_m, int tile_n,
                                               char* xchg, char* region) {
     if constexpr (EPI == Epi::StoreF32 || EPI == Epi::AccumF32)
-        gemm_epilogue_f32<EPI, NJ, WN, STREAM>(acc, g, tile_m, tile_n, region);
+        gemm_epilogue_f32<EPI, NJ, WN, STREAM, MI>(acc, g, tile_m, tile_n, region);
     else
-        gemm_epilogue_bf16<EPI, NJ, WN, STREAM>(acc, g, tile_m, tile_n, xchg, region);
+        gemm_epilogue_bf16<EPI, NJ, WN, STREAM, MI>(acc, g, tile_m, tile_n, xchg, region);
 }
 
 }  // namespace vp
