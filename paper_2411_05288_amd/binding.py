@@ -2,12 +2,14 @@
 
 Tensors are torch tensors on the GPU; bf16 data may be passed as torch.bfloat16 or as
 int16/uint16 bit patterns.  Nothing here computes: the functions check dtype / device /
-contiguity, take raw pointers and the current HIP stream, and call the library.  There is no
-fallback: if libvp.so is missing or a call fails, an exception is raised.
+contiguity, take raw pointers and the current HIP stream, and call the library.  The checks run in
+native code (_vphost.so); what does not pass there is checked again here, where the message is made.
+There is no fallback: if a library is missing or a call fails, an exception is raised.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Optional
 
@@ -29,6 +31,7 @@ VP_CALL_OUTPUT_DX_ALG2 = 6
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
+_HOST = None      # _vphost.so, loaded with the library
 
 
 class VPError(RuntimeError):
@@ -41,12 +44,19 @@ def lib_path() -> str:
 
 def load_library() -> ctypes.CDLL:
     """Loads libvp.so (built by ``python -m paper_2411_05288_amd.build``)."""
-    global _LIB
+    global _LIB, _HOST
     if _LIB is not None:
         return _LIB
     path = lib_path()
-    if not os.path.exists(path):
-        raise VPError("libvp.so not found at %s: build it with `python -m paper_2411_05288_amd.build`" % path)
+    host = os.path.join(_HERE, "_vphost.so")
+    for f in (path, host):
+        if not os.path.exists(f):
+            raise VPError("%s not found at %s: build it with `python -m paper_2411_05288_amd.build`" % (os.path.basename(f), f))
+    if _HOST is None:
+        spec = importlib.util.spec_from_file_location("_vphost", host)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        _HOST = module
     lib = ctypes.CDLL(path)
     c = ctypes
     vp, i64, i32, u32, sz, fl = c.c_void_p, c.c_int64, c.c_int32, c.c_uint32, c.c_size_t, c.c_float
@@ -136,6 +146,10 @@ def _dtype_code(t: torch.Tensor) -> int:
 def _ptr(t: Optional[torch.Tensor], name: str, dtypes=None, shape=None) -> Optional[int]:
     if t is None:
         return None
+    if _HOST is not None:
+        p = _HOST.ptr(t, dtypes, shape)
+        if p is not None:
+            return p
     if not t.is_cuda:
         raise VPError("%s must be a GPU tensor" % name)
     if not t.is_contiguous():
@@ -149,11 +163,24 @@ def _ptr(t: Optional[torch.Tensor], name: str, dtypes=None, shape=None) -> Optio
 
 def _ptrs(ts, name: str, dtypes, shape):
     """Array of the device pointers of one tensor per shard."""
+    if _HOST is not None:
+        a = _HOST.ptrs(ts, dtypes, shape)
+        if a is not None:
+            return a
     return (ctypes.c_void_p * len(ts))(*[_ptr(t, name, dtypes, shape) for t in ts])
+
+
+def same_shapes(ts) -> bool:
+    """Whether all tensors of the list have one shape."""
+    same = _HOST.same_shapes(ts) if _HOST is not None else None
+    return all(t.shape == ts[0].shape for t in ts) if same is None else same
 
 
 def _stream(stream) -> int:
     if stream is None:
+        s = _HOST.stream() if _HOST is not None else None
+        if s is not None:
+            return s
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
@@ -293,6 +320,10 @@ def _each(ts, name, dtypes, shapes):
         return None
     if len(ts) != len(shapes):
         raise VPError("%s: one tensor per shard" % name)
+    if _HOST is not None:
+        a = _HOST.ptrs(ts, dtypes, shapes)
+        if a is not None:
+            return a
     return (ctypes.c_void_p * len(ts))(*[_ptr(t, name, dtypes, s) for t, s in zip(ts, shapes)])
 
 

@@ -1,4 +1,5 @@
-"""Builds libvp.so (the C-ABI library with the HIP kernels) for gfx950 with hipcc.
+"""Builds libvp.so (the C-ABI library with the HIP kernels) for gfx950 with hipcc, and _vphost.so, the tensor checks of the
+Python binding, with the host compiler against PyTorch's headers.
 
 Usage:  python -m paper_2411_05288_amd.build
 The library is placed next to this file so that it travels with the source tree.
@@ -14,6 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvp.so")
+HOST = os.path.join(HERE, "_vphost.so")
 OBJDIR = os.path.join(HERE, "_build")
 
 SOURCES = ["vp_api.hip", "vp_profile.hip", "vp_gemm_bf16.hip", "vp_gemm_bf16_logits.hip", "vp_gemm_bf16_fast.hip", "vp_gemm_bf16_twin.hip", "vp_gemm_f32.hip", "vp_stats.hip", "vp_embed.hip"]
@@ -36,6 +38,23 @@ def _run(cmd):
     return out
 
 
+def _host():
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    tmp = HOST + ".tmp"
+    out = _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+                *["-I" + d for d in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                                     sysconfig.get_paths()["include"], os.path.join(rocm, "include"))],
+                os.path.join(CSRC, "vp_host.cpp"), "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
+                "-lc10_hip", "-o", tmp])
+    os.replace(tmp, HOST)
+    return out
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJDIR, exist_ok=True)
     objs = [os.path.join(OBJDIR, s.replace(".hip", ".o")) for s in SOURCES]
@@ -43,10 +62,12 @@ def build(verbose: bool = False) -> str:
     def one(i):
         return _run([HIPCC, *FLAGS, "-c", os.path.join(CSRC, SOURCES[i]), "-o", objs[i]])
 
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
+        host = ex.submit(_host)
         for out in ex.map(one, range(len(SOURCES))):
             if verbose and out.strip():
                 print(out)
+        host.result()
     tmp = LIB + ".tmp"
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp])
     os.replace(tmp, LIB)

@@ -267,7 +267,7 @@ class EmbeddingPlan:
         self.workspace = torch.empty((nbytes,), dtype=torch.uint8, device=dev)
 
     def forward(self, stream=None) -> None:
-        if self.p > 1 and all(t.shape == self.tables[0].shape for t in self.tables):
+        if self.p > 1 and B.same_shapes(self.tables):
             B.vp_embed_fwd_group(self.tables, self.ids, 0, self.out, stream)
             return
         for r in range(self.p):       # a single shard (the group call costs the host 1 us more), shards of different sizes
