@@ -549,8 +549,9 @@ vp_status vp_output_bwd_group(const void* H, const void* const* W_shards, const 
             }
             hipError_t e = logits_saved ? hipSuccess : launch_gemm_f32_logits((const float*)H, N, h, y, n, z.S_logits, slices, st);
             if (e == hipSuccess) e = launch_dlogits_group(l, 0, labels, global_max, global_sumexp, 0, grad_scale, (int)N, st);
-            if (e == hipSuccess && !skip_dh) e = launch_gemm_f32_dh(N, h, g, n, z.S, dH_accum, !overwrite, slices, st);
-            if (e == hipSuccess) e = launch_gemm_f32_dw((const float*)H, N, h, g, n, z.S_dw, slices, st);
+            if (e == hipSuccess)
+                e = skip_dh ? launch_gemm_f32_dw((const float*)H, N, h, g, n, z.S_dw, slices, st)
+                            : launch_gemm_f32_dh_dw((const float*)H, N, h, g, n, z.S, z.S_dw, dH_accum, !overwrite, slices, st);
             if (e != hipSuccess) return VP_ERR_DEVICE;
             r0 += n;
             continue;

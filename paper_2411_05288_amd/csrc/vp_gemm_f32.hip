@@ -166,12 +166,12 @@ struct F32Work {
 };
 
 template <bool A_KC, bool B_KC, int TM, int TN>
-__device__ __forceinline__ F32Work f32_work(const GemmF32Params& g) {
+__device__ __forceinline__ F32Work f32_work(const GemmF32Params& g, int bx, int by) {
     constexpr bool CAT_N = A_KC && B_KC, CAT_M = !A_KC && !B_KC, CAT_K = A_KC && !B_KC;
     // Tiles in panels of 8 tile rows, column by column; workgroups are dealt to the 8 XCDs round-robin, so
     // every XCD takes a contiguous run of tiles and shares the operand panels of its run in its L2.
     const int tiles_m = CAT_M ? g.total : (g.M + TM - 1) / TM, tiles_n = CAT_N ? g.total : (g.N + TN - 1) / TN;
-    const int total = tiles_m * tiles_n, b = blockIdx.x;
+    const int total = tiles_m * tiles_n, b = bx;
     const int x = b & 7, per = total >> 3, rem = total & 7;
     const int t = x * per + (x < rem ? x : rem) + (b >> 3);
     const int panel = t / (8 * tiles_n), in_panel = t - panel * 8 * tiles_n;
@@ -179,8 +179,8 @@ __device__ __forceinline__ F32Work f32_work(const GemmF32Params& g) {
     int tile_m = panel * 8 + in_panel % prows, tile_n = in_panel / prows;
 
     // the shard of this tile (or slice), its operands and its part of the output
-    int shard = CAT_K ? blockIdx.y / g.slices : 0;
-    const int slice = CAT_K ? blockIdx.y - shard * g.slices : blockIdx.y;
+    int shard = CAT_K ? by / g.slices : 0;
+    const int slice = CAT_K ? by - shard * g.slices : by;
     if (!CAT_K) {
         const int tc = CAT_N ? tile_n : tile_m;
 #pragma unroll
@@ -203,7 +203,7 @@ __device__ __forceinline__ F32Work f32_work(const GemmF32Params& g) {
     const int K = CAT_K ? s.rows : g.K;
     w.k_begin = min(K, slice * g.k_per_slice);
     w.k_end = min(K, w.k_begin + g.k_per_slice);
-    w.C = (CAT_K ? g.C : s.C) + (int64_t)blockIdx.y * g.slice_stride;
+    w.C = (CAT_K ? g.C : s.C) + (int64_t)by * g.slice_stride;
     return w;
 }
 
@@ -256,20 +256,23 @@ __device__ __forceinline__ void f32_finish(floatx16 v, const F32Work& w, int row
     }
 }
 
-// MT x NT MFMA tiles of 32 x 32 per wavefront, SK of K per LDS stage, PD stages of global loads in flight in registers,
-// WPC workgroups per compute unit.
-template <bool A_KC, bool B_KC, int MT, int NT, int SK, int PD, int WPC, bool VEC>
-__global__ __launch_bounds__(F_THREADS, WPC) void gemm_f32_kernel(GemmF32Params g) {
+// Workgroup (bx, by) of a product: MT x NT MFMA tiles of 32 x 32 per wavefront, SK of K per LDS stage, PD stages of global loads
+// in flight in registers.
+template <int MT, int NT, int SK>
+constexpr int f32_lds_bytes() { return 2 * 3 * 2 * SK * 64 * (MT + NT); }
+
+template <bool A_KC, bool B_KC, int MT, int NT, int SK, int PD, bool VEC>
+__device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& g, char* lds, int bx, int by) {
     constexpr int TM = 64 * MT, TN = 64 * NT;
     constexpr bool SCALE = !(A_KC && B_KC);      // A is D
     typedef F32Tile<A_KC, TM, SK> TA;
     typedef F32Tile<B_KC, TN, SK> TB;
     constexpr int STAGE = 3 * (TA::PLANE + TB::PLANE);
-    __shared__ __attribute__((aligned(16))) char lds[2 * STAGE];
+    static_assert(2 * STAGE == f32_lds_bytes<MT, NT, SK>(), "two stages");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const F32Work w = f32_work<A_KC, B_KC, TM, TN>(g);
+    const F32Work w = f32_work<A_KC, B_KC, TM, TN>(g, bx, by);
     constexpr int KS = SK / 16;
     static_assert(MT * NT == 8 || MT * NT == 4 ? KS == 1 : MT * NT == 1 && KS == 2, "tile");
     floatx16 acc[KS][MT][NT];
@@ -396,6 +399,24 @@ __global__ __launch_bounds__(F_THREADS, WPC) void gemm_f32_kernel(GemmF32Params 
         }
 }
 
+// WPC workgroups per compute unit.
+template <bool A_KC, bool B_KC, int MT, int NT, int SK, int PD, int WPC, bool VEC>
+__global__ __launch_bounds__(F_THREADS, WPC) void gemm_f32_kernel(GemmF32Params g) {
+    __shared__ __attribute__((aligned(16))) char lds[f32_lds_bytes<MT, NT, SK>()];
+    gemm_f32_tile<A_KC, B_KC, MT, NT, SK, PD, VEC>(g, lds, blockIdx.x, blockIdx.y);
+}
+
+// dH and dW in one launch: the first `nh` workgroups are dH's, hx in a row of its grid.  Neither needs the other, and where one
+// alone does not fill the chip, its workgroups wait (for loads, LDS and barriers) more than they multiply: N=128 h=256 V=8192
+// p=2: 12.8 + 11.3 us -> 17.6, the step 48.3 -> 40.7; N=128 h=320 V=18549 p=4: 22.9 + 20.8 -> 33.5, 81 -> 72.
+template <int MT, int NT, int SK, int PD, int WPC>
+__global__ __launch_bounds__(F_THREADS, WPC) void gemm_f32_dh_dw_kernel(GemmF32Params h, GemmF32Params w, int nh, int hx) {
+    __shared__ __attribute__((aligned(16))) char lds[f32_lds_bytes<MT, NT, SK>()];
+    const int b = blockIdx.x;
+    if (b < nh) gemm_f32_tile<true, false, MT, NT, SK, PD, true>(h, lds, b % hx, b / hx);
+    else gemm_f32_tile<false, false, MT, NT, SK, PD, true>(w, lds, b - nh, 0);
+}
+
 // Estimated time of `wg` workgroups over k steps of K each.  A workgroup alone on a compute unit takes `alone` us per 16 k
 // (a chain of load, split, LDS and products); several share the unit at `each` us (K = 1024: 256 tiles of 64 x 64 28 us, 1024 of
 // them 88; 64 tiles of 128 x 128 61; 512 of the largest 170).
@@ -426,8 +447,9 @@ size_t gemm_f32_scratch_floats(int64_t M, int64_t N, int64_t K) {
     return S > 1 ? (size_t)S * (size_t)M * (size_t)N : 0;
 }
 
+// Fills first and total for this tile and returns the grid.
 template <bool A_KC, bool B_KC>
-static void launch_f32_t(GemmF32Params& g, int tile, hipStream_t st) {
+static dim3 f32_grid(GemmF32Params& g, int tile) {
     constexpr bool DW = !A_KC;
     const int tile_m = tile == 256 && !DW ? 128 : tile, tile_n = tile == 256 && DW ? 128 : tile;
     int64_t tm = ceil_div(g.M, tile_m), tn = ceil_div(g.N, tile_n), cat = 0;
@@ -440,7 +462,13 @@ static void launch_f32_t(GemmF32Params& g, int tile, hipStream_t st) {
     if (A_KC && B_KC) tn = cat;
     else if (!A_KC) tm = cat;
     else z *= g.n;
-    const dim3 grid((unsigned)(tm * tn), (unsigned)z);
+    return dim3((unsigned)(tm * tn), (unsigned)z);
+}
+
+template <bool A_KC, bool B_KC>
+static void launch_f32_t(GemmF32Params& g, int tile, hipStream_t st) {
+    constexpr bool DW = !A_KC;
+    const dim3 grid = f32_grid<A_KC, B_KC>(g, tile);
     const bool vec = g.a_vec && g.b_vec;
 #define VP_LAUNCH(...) hipLaunchKernelGGL((gemm_f32_kernel<A_KC, B_KC, __VA_ARGS__>), grid, dim3(F_THREADS), 0, st, g)
     if (tile == 256) VP_LAUNCH((DW ? 4 : 2), (DW ? 2 : 4), 16, 1, 2, true);
@@ -473,19 +501,27 @@ static int tile_for(const GemmF32Params& g, bool a_kc, bool b_kc) {
     return tile;
 }
 
-// Launches the product; C is [M, N] with row stride ldc where the shards share the output (dH).  With more than one K slice
-// (dH: of all shards together) the partial outputs go through scratch, every slice laid out like the output, or like the
-// outputs of the shards one behind the other.
-static hipError_t launch_f32(GemmF32Params g, bool a_kc, bool b_kc, float* C, int64_t ldc, bool accumulate, float* scratch,
-                             hipStream_t st) {
+// A product ready to be launched; C is [M, N] with row stride ldc where the shards share the output (dH).  With more than one K
+// slice (dH: of all shards together) the partial outputs go through scratch, every slice laid out like the output, or like
+// the outputs of the shards one behind the other.
+struct F32Launch {
+    GemmF32Params g;
+    bool a_kc, b_kc, accumulate;
+    int tile, parts;
+    float* scratch;
+    SumList l;
+};
+
+static F32Launch prepare_f32(const GemmF32Params& g0, bool a_kc, bool b_kc, float* C, int64_t ldc, bool accumulate, float* scratch) {
+    F32Launch f{g0, a_kc, b_kc, accumulate, tile_for(g0, a_kc, b_kc), 0, scratch, {}};
+    GemmF32Params& g = f.g;
     const bool cat_n = a_kc && b_kc, cat_k = a_kc && !b_kc;
-    const int parts = g.slices * (cat_k ? g.n : 1);
-    const int tile = tile_for(g, a_kc, b_kc);
+    f.parts = g.slices * (cat_k ? g.n : 1);
     g.C = C;
     if (!cat_n) g.ldc = ldc;
     g.accumulate = accumulate ? 1 : 0;
-    SumList l{};
-    if (parts > 1) {
+    if (f.parts > 1) {
+        SumList& l = f.l;
         l.n = cat_k ? 1 : g.n;
         for (int r = 0; r < l.n; ++r) {
             GemmF32Shard& s = g.sh[r];
@@ -498,13 +534,24 @@ static hipError_t launch_f32(GemmF32Params g, bool a_kc, bool b_kc, float* C, in
         g.C = scratch;
         g.accumulate = 0;
     }
-    if (cat_n) launch_f32_t<true, true>(g, tile, st);
-    else if (cat_k) launch_f32_t<true, false>(g, tile, st);
-    else if (!b_kc) launch_f32_t<false, false>(g, tile, st);
+    return f;
+}
+
+static hipError_t launch_f32(F32Launch& f, hipStream_t st) {
+    if (f.a_kc && f.b_kc) launch_f32_t<true, true>(f.g, f.tile, st);
+    else if (f.a_kc) launch_f32_t<true, false>(f.g, f.tile, st);
+    else if (!f.b_kc) launch_f32_t<false, false>(f.g, f.tile, st);
     else return hipErrorInvalidValue;
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || parts == 1) return e;
-    return launch_sum_slices(scratch, parts, g.slice_stride, l, accumulate, st);
+    return hipGetLastError();
+}
+
+static hipError_t sum_f32(const F32Launch& f, hipStream_t st) {
+    return f.parts == 1 ? hipSuccess : launch_sum_slices(f.scratch, f.parts, f.g.slice_stride, f.l, f.accumulate, st);
+}
+
+static hipError_t launch_and_sum_f32(F32Launch f, hipStream_t st) {
+    const hipError_t e = launch_f32(f, st);
+    return e == hipSuccess ? sum_f32(f, st) : e;
 }
 
 hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float* B, int64_t sbn, int64_t sbk,
@@ -529,7 +576,7 @@ hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float
     s.A = A; s.B = B; s.C = C;
     s.rows = a_kc && b_kc ? N : a_kc ? K : M;
     s.ld = (int)(a_kc && b_kc ? ldc : g.lda);
-    return launch_f32(g, a_kc, b_kc, C, ldc, accumulate, scratch, st);
+    return launch_and_sum_f32(prepare_f32(g, a_kc, b_kc, C, ldc, accumulate, scratch), st);
 }
 
 // The three products over n shards (see GemmBf16Group for how they are laid end to end; here a K slice never crosses a
@@ -550,7 +597,7 @@ hipError_t launch_gemm_f32_logits(const float* H, int64_t N, int64_t h, const Ge
     g.slices = (int)ceil_div(h, g.k_per_slice);
     g.n = n;
     for (int r = 0; r < n; ++r) g.sh[r] = sh[r];
-    return launch_f32(g, true, true, nullptr, 0, false, scratch, st);
+    return launch_and_sum_f32(prepare_f32(g, true, true, nullptr, 0, false, scratch), st);
 }
 
 static GemmF32Params dh_params(int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices) {
@@ -573,12 +620,10 @@ static GemmF32Params dh_params(int64_t N, int64_t h, const GemmF32Shard* sh, int
 hipError_t launch_gemm_f32_dh(int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* dH, bool accumulate,
                               float* scratch, hipStream_t st) {
     ProfScope prof(K_GEMM_F32, st);
-    return launch_f32(dh_params(N, h, sh, n, slices), true, false, dH, h, accumulate, scratch, st);
+    return launch_and_sum_f32(prepare_f32(dh_params(N, h, sh, n, slices), true, false, dH, h, accumulate, scratch), st);
 }
 
-hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* scratch,
-                              hipStream_t st) {
-    ProfScope prof(K_GEMM_F32, st);
+static GemmF32Params dw_params(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices) {
     GemmF32Params g{};
     g.B = H;
     g.ldb = h;
@@ -589,7 +634,37 @@ hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF3
     g.slices = (int)ceil_div(N, g.k_per_slice);
     g.n = n;
     for (int r = 0; r < n; ++r) g.sh[r] = sh[r];
-    return launch_f32(g, false, false, nullptr, h, false, scratch, st);
+    return g;
+}
+
+hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* scratch,
+                              hipStream_t st) {
+    ProfScope prof(K_GEMM_F32, st);
+    return launch_and_sum_f32(prepare_f32(dw_params(H, N, h, sh, n, slices), false, false, nullptr, h, false, scratch), st);
+}
+
+// Both products of pass T.  One launch where both take the same tiles and together have at most four workgroups per compute
+// unit (three fit): 840 of them (N=300 h=1000 V=5001 p=3) 117 -> 115 us a step, 1024 (N=400 h=512 V=16000 p=4) 219 -> 211, 1050 (N=781
+// h=704 V=6252 p=16) 227 -> 229.  dW in slices needs the scratch that dH's slices are in, so it comes after their sum.
+hipError_t launch_gemm_f32_dh_dw(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, int dh_slices, int dw_slices,
+                                 float* dH, bool accumulate, float* scratch, hipStream_t st) {
+    F32Launch a = prepare_f32(dh_params(N, h, sh, n, dh_slices), true, false, dH, h, accumulate, scratch);
+    F32Launch b = prepare_f32(dw_params(H, N, h, sh, n, dw_slices), false, false, nullptr, h, false, scratch);
+    if (a.tile == b.tile && a.tile <= 128 && b.parts == 1 && a.g.b_vec && b.g.b_vec) {
+        const dim3 ga = f32_grid<true, false>(a.g, a.tile), gb = f32_grid<false, false>(b.g, b.tile);
+        const int na = (int)(ga.x * ga.y), nb = (int)gb.x;
+        if (na + nb <= 1024) {
+            ProfScope prof(K_GEMM_F32, st);
+            if (a.tile == 64)
+                hipLaunchKernelGGL((gemm_f32_dh_dw_kernel<1, 1, 32, 1, 3>), dim3(na + nb), dim3(F_THREADS), 0, st, a.g, b.g, na, (int)ga.x);
+            else
+                hipLaunchKernelGGL((gemm_f32_dh_dw_kernel<2, 2, 16, 2, 3>), dim3(na + nb), dim3(F_THREADS), 0, st, a.g, b.g, na, (int)ga.x);
+            const hipError_t e = hipGetLastError();
+            return e == hipSuccess ? sum_f32(a, st) : e;
+        }
+    }
+    const hipError_t e = launch_gemm_f32_dh(N, h, sh, n, dh_slices, dH, accumulate, scratch, st);
+    return e == hipSuccess ? launch_gemm_f32_dw(H, N, h, sh, n, dw_slices, scratch, st) : e;
 }
 
 hipError_t launch_gemm_f32_each(int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* out, float* scratch,

@@ -161,6 +161,9 @@ hipError_t launch_gemm_f32_dh(int64_t N, int64_t h, const GemmF32Shard* sh, int 
 // scratch, if slices > 1: slices * (rows * h of every shard, each rounded up to 4) floats
 hipError_t launch_gemm_f32_dw(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* scratch,
                               hipStream_t st);
+// dH, then dW, or both in one launch (scratch as for the two)
+hipError_t launch_gemm_f32_dh_dw(const float* H, int64_t N, int64_t h, const GemmF32Shard* sh, int n, int dh_slices, int dw_slices,
+                                 float* dH, bool accumulate, float* scratch, hipStream_t st);
 int gemm_f32_dh_slices(int64_t N, int64_t h, int64_t rows, int n);
 // A_r = P_r W_r of every shard (A in sh[].A), out [n, N, h]; scratch, if slices > 1: n * slices * N * h floats
 hipError_t launch_gemm_f32_each(int64_t N, int64_t h, const GemmF32Shard* sh, int n, int slices, float* out, float* scratch,
