@@ -40,7 +40,8 @@ typedef short short4v __attribute__((ext_vector_type(4)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
 // D is scaled by this before it is split and the sums by its inverse (exact): |D| is at most the gradient's scale, and
-// without it the lowest parts of softmax values below 2^-110 would be lost in bf16's smallest numbers.
+// without it the lowest parts of softmax values below 2^-110 would be lost in bf16's smallest numbers (as are those of H and W
+// below 2^-110, next to which every other value of a sum would have to be as small).
 constexpr float D_SCALE = 0x1p64f;
 
 __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
