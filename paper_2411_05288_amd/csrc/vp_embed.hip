@@ -458,14 +458,14 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("" ::: "memory");
 }
 
-// A run of any length by the whole workgroup of 16 wavefronts: chunks of 16 B tokens, wavefront w has tokens
+// A run of any length by the whole workgroup of NW (16) wavefronts: chunks of 16 B tokens, wavefront w has tokens
 // B w .. B w + B - 1 of a chunk and turn w in the chain, the running sum passes from wavefront to wavefront through
 // LDS, so the adds of a column happen in token order and the result equals the in-order loop bit for bit.
 // Bound by the row loads at first (one compute unit alone draws little from memory) and by the chain after that: the
 // rows of a chunk are requested by all wavefronts at once and while the previous chunk's chain runs, and every
 // wavefront turns its rows into floats (-0.0f past cnt) before the chain starts, so that a turn is nothing but
 // dependent adds.  token_at(j): token of position j of the run.
-template <typename T, int VEC, typename Rows, typename TokenAt>
+template <typename T, int VEC, int NW, typename Rows, typename TokenAt>
 __device__ __forceinline__ void sum_long_run(int len, float* d, bool active, int lane, int wave, float* xchg,
                                              const Rows& rows, const TokenAt& token_at) {
     typedef typename FusedVec<T, VEC>::type GV;
@@ -481,9 +481,9 @@ __device__ __forceinline__ void sum_long_run(int len, float* d, bool active, int
         const unsigned tok = lane < cnt ? token_at(wave * B + lane) : 0u;
         if (cnt > 0) load_batch<B>(v, rows, tok, cnt);
     }
-    for (int c = 0; c < len; c += FUSED_WAVES * B) {
-        const int turns = len - c > FUSED_WAVES * B ? FUSED_WAVES : (len - c + B - 1) / B;
-        const int first_n = c + FUSED_WAVES * B + wave * B;
+    for (int c = 0; c < len; c += NW * B) {
+        const int turns = len - c > NW * B ? NW : (len - c + B - 1) / B;
+        const int first_n = c + NW * B + wave * B;
         const int cnt_n = len - first_n < 0 ? 0 : (len - first_n > B ? B : len - first_n);
         const unsigned tok_n = lane < cnt_n ? token_at(first_n + lane) : 0u;
         if (c == 0 && wave == 0) {
@@ -716,9 +716,91 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_fused_kernel(EmbedBwd
             const int s = __builtin_amdgcn_readfirstlane((int)run_start[r]);
             const int len = __builtin_amdgcn_readfirstlane((int)run_start[r + 1]) - s;
             float* const d = dtable_row(g, __builtin_amdgcn_readfirstlane(key_row(sh[s])), (unsigned)Vs, h) + c0;
-            sum_long_run<T, VEC>(len, d, active, lane, wave, xchg, rows,
+            sum_long_run<T, VEC, FUSED_WAVES>(len, d, active, lane, wave, xchg, rows,
                                  [&](int j) { return key_token(sh[s + j]); });
         }
+    }
+}
+
+// ------------------------------------------------------------------------- backward: few tokens
+// Up to FEW_MAX_N tokens (and FEW_MAX_WAVES tokens times slabs) nothing is sorted: a wavefront per token and slab of 64 * VEC
+// columns looks its row up among all tokens' rows (in LDS, 64 per ballot), has nothing to do if an earlier token has it, and
+// else sums the row's tokens in order; rows of many tokens are summed by all wavefronts of its workgroup.  What bounds it is a
+// launch, the ids and one round of rows; the sort and the numbering of the runs above take 7 us at any N.  us, the kernel above
+// -> this one: 16 tokens, h=1024, fp32, 8 shards 9.5 -> 2.9; 128: 11.4 -> 3.7; 512: 12.2 -> 5.5; 512, h=1001: 11.2 -> 8.3; Zipf, h=4096, bf16,
+// 2 shards: 128 tokens 11.8 -> 4.9, 256: 11.6 -> 8.9, 384: 13.5 -> 12.5, 512: 15.0 -> 16.8; every token in one row, h=4096, fp32: 256:
+// 13.3 -> 9.5; three rows, h=8192, bf16: 128 tokens 11.7 -> 7.7, 256: 10.4 -> 11.3, 512: 11.6 -> 19.8 (every slab looks through all
+// tokens: hence the limit on their product).
+constexpr int FEW_MAX_N = 512, FEW_MAX_WAVES = 8192;
+constexpr int FEW_WAVES = 8;
+
+template <typename T, int VEC, int P>
+__global__ __launch_bounds__(64 * FEW_WAVES) void embed_bwd_few_kernel(EmbedBwdGroup<P> g, const int64_t* __restrict__ ids, int N,
+                                                                       int Vs, int n_rows, int64_t off,
+                                                                       const T* __restrict__ gout, unsigned grad_bytes, int h) {
+    typedef typename FusedVec<T, VEC>::type GV;
+    __shared__ int rows_of[FEW_MAX_N];                          // row of token t among those of the launch's shards, or -1
+    __shared__ unsigned short list[FEW_WAVES][FEW_MAX_N];       // of each wavefront: the tokens of its row
+    __shared__ int long_len[FEW_WAVES], long_row[FEW_WAVES];
+    __shared__ float xchg[64 * VEC];
+    for (int t = threadIdx.x; t < N; t += 64 * FEW_WAVES) {
+        const int64_t loc = ids[t] - off;
+        rows_of[t] = loc >= 0 && loc < n_rows ? (int)loc : -1;
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // early tokens, among which the long runs start, in different workgroups, and those of different slabs on different XCDs
+    const int i = wave * gridDim.x + (blockIdx.x + blockIdx.y) % gridDim.x;
+    const int row = i < N ? __builtin_amdgcn_readfirstlane(rows_of[i]) : -1;
+    bool head = row >= 0;
+    for (int t0 = 0; head && t0 < i; t0 += 64) {
+        const int t = t0 + lane;
+        head = !__builtin_amdgcn_ballot_w64(t < i && rows_of[t] == row);
+    }
+    int len = 0;
+    for (int t0 = i & ~63; head && t0 < N; t0 += 64) {
+        const int t = t0 + lane;
+        const bool mine = t >= i && t < N && rows_of[t] == row;
+        const u64 m = __builtin_amdgcn_ballot_w64(mine);
+        if (mine) list[wave][len + __builtin_popcountll(m & ((1ull << lane) - 1ull))] = (unsigned short)t;
+        len += __builtin_popcountll(m);
+    }
+    // a wavefront's LDS accesses are executed in order: what its lanes wrote is there for all of them
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int slab = blockIdx.y;
+    const bool active = (slab * 64 + lane) * VEC < h;
+    const int c0 = active ? (slab * 64 + lane) * VEC : 0;
+    const BufferRows<GV> rows{__builtin_amdgcn_make_buffer_rsrc((void*)gout, 0, (int)grad_bytes, 0x00020000),
+                              (unsigned)c0 * (unsigned)sizeof(T), (unsigned)h * (unsigned)sizeof(T)};
+    constexpr int LONG = 2 * FusedVec<T, VEC>::BATCH;
+    if (lane == 0) {
+        long_len[wave] = len > LONG ? len : 0;
+        long_row[wave] = row;
+    }
+    if (len > 0 && len <= LONG) {
+        float* const d = dtable_row(g, (unsigned)row, (unsigned)Vs, h) + c0;
+        if (len <= SHORT_TINY) {
+            const unsigned tok = lane < len ? list[wave][lane] : 0u;
+            float acc[VEC];
+            GV v[SHORT_TINY];
+            load_acc<VEC>(acc, d);
+            load_batch<SHORT_TINY>(v, rows, tok, len);
+            add_batch<SHORT_TINY, VEC>(acc, v, 0, len);
+            if (active) store_acc<VEC>(d, acc);
+        } else {
+            sum_mid_run<T, VEC>(len, d, active, lane, rows, [&](int j) { return (unsigned)list[wave][j]; });
+        }
+    }
+    // longer runs by all wavefronts of the workgroup: one alone draws too little from memory
+    __syncthreads();
+    for (int w = 0; w < FEW_WAVES; ++w) {
+        const int n = __builtin_amdgcn_readfirstlane(long_len[w]);
+        if (n > 0)
+            sum_long_run<T, VEC, FEW_WAVES>(n, dtable_row(g, (unsigned)__builtin_amdgcn_readfirstlane(long_row[w]), (unsigned)Vs, h) + c0,
+                                            active, lane, wave, xchg, rows, [&](int j) { return (unsigned)list[w][j]; });
     }
 }
 
@@ -897,7 +979,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void embed_bwd_accum_kernel(EmbedBwd
         const int len = __builtin_amdgcn_readfirstlane((int)(run >> 32));
         const unsigned row = __builtin_amdgcn_readfirstlane((unsigned)(keys[s] >> 32));
         float* const d = dtable_row(g, row, (unsigned)Vs, h) + c0;
-        sum_long_run<T, VEC>(len, d, active, lane, wave, xchg, rows,
+        sum_long_run<T, VEC, FUSED_WAVES>(len, d, active, lane, wave, xchg, rows,
                              [&](int j) { return (unsigned)keys[s + j]; });
         if (n_long <= n_groups) break;
         r = n_groups + end_draw(start_draw(runs.next + 2 * n_slabs + slab, 1u));
@@ -998,6 +1080,11 @@ static hipError_t launch_fused(const EmbedBwdGroup<P>& g, const int64_t* ids, in
                                int h, hipStream_t st) {
     ProfScope prof(K_EMBED_ACCUM, st);
     const int n_slabs = (int)ceil_div(h, 64 * VEC);
+    if (N <= FEW_MAX_N && (int64_t)N * n_slabs <= FEW_MAX_WAVES) {
+        hipLaunchKernelGGL((embed_bwd_few_kernel<T, VEC, P>), dim3((unsigned)ceil_div(N, FEW_WAVES), (unsigned)n_slabs),
+                           dim3(64 * FEW_WAVES), 0, st, g, ids, N, Vs, n_rows, off, gout, (unsigned)((size_t)N * h * sizeof(T)), h);
+        return hipGetLastError();
+    }
     int n_groups = compute_units() / n_slabs;
     const int want = (int)ceil_div(N, 64);          // no more groups than there could be work for
     if (n_groups > want) n_groups = want;
