@@ -420,11 +420,11 @@ __global__ __launch_bounds__(F_THREADS, WPC) void gemm_f32_dh_dw_kernel(GemmF32P
 
 // Estimated time of `wg` workgroups over k steps of K each.  A workgroup alone on a compute unit takes `alone` us per 16 k
 // (a chain of load, split, LDS and products); several share the unit at `each` us (K = 1024: 256 tiles of 64 x 64 28 us, 1024 of
-// them 88; 64 tiles of 128 x 128 61; 512 of the largest 170).
+// them 88; 64 tiles of 128 x 128 61; 512 of the largest 170).  A larger tile's start and end take longer (K = 64: 7.5 us, 11).
 static double product_us(int tile, int64_t wg, int64_t k) {
     const double alone = tile == 64 ? 0.42 : tile == 128 ? 0.95 : 1.6, each = tile == 64 ? 0.34 : tile == 128 ? 0.72 : 1.28;
     const double n = (double)ceil_div(wg, 256) * each;
-    return (double)ceil_div(k, 16) * (n > alone ? n : alone);
+    return (double)ceil_div(k, 16) * (n > alone ? n : alone) + (tile == 64 ? 0.0 : tile == 128 ? 3.0 : 6.0);
 }
 
 // K slices for an output of this many 64 x 64 tiles: enough workgroups to cover the chip, slices of at least min_k.
