@@ -311,6 +311,12 @@ vp_status vp_profile_read(double* ms_total, int64_t* launches, int n);
 vp_status vp_profile_force_generic_gemm(int on);
 
 /*
+ * For tests, not part of the method: bytes that the products of vp_output_fwd, vp_output_fwd_alg2 or vp_output_bwd (logits formed
+ * again, dH not skipped) with VP_F32 write to the workspace behind its [N, Vs] matrix, by the arguments of their launches.
+ */
+size_t vp_profile_f32_scratch_written(vp_call which, int64_t N, int64_t h, int64_t Vs);
+
+/*
  * Measurement aid, not part of the method: a timeline of the fast bf16 GEMM kernel.  While `buffer`
  * (device memory, 8-byte aligned, owned by the caller) is set, every launch of that kernel whose records
  * fit writes, per workgroup and output tile, four phase stamps - tile start, operands of the first k

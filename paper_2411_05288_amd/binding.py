@@ -112,6 +112,8 @@ def load_library() -> ctypes.CDLL:
     lib.vp_profile_mfma_variant_flops.argtypes = [i32]
     lib.vp_profile_force_generic_gemm.restype = c.c_int
     lib.vp_profile_force_generic_gemm.argtypes = [c.c_int]
+    lib.vp_profile_f32_scratch_written.restype = sz
+    lib.vp_profile_f32_scratch_written.argtypes = [c.c_int, i64, i64, i64]
     lib.vp_profile_gemm_trace.restype = c.c_int
     lib.vp_profile_gemm_trace.argtypes = [vp, sz, c.c_int]
     lib.vp_profile_kernel_count.restype = c.c_int

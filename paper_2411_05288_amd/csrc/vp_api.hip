@@ -34,11 +34,12 @@ int64_t d_row_stride(int64_t Vs) { return (Vs + 63) / 64 * 64; }
 size_t max3(size_t a, size_t b, size_t c) { return a > b ? (a > c ? a : c) : (b > c ? b : c); }
 
 // fp32 path: bytes of K-slice scratch behind the [N, Vs] matrix at the start of the workspace
-size_t f32_fwd_scratch(int64_t N, int64_t h, int64_t Vs) { return gemm_f32_scratch_floats(N, Vs, h) * sizeof(float); }
+size_t f32_fwd_scratch(int64_t N, int64_t h, int64_t Vs) {
+    return gemm_f32_scratch_floats(F32Product::Logits, N, Vs, h) * sizeof(float);
+}
 size_t f32_bwd_scratch(int64_t N, int64_t h, int64_t Vs) {
-    const int dh = gemm_f32_dh_slices(N, h, Vs, 1);
-    return max3(gemm_f32_scratch_floats(N, Vs, h), dh > 1 ? (size_t)dh * (size_t)N * (size_t)h : 0,
-                gemm_f32_scratch_floats(Vs, h, N)) *
+    return max3(gemm_f32_scratch_floats(F32Product::Logits, N, Vs, h), gemm_f32_scratch_floats(F32Product::DH, N, h, Vs),
+                gemm_f32_scratch_floats(F32Product::DW, Vs, h, N)) *
            sizeof(float);
 }
 size_t f32_matrix_bytes(int64_t N, int64_t Vs) { return align_up((size_t)N * Vs * sizeof(float), 256); }
@@ -246,7 +247,7 @@ vp_status vp_output_fwd(const void* H, const void* W_shard, const int64_t* label
     float* Y = logits_out ? (float*)logits_out : (float*)workspace;
     float* scratch = f32_fwd_scratch(N, h, Vs) ? (float*)((char*)workspace + (logits_out ? 0 : f32_matrix_bytes(N, Vs)))
                                                : nullptr;
-    hipError_t e = launch_gemm_f32((const float*)H, h, 1, (const float*)W_shard, h, 1, Y, Vs, (int)N, (int)Vs, (int)h,
+    hipError_t e = launch_gemm_f32(F32Product::Logits, (const float*)H, h, (const float*)W_shard, h, Y, (int)N, (int)Vs, (int)h,
                                    false, scratch, st);
     if (e != hipSuccess) return VP_ERR_DEVICE;
     return dev(launch_row_stats_f32(one_shard(Vs, shard_offset, Y), labels, (int)N, local_max, local_sumexp, local_target, st));
@@ -367,7 +368,7 @@ vp_status vp_output_bwd(const void* H, const void* W_shard, const int64_t* label
     float* scratch = f32_bwd_scratch(N, h, Vs) ? (float*)((char*)workspace + f32_matrix_bytes(N, Vs)) : nullptr;
     const float* Y = (const float*)logits_saved;
     if (!Y) {
-        e = launch_gemm_f32((const float*)H, h, 1, (const float*)W_shard, h, 1, D, Vs, (int)N, (int)Vs, (int)h, false,
+        e = launch_gemm_f32(F32Product::Logits, (const float*)H, h, (const float*)W_shard, h, D, (int)N, (int)Vs, (int)h, false,
                             scratch, st);
         if (e != hipSuccess) return VP_ERR_DEVICE;
         Y = D;   // D is formed in place
@@ -375,11 +376,11 @@ vp_status vp_output_bwd(const void* H, const void* W_shard, const int64_t* label
     e = launch_dlogits(Y, Vs, D, Vs, 0, labels, shard_offset, global_max, global_sumexp, grad_scale, (int)N, (int)Vs, st);
     if (e != hipSuccess) return VP_ERR_DEVICE;
     if (!skip_dh) {
-        e = launch_gemm_f32(D, Vs, 1, (const float*)W_shard, 1, h, dH_accum, h, (int)N, (int)h, (int)Vs, !dh_overwrite,
+        e = launch_gemm_f32(F32Product::DH, D, Vs, (const float*)W_shard, h, dH_accum, (int)N, (int)h, (int)Vs, !dh_overwrite,
                             scratch, st);
         if (e != hipSuccess) return VP_ERR_DEVICE;
     }
-    e = launch_gemm_f32(D, 1, Vs, (const float*)H, 1, h, dW_shard, h, (int)Vs, (int)h, (int)N, false, scratch, st);
+    e = launch_gemm_f32(F32Product::DW, D, Vs, (const float*)H, h, dW_shard, (int)Vs, (int)h, (int)N, false, scratch, st);
     return dev(e);
 }
 
@@ -697,7 +698,7 @@ vp_status vp_output_fwd_alg2(const void* H, const void* W_shard, const int64_t* 
     float* P = (float*)workspace;
     float* Y = logits_out ? (float*)logits_out : P;
     float* scratch = f32_bwd_scratch(N, h, Vs) ? (float*)((char*)workspace + f32_matrix_bytes(N, Vs)) : nullptr;
-    if ((e = launch_gemm_f32((const float*)H, h, 1, (const float*)W_shard, h, 1, Y, Vs, (int)N, (int)Vs, (int)h, false,
+    if ((e = launch_gemm_f32(F32Product::Logits, (const float*)H, h, (const float*)W_shard, h, Y, (int)N, (int)Vs, (int)h, false,
                              scratch, st)) != hipSuccess)
         return VP_ERR_DEVICE;
     if ((e = launch_row_stats_f32(one_shard(Vs, shard_offset, Y), labels, (int)N, local_max, local_sumexp, local_target, st)) != hipSuccess)
@@ -705,8 +706,7 @@ vp_status vp_output_fwd_alg2(const void* H, const void* W_shard, const int64_t* 
     if ((e = launch_dlogits(Y, Vs, P, Vs, 0, nullptr, shard_offset, local_max, local_sumexp, 1.0f, (int)N, (int)Vs,
                             st)) != hipSuccess)
         return VP_ERR_DEVICE;
-    if ((e = launch_gemm_f32(P, Vs, 1, (const float*)W_shard, 1, h, A_out, h, (int)N, (int)h, (int)Vs, false, scratch,
-                             st)) !=
+    if ((e = launch_gemm_f32(F32Product::DH, P, Vs, (const float*)W_shard, h, A_out, (int)N, (int)h, (int)Vs, false, scratch, st)) !=
         hipSuccess)
         return VP_ERR_DEVICE;
     return dev(launch_embed_fwd(&W_shard, labels, 1, (int)N, (int)h, (int)Vs, shard_offset, 4, &B_out, st));

@@ -443,11 +443,6 @@ int gemm_f32_group_slices(int64_t tiles, int64_t K) { return K < 1024 ? 1 : slic
 // Slices are multiples of 32 k long, the step of the small tiles.
 static int slice_length(int64_t K, int S) { return S > 1 ? (int)(ceil_div(ceil_div(K, S), 32) * 32) : (int)K; }
 
-size_t gemm_f32_scratch_floats(int64_t M, int64_t N, int64_t K) {
-    const int S = splitk_slices(M, N, K);
-    return S > 1 ? (size_t)S * (size_t)M * (size_t)N : 0;
-}
-
 // Fills first and total for this tile and returns the grid.
 template <bool A_KC, bool B_KC>
 static dim3 f32_grid(GemmF32Params& g, int tile) {
@@ -555,29 +550,51 @@ static hipError_t launch_and_sum_f32(F32Launch f, hipStream_t st) {
     return e == hipSuccess ? sum_f32(f, st) : e;
 }
 
-hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float* B, int64_t sbn, int64_t sbk,
-                           float* C, int64_t ldc, int M, int N, int K, bool accumulate, float* scratch,
-                           hipStream_t st) {
-    if (M <= 0 || N <= 0 || K <= 0) return hipErrorInvalidValue;
-    if ((sam != 1 && sak != 1) || (sbn != 1 && sbk != 1)) return hipErrorInvalidValue;
-    ProfScope prof(K_GEMM_F32, st);
-    // (a matrix of one column, or one row, is K-contiguous and K-strided at once: B is then taken as A is, because a
-    // K-strided A with a K-contiguous B is the one pair that is not instantiated - dW of hidden size 1)
-    const bool a_kc = sak == 1, b_kc = sbk == 1 && (a_kc || sbn != 1);
+// K slices of one shard's product: the launch cuts K into at most as many as the scratch is sized for.
+static int single_slices(F32Product kind, int64_t M, int64_t N, int64_t K) {
+    return kind == F32Product::DH ? gemm_f32_dh_slices(M, N, K, 1) : splitk_slices(M, N, K);
+}
+
+size_t gemm_f32_scratch_floats(F32Product kind, int64_t M, int64_t N, int64_t K) {
+    const int S = single_slices(kind, M, N, K);
+    return S > 1 ? (size_t)S * (size_t)M * (size_t)N : 0;
+}
+
+// One shard's product.  Its layouts and K slices follow from which product it is, never from the strides: a matrix of one column,
+// or of one row, is K-contiguous and K-strided at once.
+static GemmF32Params single_params(F32Product kind, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int M, int N,
+                                   int K) {
+    const bool a_kc = kind != F32Product::DW, b_kc = kind == F32Product::Logits;
     GemmF32Params g{};
     g.A = A; g.B = B;
-    g.lda = a_kc ? sam : sak; g.ldb = b_kc ? sbn : sbk;
+    g.lda = lda; g.ldb = ldb;
     g.M = M; g.N = N; g.K = K;
-    g.k_per_slice = slice_length(K, !scratch ? 1 : a_kc && !b_kc ? gemm_f32_dh_slices(M, N, K, 1) : splitk_slices(M, N, K));
+    g.k_per_slice = slice_length(K, single_slices(kind, M, N, K));
     g.slices = (int)ceil_div(K, g.k_per_slice);
-    g.a_vec = g.lda % 4 == 0 && ((uintptr_t)A & 15u) == 0 && (!a_kc || K % 4 == 0);
-    g.b_vec = g.ldb % 4 == 0 && ((uintptr_t)B & 15u) == 0 && (!b_kc || K % 4 == 0);
+    g.a_vec = lda % 4 == 0 && ((uintptr_t)A & 15u) == 0 && (!a_kc || K % 4 == 0);
+    g.b_vec = ldb % 4 == 0 && ((uintptr_t)B & 15u) == 0 && (!b_kc || K % 4 == 0);
     g.n = 1;
     GemmF32Shard& s = g.sh[0];
     s.A = A; s.B = B; s.C = C;
-    s.rows = a_kc && b_kc ? N : a_kc ? K : M;
-    s.ld = (int)(a_kc && b_kc ? ldc : g.lda);
-    return launch_and_sum_f32(prepare_f32(g, a_kc, b_kc, C, ldc, accumulate, scratch), st);
+    s.rows = b_kc ? N : a_kc ? K : M;
+    s.ld = b_kc ? N : (int)lda;
+    return g;
+}
+
+hipError_t launch_gemm_f32(F32Product kind, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int M, int N, int K,
+                           bool accumulate, float* scratch, hipStream_t st) {
+    if (M <= 0 || N <= 0 || K <= 0) return hipErrorInvalidValue;
+    ProfScope prof(K_GEMM_F32, st);
+    const GemmF32Params g = single_params(kind, A, lda, B, ldb, C, M, N, K);
+    if (g.slices > 1 && !scratch) return hipErrorInvalidValue;
+    return launch_and_sum_f32(prepare_f32(g, kind != F32Product::DW, kind == F32Product::Logits, C, N, accumulate, scratch), st);
+}
+
+// What prepare_f32 lays out for this product: every float that its launches write outside the output.
+size_t gemm_f32_written_floats(F32Product kind, int64_t M, int64_t N, int64_t K) {
+    const F32Launch f = prepare_f32(single_params(kind, nullptr, 0, nullptr, 0, nullptr, (int)M, (int)N, (int)K),
+                                    kind != F32Product::DW, kind == F32Product::Logits, nullptr, N, false, nullptr);
+    return f.parts > 1 ? (size_t)f.parts * (size_t)f.g.slice_stride : 0;
 }
 
 // The three products over n shards (see GemmBf16Group for how they are laid end to end; here a K slice never crosses a

@@ -133,14 +133,15 @@ bool gemm_bf16_out_ok(const GemmBf16Params& p);
 bool gemm_bf16_fast_ok(const GemmBf16Params& p);
 hipError_t launch_gemm_bf16_fast(const GemmBf16Params& p, hipStream_t st);
 
-// Generic strided fp32 GEMM: C[m,n] (+)= sum_k A[m*sam + k*sak] * B[n*sbn + k*sbk].  scratch: nullptr or at
-// least gemm_f32_scratch_floats(M, N, K) floats (then small outputs with a long K are computed in K slices).
-hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak,
-                           const float* B, int64_t sbn, int64_t sbk,
-                           float* C, int64_t ldc, int M, int N, int K, bool accumulate, float* scratch,
-                           hipStream_t st);
-// Floats of scratch with which launch_gemm_f32 cuts K into slices for this shape (0: it would not).
-size_t gemm_f32_scratch_floats(int64_t M, int64_t N, int64_t K);
+// The fp32 products of one shard.  Logits: C[m,n] = sum_k A[m lda + k] B[n ldb + k]; DH (and A of Algorithm 2): A[m lda + k]
+// B[k ldb + n]; DW: A[k lda + m] B[k ldb + n].  C is dense [M, N].
+enum class F32Product { Logits, DH, DW };
+// scratch: at least gemm_f32_scratch_floats(kind, M, N, K) floats (outputs with few tiles and a long K are computed in K slices).
+hipError_t launch_gemm_f32(F32Product kind, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int M, int N, int K,
+                           bool accumulate, float* scratch, hipStream_t st);
+size_t gemm_f32_scratch_floats(F32Product kind, int64_t M, int64_t N, int64_t K);
+// Floats that the launches of this product write to scratch, from their arguments.
+size_t gemm_f32_written_floats(F32Product kind, int64_t M, int64_t N, int64_t K);
 
 // The fp32 products over several shards in one launch (n <= GEMM_GROUP_MAX).
 struct GemmF32Shard {

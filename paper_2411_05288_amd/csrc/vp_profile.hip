@@ -186,6 +186,17 @@ vp_status vp_profile_force_generic_gemm(int on) {
     return VP_OK;
 }
 
+size_t vp_profile_f32_scratch_written(vp_call which, int64_t N, int64_t h, int64_t Vs) {
+    using vp::F32Product;
+    if (N < 1 || h < 1 || Vs < 1) return (size_t)-1;
+    const size_t logits = vp::gemm_f32_written_floats(F32Product::Logits, N, Vs, h);
+    const size_t dh = vp::gemm_f32_written_floats(F32Product::DH, N, h, Vs), dw = vp::gemm_f32_written_floats(F32Product::DW, Vs, h, N);
+    size_t most = logits;
+    if (which == VP_CALL_OUTPUT_FWD_ALG2 || which == VP_CALL_OUTPUT_BWD) most = dh > most ? dh : most;
+    if (which == VP_CALL_OUTPUT_BWD) most = dw > most ? dw : most;
+    return most * sizeof(float);
+}
+
 vp_status vp_profile_gemm_trace(void* buffer, size_t bytes, int kernel_id) {
     if (buffer && (((uintptr_t)buffer & 7u) != 0 || bytes < 64)) return VP_ERR_INVALID_ARG;
     if (kernel_id >= vp::K_COUNT) return VP_ERR_INVALID_ARG;
