@@ -48,7 +48,8 @@ class OutputLayerPlan:
     All shards go through one call per pass, which keeps the D matrices of all of them (at most
     4 GiB) and up to 1 GiB of partial sums in ``workspace``; one shard at a time needs the largest
     D alone.  ``workspace_limit`` (bytes) makes the plan go shard by shard where the workspace
-    would be larger than that, and so does a device without room for it."""
+    would be larger than that, and so does a device without room for it; with algorithm=2 pass S alone
+    does so where the rest fits."""
 
     def __init__(self, H: torch.Tensor, W_shards: List[torch.Tensor], labels: torch.Tensor,
                  save_logits: bool = True, grad_scale: Optional[float] = None, vocab_size: Optional[int] = None,
@@ -100,39 +101,42 @@ class OutputLayerPlan:
         # All shards of the device go through one call when the ones with real rows come first (else one by one); that
         # call's workspace is larger: the D matrices of all shards (at most 4 GiB) and the slices of a cut dH product.
         self.live = sum(v > 0 for v in self.valid)
-        self.grouped = all(v > 0 for v in self.valid[:self.live])
-        self.grouped_S = False
-        if self.grouped:
-            live = self.valid[:self.live]
-            group_bytes = max(nbytes, B.vp_output_group_workspace_bytes(B.VP_CALL_OUTPUT_BWD, N, h, live, self.dt,
-                                                                        flags | (B.VP_SKIP_DH if algorithm == 2 else 0)))
-            if algorithm == 1:
-                group_bytes = max(group_bytes, B.vp_output_group_workspace_bytes(B.VP_CALL_OUTPUT_FWD, N, h, live, self.dt,
-                                                                                 flags))
-            else:
-                try:
-                    group_bytes = max(group_bytes, B.vp_output_group_workspace_bytes(fwd_call, N, h, live, self.dt, flags))
-                    self.grouped_S = True
-                except B.VPError:      # more shards or larger ones than one call takes
-                    pass
-            self.grouped = workspace_limit is None or group_bytes <= max(nbytes, workspace_limit)
-            # a single shard gains from the group call only the K slices of dH, which need workspace
-            if self.live == 1 and group_bytes == nbytes:
-                self.grouped = False
-        if self.grouped:
+        live = self.valid[:self.live]
+        sizes = []      # workspace of the ways to group the shards, the one that groups the most first; the second value: pass S too
+        if all(v > 0 for v in live):
+            bwd = max(nbytes, B.vp_output_group_workspace_bytes(B.VP_CALL_OUTPUT_BWD, N, h, live, self.dt,
+                                                                flags | (B.VP_SKIP_DH if algorithm == 2 else 0)))
             try:
-                self.workspace = torch.empty((group_bytes,), dtype=torch.uint8, device=dev)
-            except torch.OutOfMemoryError:
-                self.grouped = False
-        if not self.grouped:
-            self.workspace = torch.empty((nbytes,), dtype=torch.uint8, device=dev)
-        # Algorithm 2 keeps A = softmax' W_r and B = G W_r of every shard until the barrier
-        self.grouped_S = self.grouped_S and self.grouped
-        # (apart from one another where the calls of a single shard, which take 16-byte aligned matrices, write them)
-        self.A = None
-        if algorithm == 2:
-            self.A = torch.empty((p, N, h), **f32) if self.grouped_S else [torch.empty((N, h), **f32) for _ in range(p)]
+                sizes.append((max(bwd, B.vp_output_group_workspace_bytes(fwd_call, N, h, live, self.dt, flags)), True))
+            except B.VPError:      # Algorithm 2: more shards or larger ones than one call takes
+                if algorithm == 1:
+                    raise
+            # (Algorithm 2: pass S of all shards keeps their softmax' matrices and slices of A, pass T and the barrier need less)
+            if algorithm == 2 and (not sizes or bwd < sizes[0][0]):
+                sizes.append((bwd, False))
+        # Algorithm 2 keeps A = softmax' W_r and B = G W_r of every shard until the barrier (A apart from one another where the
+        # calls of a single shard, which take 16-byte aligned matrices, write them)
         self.Bm = [torch.empty((N, h), dtype=H.dtype, device=dev) for _ in range(p)] if algorithm == 2 else None
+
+        def buffers(nbytes, pass_S):
+            A = None
+            if algorithm == 2:
+                A = torch.empty((p, N, h), **f32) if pass_S else [torch.empty((N, h), **f32) for _ in range(p)]
+            return torch.empty((nbytes,), dtype=torch.uint8, device=dev), A
+
+        self.grouped = self.grouped_S = False
+        for size, pass_S in sizes:
+            # a single shard gains from the group calls only their K slices, which need workspace
+            if (self.live == 1 and size == nbytes) or (workspace_limit is not None and size > max(nbytes, workspace_limit)):
+                continue
+            try:
+                self.workspace, self.A = buffers(size, pass_S)
+            except torch.OutOfMemoryError:
+                continue
+            self.grouped, self.grouped_S = True, pass_S and algorithm == 2
+            break
+        if not self.grouped:
+            self.workspace, self.A = buffers(nbytes, False)
 
     def _on(self, stream):
         """Context in which torch-side fills run on the same stream as the library's kernels."""

@@ -1,5 +1,7 @@
 """Host-side choices of the driver, on CPU tensors: which entry point a call goes to, and with how much workspace.  The
 entry points that would launch kernels are replaced by recorders."""
+import weakref
+
 import pytest
 import torch
 
@@ -86,14 +88,63 @@ def one_shard_bytes(algorithm):
     return max(B.vp_workspace_bytes(c, 300, 64, 1000, vp.VP_BF16, B.VP_SAVE_LOGITS) for c in (fwd, B.VP_CALL_OUTPUT_BWD))
 
 
+def pass_T_bytes(algorithm):
+    return B.vp_output_group_workspace_bytes(B.VP_CALL_OUTPUT_BWD, 300, 64, [1000] * 4, vp.VP_BF16,
+                                             B.VP_SAVE_LOGITS | (B.VP_SKIP_DH if algorithm == 2 else 0))
+
+
 @pytest.mark.parametrize("algorithm", [1, 2])
 def test_output_plan_workspace_limit(algorithm):
     full = output_plan(algorithm)
     assert full.grouped and full.workspace.numel() > one_shard_bytes(algorithm)
     assert output_plan(algorithm, workspace_limit=full.workspace.numel()).grouped
-    for limit in (full.workspace.numel() - 1, 0):
+    for limit in (pass_T_bytes(algorithm) - 1, 0):
         small = output_plan(algorithm, workspace_limit=limit)
         assert not small.grouped and small.workspace.numel() == one_shard_bytes(algorithm)
+
+
+def test_algorithm2_plan_with_room_for_pass_T_alone(monkeypatch):
+    # pass S of all shards needs more than pass T: without room for it the barrier and pass T still go in one call each
+    full, bwd = output_plan(2), pass_T_bytes(2)
+    assert full.grouped_S and bwd < full.workspace.numel() and torch.is_tensor(full.A)
+    limits = [dict(workspace_limit=full.workspace.numel() - 1), dict(workspace_limit=bwd)]
+    for kw in limits:
+        small = output_plan(2, **kw)
+        assert small.grouped and not small.grouped_S and small.workspace.numel() == bwd and isinstance(small.A, list)
+    empty = torch.empty
+
+    def full_device(shape, *a, dtype=None, **kw):
+        if dtype == torch.uint8 and shape[0] > bwd:
+            raise torch.OutOfMemoryError("no room")
+        return empty(shape, *a, dtype=dtype, **kw)
+
+    monkeypatch.setattr(torch, "empty", full_device)
+    small = output_plan(2)
+    assert small.grouped and not small.grouped_S and small.workspace.numel() == bwd
+
+
+def test_algorithm2_plan_on_a_device_with_little_room(monkeypatch):
+    # A and B of all shards come before the larger workspace: what has room for one shard's workspace next to them still runs
+    room, empty = [0], torch.empty
+
+    def small_device(shape, *a, dtype=None, **kw):
+        t = empty(shape, *a, dtype=dtype, **kw)
+        used = sum(x() is not None and x().numel() * x().element_size() or 0 for x in live)
+        if used + t.numel() * t.element_size() > room[0]:
+            raise torch.OutOfMemoryError("no room")
+        live.append(weakref.ref(t))
+        return t
+
+    live = []
+    room[0] = 1 << 40
+    monkeypatch.setattr(torch, "empty", small_device)
+    plan = output_plan(2, workspace_limit=0)
+    total = sum(x().numel() * x().element_size() for x in live if x() is not None)
+    del plan
+    live.clear()
+    room[0] = total
+    plan = output_plan(2)
+    assert not plan.grouped and plan.workspace.numel() == one_shard_bytes(2)
 
 
 @pytest.mark.parametrize("algorithm", [1, 2])
