@@ -7,7 +7,9 @@
 // every operand is split exactly into three bf16 parts, x = x0 + x1 + x2 (8 significant bits each, 24 together), and of
 // the nine products of parts the six down to 2^-18 of the whole are summed in fp32 accumulators: x0 y0, x0 y1, x1 y0, x1 y1,
 // x0 y2, x2 y0.  What is left out is below 2^-26 of a product, a quarter of the rounding of one fp32 addition; and one bf16 MFMA
-// adds 16 products at once, so that a sum is rounded six times per 16 k instead of eight.  Error of the results against float64
+// adds 16 products at once, so that a sum is rounded six times per 16 k instead of eight.  Sums of at most four products, in
+// which what is left out would show (one product: 3.9e-8 instead of 2.5e-8), are formed with the fp32 instruction.  Error of the
+// results against float64
 // (2-norm, relative; fp32 MFMA -> this kernel): N=1000 h=1024 V=32000 p=8: logits 5.7e-7 -> 4.9e-7, dH 1.1e-6 -> 5.0e-7, dW
 // 5.7e-7 -> 3.6e-7; N=128 h=256 V=8192: 2.9e-7 -> 2.4e-7, 2.1e-7 -> 1.9e-7, 2.0e-7 -> 1.4e-7; N=2000 h=2048 V=8000: 8.1e-7 ->
 // 7.0e-7, 1.1e-6 -> 5.0e-7, 8.0e-7 -> 5.1e-7.  Time of a product at the first of these sizes: 520-560 us -> 330-350 us
@@ -16,8 +18,9 @@
 // Workgroup: 4 wavefronts (2 x 2) on tiles of 256 x 128 (dW: vocabulary rows first) or 128 x 256 (tokens first), 128 x 128 or
 // 64 x 64.  Operands go global -> registers (fp32) -> split -> LDS (three bf16 planes), K advances 16 (small tiles: 32) at a
 // time through two LDS stages with one barrier each: while stage q is multiplied, stage q + 1 is split between its products
-// (about 6 vector instructions per value, which issue while the matrix cores work; left to the compiler they came in
-// one block, 363 instead of 328 us) and stage q + 2 is on its way into the freed registers.  Two workgroups of the large
+// (6.5 vector instructions per value, one of them the scaling, which issue while the matrix cores work; left to the compiler they
+// came in one block, 363 instead of 328 us; the two values of a pair converted apart from one another, 10.5 instructions, 1082
+// instead of 1047 us for the whole step of the first size above) and stage q + 2 is on its way into the freed registers.  Two workgroups of the large
 // tiles (three of the others) share a compute unit and fill each other's barriers.  The split happens once per workgroup and
 // value: with every wavefront splitting what it loads, without LDS, small launches took as long and large ones 1.3 times.
 //
@@ -39,17 +42,19 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
-// D is scaled by this before it is split and the sums by its inverse (exact): |D| is at most the gradient's scale, and
-// without it the lowest parts of softmax values below 2^-110 would be lost in bf16's smallest numbers (as are those of H and W
-// below 2^-110, next to which every other value of a sum would have to be as small).
-constexpr float D_SCALE = 0x1p64f;
+// Operands are scaled by this before they are split, and the sums by the square of its inverse (all exact): the last bit of the
+// smallest fp32 number is then a normal bf16 number, so that the three parts hold every finite operand exactly.  (Scaled operands
+// from 2^128 on and sums from 2^80 on are not finite and are computed again: f32_finish.)
+constexpr float IN_SCALE = 0x1p24f;
 
-__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
-    const __bf16 a = (__bf16)lo, b = (__bf16)hi;   // round to nearest even
-    return (unsigned)__builtin_bit_cast(u16, a) | ((unsigned)__builtin_bit_cast(u16, b) << 16);
+__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {      // round to nearest even, one instruction
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2{lo, hi}), bf16x2));
 }
 
 constexpr int F_THREADS = 256;
+constexpr int F_FEW = 5;                  // sums of fewer products than this: the fp32 instruction
 constexpr unsigned F_OOB = 0x80000000u;   // beyond every buffer descriptor below (each covers at most 2^30 bytes)
 
 struct GemmF32Params {
@@ -212,18 +217,17 @@ __device__ __forceinline__ F32Work f32_work(const GemmF32Params& g, int bx, int 
 // per row and store.
 template <bool A_KC, bool B_KC>
 __device__ __forceinline__ void f32_finish(floatx16 v, const F32Work& w, int row0, int col0, bool accumulate, int lane) {
-    constexpr bool SCALE = !(A_KC && B_KC);
     const int l32 = lane & 31, hf = lane >> 5;
     // A non-finite operand (or one that rounds to a bf16 infinity, or an overflow) makes the parts of the split
-    // cancel to NaN.  Elements that are not finite are computed again from the operands as they are, in fp32.
+    // cancel to NaN.  Elements that are not finite are computed again from the operands as they are, in fp32; and so are sums of
+    // fewer than five products, in which what the split leaves out shows (a single product would be off by its last bit).
     float nf = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) nf = fmaf(v[r], 0.f, nf);
-    if (SCALE) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) v[r] *= 1.f / D_SCALE;
-    }
-    if (__builtin_amdgcn_ballot_w64(!(nf == 0.f)) != 0) {
+    for (int r = 0; r < 16; ++r) v[r] *= 1.f / (IN_SCALE * IN_SCALE);
+    const bool few = w.k_end - w.k_begin < F_FEW;
+    if (few || __builtin_amdgcn_ballot_w64(!(nf == 0.f)) != 0) {
         const int ar = min(row0 + l32, w.M - 1), br = min(col0 + l32, w.N - 1);
         const float* ap = w.A + (A_KC ? (int64_t)ar * w.lda : (int64_t)ar);
         const float* bp = w.B + (B_KC ? (int64_t)br * w.ldb : (int64_t)br);
@@ -238,7 +242,7 @@ __device__ __forceinline__ void f32_finish(floatx16 v, const F32Work& w, int row
         }
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-            if (!(fabsf(v[r]) < INFINITY)) v[r] = c[r];
+            if (few || !(fabsf(v[r]) < INFINITY)) v[r] = c[r];
     }
     const int col = col0 + l32, row = row0 + 4 * hf;
     if (col >= w.N) return;
@@ -265,7 +269,6 @@ constexpr int f32_lds_bytes() { return 2 * 3 * 2 * SK * 64 * (MT + NT); }
 template <bool A_KC, bool B_KC, int MT, int NT, int SK, int PD, bool VEC>
 __device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& g, char* lds, int bx, int by) {
     constexpr int TM = 64 * MT, TN = 64 * NT;
-    constexpr bool SCALE = !(A_KC && B_KC);      // A is D
     typedef F32Tile<A_KC, TM, SK> TA;
     typedef F32Tile<B_KC, TN, SK> TB;
     constexpr int STAGE = 3 * (TA::PLANE + TB::PLANE);
@@ -300,7 +303,8 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& g, char* lds,
     auto split = [&](int u, int c, bool first, char* stage) {
         float x0 = __builtin_bit_cast(float, (unsigned)raw[u][c][first ? 0 : 2]);
         float x1 = __builtin_bit_cast(float, (unsigned)raw[u][c][first ? 1 : 3]);
-        if (SCALE && c < CA) { x0 *= D_SCALE; x1 *= D_SCALE; }
+        x0 *= IN_SCALE;
+        x1 *= IN_SCALE;
         if (first) {
             split2(x0, x1, parts[0].x, parts[1].x, parts[2].x);
             return;

@@ -81,3 +81,66 @@ def test_infinities_and_the_largest_values(N, h, rows):
     assert torch.equal(got[:t, j], torch.where(plan.H[:t, k] > 0, float("inf"), float("-inf")))
     want = 3.4e38 * torch.cat(plan.W)[:, 0].double()
     assert bool(((got[t].double() - want).abs() <= 2.0 ** -23 * want.abs())[others].all())
+
+
+def call_bwd(H, W, labels, Y, grad_scale):
+    """vp_output_bwd on given logits with statistics 0 and 1 (D = exp(Y) - one-hot): D as it left it, dH, dW."""
+    import paper_2411_05288_amd as vp
+    N, h, Vs = H.shape[0], H.shape[1], W.shape[0]
+    dH, dW = torch.empty((N, h), device="cuda"), torch.empty((Vs, h), device="cuda")
+    n = vp.vp_workspace_bytes(vp.binding.VP_CALL_OUTPUT_BWD, N, h, Vs, vp.VP_F32, vp.VP_SAVE_LOGITS)
+    ws = torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")
+    vp.vp_output_bwd(H, W, labels, 0, torch.zeros(N, device="cuda"), torch.ones(N, device="cuda"), Y, grad_scale, dH, dW, ws,
+                     dh_overwrite=True)
+    torch.cuda.synchronize()
+    return ws[:N * Vs * 4].view(torch.float32).view(N, Vs), dH, dW
+
+
+def call_fwd(H, W):
+    import paper_2411_05288_amd as vp
+    N, Vs = H.shape[0], W.shape[0]
+    out, s = torch.empty((N, Vs), device="cuda"), [torch.empty(N, device="cuda") for _ in range(3)]
+    n = vp.vp_workspace_bytes(vp.binding.VP_CALL_OUTPUT_FWD, N, H.shape[1], Vs, vp.VP_F32, vp.VP_SAVE_LOGITS)
+    ws = torch.empty((max(n, 256),), dtype=torch.uint8, device="cuda")
+    vp.vp_output_fwd(H, W, torch.zeros(N, dtype=torch.int64, device="cuda"), 0, *s, out, ws)
+    torch.cuda.synchronize()
+    return out
+
+
+@pytest.mark.parametrize("K", [1, 2, 3])
+def test_sums_of_few_products_are_rounded_once_per_product(K):
+    # one token, a shard of one row, hidden size 1: no more than the rounding of the K products' sum in fp32
+    print("few", K, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(K)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda")
+
+    def check(got, A, B):
+        A, B = A.double(), B.double()
+        assert bool(((got.double() - A @ B).abs() <= K * 2.0 ** -24 * (A.abs() @ B.abs())).all())
+
+    for N, h, Vs in ((K, 70, 131), (70, K, 131), (70, 131, K)):
+        H, W = rand(N, h), rand(Vs, h)
+        D, dH, dW = call_bwd(H, W, torch.randint(0, Vs, (N,), generator=g, device="cuda"), rand(N, Vs), 1.0)
+        if h == K:
+            check(call_fwd(H, W), H, W.t())
+        if Vs == K:
+            check(dH, D, W)
+        if N == K:
+            check(dW, D.t(), H)
+
+
+@pytest.mark.parametrize("N,h,rows", SHAPES)
+def test_the_smallest_operands_keep_all_bits(N, h, rows):
+    # scaling by powers of two leaves every bit alone, also where operands become the smallest numbers that fp32 has
+    print("smallest", N, h, rows, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    ints = lambda *s: torch.randint(-2 ** 23, 2 ** 23, s, generator=g, device="cuda").to(torch.float32) * 2.0 ** -23
+    Vs = rows[0]
+    H, W, labels = ints(N, h), ints(Vs, h), torch.randint(0, Vs, (N,), generator=g, device="cuda")
+    Y = torch.randn((N, Vs), generator=g, device="cuda")
+    tiny = lambda x: x * 2.0 ** -60 * 2.0 ** -66       # multiples of 2^-149
+    for got in (call_fwd(tiny(H), W * 2.0 ** 70), call_fwd(H * 2.0 ** 70, tiny(W))):
+        assert torch.equal(got * 2.0 ** 56, call_fwd(H, W))
+    _, dH, dW = call_bwd(H, W, labels, Y, 1.0)
+    assert torch.equal(call_bwd(H, tiny(W), labels, Y, 2.0 ** 76)[1] * 2.0 ** 50, dH)
+    assert torch.equal(call_bwd(tiny(H), W, labels, Y, 2.0 ** 76)[2] * 2.0 ** 50, dW)
