@@ -107,7 +107,7 @@ def call_fwd(H, W):
     return out
 
 
-@pytest.mark.parametrize("K", [1, 2, 3])
+@pytest.mark.parametrize("K", [1, 2, 3, 4])
 def test_sums_of_few_products_are_rounded_once_per_product(K):
     # one token, a shard of one row, hidden size 1: no more than the rounding of the K products' sum in fp32
     print("few", K, flush=True)
