@@ -3,14 +3,16 @@
 Tensors are torch tensors on the GPU; bf16 data may be passed as torch.bfloat16 or as
 int16/uint16 bit patterns.  Nothing here computes: the functions check dtype / device /
 contiguity, take raw pointers and the current HIP stream, and call the library.  The checks run in
-native code (_vphost.so); what does not pass there is checked again here, where the message is made.
-There is no fallback: if a library is missing or a call fails, an exception is raised.
+native code (_vphost.so); what does not pass there is checked again here, where the message is made
+(everything is, where that module is missing or belongs to another PyTorch: small passes then take
+twice as long).  The library has no fallback: if it is missing or a call fails, an exception is raised.
 """
 from __future__ import annotations
 
 import ctypes
 import importlib.util
 import os
+import warnings
 from typing import Optional
 
 import torch
@@ -31,7 +33,7 @@ VP_CALL_OUTPUT_DX_ALG2 = 6
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
-_HOST = None      # _vphost.so, loaded with the library
+_HOST = None      # _vphost.so, loaded with the library, or None
 
 
 class VPError(RuntimeError):
@@ -42,21 +44,37 @@ def lib_path() -> str:
     return os.path.join(_HERE, "libvp.so")
 
 
+def host_path() -> str:
+    return os.path.join(_HERE, "_vphost.so")
+
+
+def _load_host(path: str):
+    """The native checks, or None where there are none that fit this PyTorch, whose objects they read."""
+    if not os.path.exists(path):
+        return None
+    try:
+        spec = importlib.util.spec_from_file_location("_vphost", path)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+    except ImportError as e:
+        warnings.warn("%s cannot be loaded (%s): tensors are checked in Python" % (path, e))
+        return None
+    if module.torch_version != torch.__version__.split("+")[0]:
+        warnings.warn("%s was built for PyTorch %s: tensors are checked in Python" % (path, module.torch_version))
+        return None
+    return module
+
+
 def load_library() -> ctypes.CDLL:
     """Loads libvp.so (built by ``python -m paper_2411_05288_amd.build``)."""
     global _LIB, _HOST
     if _LIB is not None:
         return _LIB
     path = lib_path()
-    host = os.path.join(_HERE, "_vphost.so")
-    for f in (path, host):
-        if not os.path.exists(f):
-            raise VPError("%s not found at %s: build it with `python -m paper_2411_05288_amd.build`" % (os.path.basename(f), f))
+    if not os.path.exists(path):
+        raise VPError("libvp.so not found at %s: build it with `python -m paper_2411_05288_amd.build`" % path)
     if _HOST is None:
-        spec = importlib.util.spec_from_file_location("_vphost", host)
-        module = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(module)
-        _HOST = module
+        _HOST = _load_host(host_path())
     lib = ctypes.CDLL(path)
     c = ctypes
     vp, i64, i32, u32, sz, fl = c.c_void_p, c.c_int64, c.c_int32, c.c_uint32, c.c_size_t, c.c_float

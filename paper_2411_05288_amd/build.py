@@ -45,10 +45,11 @@ def _host():
     root = os.path.dirname(torch.__file__)
     rocm = os.path.dirname(os.path.dirname(HIPCC))
     tmp = HOST + ".tmp"
-    out = _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+    out = _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
                 "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
-                *["-I" + d for d in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
-                                     sysconfig.get_paths()["include"], os.path.join(rocm, "include"))],
+                *["-isystem" + d for d in (os.path.join(root, "include"),
+                                           os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                                           sysconfig.get_paths()["include"], os.path.join(rocm, "include"))],
                 os.path.join(CSRC, "vp_host.cpp"), "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
                 "-lc10_hip", "-o", tmp])
     os.replace(tmp, HOST)

@@ -11,6 +11,7 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <cstdint>
 #include <cstring>
@@ -115,4 +116,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_vphost", nullptr, -1, methods, nu
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__vphost(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__vphost(void) {
+    PyObject* m = PyModule_Create(&module);
+    // the PyTorch whose objects this code reads: another one's may be laid out otherwise
+    if (m && PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION) < 0) Py_CLEAR(m);
+    return m;
+}
