@@ -144,3 +144,39 @@ def test_the_smallest_operands_keep_all_bits(N, h, rows):
     _, dH, dW = call_bwd(H, W, labels, Y, 1.0)
     assert torch.equal(call_bwd(H, tiny(W), labels, Y, 2.0 ** 76)[1] * 2.0 ** 50, dH)
     assert torch.equal(call_bwd(tiny(H), W, labels, Y, 2.0 ** 76)[2] * 2.0 ** 50, dW)
+
+
+def parts(x):
+    p0 = x.bfloat16().float()
+    p1 = (x - p0).bfloat16().float()
+    return p0.double(), p1.double(), (x - p0 - p1).double()
+
+
+@pytest.mark.parametrize("m,n", [(300, 200), (9000, 2000), (16000, 4096)])      # tiles of 64 x 64, 128 x 128, 256 x 128
+@pytest.mark.parametrize("product", ["logits", "dH", "dW"])
+def test_every_layout_sums_all_six_part_products(product, m, n):
+    # operands just over 1 whose second and third parts are positive and large, so that nothing cancels: leaving out one of the
+    # six products of parts shows in every sum.  D = exp(Y) (statistics 0 and 1, labels of nobody), read where the call leaves it.
+    print("parts", product, m, n, flush=True)
+    K = 48
+    g = torch.Generator(device="cuda").manual_seed(m)
+    over_one = lambda *s: 1.0 + (torch.randint(192, 255, s, generator=g, device="cuda") * 128 + 60).double() * 2.0 ** -23
+    nobody = lambda k: torch.full((k,), -1, dtype=torch.int64, device="cuda")
+    if product == "logits":
+        A, B = over_one(m, K).float(), over_one(n, K).float()
+        got = call_fwd(A, B)
+    elif product == "dH":
+        W = over_one(K, n).float()
+        A, got, _ = call_bwd(torch.zeros(m, n, device="cuda"), W, nobody(m), over_one(m, K).log().float(), 1.0)
+        B = W.t()
+    else:
+        H = over_one(K, n).float()
+        D, _, got = call_bwd(H, torch.zeros(m, n, device="cuda"), nobody(K), over_one(K, m).log().float(), 1.0)
+        A, B = D.t(), H.t()
+    ref = A.double() @ B.double().t()
+    # 6 roundings per 16 k and the sum of the two halves of K, each by 2^-23 at most; the products left out, 2^-24 at most
+    bar = (6 * (K / 16) + 1) * 2.0 ** -23 + 2.0 ** -24
+    assert bool(((got.double() - ref).abs() <= bar * ref).all())
+    a, b = parts(A), parts(B)
+    for i, j in ((0, 0), (0, 1), (1, 0), (1, 1), (0, 2), (2, 0)):
+        assert float((a[i].mean(1).min() * b[j].mean(1).min())) > 2 * bar      # (the test can tell)
