@@ -31,13 +31,29 @@ static double tile_us(int mi, int64_t kt, bool stats) {
     static const double step[5] = {0, 0.72, 0.93, 1.04, 1.42}, end[5] = {0, 2.8, 6.2, 9.3, 17.4};
     return (double)kt * step[mi] + (stats ? end[mi] : 1.0 + mi);
 }
+// dH and A of Algorithm 2 from this many tokens on (fewer: tile_us).  Estimated time of `tiles` tiles of 192 or 256 rows (mi = 3, 4) with
+// kt k tiles each: the part is power limited, so a k tile takes the longer the more compute units work at once (`all` of them, or
+// close to none), and a lower tile must save rows that do not exist, not only fill the last round.  An estimate without that
+// (tile_us) took 192 rows and other slices where 256 are faster, h=6144 V=128256, us: 3100 tokens 4077 -> 4480, 1536: 1865 -> 1982,
+// h=4096 V=128256: 1800: 1517 -> 1718, 800: 775 -> 849; with 256 rows only, it loses 520 (h=4096 V=128256): 528 -> 615, 1300
+// (h=3072 V=50001): 353 -> 386, 2600: 709 -> 788.  Of 126 sizes of 520 to 4000 tokens this one is more than 2 % of the product behind
+// the better of the two at five, 18 us at most.
+constexpr int DH_FEW = 512;
+static double dh_us(int mi, int64_t tiles, int64_t kt, int cus) {
+    const double none = mi == 3 ? 0.85 : 0.98, all = mi == 3 ? 1.30 : 1.56, end = mi == 3 ? 3.3 : 5.2;
+    const int64_t full = tiles / cus, last = tiles % cus;
+    double us = (double)full * ((double)kt * all + end);
+    if (last) us += (double)kt * (none + (all - none) * (double)last / cus) + end;
+    return us;
+}
 // Row blocks per wavefront of the least estimated time for M rows, tn tile columns (times slices) and kt k tiles each: with
 // few tokens (or a token count just past a multiple of 256) 256 rows are mostly rows that do not exist.  256 rows -> this
 // choice, logits and dH, us, h=4096 V=64000: 64 tokens 130 -> 97 and 115 -> 97, 128: 131 -> 106 and 122 -> 105, 192: 137 -> 124 and
-// 129 -> 121, 384: 239 -> 196 and 225 -> 200.  Lower tiles must promise 15 %: the part is power limited, so a round of
+// 129 -> 121, 384: 239 -> 196 and 225 -> 200.  By tile_us, lower tiles must promise 15 %: the part is power limited, so a round of
 // tiles that is not full lets the others run faster (N=1999 h=3072 V=50001 p=8: 11 % promised, the same time; N=700 h=4096 V=100000: 3 %
 // promised, 3 % longer).
 int row_blocks_for(int64_t M, int64_t tn, int64_t kt, bool stats, int cus) {
+    if (!stats && M > DH_FEW) return dh_us(3, ceil_div(M, 192) * tn, kt, cus) < dh_us(4, ceil_div(M, 256) * tn, kt, cus) ? 3 : 4;
     auto us = [&](int mi) { return (double)ceil_div(ceil_div(M, 64 * mi) * tn, cus) * tile_us(mi, kt, stats); };
     int best = 3;
     for (int mi = 2; mi >= 1; --mi)
@@ -143,7 +159,7 @@ hipError_t launch_gemm_bf16_fast(const GemmBf16Params& p, hipStream_t st) {
 
 // A dH product has only N h / 65536 tiles but the whole vocabulary as K, so with few tokens most compute units would
 // idle (512 tokens, h = 2048: 16 tiles).  The k tiles are cut into S equal slices per output tile; the least estimated
-// time wins: rounds of 256 workgroups, and for S > 1 the partial outputs written and read once at 4 TB/s and another launch.  The products
+// time wins: rounds of 256 workgroups, and for S > 1 the partial outputs written and read once (4 TB/s; 5.5 where they are large) and another launch.  The products
 // A_r = softmax'_r W_r of Algorithm 2 are n outputs of kt k tiles each in one launch: N=71 h=896 V=14003 p=8, step 619 -> 121 us
 // (with the logits of all shards in one launch too), N=136 h=7040 V=79658 p=2 2356 -> 1369, N=4096 h=4096 V=32000 p=8 3132 -> 2947.
 static int slices_of(int64_t M, int64_t N, int64_t kt, int n) {
@@ -152,8 +168,9 @@ static int slices_of(int64_t M, int64_t N, int64_t kt, int n) {
     double best_us = 0;
     for (int64_t S = 1; S <= 32 && (S == 1 || S * 8 <= kt) && (S == 1 || S * n * M * N <= (int64_t)1 << 28); ++S) {
         const int mi = row_blocks_for(M, tn * S, ceil_div(kt, S), false, 256);
-        double us = (double)ceil_div(ceil_div(M, 64 * mi) * tn * S, 256) * tile_us(mi, ceil_div(kt, S), false);
-        if (S > 1) us += (double)(S * n * M * N) * 8.0 / 4e6 + 5.0;
+        const int64_t tiles = ceil_div(M, 64 * mi) * tn * S;
+        double us = M > DH_FEW ? dh_us(mi, tiles, ceil_div(kt, S), 256) : (double)ceil_div(tiles, 256) * tile_us(mi, ceil_div(kt, S), false);
+        if (S > 1) us += (double)(S * n * M * N) * 8.0 / (M > DH_FEW ? 5.5e6 : 4e6) + 5.0;
         if (S == 1 || us < best_us) {
             best = (int)S;
             best_us = us;
