@@ -75,6 +75,20 @@ def test_group_equals_shard_by_shard(N, h, rows, vocab, dtype, save_logits):
     check(*plans(N, h, rows, dtype, save_logits, vocab), dtype)
 
 
+@pytest.mark.parametrize("N,h,rows,vocab", [(70, 256, [4000, 4000, 40], None), (600, 256, [9000, 9000, 64], None),
+                                            (40, 1024, [3000] * 4, 9001)])
+def test_k_slices_and_a_short_last_shard(N, h, rows, vocab):
+    # the longest shard is cut into more K slices than the last one has k tiles: some of its slices are empty
+    import paper_2411_05288_amd as vp
+    print("alg2 short", N, h, rows, vocab, flush=True)
+    one, each = plans(N, h, rows, "bf16", True, vocab)
+    B, live = vp.binding, one.valid[:one.live]
+    D = sum(N * ((n + 63) // 64 * 64) * 2 for n in live)
+    slices = vp.vp_output_group_workspace_bytes(B.VP_CALL_OUTPUT_FWD_ALG2, N, h, live, vp.VP_BF16, B.VP_SAVE_LOGITS) - D
+    assert slices // (len(live) * N * h * 4) > (live[-1] + 63) // 64
+    check(one, each, "bf16")
+
+
 def test_group_with_the_generic_kernel():
     import paper_2411_05288_amd as vp
     lib = vp.binding.load_library()
