@@ -31,19 +31,19 @@ static double tile_us(int mi, int64_t kt, bool stats) {
     static const double step[5] = {0, 0.72, 0.93, 1.04, 1.42}, end[5] = {0, 2.8, 6.2, 9.3, 17.4};
     return (double)kt * step[mi] + (stats ? end[mi] : 1.0 + mi);
 }
-// dH and A of Algorithm 2 from this many tokens on (fewer: tile_us).  Estimated time of `tiles` tiles of 192 or 256 rows (mi = 3, 4) with
-// kt k tiles each: the part is power limited, so a k tile takes the longer the more compute units work at once (`all` of them, or
+// dH and A of Algorithm 2 of more tokens than this (fewer: tile_us).  Estimated time of `tiles` tiles of 64 mi rows (mi = 2, 3, 4)
+// with kt k tiles each: the part is power limited, so a k tile takes the longer the more compute units work at once (`all` of them, or
 // close to none), and a lower tile must save rows that do not exist, not only fill the last round.  An estimate without that
 // (tile_us) took 192 rows and other slices where 256 are faster, h=6144 V=128256, us: 3100 tokens 4077 -> 4480, 1536: 1865 -> 1982,
 // h=4096 V=128256: 1800: 1517 -> 1718, 800: 775 -> 849; with 256 rows only, it loses 520 (h=4096 V=128256): 528 -> 615, 1300
 // (h=3072 V=50001): 353 -> 386, 2600: 709 -> 788.  Of 126 sizes of 520 to 4000 tokens this one is more than 2 % of the product behind
-// the better of the two at five, 18 us at most.
+// the better of the two at three, 12 us at most.  (128 rows: 6 % more than measured, which keeps them to where they save the most.)
 constexpr int DH_FEW = 512;
 static double dh_us(int mi, int64_t tiles, int64_t kt, int cus) {
-    const double none = mi == 3 ? 0.85 : 0.98, all = mi == 3 ? 1.30 : 1.56, end = mi == 3 ? 3.3 : 5.2;
+    static const double none[5] = {0, 0, 0.51, 0.85, 0.98}, all[5] = {0, 0, 1.02, 1.30, 1.56}, end[5] = {0, 0, 1.5, 3.3, 5.2};
     const int64_t full = tiles / cus, last = tiles % cus;
-    double us = (double)full * ((double)kt * all + end);
-    if (last) us += (double)kt * (none + (all - none) * (double)last / cus) + end;
+    double us = (double)full * ((double)kt * all[mi] + end[mi]);
+    if (last) us += (double)kt * (none[mi] + (all[mi] - none[mi]) * (double)last / cus) + end[mi];
     return us;
 }
 // Row blocks per wavefront of the least estimated time for M rows, tn tile columns (times slices) and kt k tiles each: with
@@ -53,7 +53,12 @@ static double dh_us(int mi, int64_t tiles, int64_t kt, int cus) {
 // tiles that is not full lets the others run faster (N=1999 h=3072 V=50001 p=8: 11 % promised, the same time; N=700 h=4096 V=100000: 3 %
 // promised, 3 % longer).
 int row_blocks_for(int64_t M, int64_t tn, int64_t kt, bool stats, int cus) {
-    if (!stats && M > DH_FEW) return dh_us(3, ceil_div(M, 192) * tn, kt, cus) < dh_us(4, ceil_div(M, 256) * tn, kt, cus) ? 3 : 4;
+    if (!stats && M > DH_FEW) {
+        int low = 4;
+        for (int mi = 3; mi >= 2; --mi)
+            if (dh_us(mi, ceil_div(M, 64 * mi) * tn, kt, cus) < dh_us(low, ceil_div(M, 64 * low) * tn, kt, cus)) low = mi;
+        return low;
+    }
     auto us = [&](int mi) { return (double)ceil_div(ceil_div(M, 64 * mi) * tn, cus) * tile_us(mi, kt, stats); };
     int best = 3;
     for (int mi = 2; mi >= 1; --mi)
