@@ -44,7 +44,7 @@ typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
 // Operands are scaled by this before they are split, and the sums by the square of its inverse (all exact): the last bit of the
 // smallest fp32 number is then a normal bf16 number, so that the three parts hold every finite operand exactly.  (Scaled operands
-// from 2^128 on and sums from 2^80 on are not finite and are computed again: f32_finish.)
+// from 2^128 on and sums from 2^80 on are not finite and are computed again: f32_again.)
 constexpr float IN_SCALE = 0x1p24f;
 
 __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {      // round to nearest even, one instruction
@@ -55,7 +55,6 @@ __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {      // roun
 
 constexpr int F_THREADS = 256;
 constexpr int F_FEW = 5;                  // sums of fewer products than this: the fp32 instruction
-constexpr int F_AGAIN = 4;                // steps of two k whose loads are in flight together where elements are computed again
 constexpr unsigned F_OOB = 0x80000000u;   // beyond every buffer descriptor below (each covers at most 2^30 bytes)
 
 struct GemmF32Params {
@@ -76,12 +75,12 @@ struct GemmF32Params {
     GemmF32Shard sh[GEMM_GROUP_MAX];
 };
 
-// One operand's part of a tile: ROWS rows by SK of the K dimension.
-template <bool KC, int ROWS, int SK>
+// One operand's part of a tile: ROWS rows by SK of the K dimension, fetched by THREADS threads.
+template <bool KC, int ROWS, int SK, int THREADS = F_THREADS>
 struct F32Tile {
     static constexpr int RB = KC ? 2 * SK : 2 * ROWS;                // bytes per stored row of a plane
     static constexpr int PLANE = 2 * ROWS * SK;                      // bytes per bf16 plane; three planes
-    static constexpr int CHUNKS = ROWS * SK / 4 / F_THREADS;         // 16-byte chunks of fp32 per thread
+    static constexpr int CHUNKS = ROWS * SK / 4 / THREADS;           // 16-byte chunks of fp32 per thread
     static constexpr int CPR = KC ? SK / 4 : ROWS / 4;               // chunks per stored row
 
     // K-contiguous: position of the 16-byte chunk c (eight k) of row r within its row of SK * 2 bytes, so that the 16 rows
@@ -98,9 +97,9 @@ struct F32Tile {
 // descriptor covers exactly the rows of this tile that exist (K-contiguous) or the k-rows that exist
 // (K-strided), and elements past the end of a K-contiguous row get an offset beyond it.  (Rows past the
 // end of a K-strided operand read the neighbouring k-row: values for outputs never stored.)
-template <bool KC, int ROWS, int SK, bool VEC>
+template <bool KC, int ROWS, int SK, bool VEC, int THREADS = F_THREADS>
 __device__ __forceinline__ uintx4 f32_load(const float* p, int64_t ld, int r0, int k0, int rows, int k_end, int tid, int i) {
-    typedef F32Tile<KC, ROWS, SK> T;
+    typedef F32Tile<KC, ROWS, SK, THREADS> T;
     const float* base = KC ? p + (int64_t)r0 * ld + k0 : p + (int64_t)k0 * ld + r0;
     const int left = KC ? rows - r0 : k_end - k0;   // stored rows that exist from here on
     const int have = left < 0 ? 0 : (left < (KC ? ROWS : SK) ? left : (KC ? ROWS : SK));
@@ -108,7 +107,7 @@ __device__ __forceinline__ uintx4 f32_load(const float* p, int64_t ld, int r0, i
     const int64_t in_row = KC ? (int64_t)k_end - k0 : (int64_t)rows - r0;
     const int64_t bytes = have > 0 && in_row > 0 ? (((int64_t)have - 1) * ld + in_row) * 4 : 0;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000);
-    const int q = tid + F_THREADS * i;
+    const int q = tid + THREADS * i;
     const int row = q / T::CPR, c = (q % T::CPR) * 4;
     const unsigned off = ((unsigned)row * (unsigned)ld + (unsigned)c) * 4u;
     uintx4 r;
@@ -214,47 +213,14 @@ __device__ __forceinline__ F32Work f32_work(const GemmF32Params& g, int bx, int 
     return w;
 }
 
-// Ends the 32 x 32 block at (row0, col0): register r of lane l holds C[8 (r/4) + 4 (l/32) + r%4][l%32], 128 contiguous bytes
-// per row and store.
-template <bool A_KC, bool B_KC>
-__device__ __forceinline__ void f32_finish(floatx16 v, const F32Work& w, int row0, int col0, bool accumulate, int lane) {
+// Two stages of three planes of both operands.
+template <int MT, int NT, int SK>
+constexpr int f32_lds_bytes() { return 2 * 3 * 2 * SK * 64 * (MT + NT); }
+
+// Stores the elements `which` (bit r: register r) of the 32 x 32 block at (row0, col0): register r of lane l holds
+// C[8 (r/4) + 4 (l/32) + r%4][l%32], 128 contiguous bytes per row and store.
+__device__ __forceinline__ void f32_store(floatx16 v, unsigned which, const F32Work& w, int row0, int col0, bool accumulate, int lane) {
     const int l32 = lane & 31, hf = lane >> 5;
-    // A non-finite operand (or one that rounds to a bf16 infinity, or an overflow) makes the parts of the split
-    // cancel to NaN.  Elements that are not finite are computed again from the operands as they are, in fp32; and so are sums of
-    // fewer than five products, in which what the split leaves out shows (a single product would be off by its last bit).
-    float nf = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) nf = fmaf(v[r], 0.f, nf);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] *= 1.f / (IN_SCALE * IN_SCALE);
-    const bool few = w.k_end - w.k_begin < F_FEW;
-    if (few || __builtin_amdgcn_ballot_w64(!(nf == 0.f)) != 0) {
-        const int ar = min(row0 + l32, w.M - 1), br = min(col0 + l32, w.N - 1);
-        const float* ap = w.A + (A_KC ? (int64_t)ar * w.lda : (int64_t)ar);
-        const float* bp = w.B + (B_KC ? (int64_t)br * w.ldb : (int64_t)br);
-        floatx16 c;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) c[r] = 0.f;
-        // Bound by its loads, 4 bytes a lane without LDS: N=1000 h=1024 V=32000 p=8 with a NaN in one token, step 5.9 ms with one
-        // step of two k at a time -> 4.4, all tokens NaN 9.9 -> 8.4 (finite: 1.05; the fp32 instruction in LDS tiles took 1.7 for any)
-        for (int k0 = w.k_begin; k0 < w.k_end; k0 += 2 * F_AGAIN) {
-            float av[F_AGAIN], bv[F_AGAIN];
-#pragma unroll
-            for (int u = 0; u < F_AGAIN; ++u) {
-                const int k = k0 + 2 * u + hf, kc = k < w.k_end ? k : w.k_begin;
-                av[u] = ap[A_KC ? (int64_t)kc : (int64_t)kc * w.lda];
-                bv[u] = bp[B_KC ? (int64_t)kc : (int64_t)kc * w.ldb];
-            }
-#pragma unroll
-            for (int u = 0; u < F_AGAIN; ++u) {
-                const bool in = k0 + 2 * u + hf < w.k_end;
-                c = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? av[u] : 0.f, in ? bv[u] : 0.f, c, 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            if (few || !(fabsf(v[r]) < INFINITY)) v[r] = c[r];
-    }
     const int col = col0 + l32, row = row0 + 4 * hf;
     if (col >= w.N) return;
     float* c = w.C + (int64_t)row * w.ldc + col;
@@ -262,21 +228,92 @@ __device__ __forceinline__ void f32_finish(floatx16 v, const F32Work& w, int row
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int dr = 8 * (r >> 2) + (r & 3);
-            if (row + dr < w.M) v[r] += c[(int64_t)dr * w.ldc];
+            if (row + dr < w.M && (which >> r & 1)) v[r] += c[(int64_t)dr * w.ldc];
         }
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int dr = 8 * (r >> 2) + (r & 3);
-        if (row + dr < w.M) c[(int64_t)dr * w.ldc] = v[r];
+        if (row + dr < w.M && (which >> r & 1)) c[(int64_t)dr * w.ldc] = v[r];
     }
+}
+
+// Elements `again` (bit r: register r of block i, j) of the wavefront's blocks with the fp32 instruction from the operands as they
+// are: global -> registers -> this wavefront's part of the LDS (one stage; K-contiguous rows SK + 4 floats apart, K-strided ones
+// an odd multiple of 32, so that the two k of a read fall into different banks) -> MFMA, every stage's loads on their way while the one before it is multiplied.  No barrier: the
+// wavefronts whose elements are all finite are done.  Bound by that instruction.  Step of N=1000 h=1024 V=32000 p=8 (finite: 1.05 ms)
+// with a NaN in one token / in all / an infinity in W, ms: 4.51 / 8.42 / 5.13 with every block's operands read from global
+// memory, 4 bytes a lane -> 2.47 / 2.42 / 2.16 (before the split into parts 1.70 in every case).
+template <bool A_KC, bool B_KC, int MT, int NT, int SK, bool VEC>
+__device__ __forceinline__ void f32_again(const F32Work& w, const unsigned (&again)[MT][NT], bool accumulate, char* lds, int wave, int lane) {
+    constexpr int RA = 32 * MT, RB = 32 * NT;
+    typedef F32Tile<A_KC, RA, SK, 64> TA;
+    typedef F32Tile<B_KC, RB, SK, 64> TB;
+    // floats from stored row to stored row
+    constexpr int LA = A_KC ? SK + 4 : RA + (RA % 64 ? 0 : 32), LB = B_KC ? SK + 4 : RB + (RB % 64 ? 0 : 32);
+    constexpr int A_FLOATS = (A_KC ? RA : SK) * LA, B_FLOATS = (B_KC ? RB : SK) * LB;
+    static_assert(4 * (A_FLOATS + B_FLOATS) * 4 <= f32_lds_bytes<MT, NT, SK>(), "one stage in fp32 for each wavefront");
+    asm volatile("" : "+v"(lane));      // addresses are formed here, not held through the products of parts
+    float* const la = reinterpret_cast<float*>(lds) + wave * (A_FLOATS + B_FLOATS);
+    float* const lb = la + A_FLOATS;
+    const int l32 = lane & 31, hf = lane >> 5;
+    const int m0 = w.m0 + (wave >> 1) * RA, n0 = w.n0 + (wave & 1) * RB;
+    auto in_order = []() {      // a wavefront's LDS accesses are executed in order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    floatx16 acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    uintx4 raw[TA::CHUNKS + TB::CHUNKS];
+    auto load = [&](int k0) {
+#pragma unroll
+        for (int c = 0; c < TA::CHUNKS; ++c) raw[c] = f32_load<A_KC, RA, SK, VEC, 64>(w.A, w.lda, m0, k0, w.M, w.k_end, lane, c);
+#pragma unroll
+        for (int c = 0; c < TB::CHUNKS; ++c)
+            raw[TA::CHUNKS + c] = f32_load<B_KC, RB, SK, VEC, 64>(w.B, w.ldb, n0, k0, w.N, w.k_end, lane, c);
+    };
+    load(w.k_begin);
+    for (int k0 = w.k_begin; k0 < w.k_end; k0 += SK) {
+        in_order();
+#pragma unroll
+        for (int c = 0; c < TA::CHUNKS; ++c) {
+            const int q = lane + 64 * c;
+            *reinterpret_cast<uintx4*>(la + (q / TA::CPR) * LA + (q % TA::CPR) * 4) = raw[c];
+        }
+#pragma unroll
+        for (int c = 0; c < TB::CHUNKS; ++c) {
+            const int q = lane + 64 * c;
+            *reinterpret_cast<uintx4*>(lb + (q / TB::CPR) * LB + (q % TB::CPR) * 4) = raw[TA::CHUNKS + c];
+        }
+        load(k0 + SK);
+        in_order();
+#pragma unroll 2
+        for (int k = 0; k < SK; k += 2) {      // elements past the end of K are zeros in both operands
+            float a[MT], b[NT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[i] = A_KC ? la[(i * 32 + l32) * LA + k + hf] : la[(k + hf) * LA + i * 32 + l32];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) b[j] = B_KC ? lb[(j * 32 + l32) * LB + k + hf] : lb[(k + hf) * LB + j * 32 + l32];
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) f32_store(acc[i][j], again[i][j], w, m0 + i * 32, n0 + j * 32, accumulate, lane);
 }
 
 // Workgroup (bx, by) of a product: MT x NT MFMA tiles of 32 x 32 per wavefront, SK of K per LDS stage, PD stages of global loads
 // in flight in registers.
-template <int MT, int NT, int SK>
-constexpr int f32_lds_bytes() { return 2 * 3 * 2 * SK * 64 * (MT + NT); }
-
 template <bool A_KC, bool B_KC, int MT, int NT, int SK, int PD, bool VEC>
 __device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& g, char* lds, int bx, int by) {
     constexpr int TM = 64 * MT, TN = 64 * NT;
@@ -402,6 +439,13 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& g, char* lds,
         }
     }
 
+    // A non-finite operand (or one that rounds to a bf16 infinity, or an overflow) makes the parts of the split cancel to NaN.
+    // Elements that are not finite are computed again from the operands as they are, in fp32; and so are sums of fewer than five
+    // products, in which what the split leaves out shows (a single product would be off by its last bit).
+    const bool few = w.k_end - w.k_begin < F_FEW;
+    const int lid = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));      // the lane, not held through the loop
+    bool any = few;
+    unsigned again[MT][NT];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -411,8 +455,21 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& g, char* lds,
 #pragma unroll
                 for (int r = 0; r < 16; ++r) v[r] += acc[1][i][j][r];
             }
-            f32_finish<A_KC, B_KC>(v, w, w.m0 + (wm * MT + i) * 32, w.n0 + (wn * NT + j) * 32, g.accumulate != 0, lane);
+            float nf = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) nf = fmaf(v[r], 0.f, nf);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r] *= 1.f / (IN_SCALE * IN_SCALE);
+            again[i][j] = few ? 0xFFFFu : 0u;
+            if (__builtin_amdgcn_ballot_w64(!(nf == 0.f)) != 0) {
+                any = true;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) again[i][j] |= fabsf(v[r]) < INFINITY ? 0u : 1u << r;
+            }
+            f32_store(v, ~again[i][j], w, w.m0 + (wm * MT + i) * 32, w.n0 + (wn * NT + j) * 32, g.accumulate != 0, lid);
         }
+    // (every wavefront is done with the stages in LDS)
+    if (any) f32_again<A_KC, B_KC, MT, NT, SK, VEC>(w, again, g.accumulate != 0, lds, wave, lid);
 }
 
 // WPC workgroups per compute unit.

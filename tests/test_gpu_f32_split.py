@@ -180,3 +180,34 @@ def test_every_layout_sums_all_six_part_products(product, m, n):
     a, b = parts(A), parts(B)
     for i, j in ((0, 0), (0, 1), (1, 0), (1, 1), (0, 2), (2, 0)):
         assert float((a[i].mean(1).min() * b[j].mean(1).min())) > 2 * bar      # (the test can tell)
+
+
+@pytest.mark.parametrize("N,h,rows", SHAPES + [(2, 64, [3]), (1000, 1024, [4000])])
+def test_non_finite_operands_of_the_gradients(N, h, rows):
+    # one infinity in H, one NaN and one value that overflows in W: their columns of dW and dH as fp32 has them, all other
+    # elements the same bits as without them
+    print("non-finite", N, h, rows, flush=True)
+    import paper_2411_05288_amd as vp
+    g = torch.Generator(device="cuda").manual_seed(9)
+    Vs = rows[0]
+    H, W = (torch.randn((n, h), generator=g, device="cuda") for n in (N, Vs))
+    Y = torch.randn((N, Vs), generator=g, device="cuda")
+    labels = torch.randint(0, Vs, (N,), generator=g, device="cuda")
+    D, dH, dW = call_bwd(H, W, labels, Y, 4.0)
+    D = D.clone()
+    t, j, k = N // 2, Vs - 1, h - 1
+    H[t, k] = float("inf")
+    W[j, 0], W[0, 1] = float("nan"), 3.4e38
+    _, dH1, dW1 = call_bwd(H, W, labels, Y, 4.0)
+    assert torch.equal(dW1[:, :k], dW[:, :k]) and torch.equal(dW1[:, k], D[t] * float("inf"))
+    assert torch.equal(dH1[:, 2:], dH[:, 2:]) and bool(dH1[:, 0].isnan().all())
+    want = 3.4e38 * D[:, 0].double()      # (what W's other rows add is below its last bit)
+    finite = want.abs() < 3.4e38
+    assert bool(((dH1[:, 1].double() - want).abs() <= 2.0 ** -23 * want.abs())[finite].all())
+    assert torch.equal(dH1[~finite, 1], torch.sign(D[~finite, 0]) * float("inf"))
+    # added to what is there, once
+    n = vp.vp_workspace_bytes(vp.binding.VP_CALL_OUTPUT_BWD, N, h, Vs, vp.VP_F32, vp.VP_SAVE_LOGITS)
+    ws, acc = torch.empty((n,), dtype=torch.uint8, device="cuda"), torch.ones((N, h), device="cuda")
+    vp.vp_output_bwd(H, W, labels, 0, torch.zeros(N, device="cuda"), torch.ones(N, device="cuda"), Y, 4.0, acc, dW1, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(acc[:, 1:], dH1[:, 1:] + 1.0) and bool(acc[:, 0].isnan().all())
