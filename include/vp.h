@@ -22,8 +22,8 @@
  *     incoming embedding gradient.  Statistics, the loss and all gradients leaving the
  *     library are fp32.  With VP_BF16 the products are bf16 x bf16 MFMA with fp32
  *     accumulation; with VP_F32 everything is computed in fp32: in its products every finite operand is held
- *     exactly (in three bf16 parts that together have its 24 bits), partial products below 2^-26 of
- *     a whole one are left out of sums of five products or more, and the sums are fp32.
+ *     exactly (in three bf16 parts that together have its 24 bits), the smallest partial products (together
+ *     at most 2^-24 of a whole one) are left out of sums of five products or more, and the sums are fp32.
  *   - Labels / token ids are global vocabulary ids (int64).  An id outside the shard's
  *     range [shard_offset, shard_offset + Vs) - including ids outside [0, V) - is treated
  *     as "not owned": target logit 0, all-zero one-hot row, zero output row, no scatter.

@@ -5,15 +5,15 @@
 //
 // What bounds it: the matrix cores.  v_mfma_f32_32x32x2_f32 gives 157 TFLOP/s, the bf16 instruction sixteen times as much, so
 // every operand is split exactly into three bf16 parts, x = x0 + x1 + x2 (8 significant bits each, 24 together), and of
-// the nine products of parts the six down to 2^-18 of the whole are summed in fp32 accumulators: x0 y0, x0 y1, x1 y0, x1 y1,
-// x0 y2, x2 y0.  What is left out is below 2^-26 of a product, a quarter of the rounding of one fp32 addition; and one bf16 MFMA
-// adds 16 products at once, so that a sum is rounded six times per 16 k instead of eight.  Sums of at most four products, in
-// which what is left out would show (one product: 3.9e-8 instead of 2.5e-8), are formed with the fp32 instruction.  Error of the
-// results against float64
-// (2-norm, relative; fp32 MFMA -> this kernel): N=1000 h=1024 V=32000 p=8: logits 5.7e-7 -> 4.9e-7, dH 1.1e-6 -> 5.0e-7, dW
+// the nine products of parts the six largest are summed in fp32 accumulators: x0 y0, x0 y1, x1 y0, x1 y1 (at most 2^-16 of the
+// whole), x0 y2, x2 y0 (2^-17).  What is left out is at most 2^-24 of a product (both operands just above a power of two; 2^-27 in
+// the root mean square); and one bf16 MFMA adds 16 products at once, so that a sum is rounded six times per 16 k instead of
+// eight.  Sums of at most four products, in which what is left out would show (one product: 3.9e-8 instead of 2.5e-8), are formed
+// with the fp32 instruction; from five on both the 2-norm of the error and the largest of 630000 are smaller than its own (K = 5: 4.3e-8
+// -> 3.2e-8, 16: 7.4e-8 -> 3.4e-8, 256: 2.9e-7 -> 1.7e-7).  Error of the results against float64 (2-norm, relative; fp32 MFMA -> this kernel): N=1000 h=1024 V=32000 p=8: logits 5.7e-7 -> 4.9e-7, dH 1.1e-6 -> 5.0e-7, dW
 // 5.7e-7 -> 3.6e-7; N=128 h=256 V=8192: 2.9e-7 -> 2.4e-7, 2.1e-7 -> 1.9e-7, 2.0e-7 -> 1.4e-7; N=2000 h=2048 V=8000: 8.1e-7 ->
 // 7.0e-7, 1.1e-6 -> 5.0e-7, 8.0e-7 -> 5.1e-7.  Time of a product at the first of these sizes: 520-560 us -> 330-350 us
-// (200 TFLOP/s of fp32 work, 1.2 PFLOP/s of the matrix cores'); whole step 1700 -> 1100 us.
+// (200 TFLOP/s of fp32 work, 1.2 PFLOP/s of the matrix cores'); whole step 1700 -> 1040 us.
 //
 // Workgroup: 4 wavefronts (2 x 2) on tiles of 256 x 128 (dW: vocabulary rows first) or 128 x 256 (tokens first), 128 x 128 or
 // 64 x 64.  Operands go global -> registers (fp32) -> split -> LDS (three bf16 planes), K advances 16 (small tiles: 32) at a
@@ -121,7 +121,7 @@ __device__ __forceinline__ uintx4 f32_load(const float* p, int64_t ld, int r0, i
     return r;
 }
 
-// x = p0 + p1 + p2 with bf16 p (round to nearest: |x - p0| <= 2^-9 |x|, |x - p0 - p1| <= 2^-18 |x|, and the third holds
+// x = p0 + p1 + p2 with bf16 p (round to nearest: |x - p0| <= 2^-8 |x|, |x - p0 - p1| <= 2^-17 |x|, and the third holds
 // what is left exactly).  Two values at a time, packed.
 __device__ __forceinline__ void split2(float x0, float x1, unsigned& p0, unsigned& p1, unsigned& p2) {
     p0 = pack_bf16(x0, x1);
@@ -402,7 +402,7 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& g, char* lds,
             }
 #pragma unroll
             for (int o = 0; o < PASSES; ++o) {
-                // the six products down to 2^-18 of the whole, the small ones first; after each of them a share of the next
+                // the six largest products of parts, the small ones first; after each of them a share of the next
                 // stage's split, whose vector instructions issue while the matrix cores work
                 constexpr int LA[6] = {2, 0, 1, 1, 0, 0}, LB[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
@@ -481,7 +481,7 @@ __global__ __launch_bounds__(F_THREADS, WPC) void gemm_f32_kernel(GemmF32Params 
 
 // dH and dW in one launch: the first `nh` workgroups are dH's, hx in a row of its grid.  Neither needs the other, and where one
 // alone does not fill the chip, its workgroups wait (for loads, LDS and barriers) more than they multiply: N=128 h=256 V=8192
-// p=2: 12.8 + 11.3 us -> 17.6, the step 48.3 -> 40.7; N=128 h=320 V=18549 p=4: 22.9 + 20.8 -> 33.5, 81 -> 72.
+// p=2: 12.8 + 11.3 us -> 15.3 to 17.6, the step 48.3 -> 40.7.
 template <int MT, int NT, int SK, int PD, int WPC>
 __global__ __launch_bounds__(F_THREADS, WPC) void gemm_f32_dh_dw_kernel(GemmF32Params h, GemmF32Params w, int nh, int hx) {
     __shared__ __attribute__((aligned(16))) char lds[f32_lds_bytes<MT, NT, SK>()];
